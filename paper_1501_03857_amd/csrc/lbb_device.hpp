@@ -127,30 +127,60 @@ template <typename S> struct ThermalCfg;
 // the hardware instruction (1 ulp) in FP32
 __device__ __forceinline__ double stage_sqrt(double x) { return sqrt_nr(x); }
 __device__ __forceinline__ float stage_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
-// DPP move of a double (two 32-bit moves) with control `ctl`; lanes the
-// pattern gives no source, or whose row `rmask` leaves out, read 0.
-template <int CTL, int RMASK>
-__device__ __forceinline__ double dpp_d(double v)
+// Mass sums are exact: a node's mass is rounded once to a whole number of
+// units of P.mass_q and the whole numbers are added in 64 bits, so the domain
+// mean density of Eq. (9) does not depend on the tiles, the launches or the
+// order that formed the sum.  mass_c = 1.5 2^e, so m + mass_c lies in
+// [2^e, 2^(e+1)) for |m| < 2^(e-1), where doubles are 2^(e-52) = mass_q apart;
+// the host takes 2^(e-1) >= 4/b, four times the largest density the equation
+// of state admits (b = 2/21: units of 2.8e-14, below the rounding of a
+// 64-term sum of node masses in FP64).
+__device__ __forceinline__ long long mass_units(const double mass_c, double m)
 {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTL, RMASK, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTL, RMASK, 0xf, false);
-    return __hiloint2double(hi, lo);
+    return __double_as_longlong(m + mass_c) - __double_as_longlong(mass_c);
 }
 
-// Sum of one double per lane over the wave, valid in lane 63, in a fixed
-// order: an inclusive scan inside each row of 16 lanes (shifts by 1, 2, 4,
-// 8), then the total of row 0 added into row 1 and of row 2 into row 3, then
-// the total of rows 0-1 into rows 2-3.  Every lane must be active.
-__device__ __forceinline__ double wave_sum_to_last(double v)
+// DPP move of a 64-bit value (two 32-bit moves) with control CTL; lanes the
+// pattern gives no source, or whose row RMASK leaves out, read 0.
+template <int CTL, int RMASK>
+__device__ __forceinline__ long long dpp_i(long long v)
 {
-    v += dpp_d<0x111 /* row_shr:1 */, 0xf>(v);
-    v += dpp_d<0x112 /* row_shr:2 */, 0xf>(v);
-    v += dpp_d<0x114 /* row_shr:4 */, 0xf>(v);
-    v += dpp_d<0x118 /* row_shr:8 */, 0xf>(v);
-    v += dpp_d<0x142 /* row_bcast:15 */, 0xa>(v);
-    v += dpp_d<0x143 /* row_bcast:31 */, 0xc>(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)v, CTL, RMASK, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTL, RMASK, 0xf, false);
+    return ((long long)hi << 32) | (unsigned)lo;
+}
+
+// Sum of one whole number per lane over the wave, valid in lane 63: an
+// inclusive scan inside each row of 16 lanes (shifts by 1, 2, 4, 8), then the
+// total of row 0 added into row 1 and of row 2 into row 3, then the total of
+// rows 0-1 into rows 2-3.  Every lane must be active.
+__device__ __forceinline__ long long wave_sum_to_last(long long v)
+{
+    v += dpp_i<0x111, 0xf>(v);
+    v += dpp_i<0x112, 0xf>(v);
+    v += dpp_i<0x114, 0xf>(v);
+    v += dpp_i<0x118, 0xf>(v);
+    v += dpp_i<0x142, 0xa>(v);
+    v += dpp_i<0x143, 0xc>(v);
     return v;
 }
+
+// Two-part sums of whole numbers below 2^62: low 24 bits and the rest apart,
+// so that 2^30 terms cannot overflow.
+struct MassSum {
+    long long hi, lo;
+    __device__ __forceinline__ void add(long long v)
+    {
+        hi += v >> 24;
+        lo += v & 0xffffff;
+    }
+    __device__ __forceinline__ void add(const MassSum &o)
+    {
+        hi += o.hi;
+        lo += o.lo;
+    }
+    __device__ __forceinline__ double value(double q) const { return ((double)hi * 16777216.0 + (double)lo) * q; }
+};
 
 // The value a lane's left (lane - 1) or right (lane + 1) neighbour holds,
 // through the wave-wide row shift of DPP (0 in the first and last lane).
@@ -206,6 +236,7 @@ struct DevParams {
     double k1k, k2_Tc;            // kappa (1 + kappa), kappa^2 / T_c
     double k1k_rsTc;              // kappa (1 + kappa) / sqrt(T_c)
     double R_cv12, a_cv12;        // R / (12 c_v), a / (12 c_v)
+    double mass_c, mass_q;        // mass sums: rounding constant and unit (mass_units)
 };
 
 // Device-resident scalars of one domain.  tA is the state index seen by the
@@ -231,10 +262,16 @@ struct Inst {
     DevParams P;
     void *f[2], *T[2];
     void *rho, *vx, *vy;
-    double *mass_part, *hf_part;
+    long long *mass_part;
+    double *hf_part;
     Scalars *sc;
     int nbxA, nbyA, nbxB, nbyB;
     int blkA0, blkB0;  // first block of this lattice in the LB / thermal grids
+    // one-launch step: launches since sc->tA (two slots), mass partials of two
+    // states (npF each), tiles and tile height, first block in its grid
+    long long *rel;
+    MassSum *mpart;
+    int nbxF, nbyF, tyF, npF, blkF0;
 };
 
 // Tile of a lattice's q-th block (0 <= q < nb).  Workgroups are dispatched
@@ -366,9 +403,6 @@ __device__ __forceinline__ double block_sum_array(const double *__restrict__ a, 
     return block_sum<NTH>(s, red);
 }
 
-// Fixed-order sum of n doubles by the first 256 threads of a block of at
-// least 256 threads (the others add nothing), the same for any block size;
-// result valid in thread 0.  All threads of the block must call it.
 // s + a[k0] + a[k0 + stride] + ... (k < n), added in that order; the loads are
 // issued 16 at a time so a long sum waits for memory once per 16 terms.
 __device__ __forceinline__ double ordered_sum(const double *__restrict__ a_, int k0, int n, int stride, double s)
@@ -386,18 +420,27 @@ __device__ __forceinline__ double ordered_sum(const double *__restrict__ a_, int
     return s;
 }
 
-__device__ __forceinline__ double fixed_sum(const double *__restrict__ a, int n, double *red /* [>= 4] */)
+// Sum of n whole numbers by one block of NTH threads, valid in thread 0; the
+// loads are issued 8 at a time.  All threads of the block must call it.
+template <int NTH>
+__device__ __forceinline__ MassSum mass_sum(const long long *__restrict__ a_, size_t n, MassSum *red /* [NTH / 64] */)
 {
-    double s = 0.0;
-    if (threadIdx.x < NT) s = ordered_sum(a, threadIdx.x, n, NT, 0.0);
+    const gmem<long long> *__restrict__ a = (const gmem<long long> *)a_;
+    MassSum s{0, 0};
+    for (size_t k = threadIdx.x; k < n; k += 8 * NTH) {
+        long long v[8];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0 && w < NT / 64) red[w] = s;
+        for (int j = 0; j < 8; ++j) v[j] = k + j * NTH < n ? a[k + j * NTH] : 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s.add(v[j]);
+    }
+    s.hi = wave_sum_to_last(s.hi);
+    s.lo = wave_sum_to_last(s.lo);
+    if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = s;
     __syncthreads();
-    double t = 0.0;
+    MassSum t{0, 0};
     if (threadIdx.x == 0)
-        for (int k = 0; k < NT / 64; ++k) t += red[k];
+        for (int k = 0; k < NTH / 64; ++k) t.add(red[k]);
     return t;
 }
 
@@ -430,6 +473,31 @@ __device__ __forceinline__ void reduce_heat_flux(const double *__restrict__ hf_p
 // beyond the wall read from a ghost fluid layer that mirrors the first fluid
 // row about the wall row (so F_m has no normal part there); buoyancy still
 // skips them.
+//
+// psi at the node and its eight neighbours (mirrored beyond a wall row).
+struct PsiNb {
+    double c, E, N, W, S, NE, NW, SW, SE;
+};
+
+__device__ __forceinline__ void force_of(const DevParams &P, const PsiNb &p, bool bot, bool top, int gy, double rho,
+                                         double rho_ave, double &Fx, double &Fy, double &Q)
+{
+    // sum_a w_a psi(x + e_a) e_a with w = 1/3 (axes), 1/12 (diagonals)
+    const double sx = (p.E - p.W) * (1.0 / 3.0) + (p.NE - p.NW - p.SW + p.SE) * (1.0 / 12.0);
+    const double sy = (p.N - p.S) * (1.0 / 3.0) + (p.NE + p.NW - p.SW - p.SE) * (1.0 / 12.0);
+    Fx = -P.G * p.c * sx;
+    Fy = -P.G * p.c * sy;
+    Q = P.G * P.G * (sx * sx + sy * sy);
+    if (bot || top) return;
+    // fluid-solid force on the rows next to the walls (wall rows are the solid)
+    if (!P.periodic_y) {
+        if (gy == 1) Fy += P.Gw_bottom * p.c * p.c * (1.0 / 6.0);
+        if (gy == P.ny - 2) Fy -= P.Gw_top * p.c * p.c * (1.0 / 6.0);
+    }
+    // buoyancy, Eq. (9)
+    Fy -= (rho - rho_ave) * P.g;
+}
+
 template <int W>
 __device__ __forceinline__ void node_force(const DevParams &P, const double *psi_s, int lx, int ly, int gy,
                                            double rho, double rho_ave, double &Fx, double &Fy, double &Q)
@@ -438,27 +506,20 @@ __device__ __forceinline__ void node_force(const DevParams &P, const double *psi
     const bool bot = !P.periodic_y && gy == 0, top = !P.periodic_y && gy == P.ny - 1;
     if ((bot || top) && !P.ghost) return;
     const int c = (ly + 1) * W + (lx + 1);
-    const double pc = psi_s[c];
-    const double pE = psi_s[c + 1], pW = psi_s[c - 1];
     // the LDS row beyond a wall holds no lattice node; the ghost layer
     // replaces it by the mirror image of the row on the other side
     const int cn = top ? c - W : c + W, cs = bot ? c + W : c - W;
-    const double pN = psi_s[cn], pS = psi_s[cs];
-    const double pNE = psi_s[cn + 1], pNW = psi_s[cn - 1], pSW = psi_s[cs - 1], pSE = psi_s[cs + 1];
-    // sum_a w_a psi(x + e_a) e_a with w = 1/3 (axes), 1/12 (diagonals)
-    const double sx = (pE - pW) * (1.0 / 3.0) + (pNE - pNW - pSW + pSE) * (1.0 / 12.0);
-    const double sy = (pN - pS) * (1.0 / 3.0) + (pNE + pNW - pSW - pSE) * (1.0 / 12.0);
-    Fx = -P.G * pc * sx;
-    Fy = -P.G * pc * sy;
-    Q = P.G * P.G * (sx * sx + sy * sy);
-    if (bot || top) return;
-    // fluid-solid force on the rows next to the walls (wall rows are the solid)
-    if (!P.periodic_y) {
-        if (gy == 1) Fy += P.Gw_bottom * pc * pc * (1.0 / 6.0);
-        if (gy == P.ny - 2) Fy -= P.Gw_top * pc * pc * (1.0 / 6.0);
-    }
-    // buoyancy, Eq. (9)
-    Fy -= (rho - rho_ave) * P.g;
+    PsiNb p;
+    p.c = psi_s[c];
+    p.E = psi_s[c + 1];
+    p.W = psi_s[c - 1];
+    p.N = psi_s[cn];
+    p.S = psi_s[cs];
+    p.NE = psi_s[cn + 1];
+    p.NW = psi_s[cn - 1];
+    p.SW = psi_s[cs - 1];
+    p.SE = psi_s[cs + 1];
+    force_of(P, p, bot, top, gy, rho, rho_ave, Fx, Fy, Q);
 }
 
 // MRT collision of one node (Eqs. (2), (4), (5), (8)) in moment space with
@@ -527,6 +588,71 @@ __device__ __forceinline__ void collide(const DevParams &P, double f[9], double 
     f[6] = dm - cm;
     f[7] = dp - cp;
     f[8] = dm + cm;
+}
+
+// Push streaming (Eq. (3)) of the post-collision populations of node
+// (gx, gy) into fout; populations leaving through a wall are dropped.  Returns
+// the mass the node hands to the streamed state, in units of P.mass_q: each
+// population counts once, except those that leave through a wall (0) and
+// those that arrive on a wall row, whose Zou-He partners are reconstructed
+// with the same sum (2).  The mass sums the populations before they are
+// rounded to the storage precision: in FP32 storage it then differs from the
+// stored mass by the rounding of the populations (relative ~1e-7 per node,
+// ~1e-10 over a lattice), far below what rho_ave moves the buoyancy by.
+template <typename S>
+__device__ __forceinline__ long long push_node(const DevParams &P, S *__restrict__ fout, size_t N, int gx, int gy,
+                                               const double f[9])
+{
+    constexpr unsigned sz = (unsigned)sizeof(S);
+    const bool walls = !P.periodic_y;
+    const unsigned gxu = (unsigned)gx, rowc = (unsigned)gy * (unsigned)P.nx;
+    const int xe = gx + 1 == P.nx ? 0 : gx + 1;
+    const int xw = gx == 0 ? P.nx - 1 : gx - 1;
+    int yn = gy + 1, ys = gy - 1;
+    if (P.periodic_y) {
+        if (yn == P.ny) yn = 0;
+        if (ys < 0) ys = P.ny - 1;
+    }
+    const bool has_n = yn < P.ny, has_s = ys >= 0;
+    const unsigned rown = (unsigned)yn * (unsigned)P.nx, rows = (unsigned)ys * (unsigned)P.nx;
+    const unsigned xeu = (unsigned)xe, xwu = (unsigned)xw;
+    st_at(fout + 0 * N, (rowc + gxu) * sz, S(f[0]));
+    st_at(fout + 1 * N, (rowc + xeu) * sz, S(f[1]));
+    st_at(fout + 3 * N, (rowc + xwu) * sz, S(f[3]));
+    if (has_n) {
+        st_at(fout + 2 * N, (rown + gxu) * sz, S(f[2]));
+        st_at(fout + 5 * N, (rown + xeu) * sz, S(f[5]));
+        st_at(fout + 6 * N, (rown + xwu) * sz, S(f[6]));
+    }
+    if (has_s) {
+        st_at(fout + 4 * N, (rows + gxu) * sz, S(f[4]));
+        st_at(fout + 7 * N, (rows + xwu) * sz, S(f[7]));
+        st_at(fout + 8 * N, (rows + xeu) * sz, S(f[8]));
+    }
+    const double up = f[2] + f[5] + f[6];
+    const double dn = f[4] + f[7] + f[8];
+    double mm = f[0] + f[1] + f[3];
+    const double wu = !walls ? 1.0 : (gy == P.ny - 1 ? 0.0 : (gy == P.ny - 2 ? 2.0 : 1.0));
+    const double wd = !walls ? 1.0 : (gy == 0 ? 0.0 : (gy == 1 ? 2.0 : 1.0));
+    mm += wu * up + wd * dn;
+    return mass_units(P.mass_c, mm);
+}
+
+// Density of a node from its stored populations: their sum, or on a wall row
+// (kind 1: bottom, 2: top) the Zou-He identity, whose three unknowns sum to
+// the three opposite knowns.
+template <typename S>
+__device__ __forceinline__ double node_density(const S fs[9], int kind)
+{
+    double fl[9];
+#pragma unroll
+    for (int a = 0; a < 9; ++a) fl[a] = (double)fs[a];
+    if (kind == 1) return fl[0] + fl[1] + fl[3] + 2.0 * (fl[4] + fl[7] + fl[8]);
+    if (kind == 2) return fl[0] + fl[1] + fl[3] + 2.0 * (fl[2] + fl[5] + fl[6]);
+    double rr = fl[0];
+#pragma unroll
+    for (int a = 1; a < 9; ++a) rr += fl[a];
+    return rr;
 }
 
 __constant__ const int kEX[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
@@ -633,20 +759,7 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 7 : 1) void k_lb(const Inst 
         return gy == 0 ? 1 : (gy == P.ny - 1 ? 2 : 0);
     };
     auto psi_node = [&](int r, int gy, const S fs[9], S Tn) -> double {
-        double fl[9];
-#pragma unroll
-        for (int a = 0; a < 9; ++a) fl[a] = (double)fs[a];
-        // rho = sum of the completed populations; on a wall row the three
-        // unknowns sum to the three opposite knowns (Zou-He, zero velocity)
-        double rr;
-        const int kind = kind_of(gy);
-        if (kind == 1) rr = fl[0] + fl[1] + fl[3] + 2.0 * (fl[4] + fl[7] + fl[8]);
-        else if (kind == 2) rr = fl[0] + fl[1] + fl[3] + 2.0 * (fl[2] + fl[5] + fl[6]);
-        else {
-            rr = fl[0];
-#pragma unroll
-            for (int a = 1; a < 9; ++a) rr += fl[a];
-        }
+        const double rr = node_density<S>(fs, kind_of(gy));
         if (!frozen) {
             const double T = P.T_ref + (double)Tn;
             const double psi = pseudopotential(P, rr, T);
@@ -699,12 +812,12 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 7 : 1) void k_lb(const Inst 
     __syncthreads();
     const double rho_ave = sc->rho_ave;
 
-    double mrow[IPW_A];
+    long long mrow[IPW_A];
 #pragma unroll
     for (int m = 0; m < IPW_A; ++m) {
         const int r = 1 + wv + NWA * m;
         const int gy = gys[m];
-        mrow[m] = 0.0;
+        mrow[m] = 0;
         if (!live[m] || lane < 1 || lane > TXA || x0 + lane - 1 >= P.nx) continue;
         constexpr unsigned sz = (unsigned)sizeof(S);
         const unsigned rowc = (unsigned)gy * (unsigned)P.nx, oc = (rowc + gxu) * sz;
@@ -722,7 +835,7 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 7 : 1) void k_lb(const Inst 
             double mm = 0.0;
 #pragma unroll
             for (int a = 0; a < 9; ++a) mm += f[a];
-            mrow[m] = mm;
+            mrow[m] = mass_units(P.mass_c, mm);
             continue;
         }
         double Fx, Fy, Q;
@@ -734,52 +847,12 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 7 : 1) void k_lb(const Inst 
         st_at(vx_o, oc, wall_row ? S(0) : S(vx));
         st_at(vy_o, oc, wall_row ? S(0) : S(vy));
         collide(P, f, rh, vx, vy, Fx, Fy, Q, rcp_nr(P.tau_V + (rh - P.rho_V) * P.tau_slope));
-        // The mass partial sums the post-collision populations before they
-        // are rounded to the storage precision: in FP32 storage it then
-        // differs from the stored mass by the rounding of the populations
-        // (relative ~1e-7 per node, ~1e-10 over a lattice), far below what
-        // rho_ave moves the buoyancy by.
-        // push streaming, Eq. (3); populations leaving through a wall are
-        // dropped.  Mass of the streamed state: each population counts once,
-        // except those that leave through a wall (0) and those that arrive on
-        // a wall row, whose Zou-He partners are reconstructed with the same
-        // sum (2).
-        const int xe = gx + 1 == P.nx ? 0 : gx + 1;
-        const int xw = gx == 0 ? P.nx - 1 : gx - 1;
-        int yn = gy + 1, ys = gy - 1;
-        if (P.periodic_y) {
-            if (yn == P.ny) yn = 0;
-            if (ys < 0) ys = P.ny - 1;
-        }
-        const bool has_n = yn < P.ny, has_s = ys >= 0;
-        const unsigned rown = (unsigned)yn * (unsigned)P.nx, rows = (unsigned)ys * (unsigned)P.nx;
-        const unsigned xeu = (unsigned)xe, xwu = (unsigned)xw;
-        st_at(fout + 0 * N, oc, S(f[0]));
-        st_at(fout + 1 * N, (rowc + xeu) * sz, S(f[1]));
-        st_at(fout + 3 * N, (rowc + xwu) * sz, S(f[3]));
-        if (has_n) {
-            st_at(fout + 2 * N, (rown + gxu) * sz, S(f[2]));
-            st_at(fout + 5 * N, (rown + xeu) * sz, S(f[5]));
-            st_at(fout + 6 * N, (rown + xwu) * sz, S(f[6]));
-        }
-        if (has_s) {
-            st_at(fout + 4 * N, (rows + gxu) * sz, S(f[4]));
-            st_at(fout + 7 * N, (rows + xwu) * sz, S(f[7]));
-            st_at(fout + 8 * N, (rows + xeu) * sz, S(f[8]));
-        }
-        const double up = f[2] + f[5] + f[6];
-        const double dn = f[4] + f[7] + f[8];
-        double mm = f[0] + f[1] + f[3];
-        const double wu = !walls ? 1.0 : (gy == P.ny - 1 ? 0.0 : (gy == P.ny - 2 ? 2.0 : 1.0));
-        const double wd = !walls ? 1.0 : (gy == 0 ? 0.0 : (gy == 1 ? 2.0 : 1.0));
-        mm += wu * up + wd * dn;
-        mrow[m] = mm;
+        mrow[m] = push_node<S>(P, fout, N, gx, gy, f);
     }
-    // mass partials per lattice row and 62-column chunk, summed over the wave
-    // in a fixed order (the same for every tile height)
+    // mass partials per lattice row and 62-column chunk
 #pragma unroll
     for (int m = 0; m < IPW_A; ++m) {
-        const double v = wave_sum_to_last(mrow[m]);
+        const long long v = wave_sum_to_last(mrow[m]);
         if (live[m] && lane == 63) I.mass_part[(size_t)gys[m] * nbx + bx] = v;
     }
 }
@@ -803,6 +876,88 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 7 : 1) void k_lb(const Inst 
 // stage) and the RK4 sums stay in registers.  The parameters are copied into
 // registers once: read through the lattice table they would be fetched again
 // after every barrier.
+// Per-node coefficients of K, formed once per step: the advection
+// coefficients with the 1/12 of the column-sum stencils folded in, c1, c2.
+template <typename C>
+struct SlopeCoef {
+    C ax, ay, c1, c2;
+};
+
+// Coefficients of a lane's node from rho and v of its own column (rows south
+// of, at and north of the node): the column sums of the gradient stencils are
+// formed by every lane and passed to its neighbours, so every lane of the wave
+// must call it; the first and last lane get no meaningful result.
+template <typename C>
+__device__ __forceinline__ SlopeCoef<C> slope_coef(const DevParams &P, C rc, C rN, C rS, C uc, C uN, C uS, C vc, C vN,
+                                                   C vS)
+{
+    const C sr = (rN + rS) + C(4) * rc, dr = rN - rS;
+    const C su = (uN + uS) + C(4) * uc, dv = vN - vS;
+    const C srW = lane_from_left(sr), srE = lane_from_right(sr);
+    const C drW = lane_from_left(dr), drE = lane_from_right(dr);
+    const C suW = lane_from_left(su), suE = lane_from_right(su);
+    const C dvW = lane_from_left(dv), dvE = lane_from_right(dv);
+    const double rho = (double)rc;
+    // 12 d_x rho, 12 d_y rho and 12 div v from the column sums
+    const C gx = srE - srW, gy = fma(C(4), dr, drW + drE);
+    const double div12 = (double)((suE - suW) + fma(C(4), dv, dvW + dvE));
+    // A w = (R/c_v) div v / D1 and B w = (a/c_v) rho div v / D2 with
+    // D1 = 1 - b rho, D2 = 1 + 2 b rho - b^2 rho^2; one reciprocal
+    // 1/(rho D1 D2) gives 1/rho, 1/D1 and 1/D2
+    const double D1 = 1.0 - P.b * rho;
+    const double D2 = 1.0 + 2.0 * P.b * rho - P.b * P.b * rho * rho;
+    const double inv = rcp_nr(rho * D1 * D2);
+    // the stages read the column sums unscaled: 12 d_x T and 12 d_y T,
+    // so the advection coefficients carry the 1/12
+    // (a_x/12 = (chi/rho) d_x rho/12 - v_x/12 = (chi/rho) gx/144 - v_x/12)
+    const C k144 = (C)(P.chi * (1.0 / 144.0) * D1 * D2 * inv);
+    SlopeCoef<C> k;
+    k.ax = fma(k144, gx, -uc * C(1.0 / 12.0));
+    k.ay = fma(k144, gy, -vc * C(1.0 / 12.0));
+    const double Aw = P.R_cv12 * div12 * (rho * D2 * inv), Bw = P.a_cv12 * rho * div12 * (rho * D1 * inv);
+    k.c1 = (C)(Bw * P.k2_Tc - Aw);
+    k.c2 = (C)(-Bw * P.k1k_rsTc);
+    return k;
+}
+
+// Column sums of the 3x3 stencil of a stage input, formed by every lane for
+// its own column and passed to the neighbouring columns:
+// v = T_S + 4 T_c + T_N, w = T_N - T_S give
+//   d_x T = (v_E - v_W)/12, d_y T = (w_W + 4 w + w_E)/12,
+//   lap T = (v_W + v_E + 4 v - 36 T_c)/6,
+// the isotropic stencils of the gradient and the Laplacian (the 1/12 and 1/6
+// are carried by the coefficients).  Every lane of the wave must call it.
+template <typename C>
+struct StageCols {
+    C tc, v, w, vW, vE, wW, wE;
+};
+
+template <typename C>
+__device__ __forceinline__ StageCols<C> stage_cols(C tc, C tN, C tS)
+{
+    StageCols<C> s;
+    s.tc = tc;
+    s.v = fma(C(4), tc, tN + tS);
+    s.w = tN - tS;
+    s.vW = lane_from_left(s.v);
+    s.vE = lane_from_right(s.v);
+    s.wW = lane_from_left(s.w);
+    s.wE = lane_from_right(s.w);
+    return s;
+}
+
+template <typename C>
+__device__ __forceinline__ C stage_slope(const StageCols<C> &s, const SlopeCoef<C> &k, C Tref, C chi6)
+{
+    const C T = Tref + s.tc;
+    const C lap6 = fma(C(-36), s.tc, fma(C(4), s.v, s.vW + s.vE));
+    C h = k.c1 * T;
+    h = fma(k.c2, stage_sqrt(T), h);
+    h = fma(chi6, lap6, h);
+    h = fma(k.ax, s.vE - s.vW, h);
+    return fma(k.ay, fma(C(4), s.w, s.wW + s.wE), h);
+}
+
 template <typename S, int TY, int NWB>
 __global__ __launch_bounds__(64 * NWB) void k_thermal(const Inst *__restrict__ insts,
                                                       const int *__restrict__ blk2inst, int cf, int cT)
@@ -824,12 +979,12 @@ __global__ __launch_bounds__(64 * NWB) void k_thermal(const Inst *__restrict__ i
     __shared__ C T0[H][64];
     __shared__ C X[3][H][64];   // rho, vx, vy
     __shared__ C Ts[2][H][64];  // stage values T0 + c h (ping-pong); new T for the heat flux
-    __shared__ double red[NWB];
+    __shared__ MassSum red[NWB];
     const long long t = sc->tB;
     if (blk == 0) {  // reduction of the LB launch's mass partials, first in the grid
-        const double m = fixed_sum(I.mass_part, I.nbxA * P.ny, red);
+        const MassSum m = mass_sum<64 * NWB>(I.mass_part, (size_t)I.nbxA * P.ny, red);
         if (threadIdx.x == 0) {
-            sc->rho_ave = m / ((double)P.nx * (double)P.ny);
+            sc->rho_ave = m.value(P.mass_q) / ((double)P.nx * (double)P.ny);
             sc->tA = t + 1;
         }
         return;
@@ -882,45 +1037,17 @@ __global__ __launch_bounds__(64 * NWB) void k_thermal(const Inst *__restrict__ i
 
     // Per-node coefficients of K on the region shrunk by one node, kept in
     // registers (each wave evaluates K only at its own rows).
-    C cfr[4][RPW];
+    SlopeCoef<C> cfr[RPW];
 #pragma unroll
-    for (int m = 0; m < RPW; ++m) cfr[0][m] = cfr[1][m] = cfr[2][m] = cfr[3][m] = C(0);
+    for (int m = 0; m < RPW; ++m) cfr[m] = SlopeCoef<C>{C(0), C(0), C(0), C(0)};
     if (run) {
 #pragma unroll
         for (int m = 0; m < RPW; ++m) {
             const int r = wv + NWB * m;
             if (r < 1 || r >= H - 1 || !act[m]) continue;
-            // column sums of the gradient stencils (see the stages below),
-            // every lane for its own column, passed to the neighbours
-            const C rc = X[0][r][lane], rN = X[0][r + 1][lane], rS = X[0][r - 1][lane];
-            const C uc = X[1][r][lane], uN = X[1][r + 1][lane], uS = X[1][r - 1][lane];
-            const C vN = X[2][r + 1][lane], vS = X[2][r - 1][lane];
-            const C sr = (rN + rS) + C(4) * rc, dr = rN - rS;
-            const C su = (uN + uS) + C(4) * uc, dv = vN - vS;
-            const C srW = lane_from_left(sr), srE = lane_from_right(sr);
-            const C drW = lane_from_left(dr), drE = lane_from_right(dr);
-            const C suW = lane_from_left(su), suE = lane_from_right(su);
-            const C dvW = lane_from_left(dv), dvE = lane_from_right(dv);
-            if (lane < 1 || lane >= 63) continue;
-            const double rho = (double)rc;
-            // 12 d_x rho, 12 d_y rho and 12 div v from the column sums
-            const C gx = srE - srW, gy = fma(C(4), dr, drW + drE);
-            const double div12 = (double)((suE - suW) + fma(C(4), dv, dvW + dvE));
-            // A w = (R/c_v) div v / D1 and B w = (a/c_v) rho div v / D2 with
-            // D1 = 1 - b rho, D2 = 1 + 2 b rho - b^2 rho^2; one reciprocal
-            // 1/(rho D1 D2) gives 1/rho, 1/D1 and 1/D2
-            const double D1 = 1.0 - P.b * rho;
-            const double D2 = 1.0 + 2.0 * P.b * rho - P.b * P.b * rho * rho;
-            const double inv = rcp_nr(rho * D1 * D2);
-            // the stages read the column sums unscaled: 12 d_x T and 12 d_y T,
-            // so the advection coefficients carry the 1/12
-            // (a_x/12 = (chi/rho) d_x rho/12 - v_x/12 = (chi/rho) gx/144 - v_x/12)
-            const C k144 = (C)(P.chi * (1.0 / 144.0) * D1 * D2 * inv);
-            cfr[0][m] = fma(k144, gx, -uc * C(1.0 / 12.0));
-            cfr[1][m] = fma(k144, gy, -X[2][r][lane] * C(1.0 / 12.0));
-            const double Aw = P.R_cv12 * div12 * (rho * D2 * inv), Bw = P.a_cv12 * rho * div12 * (rho * D1 * inv);
-            cfr[2][m] = (C)(Bw * P.k2_Tc - Aw);
-            cfr[3][m] = (C)(-Bw * P.k1k_rsTc);
+            cfr[m] = slope_coef<C>(P, X[0][r][lane], X[0][r + 1][lane], X[0][r - 1][lane], X[1][r][lane],
+                                   X[1][r + 1][lane], X[1][r - 1][lane], X[2][r][lane], X[2][r + 1][lane],
+                                   X[2][r - 1][lane]);
         }
 
         const C Tref = (C)P.T_ref;
@@ -937,27 +1064,11 @@ __global__ __launch_bounds__(64 * NWB) void k_thermal(const Inst *__restrict__ i
             for (int m = 0; m < RPW; ++m) {
                 const int r = wv + NWB * m;
                 if (r >= H || r < HB - rad || r >= HB + TY + rad) continue;
-                // Column sums of the 3x3 stencil, formed by every lane for its
-                // own column and passed to the neighbouring columns:
-                // v = T_S + 4 T_c + T_N, w = T_N - T_S give
-                //   d_x T = (v_E - v_W)/12, d_y T = (w_W + 4 w + w_E)/12,
-                //   lap T = (v_W + v_E + 4 v - 36 T_c)/6,
-                // the isotropic stencils of the gradient and the Laplacian
-                // (the 1/12 and 1/6 are carried by the coefficients).
-                const C tc = in[r][lane], tN = in[r + 1][lane], tS = in[r - 1][lane];
-                const C v = fma(C(4), tc, tN + tS), w = tN - tS;
-                const C vW = lane_from_left(v), vE = lane_from_right(v);
-                const C wW = lane_from_left(w), wE = lane_from_right(w);
+                const StageCols<C> sc_ = stage_cols<C>(in[r][lane], in[r + 1][lane], in[r - 1][lane]);
                 if (lane < HB - rad || lane >= HB + TXB + rad) continue;
                 C h = C(0);
                 if (act[m]) {
-                    const C T = Tref + tc;
-                    const C lap6 = fma(C(-36), tc, fma(C(4), v, vW + vE));
-                    h = cfr[2][m] * T;
-                    h = fma(cfr[3][m], stage_sqrt(T), h);
-                    h = fma(chi6, lap6, h);
-                    h = fma(cfr[0][m], vE - vW, h);
-                    h = fma(cfr[1][m], fma(C(4), w, wW + wE), h);
+                    h = stage_slope<C>(sc_, cfr[m], Tref, chi6);
                     acc[m] = st == 0 ? h : fma(wst[st], h, acc[m]);
                 }
                 if (st < 3) Ts[st & 1][r][lane] = fma(cst[st], h, T0[r][lane]);
@@ -1036,9 +1147,10 @@ __global__ void k_set_state(DevParams P, const double *__restrict__ rho, const d
     }
 }
 
-// Mass partials of the current (post-streaming) state, plain sum of f.
+// Mass partials of the current (post-streaming) state, plain sum of f, one
+// per block of NT threads.
 template <typename S>
-__global__ __launch_bounds__(NT) void k_mass(DevParams P, const S *__restrict__ f, double *__restrict__ part)
+__device__ __forceinline__ void mass_partial(const DevParams &P, const S *__restrict__ f, double *__restrict__ part)
 {
     __shared__ double red[NT / 64];
     const size_t N = (size_t)P.nx * P.ny;
@@ -1053,6 +1165,12 @@ __global__ __launch_bounds__(NT) void k_mass(DevParams P, const S *__restrict__ 
     }
     const double s = block_sum(m, red);
     if (threadIdx.x == 0) part[blockIdx.x] = s;
+}
+
+template <typename S>
+__global__ __launch_bounds__(NT) void k_mass(DevParams P, const S *__restrict__ f, double *__restrict__ part)
+{
+    mass_partial<S>(P, f, part);
 }
 
 __global__ void k_reduce_mass(DevParams P, const double *__restrict__ part, int n, Scalars *sc)

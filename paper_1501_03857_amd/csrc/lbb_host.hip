@@ -5,6 +5,7 @@
 #include "lbboil.h"
 
 #include "lbb_device.hpp"
+#include "lbb_step.hpp"
 #include "lbb_adjoint.hpp"
 
 #include <hip/hip_runtime.h>
@@ -221,10 +222,16 @@ struct lbb_domain {
     void *f[2] = {nullptr, nullptr};
     void *T[2] = {nullptr, nullptr};
     void *rho = nullptr, *vx = nullptr, *vy = nullptr;
-    double *mass_part = nullptr, *hf_part = nullptr, *Tb_dev = nullptr;
+    long long *mass_part = nullptr;
+    double *hf_part = nullptr, *Tb_dev = nullptr;
     lbb::Scalars *sc = nullptr;
     int nbxA = 0, nbyA = 0, nbxB = 0, nbyB = 0;
     int shA = 0, shB = 0;                // tile shapes (indices into kShapeA, kShapeB)
+    bool fixed_tiles = false;            // shapes chosen by the caller: two launches per step in them
+    int nbxF = 0, nbyF = 0, tyF = 0;     // tiles of the one-launch step (tyF = 0: not for this lattice)
+    long long *rel = nullptr;
+    lbb::MassSum *mpart = nullptr;
+    int *d_blkF = nullptr;
     int cf = 0, cT = 0;
     lbb::Inst *d_inst = nullptr;         // this lattice as a one-entry launch table
     int *d_blkA = nullptr, *d_blkB = nullptr;
@@ -318,6 +325,10 @@ void make_dev_params(const lbb_params &p, double Tc, double kap, lbb::DevParams 
     q.k1k_rsTc = kap * (1.0 + kap) / std::sqrt(Tc);
     q.R_cv12 = p.R / (12.0 * p.cv);
     q.a_cv12 = p.a / (12.0 * p.cv);
+    int e = 0;
+    (void)std::frexp(8.0 / p.b, &e);  // 2^(e-1) <= 8/b < 2^e
+    q.mass_c = std::ldexp(1.5, e);
+    q.mass_q = std::ldexp(1.0, e - 52);
 }
 
 uint64_t param_hash(const lbb_params &p)
@@ -350,6 +361,13 @@ lbb::Inst make_inst(const lbb_domain *d)
     I.nbyB = d->nbyB;
     I.blkA0 = 0;
     I.blkB0 = 0;
+    I.rel = d->rel;
+    I.mpart = d->mpart;
+    I.nbxF = d->nbxF;
+    I.nbyF = d->nbyF;
+    I.tyF = d->tyF;
+    I.npF = d->nbxF * d->nbyF;
+    I.blkF0 = 0;
     return I;
 }
 
@@ -402,6 +420,74 @@ void launch_thermal(hipStream_t st, const lbb::Inst *insts, const int *blk, int 
     }
 }
 
+// ---- the one-launch step (k_step) ----
+//
+// Where it is taken.  Its tiles recompute a halo of five rows and columns, so
+// it pays while a step is bound by launch and phase latencies, not by the work
+// itself: when tiles of some height fit the compute units in one round.  Timed
+// on graph replays, one launch against two (us per step): 128x64 FP64 7.1
+// against 13.6, 301x77 FP32 6.9 against 12.4, 600x151 FP32 9.2 against 13.1,
+// 511x257 FP64 12.1 against 15.8, 512x256 FP32 10.2 against 13.2, 1024x512 FP32
+// 21.6 against 23.0.  One block more than compute units costs a second round
+// (600x151: 18.3 with 912 blocks, 14.6 with 612, 9.2 with 228), and a block
+// alone on a compute unit cannot hide its loads under another's arithmetic
+// (2048x1024: 77 against 64), so larger lattices take two launches.
+//
+// The height is the smallest that fits one round, but at least 4: lower tiles
+// only add halo (128x64: 7.0-7.1 for heights 1 to 4; 256x128 FP64 8.1 with 3
+// and 7.9 with 4; 600x151 9.2 with 8, 10.1 with 13, 12.6 with 22).
+struct StepDims {
+    int nx, ny;
+};
+
+constexpr int kStepMinHeight = 4;
+// region rows a block of 16 waves has room for: four rows a wave in FP32,
+// three in FP64 (whose planes take twice the LDS)
+constexpr int step_max_rows(int precision) { return precision == LBB_FP64 ? 48 : 64; }
+
+int64_t step_tiles(const StepDims &l, int ty)
+{
+    return (int64_t)((l.nx + lbb::TXF - 1) / lbb::TXF) * ((l.ny + ty - 1) / ty);
+}
+
+// Tile height of the one-launch step for lattices that step together, each
+// with one more block for its bookkeeping; 0 when none fits one round.
+int step_height(const std::vector<StepDims> &ls, int precision, int mode, int ncu)
+{
+    if (mode != LBB_COUPLED) return 0;
+    for (int ty = kStepMinHeight; ty + 2 * lbb::HF <= step_max_rows(precision); ++ty) {
+        int64_t blocks = 0;
+        for (const StepDims &l : ls) blocks += step_tiles(l, ty) + 1;
+        if (blocks <= ncu) return ty;
+    }
+    return 0;
+}
+
+// Compute units of the current device (0 if it cannot be asked).
+int compute_units()
+{
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    return n;
+}
+
+// The block shape follows from the height: 16 waves with as few rows each as
+// hold the tile and its halo.
+template <typename S>
+void launch_step(hipStream_t st, const lbb::Inst *insts, const int *blk, int nblocks, int cf, int cT, int par, int aux,
+                 int ty)
+{
+    using namespace lbb;
+    const dim3 g(nblocks), b(1024);
+    const int rows = ty + 2 * HF;
+    if (rows <= 16) hipLaunchKernelGGL((k_step<S, 16, 1>), g, b, 0, st, insts, blk, cf, cT, par, aux);
+    else if (rows <= 32) hipLaunchKernelGGL((k_step<S, 16, 2>), g, b, 0, st, insts, blk, cf, cT, par, aux);
+    else if (rows <= 48) hipLaunchKernelGGL((k_step<S, 16, 3>), g, b, 0, st, insts, blk, cf, cT, par, aux);
+    else if constexpr (sizeof(S) == 4)
+        hipLaunchKernelGGL((k_step<S, 16, 4>), g, b, 0, st, insts, blk, cf, cT, par, aux);
+}
+
 template <typename S>
 void launch_lb(lbb_domain *d, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr)
 {
@@ -421,6 +507,14 @@ void set_grid(lbb_domain *d)
     d->nbyA = (d->p.ny + lbb::kShapeA[d->shA].ty - 1) / lbb::kShapeA[d->shA].ty;
     d->nbxB = (d->p.nx + lbb::TXB - 1) / lbb::TXB;
     d->nbyB = (d->p.ny + lbb::kShapeB[d->shB].ty - 1) / lbb::kShapeB[d->shB].ty;
+}
+
+// Tiles of the one-launch step in tiles of height ty (0: two launches).
+void set_step_grid(lbb_domain *d, int ty)
+{
+    d->tyF = ty;
+    d->nbxF = ty ? (d->p.nx + lbb::TXF - 1) / lbb::TXF : 0;
+    d->nbyF = ty ? (d->p.ny + ty - 1) / ty : 0;
 }
 
 // Largest block counts over all tile shapes (sizes of the partial-sum and
@@ -444,18 +538,33 @@ void advance_buffers(lbb_domain *d)
     if (d->dp.mode != lbb::MODE_ISOTHERMAL) d->cT ^= 1;
 }
 
+bool one_launch(const lbb_domain *d) { return d->tyF > 0 && !d->fixed_tiles; }
+
+// Step number k of a sequence that ends in enqueue_flush.
 template <typename S>
-void enqueue_step(lbb_domain *d)
+void enqueue_step(lbb_domain *d, int64_t k)
 {
-    launch_lb<S>(d);
-    launch_thermal<S>(d);
+    if (one_launch(d)) {
+        launch_step<S>(d->stream, d->d_inst, d->d_blkF, d->nbxF * d->nbyF + 1, d->cf, d->cT, (int)(k & 1), 0, d->tyF);
+    } else {
+        launch_lb<S>(d);
+        launch_thermal<S>(d);
+    }
     advance_buffers(d);
 }
 
-void enqueue_step_any(lbb_domain *d)
+void enqueue_step_any(lbb_domain *d, int64_t k)
 {
-    if (d->p.precision == LBB_FP64) enqueue_step<double>(d);
-    else enqueue_step<float>(d);
+    if (d->p.precision == LBB_FP64) enqueue_step<double>(d, k);
+    else enqueue_step<float>(d, k);
+}
+
+// Heat-flux bookkeeping of the last state of `n` lattices' sequences.
+void launch_flush(hipStream_t st, const lbb::Inst *insts, int n, bool one, int precision, int cf, int cT)
+{
+    if (!one) hipLaunchKernelGGL(lbb::k_flush_heat_flux, dim3(n), dim3(lbb::NT), 0, st, insts);
+    else if (precision == LBB_FP64) hipLaunchKernelGGL(lbb::k_flush_step<double>, dim3(n), dim3(lbb::NT), 0, st, insts, cf, cT);
+    else hipLaunchKernelGGL(lbb::k_flush_step<float>, dim3(n), dim3(lbb::NT), 0, st, insts, cf, cT);
 }
 
 void drop_graphs(lbb_domain *d)
@@ -472,7 +581,7 @@ int build_graph(lbb_domain *d, hipGraphExec_t *out)
 {
     const int cf = d->cf, cT = d->cT;
     LBB_HIP(hipStreamBeginCapture(d->stream, hipStreamCaptureModeThreadLocal));
-    for (int k = 0; k < kGraphSteps; ++k) enqueue_step_any(d);
+    for (int k = 0; k < kGraphSteps; ++k) enqueue_step_any(d, k);
     hipGraph_t g = nullptr;
     LBB_HIP(hipStreamEndCapture(d->stream, &g));
     d->cf = cf;  // capture recorded the launches; the state did not move
@@ -495,8 +604,8 @@ int enqueue_steps(lbb_domain *d, int64_t n)
         // the buffers return to the same parity after an even number of steps
         n -= kGraphSteps;
     }
-    for (int64_t k = 0; k < n; ++k) enqueue_step_any(d);
-    hipLaunchKernelGGL(lbb::k_flush_heat_flux, dim3(1), dim3(lbb::NT), 0, d->stream, d->d_inst);
+    for (int64_t k = 0; k < n; ++k) enqueue_step_any(d, k);
+    launch_flush(d->stream, d->d_inst, 1, one_launch(d), d->p.precision, d->cf, d->cT);
     LBB_HIP(hipGetLastError());
     return LBB_OK;
 }
@@ -523,8 +632,10 @@ int refresh_reductions(lbb_domain *d)
 {
     using namespace lbb;
     const int nm = d->nbxA * d->nbyA;
-    hipLaunchKernelGGL(k_mass<S>, dim3(nm), dim3(NT), 0, d->stream, d->dp, static_cast<const S *>(d->f[d->cf]), d->mass_part);
-    hipLaunchKernelGGL(k_reduce_mass, dim3(1), dim3(NT), 0, d->stream, d->dp, d->mass_part, nm, d->sc);
+    hipLaunchKernelGGL(k_mass<S>, dim3(nm), dim3(NT), 0, d->stream, d->dp, static_cast<const S *>(d->f[d->cf]),
+                       reinterpret_cast<double *>(d->mass_part));
+    hipLaunchKernelGGL(k_reduce_mass, dim3(1), dim3(NT), 0, d->stream, d->dp,
+                       reinterpret_cast<const double *>(d->mass_part), nm, d->sc);
     hipLaunchKernelGGL(k_heat_flux_state<S>, dim3(d->nbxB), dim3(64), 0, d->stream, d->dp,
                        static_cast<const S *>(d->f[d->cf]), static_cast<const S *>(d->T[d->cT]), d->hf_part,
                        (double *)nullptr);
@@ -583,7 +694,8 @@ void release(lbb_domain *d)
     for (void *q : {d->f[0], d->f[1], d->T[0], d->T[1], d->rho, d->vx, d->vy})
         if (q) (void)hipFree(q);
     for (void *q : {(void *)d->mass_part, (void *)d->hf_part, (void *)d->Tb_dev, (void *)d->sc,
-                    (void *)d->d_inst, (void *)d->d_blkA, (void *)d->d_blkB, d->adj_mem})
+                    (void *)d->d_inst, (void *)d->d_blkA, (void *)d->d_blkB, (void *)d->d_blkF, (void *)d->rel,
+                    (void *)d->mpart, d->adj_mem})
         if (q) (void)hipFree(q);
     if (d->stream) (void)hipStreamDestroy(d->stream);
     delete d;
@@ -748,6 +860,7 @@ int lbb_init_domain(const lbb_params *pin, const double *T_bottom, const double 
     d->Tb = Tb;
     make_dev_params(p, Tc, kap, d->dp);
     set_grid(d);
+    set_step_grid(d, step_height({{p.nx, p.ny}}, p.precision, p.thermal_mode, prop.multiProcessorCount));
     const lbb_param_dims dims{p.nx, p.ny};
     const int mbA = max_blocks_A(dims), mbB = max_blocks_B(dims);
 
@@ -770,6 +883,11 @@ int lbb_init_domain(const lbb_params *pin, const double *T_bottom, const double 
     ok = ok && alloc((void **)&d->d_inst, sizeof(lbb::Inst));
     ok = ok && alloc((void **)&d->d_blkA, (size_t)(mbA + 1) * sizeof(int));
     ok = ok && alloc((void **)&d->d_blkB, (size_t)(mbB + 1) * sizeof(int));
+    if (d->tyF) {
+        const size_t np = (size_t)d->nbxF * d->nbyF;
+        ok = ok && alloc((void **)&d->rel, 2 * sizeof(long long)) && alloc((void **)&d->mpart, 2 * np * sizeof(lbb::MassSum));
+        ok = ok && alloc((void **)&d->d_blkF, (np + 1) * sizeof(int));
+    }
     if (!ok) {
         (void)hipGetLastError();
         release(d);
@@ -1113,6 +1231,9 @@ struct lbb_batch {
     int cf = 0, cT = 0;
     int precision = 0, mode = 0;
     int shA = 0, shB = 0;                // tile shapes of the batch's launches
+    bool fixed_tiles = false;            // shapes chosen by the caller
+    int tyF = 0, totF = 0;               // one-launch step: tile height (0: two launches), blocks
+    int *d_blkF = nullptr;
     hipGraphExec_t graph[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
     void *adj_mem = nullptr;             // adjoint workspace, kept between calls
     size_t adj_bytes = 0;
@@ -1126,7 +1247,7 @@ static void batch_release(lbb_batch *b)
     for (auto &row : b->graph)
         for (auto &g : row)
             if (g) (void)hipGraphExecDestroy(g);
-    for (void *q : {(void *)b->d_insts, (void *)b->d_blkA, (void *)b->d_blkB, b->adj_mem})
+    for (void *q : {(void *)b->d_insts, (void *)b->d_blkA, (void *)b->d_blkB, (void *)b->d_blkF, b->adj_mem})
         if (q) (void)hipFree(q);
     if (b->stream) (void)hipStreamDestroy(b->stream);
     for (lbb_domain *d : b->doms) release(d);
@@ -1161,6 +1282,19 @@ static int batch_tables(lbb_batch *b)
     return LBB_OK;
 }
 
+// The one-launch grid of member d in the batch's launches (its own grid when
+// it steps alone may have lower tiles), first block f0.
+static void batch_step_grid(const lbb_batch *b, const lbb_domain *d, int f0, lbb::Inst &I)
+{
+    I.tyF = b->tyF;
+    I.nbxF = b->tyF ? (d->p.nx + lbb::TXF - 1) / lbb::TXF : 0;
+    I.nbyF = b->tyF ? (d->p.ny + b->tyF - 1) / b->tyF : 0;
+    I.npF = I.nbxF * I.nbyF;
+    I.blkF0 = f0;
+}
+
+static bool one_launch(const lbb_batch *b) { return b->tyF > 0 && !b->fixed_tiles; }
+
 // Upload the launch table (all members, with their block offsets); members
 // take the batch's tile shapes.
 static int batch_push(lbb_batch *b)
@@ -1182,13 +1316,15 @@ static int batch_push(lbb_batch *b)
         batch_drop_graphs(b);
     }
     std::vector<lbb::Inst> insts;
-    int a0 = 0, b0 = 0;
+    int a0 = 0, b0 = 0, f0 = 0;
     for (lbb_domain *d : b->doms) {
         lbb::Inst I = make_inst(d);
         I.blkA0 = a0;
         I.blkB0 = b0;
         a0 += d->nbxA * d->nbyA + 1;
         b0 += d->nbxB * d->nbyB + 1;
+        batch_step_grid(b, d, f0, I);
+        f0 += I.npF + 1;
         insts.push_back(I);
     }
     LBB_HIP(hipMemcpyAsync(b->d_insts, insts.data(), insts.size() * sizeof(lbb::Inst), hipMemcpyHostToDevice,
@@ -1197,9 +1333,16 @@ static int batch_push(lbb_batch *b)
     return LBB_OK;
 }
 
-static void batch_enqueue_step(lbb_batch *b)
+// Step number k of a sequence that ends in launch_flush.
+static void batch_enqueue_step(lbb_batch *b, int64_t k)
 {
-    if (b->precision == LBB_FP64) {
+    if (one_launch(b)) {
+        const int par = (int)(k & 1);
+        if (b->precision == LBB_FP64)
+            launch_step<double>(b->stream, b->d_insts, b->d_blkF, b->totF, b->cf, b->cT, par, 0, b->tyF);
+        else
+            launch_step<float>(b->stream, b->d_insts, b->d_blkF, b->totF, b->cf, b->cT, par, 0, b->tyF);
+    } else if (b->precision == LBB_FP64) {
         launch_lb<double>(b->stream, b->d_insts, b->d_blkA, b->totA, b->cf, b->cT, b->shA);
         launch_thermal<double>(b->stream, b->d_insts, b->d_blkB, b->totB, b->cf, b->cT, b->shB);
     } else {
@@ -1239,7 +1382,15 @@ extern "C" int lbb_batch_init(const lbb_params *ps, int n, const double *const *
         capA += max_blocks_A(dims) + 1;
         capB += max_blocks_B(dims) + 1;
     }
+    std::vector<StepDims> dims;
+    for (lbb_domain *d : b->doms) dims.push_back({d->p.nx, d->p.ny});
+    b->tyF = step_height(dims, b->precision, b->mode, compute_units());
+    std::vector<int> tf;  // block -> member of the one-launch step
+    for (int i = 0; i < n && b->tyF; ++i) tf.insert(tf.end(), step_tiles(dims[i], b->tyF) + 1, i);
+    b->totF = (int)tf.size();
     bool ok = hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking) == hipSuccess &&
+              (tf.empty() || (hipMalloc(&b->d_blkF, tf.size() * sizeof(int)) == hipSuccess &&
+                              hipMemcpy(b->d_blkF, tf.data(), tf.size() * sizeof(int), hipMemcpyHostToDevice) == hipSuccess)) &&
               hipMalloc(&b->d_insts, n * sizeof(lbb::Inst)) == hipSuccess &&
               hipMalloc(&b->d_blkA, capA * sizeof(int)) == hipSuccess &&
               hipMalloc(&b->d_blkB, capB * sizeof(int)) == hipSuccess && batch_tables(b) == LBB_OK;
@@ -1278,7 +1429,7 @@ extern "C" int lbb_batch_step_async(lbb_batch *b, int64_t n)
         if (!g) {
             const int cf = b->cf, cT = b->cT;
             LBB_HIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-            for (int k = 0; k < kGraphSteps; ++k) batch_enqueue_step(b);
+            for (int k = 0; k < kGraphSteps; ++k) batch_enqueue_step(b, k);
             hipGraph_t gr = nullptr;
             LBB_HIP(hipStreamEndCapture(b->stream, &gr));
             b->cf = cf;
@@ -1290,8 +1441,8 @@ extern "C" int lbb_batch_step_async(lbb_batch *b, int64_t n)
         LBB_HIP(hipGraphLaunch(g, b->stream));
         n -= kGraphSteps;
     }
-    for (int64_t k = 0; k < n; ++k) batch_enqueue_step(b);
-    hipLaunchKernelGGL(lbb::k_flush_heat_flux, dim3((unsigned)b->doms.size()), dim3(lbb::NT), 0, b->stream, b->d_insts);
+    for (int64_t k = 0; k < n; ++k) batch_enqueue_step(b, k);
+    launch_flush(b->stream, b->d_insts, (int)b->doms.size(), one_launch(b), b->precision, b->cf, b->cT);
     LBB_HIP(hipGetLastError());
     for (lbb_domain *d : b->doms) {
         d->cf = b->cf;
@@ -1523,6 +1674,7 @@ int lbb_set_tiles(lbb_domain *d, int32_t shape_lb, int32_t shape_thermal)
     if (!d) return fail(LBB_EINVAL, "domain is NULL");
     if (!valid_shapes(shape_lb, shape_thermal)) return fail(LBB_EINVAL, "unknown tile shape");
     LBB_HIP(hipStreamSynchronize(d->stream));
+    d->fixed_tiles = true;
     return domain_set_tiles(d, shape_lb, shape_thermal);
 }
 
@@ -1562,6 +1714,8 @@ int lbb_batch_set_tiles(lbb_batch *b, int32_t shape_lb, int32_t shape_thermal)
     LBB_HIP(hipStreamSynchronize(b->stream));
     b->shA = shape_lb;
     b->shB = shape_thermal;
+    b->fixed_tiles = true;
+    batch_drop_graphs(b);
     return batch_push(b);
 }
 
@@ -1632,6 +1786,10 @@ struct AdjGroup {
     const int *blkA = nullptr, *blkB = nullptr;
     int totA = 0, totB = 0;
     std::vector<int> blkA0, blkB0;  // member offsets in the forward grids
+    // one-launch forward steps (tyF > 0): blocks, table, the members' grids
+    int tyF = 0, totF = 0;
+    const int *blkF = nullptr;
+    std::function<void(int, lbb::Inst &)> step_grid;
     int *cf = nullptr, *cT = nullptr;
     int shA = 0, shB = 0;           // tile shapes of the forward launches
     void **mem = nullptr;           // cached workspace of the owner
@@ -1809,8 +1967,19 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
     };
     auto slot_step = [&](hipStream_t s, int b, int64_t k) {
         const Inst *tab = inst_seg + ((size_t)b * K + k) * nm;
+        if (g.tyF) {
+            launch_step<S>(s, tab, g.blkF, g.totF, 0, 0, (int)(k & 1), 0, g.tyF);
+            return;
+        }
         launch_lb<S>(s, tab, g.blkA, g.totA, 0, 0, g.shA);
         launch_thermal<S>(s, tab, g.blkB, g.totB, 0, 0, g.shB);
+    };
+    // a sequence of one-launch steps starts with its launch counts at zero
+    auto restart = [&](hipStream_t s) -> hipError_t {
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < nm && g.tyF && e == hipSuccess; ++i)
+            e = hipMemsetAsync(g.doms[i]->rel, 0, 2 * sizeof(long long), s);
+        return e;
     };
     // buffer holding segment sg's states (the last segment uses buffer 0)
     auto buf_of = [&](int64_t sg) { return (int)((nck - 1 - sg) & 1); };
@@ -1844,6 +2013,7 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
                 I.T[1] = y + 9 * n;
                 I.blkA0 = g.blkA0[i];
                 I.blkB0 = g.blkB0[i];
+                if (g.tyF) g.step_grid(i, I);
                 hinst[((size_t)b * K + k) * nm + i] = I;
             }
         AdjInst A{};
@@ -1904,7 +2074,9 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
             ++t;
         }
     }
-    hipLaunchKernelGGL(k_flush_heat_flux, dim3(nm), dim3(NT), 0, st, g.fwd_insts);
+    // the last state is slot N - tL, the second state of the step before it
+    launch_flush(st, g.tyF ? inst_seg + (size_t)(N - tL - 1) * nm : g.fwd_insts, nm, g.tyF > 0,
+                 sizeof(S) == 8 ? LBB_FP64 : LBB_FP32, 1, 1);
     LBB_HIP(hipStreamSynchronize(st));
     std::vector<Scalars> s1(nm);
     for (int i = 0; i < nm; ++i) {
@@ -1939,6 +2111,7 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
             if (e == hipSuccess)
                 e = hipMemcpyAsync(g.doms[i]->sc, &m[i].ck_sc[sg], sizeof(Scalars), hipMemcpyDeviceToDevice, rs.c);
         }
+        if (e == hipSuccess) e = restart(rs.c);
         if (e != hipSuccess) return e;
         for (int64_t t = t0; t + 1 < t1; ++t) slot_step(rs.c, b, t - t0);
         e = hipGetLastError();
@@ -1975,6 +2148,7 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
         LBB_HIP(hipMemcpyAsync(&gGw[i], m[i].w.scal + 2, sizeof(double), hipMemcpyDeviceToHost, st));
     }
     // restore every lattice's state
+    LBB_HIP(restart(st));
     for (int i = 0; i < nm; ++i) {
         lbb_domain *d = g.doms[i];
         const size_t n = m[i].n;
@@ -2046,6 +2220,12 @@ extern "C" int lbb_adjoint(lbb_domain *d, int64_t N, int64_t K, const int32_t *h
     g.cT = &d->cT;
     g.shA = d->shA;
     g.shB = d->shB;
+    if (one_launch(d)) {
+        g.tyF = d->tyF;
+        g.totF = d->nbxF * d->nbyF + 1;
+        g.blkF = d->d_blkF;
+        g.step_grid = [](int, lbb::Inst &) {};  // as make_inst sets it
+    }
     const size_t before = d->adj_bytes;
     g.mem = &d->adj_mem;
     g.bytes = &d->adj_bytes;
@@ -2089,6 +2269,14 @@ extern "C" int lbb_batch_adjoint(lbb_batch *b, int64_t N, int64_t K, double *J, 
     g.cT = &b->cT;
     g.shA = b->shA;
     g.shB = b->shB;
+    if (one_launch(b)) {
+        g.tyF = b->tyF;
+        g.totF = b->totF;
+        g.blkF = b->d_blkF;
+        std::vector<int> f0(1, 0);
+        for (lbb_domain *d : b->doms) f0.push_back(f0.back() + (int)step_tiles({d->p.nx, d->p.ny}, b->tyF) + 1);
+        g.step_grid = [b, f0](int i, lbb::Inst &I) { batch_step_grid(b, b->doms[i], f0[i], I); };
+    }
     g.mem = &b->adj_mem;
     g.bytes = &b->adj_bytes;
     g.held = &b->held;
@@ -2163,11 +2351,12 @@ int noalloc_scratch(int dev, unsigned char **out)
 // Byte offsets of the pieces of the scratch array for one lattice (default
 // tile shapes), each 256-byte aligned; `total` is the bytes needed.
 struct NoallocLayout {
-    size_t inst, sc, blkA, blkB, mass, hf, total;
+    size_t inst, sc, blkA, blkB, mass, hf, rel, mpart, blkF, total;
     int nbxA, nbyA, nbxB, nbyB;
+    int tyF, nbxF, nbyF;  // one-launch step (tyF = 0: two launches)
 };
 
-NoallocLayout noalloc_layout(int nx, int ny)
+NoallocLayout noalloc_layout(int nx, int ny, int precision, int mode, int ncu)
 {
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     NoallocLayout L{};
@@ -2191,13 +2380,31 @@ NoallocLayout noalloc_layout(int nx, int ny)
     L.hf = o;
     o += up((size_t)L.nbxB * sizeof(double));
     L.total = o;
+    // the one-launch step adds its partials only where they fit as well
+    const int ty = step_height({{nx, ny}}, precision, mode, ncu);
+    const size_t np = ty ? (size_t)step_tiles({nx, ny}, ty) : 0;
+    L.rel = o;
+    o += up(2 * sizeof(long long));
+    L.mpart = o;
+    o += up(2 * np * sizeof(lbb::MassSum));
+    L.blkF = o;
+    o += up((np + 1) * sizeof(int));
+    if (ty && o <= LBB_NOALLOC_SCRATCH_BYTES) {
+        L.tyF = ty;
+        L.nbxF = (nx + lbb::TXF - 1) / lbb::TXF;
+        L.nbyF = (ny + ty - 1) / ty;
+        L.total = o;
+    }
     return L;
 }
 
-// Launch table, zeroed block maps (a single lattice: every block belongs to
-// entry 0) and reset scalars, written by a kernel so that nothing is copied
-// from host memory and no memset node is involved.
-__global__ void k_noalloc_setup(lbb::Inst I, lbb::Inst *inst, int *blkA, int nA, int *blkB, int nB, lbb::Scalars *sc)
+// Mass partials of the given state (k_mass), and the launch table, zeroed
+// block maps (a single lattice: every block belongs to entry 0) and reset
+// scalars, written by the kernel so that nothing is copied from host memory
+// and no memset node is involved.
+template <typename S>
+__global__ __launch_bounds__(lbb::NT) void k_noalloc_begin(lbb::Inst I, const S *f, lbb::Inst *inst, int *blkA, int nA,
+                                                           int *blkB, int nB, int *blkF, lbb::Scalars *sc, double *part)
 {
     const int tid = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
     if (tid == 0) {
@@ -2205,14 +2412,17 @@ __global__ void k_noalloc_setup(lbb::Inst I, lbb::Inst *inst, int *blkA, int nA,
         lbb::Scalars s{};
         s.err_step = ~0ULL;
         *sc = s;
+        if (I.tyF) I.rel[0] = I.rel[1] = 0;
     }
     for (int k = tid; k < nA; k += stride) blkA[k] = 0;
     for (int k = tid; k < nB; k += stride) blkB[k] = 0;
+    for (int k = tid; k <= I.npF; k += stride)
+        if (I.tyF) blkF[k] = 0;
+    lbb::mass_partial<S>(I.P, f, part);
 }
 
-__global__ void k_noalloc_result(const lbb::Scalars *sc, lbb_noalloc_result *out)
+__device__ void noalloc_result(const lbb::Scalars *sc, lbb_noalloc_result *out)
 {
-    if (threadIdx.x != 0) return;
     lbb_noalloc_result r{};
     r.q_now = sc->q_now;
     r.n_samples = sc->n_samples;
@@ -2220,6 +2430,20 @@ __global__ void k_noalloc_result(const lbb::Scalars *sc, lbb_noalloc_result *out
     r.err_step = sc->err_step == ~0ULL ? -1 : (int64_t)sc->err_step;
     r.err_code = sc->err_code;
     *out = r;
+}
+
+__global__ void k_noalloc_result(const lbb::Scalars *sc, lbb_noalloc_result *out)
+{
+    if (threadIdx.x == 0) noalloc_result(sc, out);
+}
+
+// End of a sequence of one-launch steps and the result (thread 0 writes the
+// scalars it then reads).
+template <typename S>
+__global__ __launch_bounds__(lbb::NT) void k_noalloc_end(const lbb::Inst *inst, int cf, int cT, lbb_noalloc_result *out)
+{
+    lbb::flush_step<S>(*inst, cf, cT);
+    if (threadIdx.x == 0) noalloc_result(inst->sc, out);
 }
 
 // The work of lbb_step_noalloc after validation: the set-up reductions of
@@ -2233,14 +2457,24 @@ void noalloc_enqueue(const lbb::Inst &I, unsigned char *base, const NoallocLayou
     Inst *inst = reinterpret_cast<Inst *>(base + L.inst);
     Scalars *sc = reinterpret_cast<Scalars *>(base + L.sc);
     int *blkA = reinterpret_cast<int *>(base + L.blkA);
-    int *blkB = reinterpret_cast<int *>(base + L.blkB);
+    int *blkB = reinterpret_cast<int *>(base + L.blkB), *blkF = reinterpret_cast<int *>(base + L.blkF);
     const int nA = L.nbxA * L.nbyA + 1, nB = L.nbxB * L.nbyB + 1;
-    hipLaunchKernelGGL(k_noalloc_setup, dim3((std::max(nA, nB) + 255) / 256), dim3(256), 0, st, I, inst, blkA, nA,
-                       blkB, nB, sc);
     const int nm = L.nbxA * L.nbyA;
     const S *f = static_cast<const S *>(I.f[cf]);
-    hipLaunchKernelGGL(k_mass<S>, dim3(nm), dim3(NT), 0, st, I.P, f, I.mass_part);
-    hipLaunchKernelGGL(k_reduce_mass, dim3(1), dim3(NT), 0, st, I.P, I.mass_part, nm, sc);
+    double *part = reinterpret_cast<double *>(I.mass_part);
+    hipLaunchKernelGGL(k_noalloc_begin<S>, dim3(nm), dim3(NT), 0, st, I, f, inst, blkA, nA, blkB, nB, blkF,
+                       sc, part);
+    hipLaunchKernelGGL(k_reduce_mass, dim3(1), dim3(NT), 0, st, I.P, part, nm, sc);
+    if (L.tyF && n > 0) {
+        // the first launch samples the heat flux of the given state itself
+        for (int64_t k = 0; k < n; ++k) {
+            launch_step<S>(st, inst, blkF, L.nbxF * L.nbyF + 1, cf, cT, (int)(k & 1), k == n - 1, L.tyF);
+            cf ^= 1;
+            cT ^= 1;
+        }
+        hipLaunchKernelGGL(k_noalloc_end<S>, dim3(1), dim3(NT), 0, st, inst, cf, cT, result);
+        return;
+    }
     hipLaunchKernelGGL(k_heat_flux_state<S>, dim3(L.nbxB), dim3(64), 0, st, I.P, f,
                        static_cast<const S *>(I.T[cT]), I.hf_part, (double *)nullptr);
     hipLaunchKernelGGL(k_flush_heat_flux, dim3(1), dim3(NT), 0, st, inst);
@@ -2274,7 +2508,7 @@ extern "C" int lbb_step_noalloc(const lbb_params *pin, void *const f[2], void *c
         if (rc) return fail(LBB_EINVAL, "rho_L = rho_V = 0 needs T_s < T_c for the Maxwell densities");
     }
     if (p.rho_L == p.rho_V) return fail(LBB_EINVAL, "rho_L must differ from rho_V");
-    const NoallocLayout L = noalloc_layout(p.nx, p.ny);
+    const NoallocLayout L = noalloc_layout(p.nx, p.ny, p.precision, p.thermal_mode, compute_units());
     if (L.total > LBB_NOALLOC_SCRATCH_BYTES)
         return fail(LBB_EINVAL, "lbb_step_noalloc: a " + std::to_string(p.nx) + "x" + std::to_string(p.ny) +
                                     " lattice needs " + std::to_string(L.total) + " scratch bytes, more than the " +
@@ -2293,13 +2527,19 @@ extern "C" int lbb_step_noalloc(const lbb_params *pin, void *const f[2], void *c
     I.rho = rho;
     I.vx = vx;
     I.vy = vy;
-    I.mass_part = reinterpret_cast<double *>(base + L.mass);
+    I.mass_part = reinterpret_cast<long long *>(base + L.mass);
     I.hf_part = reinterpret_cast<double *>(base + L.hf);
     I.sc = reinterpret_cast<lbb::Scalars *>(base + L.sc);
     I.nbxA = L.nbxA;
     I.nbyA = L.nbyA;
     I.nbxB = L.nbxB;
     I.nbyB = L.nbyB;
+    I.rel = reinterpret_cast<long long *>(base + L.rel);
+    I.mpart = reinterpret_cast<lbb::MassSum *>(base + L.mpart);
+    I.tyF = L.tyF;
+    I.nbxF = L.nbxF;
+    I.nbyF = L.nbyF;
+    I.npF = L.nbxF * L.nbyF;
     int cf = phase[0], cT = phase[1];
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (p.precision == LBB_FP64) noalloc_enqueue<double>(I, base, L, cf, cT, n, result, st);
