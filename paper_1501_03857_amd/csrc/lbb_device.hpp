@@ -693,6 +693,36 @@ __device__ __forceinline__ void tile_psi(const DevParams &P, const S *__restrict
     }
 }
 
+// Heat flux of the state (f, T) from its bottom rows by one block of NW
+// waves: the per-tile partials of k_thermal (same chunks, same order) and the
+// sample of state index t.
+template <typename S, int NW>
+__device__ __forceinline__ void sample_heat_flux(const Inst &I, const S *__restrict__ f_, const S *__restrict__ T_,
+                                                 long long t)
+{
+    const DevParams &P = I.P;
+    const gmem<S> *f = (const gmem<S> *)f_, *T = (const gmem<S> *)T_;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (int b = wv; b < I.nbxB; b += NW) {
+        const int gx = b * TXB + lane - HB;
+        double qw = 0.0;
+        if (!P.periodic_y && lane >= HB && lane < HB + TXB && gx < P.nx) {
+            double fl[9];
+            load_node(P, f, (size_t)P.nx * P.ny, (size_t)gx, 0, fl);
+            double r0 = fl[0];
+#pragma unroll
+            for (int a = 1; a < 9; ++a) r0 += fl[a];
+            const double t0 = (double)T[gx], t1 = (double)T[P.nx + gx], t2 = (double)T[2 * P.nx + gx];
+            qw = -P.cv_chi * r0 * (-3.0 * t0 + 4.0 * t1 - t2) / 2.0;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) qw += __shfl_xor(qw, off, 64);
+        if (lane == 0) I.hf_part[b] = qw;
+    }
+    __syncthreads();
+    reduce_heat_flux(I.hf_part, I.nbxB, P.nx, I.sc, t);
+}
+
 // ---------------------------------------------------------------------------
 // LB step: forces, collision and push streaming; mass partials.
 // Layout: the tile (TXA x TYA) with its halo of one node is 64 columns wide,
@@ -702,9 +732,17 @@ __device__ __forceinline__ void tile_psi(const DevParams &P, const S *__restrict
 // node's populations in registers; phase 2 collides the interior nodes and
 // pushes.  The parameters are read in place through the lattice table
 // (copied, they would not fit the scalar registers beside the plane bases).
-template <typename S, int TYA, int NWA>
-__global__ __launch_bounds__(64 * NWA, TYA == NWA ? 7 : 1) void k_lb(const Inst *__restrict__ insts, const int *__restrict__ blk2inst,
-                                                 int cf, int cT)
+//
+// ONE: the whole step of an isothermal lattice, whose temperature launch would
+// only reduce.  Nothing in a launch may then wait for another block of it, so
+// the bookkeeping runs one launch behind: every block adds up the mass
+// partials of the launch before (integers, I.rel launches since state sc->tA,
+// two halves of I.mass_part used in turn), block 0 samples the heat flux of
+// the launch's own input state, and flush_step ends the sequence.  rho and v
+// are not written.
+template <typename S, int TYA, int NWA, bool ONE = false>
+__global__ __launch_bounds__(64 * NWA, TYA == NWA ? (ONE ? 6 : 7) : 1) void k_lb(const Inst *__restrict__ insts, const int *__restrict__ blk2inst,
+                                                 int cf, int cT, int par)
 {
     const Inst &I = insts[blk2inst[blockIdx.x]];
     const DevParams &P = I.P;
@@ -722,7 +760,14 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 7 : 1) void k_lb(const Inst 
     constexpr int IPW_A = TYA / NWA;             // interior rows per wave
     constexpr int H = TYA + 2;                   // region rows (halo rows 0 and H-1)
     __shared__ double psi_s[H * 64];
-    const long long t = sc->tA;
+    const long long since = ONE ? I.rel[par] : 0;
+    const long long t = sc->tA + since;
+    if constexpr (ONE)
+        if (blk == 0) {
+            sample_heat_flux<S, NWA>(I, fin, Tin, t);
+            if (threadIdx.x == 0) I.rel[par ^ 1] = since + 1;
+            return;
+        }
     // block 0 of the lattice reduces the previous thermal launch's partials; it
     // needs nothing from this launch, so it runs first, beside the tiles
     if (blk == 0) {
@@ -803,6 +848,17 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 7 : 1) void k_lb(const Inst 
         for (int a = 0; a < 9; ++a) hs[a] = ld_at(fin + (size_t)a * N, o);
         Th = frozen ? S(0) : ld_at(Tin, o);
     }
+    __shared__ MassSum red[ONE ? NWA : 1];
+    const size_t np = (size_t)nbx * P.ny;
+    if constexpr (ONE) {
+        const gmem<long long> *part = (const gmem<long long> *)I.mass_part + par * np;
+        MassSum ms{0, 0};
+        if (since)
+            for (size_t k = threadIdx.x; k < np; k += 64 * NWA) ms.add(part[k]);
+        ms.hi = wave_sum_to_last(ms.hi);
+        ms.lo = wave_sum_to_last(ms.lo);
+        if (lane == 63) red[wv] = ms;
+    }
 #pragma unroll
     for (int m = 0; m < IPW_A; ++m) {
         rho[m] = 1.0;
@@ -810,7 +866,14 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 7 : 1) void k_lb(const Inst 
     }
     if (halo) (void)psi_node(rh_, gyh, hs, Th);
     __syncthreads();
-    const double rho_ave = sc->rho_ave;
+    double rho_ave = sc->rho_ave;
+    if constexpr (ONE)
+        if (since) {
+            MassSum ms{0, 0};
+#pragma unroll
+            for (int k = 0; k < NWA; ++k) ms.add(red[k]);
+            rho_ave = ms.value(P.mass_q) / ((double)P.nx * (double)P.ny);
+        }
 
     long long mrow[IPW_A];
 #pragma unroll
@@ -843,9 +906,11 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 7 : 1) void k_lb(const Inst 
         const double inv_rho = rcp_nr(rh);
         const double vx = (jx + 0.5 * Fx) * inv_rho;
         const double vy = (jy + 0.5 * Fy) * inv_rho;
-        st_at(rho_o, oc, S(rh));
-        st_at(vx_o, oc, wall_row ? S(0) : S(vx));
-        st_at(vy_o, oc, wall_row ? S(0) : S(vy));
+        if constexpr (!ONE) {
+            st_at(rho_o, oc, S(rh));
+            st_at(vx_o, oc, wall_row ? S(0) : S(vx));
+            st_at(vy_o, oc, wall_row ? S(0) : S(vy));
+        }
         collide(P, f, rh, vx, vy, Fx, Fy, Q, rcp_nr(P.tau_V + (rh - P.rho_V) * P.tau_slope));
         mrow[m] = push_node<S>(P, fout, N, gx, gy, f);
     }
@@ -853,7 +918,7 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 7 : 1) void k_lb(const Inst 
 #pragma unroll
     for (int m = 0; m < IPW_A; ++m) {
         const long long v = wave_sum_to_last(mrow[m]);
-        if (live[m] && lane == 63) I.mass_part[(size_t)gys[m] * nbx + bx] = v;
+        if (live[m] && lane == 63) I.mass_part[(ONE ? (par ^ 1) * np : 0) + (size_t)gys[m] * nbx + bx] = v;
     }
 }
 

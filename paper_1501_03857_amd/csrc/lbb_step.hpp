@@ -26,36 +26,6 @@ namespace lbb {
 constexpr int HF = 5;             // halo of the one-launch step
 constexpr int TXF = 64 - 2 * HF;  // its tile width: tile + halo is one wave wide
 
-// Heat flux of the state (f, T) from its bottom rows by one block of NW
-// waves: the per-tile partials of k_thermal (same chunks, same order) and the
-// sample of state index t.
-template <typename S, int NW>
-__device__ __forceinline__ void sample_heat_flux(const Inst &I, const S *__restrict__ f_, const S *__restrict__ T_,
-                                                 long long t)
-{
-    const DevParams &P = I.P;
-    const gmem<S> *f = (const gmem<S> *)f_, *T = (const gmem<S> *)T_;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int b = wv; b < I.nbxB; b += NW) {
-        const int gx = b * TXB + lane - HB;
-        double qw = 0.0;
-        if (!P.periodic_y && lane >= HB && lane < HB + TXB && gx < P.nx) {
-            double fl[9];
-            load_node(P, f, (size_t)P.nx * P.ny, (size_t)gx, 0, fl);
-            double r0 = fl[0];
-#pragma unroll
-            for (int a = 1; a < 9; ++a) r0 += fl[a];
-            const double t0 = (double)T[gx], t1 = (double)T[P.nx + gx], t2 = (double)T[2 * P.nx + gx];
-            qw = -P.cv_chi * r0 * (-3.0 * t0 + 4.0 * t1 - t2) / 2.0;
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) qw += __shfl_xor(qw, off, 64);
-        if (lane == 0) I.hf_part[b] = qw;
-    }
-    __syncthreads();
-    reduce_heat_flux(I.hf_part, I.nbxB, P.nx, I.sc, t);
-}
-
 // Sum of this launch's input mass partials by one wave (all lanes take part),
 // valid in every lane.
 __device__ __forceinline__ double wave_rho_ave(const Inst &I, const MassSum *__restrict__ part_)
@@ -276,10 +246,16 @@ __device__ __forceinline__ void flush_step(const Inst &I, int cf, int cT)
         return;
     }
     MassSum s{0, 0};
-    const gmem<MassSum> *part = (const gmem<MassSum> *)I.mpart + (size_t)par * I.npF;
-    for (int k = threadIdx.x; k < I.npF; k += NT) {
-        s.hi += part[k].hi;
-        s.lo += part[k].lo;
+    if (I.P.mode == MODE_ISOTHERMAL) {  // the partials of k_lb
+        const size_t np = (size_t)I.nbxA * I.P.ny;
+        const gmem<long long> *part = (const gmem<long long> *)I.mass_part + par * np;
+        for (size_t k = threadIdx.x; k < np; k += NT) s.add(part[k]);
+    } else {
+        const gmem<MassSum> *part = (const gmem<MassSum> *)I.mpart + (size_t)par * I.npF;
+        for (int k = threadIdx.x; k < I.npF; k += NT) {
+            s.hi += part[k].hi;
+            s.lo += part[k].lo;
+        }
     }
     s.hi = wave_sum_to_last(s.hi);
     s.lo = wave_sum_to_last(s.lo);

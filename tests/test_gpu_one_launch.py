@@ -43,6 +43,9 @@ def _same_state(a, b):
     (3, 4, {}), (3, 3, dict(periodic_y=1)), (54, 6, {}), (55, 23, {}), (20, 40, dict(periodic_y=1)),
     (70, 37, dict(periodic_y=1)), (100, 37, dict(ghost_layer=1)), (300, 77, {}), (600, 151, {}),
     (601, 150, dict(periodic_y=1)), (511, 257, {}), (800, 380, {}), (1024, 512, {}), (1080, 513, {}),
+    (160, 60, dict(thermal_mode=L.ISOTHERMAL)), (62, 5, dict(thermal_mode=L.ISOTHERMAL)),
+    (63, 33, dict(thermal_mode=L.ISOTHERMAL, periodic_y=1)), (248, 512, dict(thermal_mode=L.ISOTHERMAL)),
+    (249, 512, dict(thermal_mode=L.ISOTHERMAL)), (90, 40, dict(thermal_mode=L.THERMAL_ONLY)),
 ])
 def test_one_launch_equals_two_launches_bitwise(nx, ny, kw, precision):
     _say("one launch vs two", nx, ny, kw, precision)
@@ -56,11 +59,12 @@ def test_one_launch_equals_two_launches_bitwise(nx, ny, kw, precision):
 
 
 @pytest.mark.parametrize("precision", [L.FP64, L.FP32])
-def test_one_launch_batch_equals_members_alone(precision):
+@pytest.mark.parametrize("mode", [L.COUPLED, L.ISOTHERMAL])
+def test_one_launch_batch_equals_members_alone(precision, mode):
     """A batch whose lattices fit one round together steps in tiles of its own
     height; a change of heater and wall strength between the calls."""
-    _say("one-launch batch", precision)
-    mem = [_domain(nx, ny, precision) for nx, ny in ((128, 64), (100, 37), (256, 60), (3, 4), (62, 9))]
+    _say("one-launch batch", precision, mode)
+    mem = [_domain(nx, ny, precision, thermal_mode=mode) for nx, ny in ((128, 64), (100, 37), (256, 60), (3, 4), (62, 9))]
     b = L.Batch([m[0] for m in mem], [m[1] for m in mem], [m[2] for m in mem])
     doms = [L.Domain(*m) for m in mem]
     doms[1].set_tiles(1, 2)
