@@ -58,17 +58,16 @@ constexpr int NSHAPE_A = 4, NSHAPE_B = 4;
 constexpr TileShape kShapeA[NSHAPE_A] = {{4, 4}, {8, 8}, {12, 4}, {4, 2}};
 constexpr TileShape kShapeB[NSHAPE_B] = {{24, 16}, {40, 16}, {16, 16}, {8, 8}};
 
-// 1/x from the hardware reciprocal estimate (relative error near 2^-23)
-// refined by two Newton-Raphson steps, r <- r + r (1 - x r), each of which
-// squares the error: within a few ulp for finite nonzero normal x.  Cheaper
-// than the correctly rounded division sequence; the FP64 tolerances allow it.
+// 1/x from the hardware reciprocal estimate r (relative error e near 2^-23):
+// 1/x = r/(1 - e) = r (1 + e + e^2) up to e^3 (2^-69), one rounding at the end:
+// within an ulp for finite nonzero normal x.  Cheaper than the correctly
+// rounded division sequence and, by one operation, than two Newton-Raphson
+// steps; the FP64 tolerances allow it.
 __device__ __forceinline__ double rcp_nr(double x)
 {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-x, r, 1.0);
-    return fma(r, e, r);
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
 
 // 1/sqrt(x) from the hardware estimate refined by two Newton-Raphson steps,
@@ -83,40 +82,26 @@ __device__ __forceinline__ double rsq_nr(double x)
     return fma(y, e, y);
 }
 
-// sqrt(x) from the hardware reciprocal square root y ~ 1/sqrt(x):
-// Goldschmidt's coupled iteration on g ~ sqrt(x), h ~ 1/(2 sqrt(x))
-// (r = 1/2 - g h; g <- g + g r; h <- h + h r), twice, then one Newton
-// correction g <- g + h (x - g^2).  Within a few ulp for normal x > 0;
-// 0 for x = 0, NaN below.
-__device__ __forceinline__ double sqrt_nr(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, h = 0.5 * y;
-    double r = fma(-g, h, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    r = fma(-g, h, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    const double d = fma(-g, g, x);
-    g = fma(d, h, g);
-    return x > 0.0 ? g : (x == 0.0 ? 0.0 : __builtin_nan(""));
-}
-
-// sqrt(x) as sqrt_nr for normal x > 0 only (no zero or negative handling):
-// for arguments that are positive by construction or checked around it.
+// sqrt(x) for normal x > 0 (no zero or negative handling), for arguments that
+// are positive by construction or checked around it.  With the hardware
+// estimate y ~ 1/sqrt(x), g = x y and h = y/2, the defect r = 1/2 - g h is
+// near 2^-23 and sqrt(x) = g (1 - 2 r)^(-1/2) = g (1 + r + 3/2 r^2) up to r^3;
+// one Newton correction g <- g + h (x - g^2) then leaves less than an ulp.
 __device__ __forceinline__ double sqrt_pos(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, h = 0.5 * y;
-    double r = fma(-g, h, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    r = fma(-g, h, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
+    const double g0 = x * y, h = 0.5 * y;
+    const double r = fma(-g0, h, 0.5);
+    const double g = fma(g0, r * fma(1.5, r, 1.0), g0);
     const double d = fma(-g, g, x);
     return fma(d, h, g);
+}
+
+// sqrt(x) as sqrt_pos; 0 for x = 0, NaN below.
+__device__ __forceinline__ double sqrt_nr(double x)
+{
+    const double g = sqrt_pos(x);
+    return x > 0.0 ? g : (x == 0.0 ? 0.0 : __builtin_nan(""));
 }
 
 // Type of the RK4 stage arithmetic: FP64 storage keeps FP64; FP32 storage
@@ -237,6 +222,14 @@ struct DevParams {
     double k1k_rsTc;              // kappa (1 + kappa) / sqrt(T_c)
     double R_cv12, a_cv12;        // R / (12 c_v), a / (12 c_v)
     double mass_c, mass_q;        // mass sums: rounding constant and unit (mass_units)
+    // collision: (1 - s_e)/36, s_e/36, 6 (1 - s_e/2)/36, (1 - s_e/2) sig_e/36,
+    // the same of s_zeta, (1 - s_q)/12, s_q/12, (1 - s_q/2)/12
+    double ce_m, ce_r, ce_F, ce_Q, cz_m, cz_r, cz_F, cz_Q, cq_m, cq_r, cq_F;
+    // EOS: kappa / sqrt(T_c), 1 + kappa, 2 R / G, 2 a / G, 2 / (3 G)
+    double k_rsTc, k1, RT2G, a2G, third2G;
+    double f12;                   // force: -G / 12
+    double tau_0;                 // tau_nu(rho) = tau_0 + rho tau_slope
+    double chi144, aB, aC;        // chi / 144, a k2_Tc / (12 c_v), a k1k_rsTc / (12 c_v)
 };
 
 // Device-resident scalars of one domain.  tA is the state index seen by the
@@ -354,28 +347,53 @@ __device__ __forceinline__ void complete_node(const DevParams &P, const S fs[9],
     }
 }
 
-// psi = sqrt(2 (p_EOS - rho/3) / G) with the Peng-Robinson p_EOS (Eq. (21)),
-// always in FP64.  Returns a negative value on a negative radicand.
-// The two fractions of p_EOS share one reciprocal:
-//   p = [rho R T D2 - a phi rho^2 D1] / (D1 D2), D1 = 1 - b rho,
-//   D2 = 1 + 2 b rho - b^2 rho^2.
+// psi^2 = 2 (p_EOS - rho/3) / G with the Peng-Robinson p_EOS (Eq. (21)),
+// always in FP64.  The two fractions of p_EOS share one reciprocal, and the
+// factors of 2/G are folded into uniform ones:
+//   psi^2 = rho { [(2R/G) T D2 - (2a/G) phi rho D1] / (D1 D2) - 2/(3G) },
+//   D1 = 1 - b rho, D2 = 1 + 2 b rho - b^2 rho^2 = 2 - D1^2,
+//   phi = (1 + kappa (1 - sqrt(T/T_c)))^2.
+// T > 0 on every node (the temperature step flags any other value), so the
+// root needs no zero or sign handling.
+__device__ __forceinline__ double psi_squared(const DevParams &P, double rho, double T)
+{
+    const double s = P.k1 - P.k_rsTc * sqrt_pos(T);
+    const double D1 = 1.0 - P.b * rho;
+    const double D2 = 2.0 - D1 * D1;
+    const double num = (P.RT2G * T) * D2 - P.a2G * ((s * s) * (rho * D1));
+    return rho * (num * rcp_nr(D1 * D2) - P.third2G);
+}
+
+// psi; a negative value on a negative or non-finite radicand.
 __device__ __forceinline__ double pseudopotential(const DevParams &P, double rho, double T)
 {
-    // T > 0 on every node (the temperature step flags any other value), so
-    // the root of T/T_c needs no zero or sign handling
-    const double s = 1.0 + P.kappa * (1.0 - sqrt_pos(T * P.inv_Tc));
-    const double phi = s * s;
-    const double D1 = 1.0 - P.b * rho;
-    const double D2 = 1.0 + 2.0 * P.b * rho - P.b * P.b * rho * rho;
-    const double p = (rho * P.R * T * D2 - P.a * phi * rho * rho * D1) * rcp_nr(D1 * D2);
-    const double r = P.two_over_G * (p - rho * (1.0 / 3.0));
+    const double r = psi_squared(P, rho, T);
     return r > 0.0 ? sqrt_pos(r) : (r == 0.0 ? 0.0 : -1.0);
 }
 
-__device__ __forceinline__ void flag_error(Scalars *sc, long long t, unsigned code)
+// (global, not flat, atomics: a flat access on a path that joins the main one
+// would make every later wait there a wait for all memory operations)
+__device__ __forceinline__ void flag_error(Scalars *sc_, long long t, unsigned code)
 {
-    atomicMin(&sc->err_step, (unsigned long long)t);
-    atomicOr(&sc->err_code, code);
+    gmem<Scalars> *sc = (gmem<Scalars> *)sc_;
+    (void)__hip_atomic_fetch_min(&sc->err_step, (unsigned long long)t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    (void)__hip_atomic_fetch_or(&sc->err_code, code, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// psi of a node at step t, with the validity of its density and psi checked.
+// Positive normal numbers pass two class tests; only what fails them (a zero
+// psi among it, which is valid) is looked at closely.
+__device__ __forceinline__ double checked_psi(const DevParams &P, double rho, double T, Scalars *sc, long long t)
+{
+    constexpr int kPosNormal = 1 << 8;
+    const double r = psi_squared(P, rho, T);
+    double psi = sqrt_pos(r);
+    if (!(__builtin_amdgcn_class(rho, kPosNormal) & __builtin_amdgcn_class(psi, kPosNormal))) {
+        psi = r > 0.0 ? psi : (r == 0.0 ? 0.0 : -1.0);
+        if (!(rho > 0.0) || !(rho < 1e300)) flag_error(sc, t, ERR_RHO);
+        if (!(psi >= 0.0) || !(psi < 1e300)) flag_error(sc, t, ERR_PSI);
+    }
+    return psi;
 }
 
 // Wave64 + block sum of one double per thread (NTH threads), result valid in
@@ -474,25 +492,22 @@ __device__ __forceinline__ void reduce_heat_flux(const double *__restrict__ hf_p
 // row about the wall row (so F_m has no normal part there); buoyancy still
 // skips them.
 //
-// psi at the node and its eight neighbours (mirrored beyond a wall row).
-struct PsiNb {
-    double c, E, N, W, S, NE, NW, SW, SE;
-};
-
-__device__ __forceinline__ void force_of(const DevParams &P, const PsiNb &p, bool bot, bool top, int gy, double rho,
-                                         double rho_ave, double &Fx, double &Fy, double &Q)
+// Force of a node of density rho in lattice row gy, psi its own psi, from the
+// stencil sums sx = 12 sum_a w_a psi(x + e_a) e_ax and sy, w = 1/3 (axes), 1/12
+// (diagonals): with the column sums u = 4 psi + psi_N + psi_S and
+// d = psi_N - psi_S, sx = u_E - u_W and sy = 4 d + d_E + d_W.
+__device__ __forceinline__ void force_of(const DevParams &P, double psi, double sx, double sy, bool wall_row, int gy,
+                                         double rho, double rho_ave, double &Fx, double &Fy, double &Q)
 {
-    // sum_a w_a psi(x + e_a) e_a with w = 1/3 (axes), 1/12 (diagonals)
-    const double sx = (p.E - p.W) * (1.0 / 3.0) + (p.NE - p.NW - p.SW + p.SE) * (1.0 / 12.0);
-    const double sy = (p.N - p.S) * (1.0 / 3.0) + (p.NE + p.NW - p.SW - p.SE) * (1.0 / 12.0);
-    Fx = -P.G * p.c * sx;
-    Fy = -P.G * p.c * sy;
-    Q = P.G * P.G * (sx * sx + sy * sy);
-    if (bot || top) return;
+    const double ax = P.f12 * sx, ay = P.f12 * sy;
+    Fx = psi * ax;
+    Fy = psi * ay;
+    Q = ax * ax + ay * ay;
+    if (wall_row) return;
     // fluid-solid force on the rows next to the walls (wall rows are the solid)
-    if (!P.periodic_y) {
-        if (gy == 1) Fy += P.Gw_bottom * p.c * p.c * (1.0 / 6.0);
-        if (gy == P.ny - 2) Fy -= P.Gw_top * p.c * p.c * (1.0 / 6.0);
+    if (!P.periodic_y && (gy <= 1 || gy >= P.ny - 2)) {
+        if (gy == 1) Fy += P.Gw_bottom * psi * psi * (1.0 / 6.0);
+        if (gy == P.ny - 2) Fy -= P.Gw_top * psi * psi * (1.0 / 6.0);
     }
     // buoyancy, Eq. (9)
     Fy -= (rho - rho_ave) * P.g;
@@ -509,77 +524,86 @@ __device__ __forceinline__ void node_force(const DevParams &P, const double *psi
     // the LDS row beyond a wall holds no lattice node; the ghost layer
     // replaces it by the mirror image of the row on the other side
     const int cn = top ? c - W : c + W, cs = bot ? c + W : c - W;
-    PsiNb p;
-    p.c = psi_s[c];
-    p.E = psi_s[c + 1];
-    p.W = psi_s[c - 1];
-    p.N = psi_s[cn];
-    p.S = psi_s[cs];
-    p.NE = psi_s[cn + 1];
-    p.NW = psi_s[cn - 1];
-    p.SW = psi_s[cs - 1];
-    p.SE = psi_s[cs + 1];
-    force_of(P, p, bot, top, gy, rho, rho_ave, Fx, Fy, Q);
+    const double pN = psi_s[cn], pS = psi_s[cs];
+    const double pNE = psi_s[cn + 1], pNW = psi_s[cn - 1], pSW = psi_s[cs - 1], pSE = psi_s[cs + 1];
+    const double uE = 4.0 * psi_s[c + 1] + (pNE + pSE), uW = 4.0 * psi_s[c - 1] + (pNW + pSW);
+    const double d = pN - pS, dE = pNE - pSE, dW = pNW - pSW;
+    force_of(P, psi_s[c], uE - uW, 4.0 * d + (dE + dW), bot || top, gy, rho, rho_ave, Fx, Fy, Q);
 }
 
-// MRT collision of one node (Eqs. (2), (4), (5), (8)) in moment space with
-// the D2Q9 basis (rho, e, zeta, jx, qx, jy, qy, pxx, pxy); returns f*.
-// s_nu = 1/tau_nu(rho) comes from the caller, which forms it with 1/rho from
-// one reciprocal.
-__device__ __forceinline__ void collide(const DevParams &P, double f[9], double rho, double vx, double vy,
-                                        double Fx, double Fy, double Q, double s_nu)
+// Density of a node from its completed populations, by the sums that the
+// moments share.
+__device__ __forceinline__ double node_density(const double f[9])
 {
-    // moments m = M f, from sums and differences shared between the rows of M
+    return (f[0] + ((f[1] + f[3]) + (f[2] + f[4]))) + ((f[5] + f[7]) + (f[6] + f[8]));
+}
+
+// Moments of one node in the D2Q9 basis (rho, e, zeta, jx, qx, jy, qy, pxx,
+// pxy; rho apart), from sums and differences shared between the rows of M.
+struct Moments {
+    double e, z, jx, qx, jy, qy, pxx, pxy;
+};
+
+__device__ __forceinline__ Moments node_moments(const double f[9])
+{
     const double d13 = f[1] - f[3], d24 = f[2] - f[4];
     const double d57 = f[5] - f[7], d68 = f[6] - f[8];
     const double s13 = f[1] + f[3], s24 = f[2] + f[4];
     const double s57 = f[5] + f[7], s68 = f[6] + f[8];
     const double s14 = s13 + s24, s58 = s57 + s68;
-    const double m_e = -(4) * f[0] - s14 + (2) * s58;
-    const double m_z = (4) * f[0] - (2) * s14 + s58;
     const double dx58 = d57 - d68, dy58 = d57 + d68;  // sum over the diagonals of e_x f, e_y f
-    const double jx = d13 + dx58;
-    const double qx = -(2) * d13 + dx58;
-    const double jy = d24 + dy58;
-    const double qy = -(2) * d24 + dy58;
-    const double pxx = s13 - s24;
-    const double pxy = s57 - s68;
+    Moments m;
+    m.e = 2.0 * s58 - (4.0 * f[0] + s14);
+    m.z = (4.0 * f[0] - 2.0 * s14) + s58;
+    m.jx = d13 + dx58;
+    m.qx = dx58 - 2.0 * d13;
+    m.jy = d24 + dy58;
+    m.qy = dy58 - 2.0 * d24;
+    m.pxx = s13 - s24;
+    m.pxy = s57 - s68;
+    return m;
+}
 
-    const double v2 = vx * vx + vy * vy;
-    const double vF = vx * Fx + vy * Fy;
-    const double s_e = (P.s_e), s_z = (P.s_zeta), s_j = (P.s_j), s_q = (P.s_q);
-
-    // m* = m - L (m - m_eq) + (I - L/2) S
-    const double e_s = m_e - s_e * (m_e - rho * ((-2) + (3) * v2)) + ((1) - (0.5) * s_e) * ((6) * vF + (P.sig_e) * Q);
-    const double z_s = m_z - s_z * (m_z - rho * ((1) - (3) * v2)) + ((1) - (0.5) * s_z) * (-(6) * vF - (P.sig_z) * Q);
-    const double jx_s = jx - s_j * (jx - rho * vx) + ((1) - (0.5) * s_j) * Fx;
-    const double qx_s = qx - s_q * (qx + rho * vx) - ((1) - (0.5) * s_q) * Fx;
-    const double jy_s = jy - s_j * (jy - rho * vy) + ((1) - (0.5) * s_j) * Fy;
-    const double qy_s = qy - s_q * (qy + rho * vy) - ((1) - (0.5) * s_q) * Fy;
-    const double pxx_s = pxx - s_nu * (pxx - rho * (vx * vx - vy * vy)) + ((1) - (0.5) * s_nu) * (2) * (vx * Fx - vy * Fy);
-    const double pxy_s = pxy - s_nu * (pxy - rho * vx * vy) + ((1) - (0.5) * s_nu) * (vx * Fy + vy * Fx);
-    // rho* = rho (s_rho drops out: m_eq,rho = rho and S_rho = 0)
-
-    // f* = M^{-1} m* with M^{-1} = M^T diag(1/9, 1/36, 1/36, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4)
-    // rho/9 rounded once: 1/9 as its nearest double plus the remainder.
+// MRT collision of one node (Eqs. (2), (4), (5), (8)) with the improved
+// forcing: m* = m - L (m - m_eq) + (I - L/2) S, f* = M^{-1} m*; writes f*.
+// hx, hy = j + F/2 = rho v (Eq. (6)), so rho v v is formed from h and v, and
+// j* = j + F whatever s_j (j - s_j (j - h) + (1 - s_j/2) F).  Rates, the
+// forcing factors and the row norms of M^{-1} = M^T diag(1/9, 1/36, 1/36, 1/6,
+// 1/12, 1/6, 1/12, 1/4, 1/4) are folded into uniform factors on the host
+// (P.ce*, cz*, cq*).  s_nu = 1/tau_nu(rho).
+__device__ __forceinline__ void collide(const DevParams &P, const Moments &m, double rho, double hx, double hy,
+                                        double vx, double vy, double Fx, double Fy, double Q, double s_nu, double f[9])
+{
+    const double hvx = hx * vx, hvy = hy * vy, vFx = vx * Fx, vFy = vy * Fy;
+    const double w = hvx + hvy, vF = vFx + vFy;  // rho v^2, v . F
+    const double eq = 3.0 * w - rho;             // e_eq + rho = -zeta_eq = 3 rho v^2 - rho
+    // e*/36, zeta*/36
+    const double e36 = P.ce_m * m.e + (P.ce_r * (eq - rho) + (P.ce_F * vF + P.ce_Q * Q));
+    const double z36 = P.cz_m * m.z - (P.cz_r * eq + (P.cz_F * vF + P.cz_Q * Q));
+    const double jx = m.jx + Fx, jy = m.jy + Fy;
+    // q*/12
+    const double qx12 = P.cq_m * m.qx - (P.cq_r * hx + P.cq_F * Fx);
+    const double qy12 = P.cq_m * m.qy - (P.cq_r * hy + P.cq_F * Fy);
+    // p* = p + s_nu (p_eq - p - S/2) + S with S_xx = 2 (vx Fx - vy Fy), S_xy = vx Fy + vy Fx
+    const double bxx = vFx - vFy, bxy = vx * Fy + vy * Fx;
+    const double pxx = s_nu * ((hvx - hvy) - (m.pxx + bxx)) + (2.0 * bxx + m.pxx);
+    const double pxy = s_nu * (hx * vy - (0.5 * bxy + m.pxy)) + (bxy + m.pxy);
+    // rho* = rho (s_rho drops out: m_eq,rho = rho and S_rho = 0), and rho/9 is
+    // rounded once: 1/9 as its nearest double plus the remainder.
     // rho * fl(1/9) alone is biased (fl(1/9) < 1/9), and the nine outputs
     // sum to 9 r9, so every node would lose a fixed 5.6e-17 rho of mass per
     // step; this product gives the correctly rounded quotient instead.
     const double r9 = fma(rho, 1.0 / 9.0, rho * 0x1.c71c71c71c71cp-58);
-    const double e36 = e_s * (1.0 / 36.0), z36 = z_s * (1.0 / 36.0);
-    const double jx6 = jx_s * (1.0 / 6.0), jy6 = jy_s * (1.0 / 6.0);
-    const double qx12 = qx_s * (1.0 / 12.0), qy12 = qy_s * (1.0 / 12.0);
-    const double pxx4 = pxx_s * (0.25), pxy4 = pxy_s * (0.25);
-    const double axis = r9 - e36 - (2) * z36;
-    const double diag = r9 + (2) * e36 + z36;
+    const double axis = (r9 - e36) - 2.0 * z36;
+    const double diag = (r9 + z36) + 2.0 * e36;
     // shared sums of the columns of M^T: axis and diagonal pairs differ only
     // in the signs of these
-    const double ax = jx6 - (2) * qx12, ay = jy6 - (2) * qy12;
-    const double cx = jx6 + qx12, cy = jy6 + qy12;
-    const double ap = axis + pxx4, am = axis - pxx4;
-    const double dp = diag + pxy4, dm = diag - pxy4;
+    const double ax = jx * (1.0 / 6.0) - 2.0 * qx12, ay = jy * (1.0 / 6.0) - 2.0 * qy12;
+    const double cx = jx * (1.0 / 6.0) + qx12, cy = jy * (1.0 / 6.0) + qy12;
+    const double ap = 0.25 * pxx + axis, am = axis - 0.25 * pxx;
+    const double dp = 0.25 * pxy + diag, dm = diag - 0.25 * pxy;
     const double cp = cx + cy, cm = cx - cy;
-    f[0] = r9 - (4) * e36 + (4) * z36;
+    f[0] = 4.0 * (z36 - e36) + r9;
     f[1] = ap + ax;
     f[2] = am + ay;
     f[3] = ap - ax;
@@ -590,21 +614,35 @@ __device__ __forceinline__ void collide(const DevParams &P, double f[9], double 
     f[8] = dm + cm;
 }
 
-// Push streaming (Eq. (3)) of the post-collision populations of node
-// (gx, gy) into fout; populations leaving through a wall are dropped.  Returns
-// the mass the node hands to the streamed state, in units of P.mass_q: each
-// population counts once, except those that leave through a wall (0) and
+// Mass that node row gy hands to the streamed state, in units of P.mass_q:
+// each population counts once, except those that leave through a wall (0) and
 // those that arrive on a wall row, whose Zou-He partners are reconstructed
 // with the same sum (2).  The mass sums the populations before they are
 // rounded to the storage precision: in FP32 storage it then differs from the
 // stored mass by the rounding of the populations (relative ~1e-7 per node,
 // ~1e-10 over a lattice), far below what rho_ave moves the buoyancy by.
+__device__ __forceinline__ long long pushed_mass(const DevParams &P, int gy, const double f[9])
+{
+    const double up = f[2] + f[5] + f[6];
+    const double dn = f[4] + f[7] + f[8];
+    const double mid = f[0] + f[1] + f[3];
+    double mm = mid + (up + dn);
+    if (!P.periodic_y && (gy <= 1 || gy >= P.ny - 2)) {  // uniform over the wave
+        const double wu = gy == P.ny - 1 ? 0.0 : (gy == P.ny - 2 ? 2.0 : 1.0);
+        const double wd = gy == 0 ? 0.0 : (gy == 1 ? 2.0 : 1.0);
+        mm = mid + (wu * up + wd * dn);
+    }
+    return mass_units(P.mass_c, mm);
+}
+
+// Push streaming (Eq. (3)) of the post-collision populations of node
+// (gx, gy) into fout; populations leaving through a wall are dropped.  Returns
+// the mass handed on.
 template <typename S>
 __device__ __forceinline__ long long push_node(const DevParams &P, S *__restrict__ fout, size_t N, int gx, int gy,
                                                const double f[9])
 {
     constexpr unsigned sz = (unsigned)sizeof(S);
-    const bool walls = !P.periodic_y;
     const unsigned gxu = (unsigned)gx, rowc = (unsigned)gy * (unsigned)P.nx;
     const int xe = gx + 1 == P.nx ? 0 : gx + 1;
     const int xw = gx == 0 ? P.nx - 1 : gx - 1;
@@ -629,30 +667,7 @@ __device__ __forceinline__ long long push_node(const DevParams &P, S *__restrict
         st_at(fout + 7 * N, (rows + xwu) * sz, S(f[7]));
         st_at(fout + 8 * N, (rows + xeu) * sz, S(f[8]));
     }
-    const double up = f[2] + f[5] + f[6];
-    const double dn = f[4] + f[7] + f[8];
-    double mm = f[0] + f[1] + f[3];
-    const double wu = !walls ? 1.0 : (gy == P.ny - 1 ? 0.0 : (gy == P.ny - 2 ? 2.0 : 1.0));
-    const double wd = !walls ? 1.0 : (gy == 0 ? 0.0 : (gy == 1 ? 2.0 : 1.0));
-    mm += wu * up + wd * dn;
-    return mass_units(P.mass_c, mm);
-}
-
-// Density of a node from its stored populations: their sum, or on a wall row
-// (kind 1: bottom, 2: top) the Zou-He identity, whose three unknowns sum to
-// the three opposite knowns.
-template <typename S>
-__device__ __forceinline__ double node_density(const S fs[9], int kind)
-{
-    double fl[9];
-#pragma unroll
-    for (int a = 0; a < 9; ++a) fl[a] = (double)fs[a];
-    if (kind == 1) return fl[0] + fl[1] + fl[3] + 2.0 * (fl[4] + fl[7] + fl[8]);
-    if (kind == 2) return fl[0] + fl[1] + fl[3] + 2.0 * (fl[2] + fl[5] + fl[6]);
-    double rr = fl[0];
-#pragma unroll
-    for (int a = 1; a < 9; ++a) rr += fl[a];
-    return rr;
+    return pushed_mass(P, gy, f);
 }
 
 __constant__ const int kEX[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
@@ -741,7 +756,7 @@ __device__ __forceinline__ void sample_heat_flux(const Inst &I, const S *__restr
 // the launch's own input state, and flush_step ends the sequence.  rho and v
 // are not written.
 template <typename S, int TYA, int NWA, bool ONE = false>
-__global__ __launch_bounds__(64 * NWA, TYA == NWA ? (ONE ? 6 : 7) : 1) void k_lb(const Inst *__restrict__ insts, const int *__restrict__ blk2inst,
+__global__ __launch_bounds__(64 * NWA, TYA == NWA ? 6 : 1) void k_lb(const Inst *__restrict__ insts, const int *__restrict__ blk2inst,
                                                  int cf, int cT, int par)
 {
     const Inst &I = insts[blk2inst[blockIdx.x]];
@@ -794,24 +809,12 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? (ONE ? 6 : 7) : 1) void k_lb
         }
         return gy >= 0 && gy < P.ny;
     };
-    // rho and psi of node (r, lane) into LDS; returns rho
-    // Row kind, uniform over the wave (one lattice row per wave): 1 bottom
-    // wall, 2 top wall, 0 any other row (or no walls, or f frozen).  Wall
-    // rows complete their populations by the Zou-He rule; the code of each
-    // kind is generated separately, so other rows carry none of it.
-    auto kind_of = [&](int gy) -> int {
-        if (!walls || frozen) return 0;
-        return gy == 0 ? 1 : (gy == P.ny - 1 ? 2 : 0);
-    };
+    // psi of node (r, lane) into LDS; returns rho
     auto psi_node = [&](int r, int gy, const S fs[9], S Tn) -> double {
-        const double rr = node_density<S>(fs, kind_of(gy));
-        if (!frozen) {
-            const double T = P.T_ref + (double)Tn;
-            const double psi = pseudopotential(P, rr, T);
-            if (!(rr > 0.0) || !(rr < 1e300)) flag_error(sc, t, ERR_RHO);
-            if (!(psi >= 0.0) || !(psi < 1e300)) flag_error(sc, t, ERR_PSI);
-            psi_s[r * 64 + lane] = psi;
-        }
+        double fl[9];
+        complete_node(P, fs, gy, fl);
+        const double rr = node_density(fl);
+        if (!frozen) psi_s[r * 64 + lane] = checked_psi(P, rr, P.T_ref + (double)Tn, sc, t);
         return rr;
     };
 
@@ -887,14 +890,13 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? (ONE ? 6 : 7) : 1) void k_lb
         double f[9];
         complete_node(P, fs[m], gy, f);
         const double rh = rho[m];
-        const double jx = f[1] - f[3] + f[5] - f[6] - f[7] + f[8];
-        const double jy = f[2] - f[4] + f[5] + f[6] - f[7] - f[8];
+        const Moments mo = node_moments(f);
         const bool wall_row = walls && (gy == 0 || gy == P.ny - 1);
         if (frozen) {
             // THERMAL_ONLY: f is frozen, the temperature sees sum e f / rho
             st_at(rho_o, oc, S(rh));
-            st_at(vx_o, oc, wall_row ? S(0) : S(jx / rh));
-            st_at(vy_o, oc, wall_row ? S(0) : S(jy / rh));
+            st_at(vx_o, oc, wall_row ? S(0) : S(mo.jx / rh));
+            st_at(vy_o, oc, wall_row ? S(0) : S(mo.jy / rh));
             double mm = 0.0;
 #pragma unroll
             for (int a = 0; a < 9; ++a) mm += f[a];
@@ -903,15 +905,17 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? (ONE ? 6 : 7) : 1) void k_lb
         }
         double Fx, Fy, Q;
         node_force<64>(P, psi_s, lane - 1, r - 1, gy, rh, rho_ave, Fx, Fy, Q);
-        const double inv_rho = rcp_nr(rh);
-        const double vx = (jx + 0.5 * Fx) * inv_rho;
-        const double vy = (jy + 0.5 * Fy) * inv_rho;
+        // 1/rho and s_nu = 1/tau_nu from one reciprocal
+        const double tau = P.tau_0 + rh * P.tau_slope, i2 = rcp_nr(rh * tau);
+        const double inv_rho = tau * i2, s_nu = rh * i2;
+        const double hx = mo.jx + 0.5 * Fx, hy = mo.jy + 0.5 * Fy;
+        const double vx = hx * inv_rho, vy = hy * inv_rho;
         if constexpr (!ONE) {
             st_at(rho_o, oc, S(rh));
             st_at(vx_o, oc, wall_row ? S(0) : S(vx));
             st_at(vy_o, oc, wall_row ? S(0) : S(vy));
         }
-        collide(P, f, rh, vx, vy, Fx, Fy, Q, rcp_nr(P.tau_V + (rh - P.rho_V) * P.tau_slope));
+        collide(P, mo, rh, hx, hy, vx, vy, Fx, Fy, Q, s_nu, f);
         mrow[m] = push_node<S>(P, fout, N, gx, gy, f);
     }
     // mass partials per lattice row and 62-column chunk
@@ -941,11 +945,12 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? (ONE ? 6 : 7) : 1) void k_lb
 // stage) and the RK4 sums stay in registers.  The parameters are copied into
 // registers once: read through the lattice table they would be fetched again
 // after every barrier.
-// Per-node coefficients of K, formed once per step: the advection
-// coefficients with the 1/12 of the column-sum stencils folded in, c1, c2.
+// Per-node coefficients of K, formed once per step: with the advection
+// coefficients a_x, a_y of the column-sum stencils (their 1/12 folded in),
+// ap = chi/6 + a_x and am = chi/6 - a_x, a_y, c1 and c2.
 template <typename C>
 struct SlopeCoef {
-    C ax, ay, c1, c2;
+    C ap, am, ay, c1, c2;
 };
 
 // Coefficients of a lane's node from rho and v of its own column (rows south
@@ -953,74 +958,81 @@ struct SlopeCoef {
 // formed by every lane and passed to its neighbours, so every lane of the wave
 // must call it; the first and last lane get no meaningful result.
 template <typename C>
-__device__ __forceinline__ SlopeCoef<C> slope_coef(const DevParams &P, C rc, C rN, C rS, C uc, C uN, C uS, C vc, C vN,
-                                                   C vS)
+__device__ __forceinline__ SlopeCoef<C> slope_coef(const DevParams &P, C chi6, C rc, C rN, C rS, C uc, C uN, C uS,
+                                                   C vc, C vN, C vS)
 {
-    const C sr = (rN + rS) + C(4) * rc, dr = rN - rS;
-    const C su = (uN + uS) + C(4) * uc, dv = vN - vS;
-    const C srW = lane_from_left(sr), srE = lane_from_right(sr);
-    const C drW = lane_from_left(dr), drE = lane_from_right(dr);
-    const C suW = lane_from_left(su), suE = lane_from_right(su);
-    const C dvW = lane_from_left(dv), dvE = lane_from_right(dv);
+    const C sr = C(4) * rc + (rN + rS), dr = rN - rS;
+    const C su = C(4) * uc + (uN + uS), dv = vN - vS;
     const double rho = (double)rc;
     // 12 d_x rho, 12 d_y rho and 12 div v from the column sums
-    const C gx = srE - srW, gy = fma(C(4), dr, drW + drE);
-    const double div12 = (double)((suE - suW) + fma(C(4), dv, dvW + dvE));
+    const C gx = lane_from_right(sr) - lane_from_left(sr);
+    const C gy = C(4) * dr + (lane_from_left(dr) + lane_from_right(dr));
+    const double div12 = (double)((lane_from_right(su) - lane_from_left(su)) +
+                                  (C(4) * dv + (lane_from_left(dv) + lane_from_right(dv))));
     // A w = (R/c_v) div v / D1 and B w = (a/c_v) rho div v / D2 with
-    // D1 = 1 - b rho, D2 = 1 + 2 b rho - b^2 rho^2; one reciprocal
-    // 1/(rho D1 D2) gives 1/rho, 1/D1 and 1/D2
+    // D1 = 1 - b rho, D2 = 1 + 2 b rho - b^2 rho^2 = 2 - D1^2; one reciprocal
+    // 1/(rho D1 D2) gives 1/rho and 1/(D1 D2)
     const double D1 = 1.0 - P.b * rho;
-    const double D2 = 1.0 + 2.0 * P.b * rho - P.b * P.b * rho * rho;
-    const double inv = rcp_nr(rho * D1 * D2);
+    const double D2 = 2.0 - D1 * D1;
+    const double D12 = D1 * D2, inv = rcp_nr(rho * D12);
+    const double w = div12 * (rho * inv), wB = rho * (D1 * w);
     // the stages read the column sums unscaled: 12 d_x T and 12 d_y T,
     // so the advection coefficients carry the 1/12
     // (a_x/12 = (chi/rho) d_x rho/12 - v_x/12 = (chi/rho) gx/144 - v_x/12)
-    const C k144 = (C)(P.chi * (1.0 / 144.0) * D1 * D2 * inv);
+    const C k144 = (C)(P.chi144 * (D12 * inv));
+    const C ax = k144 * gx - uc * C(1.0 / 12.0);
     SlopeCoef<C> k;
-    k.ax = fma(k144, gx, -uc * C(1.0 / 12.0));
-    k.ay = fma(k144, gy, -vc * C(1.0 / 12.0));
-    const double Aw = P.R_cv12 * div12 * (rho * D2 * inv), Bw = P.a_cv12 * rho * div12 * (rho * D1 * inv);
-    k.c1 = (C)(Bw * P.k2_Tc - Aw);
-    k.c2 = (C)(-Bw * P.k1k_rsTc);
+    k.ap = chi6 + ax;
+    k.am = chi6 - ax;
+    k.ay = k144 * gy - vc * C(1.0 / 12.0);
+    k.c1 = (C)(P.aB * wB - P.R_cv12 * (D2 * w));
+    k.c2 = (C)(-P.aC * wB);
     return k;
 }
 
-// Column sums of the 3x3 stencil of a stage input, formed by every lane for
-// its own column and passed to the neighbouring columns:
-// v = T_S + 4 T_c + T_N, w = T_N - T_S give
-//   d_x T = (v_E - v_W)/12, d_y T = (w_W + 4 w + w_E)/12,
-//   lap T = (v_W + v_E + 4 v - 36 T_c)/6,
-// the isotropic stencils of the gradient and the Laplacian (the 1/12 and 1/6
-// are carried by the coefficients).  Every lane of the wave must call it.
-template <typename C>
-struct StageCols {
-    C tc, v, w, vW, vE, wW, wE;
-};
-
-template <typename C>
-__device__ __forceinline__ StageCols<C> stage_cols(C tc, C tN, C tS)
+// h + v_E ap + v_W am + (w_E + w_W) ay, in that order, with the values v and w
+// of the lanes to the right (E) and left (W).  In FP32 each multiply-add takes
+// its lane shift along (the compiler merges lane shifts into additions but
+// not into multiply-adds); the leading s_nop covers the two wait states
+// between the write of v or w and its lane-shifted read.
+__device__ __forceinline__ float add_shifted(float h, float v, float ap, float am, float w, float ay)
 {
-    StageCols<C> s;
-    s.tc = tc;
-    s.v = fma(C(4), tc, tN + tS);
-    s.w = tN - tS;
-    s.vW = lane_from_left(s.v);
-    s.vE = lane_from_right(s.v);
-    s.wW = lane_from_left(s.w);
-    s.wE = lane_from_right(s.w);
-    return s;
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %1, %2 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"
+        "v_fmac_f32_dpp %0, %1, %3 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"
+        "v_fmac_f32_dpp %0, %4, %5 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"
+        "v_fmac_f32_dpp %0, %4, %5 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0"
+        : "+v"(h)
+        : "v"(v), "v"(ap), "v"(am), "v"(w), "v"(ay));
+    return h;
+}
+__device__ __forceinline__ double add_shifted(double h, double v, double ap, double am, double w, double ay)
+{
+    h = fma(lane_from_right(v), ap, h);
+    h = fma(lane_from_left(v), am, h);
+    h = fma(lane_from_right(w), ay, h);
+    return fma(lane_from_left(w), ay, h);
 }
 
+// Slope of a stage at a lane's node from the stage input in its own column:
+// the column sums v = T_S + 4 T_c + T_N and w = T_N - T_S, formed by every lane
+// and passed to the neighbouring columns, give
+//   12 d_x T = v_E - v_W, 12 d_y T = w_W + 4 w + w_E,
+//   6 lap T = v_W + v_E + 4 v - 36 T_c = v_W + v_E + 4 (T_N + T_S) - 20 T_c,
+// the isotropic stencils of the gradient and the Laplacian.  Each shifted
+// value enters one multiply-add (a_x and chi/6 are merged into ap, am), which
+// in FP32 takes the lane shift along.  Every lane of the wave must call it.
 template <typename C>
-__device__ __forceinline__ C stage_slope(const StageCols<C> &s, const SlopeCoef<C> &k, C Tref, C chi6)
+__device__ __forceinline__ C stage_slope(C tc, C tN, C tS, const SlopeCoef<C> &k, C Tref, C chi6)
 {
-    const C T = Tref + s.tc;
-    const C lap6 = fma(C(-36), s.tc, fma(C(4), s.v, s.vW + s.vE));
+    const C s = tN + tS, v = fma(C(4), tc, s), w = tN - tS;
+    const C T = Tref + tc;
     C h = k.c1 * T;
     h = fma(k.c2, stage_sqrt(T), h);
-    h = fma(chi6, lap6, h);
-    h = fma(k.ax, s.vE - s.vW, h);
-    return fma(k.ay, fma(C(4), s.w, s.wW + s.wE), h);
+    h = fma(C(4) * chi6, s, h);
+    h = fma(C(-20) * chi6, tc, h);
+    h = fma(k.ay, C(4) * w, h);
+    return add_shifted(h, v, k.ap, k.am, w, k.ay);
 }
 
 template <typename S, int TY, int NWB>
@@ -1102,21 +1114,21 @@ __global__ __launch_bounds__(64 * NWB) void k_thermal(const Inst *__restrict__ i
 
     // Per-node coefficients of K on the region shrunk by one node, kept in
     // registers (each wave evaluates K only at its own rows).
+    const C chi6 = (C)(P.chi * (1.0 / 6.0));
     SlopeCoef<C> cfr[RPW];
 #pragma unroll
-    for (int m = 0; m < RPW; ++m) cfr[m] = SlopeCoef<C>{C(0), C(0), C(0), C(0)};
+    for (int m = 0; m < RPW; ++m) cfr[m] = SlopeCoef<C>{};
     if (run) {
 #pragma unroll
         for (int m = 0; m < RPW; ++m) {
             const int r = wv + NWB * m;
             if (r < 1 || r >= H - 1 || !act[m]) continue;
-            cfr[m] = slope_coef<C>(P, X[0][r][lane], X[0][r + 1][lane], X[0][r - 1][lane], X[1][r][lane],
+            cfr[m] = slope_coef<C>(P, chi6, X[0][r][lane], X[0][r + 1][lane], X[0][r - 1][lane], X[1][r][lane],
                                    X[1][r + 1][lane], X[1][r - 1][lane], X[2][r][lane], X[2][r + 1][lane],
                                    X[2][r - 1][lane]);
         }
 
         const C Tref = (C)P.T_ref;
-        const C chi6 = (C)(P.chi * (1.0 / 6.0));
         const C cst[3] = {C(0.5), C(0.5), C(1.0)};
         const C wst[4] = {C(1), C(2), C(2), C(1)};
         // stage st reads T0 (st = 0) or Ts[(st - 1) & 1] and writes Ts[st & 1]:
@@ -1129,11 +1141,9 @@ __global__ __launch_bounds__(64 * NWB) void k_thermal(const Inst *__restrict__ i
             for (int m = 0; m < RPW; ++m) {
                 const int r = wv + NWB * m;
                 if (r >= H || r < HB - rad || r >= HB + TY + rad) continue;
-                const StageCols<C> sc_ = stage_cols<C>(in[r][lane], in[r + 1][lane], in[r - 1][lane]);
-                if (lane < HB - rad || lane >= HB + TXB + rad) continue;
                 C h = C(0);
                 if (act[m]) {
-                    h = stage_slope<C>(sc_, cfr[m], Tref, chi6);
+                    h = stage_slope<C>(in[r][lane], in[r + 1][lane], in[r - 1][lane], cfr[m], Tref, chi6);
                     acc[m] = st == 0 ? h : fma(wst[st], h, acc[m]);
                 }
                 if (st < 3) Ts[st & 1][r][lane] = fma(cst[st], h, T0[r][lane]);

@@ -325,6 +325,27 @@ void make_dev_params(const lbb_params &p, double Tc, double kap, lbb::DevParams 
     q.k1k_rsTc = kap * (1.0 + kap) / std::sqrt(Tc);
     q.R_cv12 = p.R / (12.0 * p.cv);
     q.a_cv12 = p.a / (12.0 * p.cv);
+    q.ce_m = (1.0 - p.s_e) / 36.0;
+    q.ce_r = p.s_e / 36.0;
+    q.ce_F = 6.0 * (1.0 - 0.5 * p.s_e) / 36.0;
+    q.ce_Q = (1.0 - 0.5 * p.s_e) * q.sig_e / 36.0;
+    q.cz_m = (1.0 - p.s_zeta) / 36.0;
+    q.cz_r = p.s_zeta / 36.0;
+    q.cz_F = 6.0 * (1.0 - 0.5 * p.s_zeta) / 36.0;
+    q.cz_Q = (1.0 - 0.5 * p.s_zeta) * q.sig_z / 36.0;
+    q.cq_m = (1.0 - p.s_q) / 12.0;
+    q.cq_r = p.s_q / 12.0;
+    q.cq_F = (1.0 - 0.5 * p.s_q) / 12.0;
+    q.k_rsTc = kap / std::sqrt(Tc);
+    q.k1 = 1.0 + kap;
+    q.RT2G = 2.0 * p.R / p.G;
+    q.a2G = 2.0 * p.a / p.G;
+    q.third2G = 2.0 / (3.0 * p.G);
+    q.f12 = -p.G / 12.0;
+    q.tau_0 = tauV - p.rho_V * q.tau_slope;
+    q.chi144 = q.chi / 144.0;
+    q.aB = q.a_cv12 * q.k2_Tc;
+    q.aC = q.a_cv12 * q.k1k_rsTc;
     int e = 0;
     (void)std::frexp(8.0 / p.b, &e);  // 2^(e-1) <= 8/b < 2^e
     q.mass_c = std::ldexp(1.5, e);

@@ -32,9 +32,19 @@ __device__ __forceinline__ double wave_rho_ave(const Inst &I, const MassSum *__r
 {
     const gmem<MassSum> *__restrict__ part = (const gmem<MassSum> *)part_;
     MassSum s{0, 0};
-    for (int k = threadIdx.x & 63; k < I.npF; k += 64) {
-        s.hi += part[k].hi;
-        s.lo += part[k].lo;
+    for (int k = threadIdx.x & 63; k < I.npF; k += 4 * 64) {
+        long long hi[4], lo[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool in = k + 64 * j < I.npF;
+            hi[j] = in ? part[k + 64 * j].hi : 0;
+            lo[j] = in ? part[k + 64 * j].lo : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            s.hi += hi[j];
+            s.lo += lo[j];
+        }
     }
     s.hi = wave_sum_to_last(s.hi);
     s.lo = wave_sum_to_last(s.lo);
@@ -118,12 +128,10 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
         rho[m] = 1.0;
         if (!inl[m]) continue;
         const int r = wv + NW * m;
-        const int kind = !walls ? 0 : (gys[m] == 0 ? 1 : (gys[m] == P.ny - 1 ? 2 : 0));
-        rho[m] = node_density<S>(fs[m], kind);
-        const double psi = pseudopotential(P, rho[m], P.T_ref + (double)Tv[m]);
-        if (!(rho[m] > 0.0) || !(rho[m] < 1e300)) flag_error(sc, t, ERR_RHO);
-        if (!(psi >= 0.0) || !(psi < 1e300)) flag_error(sc, t, ERR_PSI);
-        buf[r][lane] = psi;
+        double fl[9];
+        complete_node(P, fs[m], gys[m], fl);
+        rho[m] = node_density(fl);
+        buf[r][lane] = checked_psi(P, rho[m], P.T_ref + (double)Tv[m], sc, t);
         X[0][r][lane] = (C)(S)rho[m];
         T0[r][lane] = (C)Tv[m];
     }
@@ -142,15 +150,15 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
         long long units = 0;
         if (lane >= 1 && lane < 63) {
             double f[9];
-            complete_node(P, fs[m], gy, f);
             const double rh = rho[m];
-            const double jx = f[1] - f[3] + f[5] - f[6] - f[7] + f[8];
-            const double jy = f[2] - f[4] + f[5] + f[6] - f[7] - f[8];
             double Fx, Fy, Q;
             node_force<64>(P, &buf[0][0], lane - 1, r - 1, gy, rh, rho_ave, Fx, Fy, Q);
-            const double inv_rho = rcp_nr(rh);
-            const double vx = (jx + 0.5 * Fx) * inv_rho;
-            const double vy = (jy + 0.5 * Fy) * inv_rho;
+            complete_node(P, fs[m], gy, f);
+            const Moments mo = node_moments(f);
+            const double tau = P.tau_0 + rh * P.tau_slope, i2 = rcp_nr(rh * tau);
+            const double inv_rho = tau * i2, s_nu = rh * i2;
+            const double hx = mo.jx + 0.5 * Fx, hy = mo.jy + 0.5 * Fy;
+            const double vx = hx * inv_rho, vy = hy * inv_rho;
             const S vxs = wall_row ? S(0) : S(vx), vys = wall_row ? S(0) : S(vy);
             X[1][r][lane] = (C)vxs;
             X[2][r][lane] = (C)vys;
@@ -161,7 +169,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
                     st_at(static_cast<S *>(I.vx), oc, vxs);
                     st_at(static_cast<S *>(I.vy), oc, vys);
                 }
-                collide(P, f, rh, vx, vy, Fx, Fy, Q, rcp_nr(P.tau_V + (rh - P.rho_V) * P.tau_slope));
+                collide(P, mo, rh, hx, hy, vx, vy, Fx, Fy, Q, s_nu, f);
                 units = push_node<S>(P, fout, N, gx, gy, f);
             }
         }
@@ -176,6 +184,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
     }
 
     // phase 3: coefficients of the temperature equation
+    const C chi6 = (C)(P.chi * (1.0 / 6.0));
     bool act[RPW];
     SlopeCoef<C> cfr[RPW];
     C acc[RPW];
@@ -183,10 +192,10 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
     for (int m = 0; m < RPW; ++m) {
         const int r = wv + NW * m;
         acc[m] = C(0);
-        cfr[m] = SlopeCoef<C>{C(0), C(0), C(0), C(0)};
+        cfr[m] = SlopeCoef<C>{};
         act[m] = inl[m] && !(walls && (gys[m] == 0 || gys[m] == P.ny - 1));
         if (!act[m] || r < 2 || r >= H - 2) continue;
-        cfr[m] = slope_coef<C>(P, X[0][r][lane], X[0][r + 1][lane], X[0][r - 1][lane], X[1][r][lane], X[1][r + 1][lane],
+        cfr[m] = slope_coef<C>(P, chi6, X[0][r][lane], X[0][r + 1][lane], X[0][r - 1][lane], X[1][r][lane], X[1][r + 1][lane],
                                X[1][r - 1][lane], X[2][r][lane], X[2][r + 1][lane], X[2][r - 1][lane]);
     }
 
@@ -197,7 +206,6 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
     Ts[0] = reinterpret_cast<C(*)[64]>(&buf[0][0]);
     Ts[1] = sizeof(C) == 4 ? Ts[0] + HM : X[0];
     const C Tref = (C)P.T_ref;
-    const C chi6 = (C)(P.chi * (1.0 / 6.0));
     const C cst[3] = {C(0.5), C(0.5), C(1.0)};
     const C wst[4] = {C(1), C(2), C(2), C(1)};
 #pragma unroll
@@ -208,10 +216,9 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
         for (int m = 0; m < RPW; ++m) {
             const int r = wv + NW * m;
             if (r >= H || r < HF - rad || r >= HF + TY + rad) continue;
-            const StageCols<C> cols = stage_cols<C>(in[r][lane], in[r + 1][lane], in[r - 1][lane]);
             C h = C(0);
             if (act[m]) {
-                h = stage_slope<C>(cols, cfr[m], Tref, chi6);
+                h = stage_slope<C>(in[r][lane], in[r + 1][lane], in[r - 1][lane], cfr[m], Tref, chi6);
                 acc[m] = st == 0 ? h : fma(wst[st], h, acc[m]);
             }
             if (st < 3) Ts[st & 1][r][lane] = fma(cst[st], h, T0[r][lane]);
