@@ -211,6 +211,13 @@ struct BlobHeader {
 };
 constexpr uint64_t kMagic = 0x6c62626f696c3031ULL;  // "lbboil01"
 
+// How lattices step: two launches (height 0), or one in tiles or marching
+// strips of `height` rows.
+struct StepForm {
+    int height = 0;
+    bool march = false;
+};
+
 }  // namespace
 
 struct lbb_domain {
@@ -228,7 +235,7 @@ struct lbb_domain {
     int nbxA = 0, nbyA = 0, nbxB = 0, nbyB = 0;
     int shA = 0, shB = 0;                // tile shapes (indices into kShapeA, kShapeB)
     bool fixed_tiles = false;            // shapes chosen by the caller: two launches per step in them
-    int nbxF = 0, nbyF = 0, tyF = 0;     // tiles of the one-launch step (tyF = 0: not for this lattice)
+    StepForm form;                       // of its steps, unless the caller chose shapes
     long long *rel = nullptr;
     lbb::MassSum *mpart = nullptr;
     int *d_blkF = nullptr;
@@ -362,6 +369,101 @@ uint64_t param_hash(const lbb_params &p)
     return fnv1a(&q, sizeof q);
 }
 
+// ---- the one-launch step (k_step, k_march) ----
+//
+// Where tiles (k_step) are taken.  They recompute a halo of five rows and
+// columns, so they pay while a step is bound by launch and phase latencies,
+// not by the work itself: when tiles of some height fit the compute units in
+// one round.  Timed on graph replays, one launch against two (us per step):
+// 128x64 FP64 7.1 against 13.6, 301x77 FP32 6.9 against 12.4, 600x151 FP32 9.2
+// against 13.1, 511x257 FP64 12.1 against 15.8, 512x256 FP32 10.2 against 13.2,
+// 1024x512 FP32 21.6 against 23.0.  One block more than compute units costs a
+// second round (600x151: 18.3 with 912 blocks, 14.6 with 612, 9.2 with 228),
+// and a block alone on a compute unit cannot hide its loads under another's
+// arithmetic (2048x1024: 77 against 64).
+//
+// The tile height is the smallest that fits one round, but at least 4: lower
+// tiles only add halo (128x64: 7.0-7.1 for heights 1 to 4; 256x128 FP64 8.1
+// with 3 and 7.9 with 4; 600x151 9.2 with 8, 10.1 with 13, 12.6 with 22).
+//
+// Where marching strips (k_march) are taken: from the size on at which strips
+// of kMarchMin rows fill every wave slot.  The height is then the smallest
+// that still fits one round, up to kMarchMax, where more rows no longer pay
+// (4096x2048 FP32: 205, 202, 202 us with 26, 32, 53 rows; two launches 265).
+// Below, too few rows a wave leave too much halo: 2048x1024 FP32 61 us either
+// way with 14 rows, 1024x512 36 against 22 with 8; FP64 gains earlier, since its
+// two launches are slower: 1500x700 51 against 59 with 11 rows.  Heights are 2
+// modulo 3: with the ten rows of the halo whole turns of the kernel's loop.
+struct StepDims {
+    int nx, ny;
+};
+
+constexpr int kStepMinHeight = 4;
+constexpr int kMarchWaves = 4;  // waves of a block
+constexpr int kMarchMax = 53;
+constexpr int march_min(int precision) { return precision == LBB_FP64 ? 11 : 17; }
+constexpr int kMarchMinNy = 32;     // rows a strip's halo may wrap around once
+constexpr int kMarchMaxNx = 8192;   // its one block for the heat flux walks the bottom rows
+// region rows a block of 16 waves has room for: four rows a wave in FP32,
+// three in FP64 (whose planes take twice the LDS)
+constexpr int step_max_rows(int precision) { return precision == LBB_FP64 ? 48 : 64; }
+
+// Blocks of a lattice (without the one for its bookkeeping).
+int64_t step_blocks(const StepDims &l, const StepForm &f)
+{
+    if (!f.height) return 0;
+    const int64_t tiles = (int64_t)((l.nx + lbb::TXF - 1) / lbb::TXF) * ((l.ny + f.height - 1) / f.height);
+    return f.march ? (tiles + kMarchWaves - 1) / kMarchWaves : tiles;
+}
+
+// Form of the step of lattices that step together.
+StepForm step_form(const std::vector<StepDims> &ls, int precision, int mode, int ncu)
+{
+    StepForm f;
+    if (mode != LBB_COUPLED) return f;
+    auto blocks = [&](const StepForm &g) {
+        int64_t n = 0;
+        for (const StepDims &l : ls) n += step_blocks(l, g) + 1;
+        return n;
+    };
+    for (f.height = kStepMinHeight; f.height + 2 * lbb::HF <= step_max_rows(precision); ++f.height)
+        if (blocks(f) <= ncu) return f;
+    f = StepForm{march_min(precision), true};
+    const int64_t slots = (int64_t)ncu * (precision == LBB_FP64 ? 2 : 3);  // blocks resident at once
+    for (const StepDims &l : ls)
+        if (l.ny < kMarchMinNy || l.nx > kMarchMaxNx) return StepForm{};
+    if (blocks(f) <= slots) return StepForm{};
+    while (f.height < kMarchMax && blocks(f) > slots) f.height += 3;
+    return f;
+}
+
+// Most blocks any form gives a lattice alone or in a batch (a batch's tiles
+// and strips are no lower than a lattice's own).
+int64_t step_max_blocks(const StepDims &l, int precision, int mode, int ncu)
+{
+    const StepForm own = step_form({l}, precision, mode, ncu);
+    return std::max(own.march ? 0 : step_blocks(l, own), step_blocks(l, StepForm{march_min(precision), true}));
+}
+
+// The one-launch grid of a lattice in a launch table.
+void set_step_grid(lbb::Inst &I, const StepForm &f, const StepDims &l, int blk0)
+{
+    I.tyF = f.height;
+    I.nbxF = f.height ? (l.nx + lbb::TXF - 1) / lbb::TXF : 0;
+    I.nbyF = f.height ? (l.ny + f.height - 1) / f.height : 0;
+    I.npF = (int)step_blocks(l, f);
+    I.blkF0 = blk0;
+}
+
+// Compute units of the current device (0 if it cannot be asked).
+int compute_units()
+{
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    return n;
+}
+
 lbb::Inst make_inst(const lbb_domain *d)
 {
     lbb::Inst I{};
@@ -384,11 +486,7 @@ lbb::Inst make_inst(const lbb_domain *d)
     I.blkB0 = 0;
     I.rel = d->rel;
     I.mpart = d->mpart;
-    I.nbxF = d->nbxF;
-    I.nbyF = d->nbyF;
-    I.tyF = d->tyF;
-    I.npF = d->nbxF * d->nbyF;
-    I.blkF0 = 0;
+    set_step_grid(I, d->form, {d->p.nx, d->p.ny}, 0);
     return I;
 }
 
@@ -441,67 +539,19 @@ void launch_thermal(hipStream_t st, const lbb::Inst *insts, const int *blk, int 
     }
 }
 
-// ---- the one-launch step (k_step) ----
-//
-// Where it is taken.  Its tiles recompute a halo of five rows and columns, so
-// it pays while a step is bound by launch and phase latencies, not by the work
-// itself: when tiles of some height fit the compute units in one round.  Timed
-// on graph replays, one launch against two (us per step): 128x64 FP64 7.1
-// against 13.6, 301x77 FP32 6.9 against 12.4, 600x151 FP32 9.2 against 13.1,
-// 511x257 FP64 12.1 against 15.8, 512x256 FP32 10.2 against 13.2, 1024x512 FP32
-// 21.6 against 23.0.  One block more than compute units costs a second round
-// (600x151: 18.3 with 912 blocks, 14.6 with 612, 9.2 with 228), and a block
-// alone on a compute unit cannot hide its loads under another's arithmetic
-// (2048x1024: 77 against 64), so larger lattices take two launches.
-//
-// The height is the smallest that fits one round, but at least 4: lower tiles
-// only add halo (128x64: 7.0-7.1 for heights 1 to 4; 256x128 FP64 8.1 with 3
-// and 7.9 with 4; 600x151 9.2 with 8, 10.1 with 13, 12.6 with 22).
-struct StepDims {
-    int nx, ny;
-};
-
-constexpr int kStepMinHeight = 4;
-// region rows a block of 16 waves has room for: four rows a wave in FP32,
-// three in FP64 (whose planes take twice the LDS)
-constexpr int step_max_rows(int precision) { return precision == LBB_FP64 ? 48 : 64; }
-
-int64_t step_tiles(const StepDims &l, int ty)
-{
-    return (int64_t)((l.nx + lbb::TXF - 1) / lbb::TXF) * ((l.ny + ty - 1) / ty);
-}
-
-// Tile height of the one-launch step for lattices that step together, each
-// with one more block for its bookkeeping; 0 when none fits one round.
-int step_height(const std::vector<StepDims> &ls, int precision, int mode, int ncu)
-{
-    if (mode != LBB_COUPLED) return 0;
-    for (int ty = kStepMinHeight; ty + 2 * lbb::HF <= step_max_rows(precision); ++ty) {
-        int64_t blocks = 0;
-        for (const StepDims &l : ls) blocks += step_tiles(l, ty) + 1;
-        if (blocks <= ncu) return ty;
-    }
-    return 0;
-}
-
-// Compute units of the current device (0 if it cannot be asked).
-int compute_units()
-{
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    return n;
-}
-
-// The block shape follows from the height: 16 waves with as few rows each as
-// hold the tile and its halo.
+// Tiles: the block shape follows from the height, 16 waves with as few rows
+// each as hold the tile and its halo.
 template <typename S>
 void launch_step(hipStream_t st, const lbb::Inst *insts, const int *blk, int nblocks, int cf, int cT, int par, int aux,
-                 int ty)
+                 const StepForm &f)
 {
     using namespace lbb;
+    if (f.march) {
+        hipLaunchKernelGGL((k_march<S, kMarchWaves>), dim3(nblocks), dim3(64 * kMarchWaves), 0, st, insts, blk, cf, cT, par);
+        return;
+    }
     const dim3 g(nblocks), b(1024);
-    const int rows = ty + 2 * HF;
+    const int rows = f.height + 2 * HF;
     if (rows <= 16) hipLaunchKernelGGL((k_step<S, 16, 1>), g, b, 0, st, insts, blk, cf, cT, par, aux);
     else if (rows <= 32) hipLaunchKernelGGL((k_step<S, 16, 2>), g, b, 0, st, insts, blk, cf, cT, par, aux);
     else if (rows <= 48) hipLaunchKernelGGL((k_step<S, 16, 3>), g, b, 0, st, insts, blk, cf, cT, par, aux);
@@ -549,14 +599,6 @@ void set_grid(lbb_domain *d)
     d->nbyB = (d->p.ny + lbb::kShapeB[d->shB].ty - 1) / lbb::kShapeB[d->shB].ty;
 }
 
-// Tiles of the one-launch step in tiles of height ty (0: two launches).
-void set_step_grid(lbb_domain *d, int ty)
-{
-    d->tyF = ty;
-    d->nbxF = ty ? (d->p.nx + lbb::TXF - 1) / lbb::TXF : 0;
-    d->nbyF = ty ? (d->p.ny + ty - 1) / ty : 0;
-}
-
 // Largest block counts over all tile shapes (sizes of the partial-sum and
 // block-table buffers).
 int max_blocks_A(const lbb_param_dims &g)
@@ -581,7 +623,7 @@ void advance_buffers(lbb_domain *d)
 // Whether the domain steps in one launch: by k_step, or isothermal by k_lb.
 bool one_launch(const lbb_domain *d)
 {
-    return !d->fixed_tiles && (d->tyF > 0 || (isothermal_one(d->p) && d->shA == 0));
+    return !d->fixed_tiles && (d->form.height > 0 || (isothermal_one(d->p) && d->shA == 0));
 }
 
 // Step number k of a sequence that ends in enqueue_flush.
@@ -590,8 +632,9 @@ void enqueue_step(lbb_domain *d, int64_t k)
 {
     const int par = (int)(k & 1);
     if (one_launch(d)) {
-        if (d->tyF)
-            launch_step<S>(d->stream, d->d_inst, d->d_blkF, d->nbxF * d->nbyF + 1, d->cf, d->cT, par, 0, d->tyF);
+        if (d->form.height)
+            launch_step<S>(d->stream, d->d_inst, d->d_blkF, (int)step_blocks({d->p.nx, d->p.ny}, d->form) + 1, d->cf,
+                           d->cT, par, 0, d->form);
         else
             launch_lb_one<S>(d->stream, d->d_inst, d->d_blkA, d->nbxA * d->nbyA + 1, d->cf, d->cT, par);
     } else {
@@ -908,7 +951,7 @@ int lbb_init_domain(const lbb_params *pin, const double *T_bottom, const double 
     d->Tb = Tb;
     make_dev_params(p, Tc, kap, d->dp);
     set_grid(d);
-    set_step_grid(d, step_height({{p.nx, p.ny}}, p.precision, p.thermal_mode, prop.multiProcessorCount));
+    d->form = step_form({{p.nx, p.ny}}, p.precision, p.thermal_mode, prop.multiProcessorCount);
     const lbb_param_dims dims{p.nx, p.ny};
     const int mbA = max_blocks_A(dims), mbB = max_blocks_B(dims);
 
@@ -933,10 +976,12 @@ int lbb_init_domain(const lbb_params *pin, const double *T_bottom, const double 
     ok = ok && alloc((void **)&d->d_blkA, (size_t)(mbA + 1) * sizeof(int));
     ok = ok && alloc((void **)&d->d_blkB, (size_t)(mbB + 1) * sizeof(int));
     ok = ok && alloc((void **)&d->rel, 2 * sizeof(long long));
-    if (d->tyF) {
-        const size_t np = (size_t)d->nbxF * d->nbyF;
+    if (p.thermal_mode == LBB_COUPLED) {
+        // a batch may step a lattice in one launch that alone takes two
+        const StepDims l{p.nx, p.ny};
+        const size_t np = (size_t)step_max_blocks(l, p.precision, p.thermal_mode, prop.multiProcessorCount);
         ok = ok && alloc((void **)&d->mpart, 2 * np * sizeof(lbb::MassSum));
-        ok = ok && alloc((void **)&d->d_blkF, (np + 1) * sizeof(int));
+        ok = ok && alloc((void **)&d->d_blkF, (size_t)(step_blocks(l, d->form) + 1) * sizeof(int));
     }
     if (!ok) {
         (void)hipGetLastError();
@@ -1282,7 +1327,8 @@ struct lbb_batch {
     int precision = 0, mode = 0;
     int shA = 0, shB = 0;                // tile shapes of the batch's launches
     bool fixed_tiles = false;            // shapes chosen by the caller
-    int tyF = 0, totF = 0;               // one-launch step: tile height (0: two launches), blocks
+    StepForm form;                       // of its steps, unless the caller chose shapes
+    int totF = 0;                        // blocks of the one-launch step
     int *d_blkF = nullptr;
     hipGraphExec_t graph[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
     void *adj_mem = nullptr;             // adjoint workspace, kept between calls
@@ -1332,22 +1378,11 @@ static int batch_tables(lbb_batch *b)
     return LBB_OK;
 }
 
-// The one-launch grid of member d in the batch's launches (its own grid when
-// it steps alone may have lower tiles), first block f0.
-static void batch_step_grid(const lbb_batch *b, const lbb_domain *d, int f0, lbb::Inst &I)
-{
-    I.tyF = b->tyF;
-    I.nbxF = b->tyF ? (d->p.nx + lbb::TXF - 1) / lbb::TXF : 0;
-    I.nbyF = b->tyF ? (d->p.ny + b->tyF - 1) / b->tyF : 0;
-    I.npF = I.nbxF * I.nbyF;
-    I.blkF0 = f0;
-}
-
 // Whether the batch steps in one launch: by k_step, or isothermal by k_lb.
 static bool one_launch(const lbb_batch *b)
 {
     if (b->fixed_tiles) return false;
-    if (b->tyF > 0) return true;
+    if (b->form.height > 0) return true;
     if (b->shA != 0) return false;
     for (const lbb_domain *d : b->doms)
         if (!isothermal_one(d->p)) return false;
@@ -1382,7 +1417,7 @@ static int batch_push(lbb_batch *b)
         I.blkB0 = b0;
         a0 += d->nbxA * d->nbyA + 1;
         b0 += d->nbxB * d->nbyB + 1;
-        batch_step_grid(b, d, f0, I);
+        set_step_grid(I, b->form, {d->p.nx, d->p.ny}, f0);
         f0 += I.npF + 1;
         insts.push_back(I);
     }
@@ -1397,14 +1432,14 @@ static void batch_enqueue_step(lbb_batch *b, int64_t k)
 {
     const int par = (int)(k & 1);
     if (one_launch(b)) {
-        if (!b->tyF && b->precision == LBB_FP64)
+        if (!b->form.height && b->precision == LBB_FP64)
             launch_lb_one<double>(b->stream, b->d_insts, b->d_blkA, b->totA, b->cf, b->cT, par);
-        else if (!b->tyF)
+        else if (!b->form.height)
             launch_lb_one<float>(b->stream, b->d_insts, b->d_blkA, b->totA, b->cf, b->cT, par);
         else if (b->precision == LBB_FP64)
-            launch_step<double>(b->stream, b->d_insts, b->d_blkF, b->totF, b->cf, b->cT, par, 0, b->tyF);
+            launch_step<double>(b->stream, b->d_insts, b->d_blkF, b->totF, b->cf, b->cT, par, 0, b->form);
         else
-            launch_step<float>(b->stream, b->d_insts, b->d_blkF, b->totF, b->cf, b->cT, par, 0, b->tyF);
+            launch_step<float>(b->stream, b->d_insts, b->d_blkF, b->totF, b->cf, b->cT, par, 0, b->form);
     } else if (b->precision == LBB_FP64) {
         launch_lb<double>(b->stream, b->d_insts, b->d_blkA, b->totA, b->cf, b->cT, b->shA);
         launch_thermal<double>(b->stream, b->d_insts, b->d_blkB, b->totB, b->cf, b->cT, b->shB);
@@ -1447,9 +1482,9 @@ extern "C" int lbb_batch_init(const lbb_params *ps, int n, const double *const *
     }
     std::vector<StepDims> dims;
     for (lbb_domain *d : b->doms) dims.push_back({d->p.nx, d->p.ny});
-    b->tyF = step_height(dims, b->precision, b->mode, compute_units());
+    b->form = step_form(dims, b->precision, b->mode, compute_units());
     std::vector<int> tf;  // block -> member of the one-launch step
-    for (int i = 0; i < n && b->tyF; ++i) tf.insert(tf.end(), step_tiles(dims[i], b->tyF) + 1, i);
+    for (int i = 0; i < n && b->form.height; ++i) tf.insert(tf.end(), step_blocks(dims[i], b->form) + 1, i);
     b->totF = (int)tf.size();
     bool ok = hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking) == hipSuccess &&
               (tf.empty() || (hipMalloc(&b->d_blkF, tf.size() * sizeof(int)) == hipSuccess &&
@@ -1849,10 +1884,11 @@ struct AdjGroup {
     const int *blkA = nullptr, *blkB = nullptr;
     int totA = 0, totB = 0;
     std::vector<int> blkA0, blkB0;  // member offsets in the forward grids
-    // one-launch forward steps (tyF > 0): blocks, table, the members' grids
-    int tyF = 0, totF = 0;
+    // one-launch forward steps: form, blocks, table, the members' first blocks
+    StepForm form;
+    int totF = 0;
     const int *blkF = nullptr;
-    std::function<void(int, lbb::Inst &)> step_grid;
+    std::vector<int> blkF0;
     int *cf = nullptr, *cT = nullptr;
     int shA = 0, shB = 0;           // tile shapes of the forward launches
     void **mem = nullptr;           // cached workspace of the owner
@@ -2030,8 +2066,8 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
     };
     auto slot_step = [&](hipStream_t s, int b, int64_t k) {
         const Inst *tab = inst_seg + ((size_t)b * K + k) * nm;
-        if (g.tyF) {
-            launch_step<S>(s, tab, g.blkF, g.totF, 0, 0, (int)(k & 1), 0, g.tyF);
+        if (g.form.height) {
+            launch_step<S>(s, tab, g.blkF, g.totF, 0, 0, (int)(k & 1), 0, g.form);
             return;
         }
         launch_lb<S>(s, tab, g.blkA, g.totA, 0, 0, g.shA);
@@ -2040,7 +2076,7 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
     // a sequence of one-launch steps starts with its launch counts at zero
     auto restart = [&](hipStream_t s) -> hipError_t {
         hipError_t e = hipSuccess;
-        for (int i = 0; i < nm && g.tyF && e == hipSuccess; ++i)
+        for (int i = 0; i < nm && g.form.height && e == hipSuccess; ++i)
             e = hipMemsetAsync(g.doms[i]->rel, 0, 2 * sizeof(long long), s);
         return e;
     };
@@ -2076,7 +2112,7 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
                 I.T[1] = y + 9 * n;
                 I.blkA0 = g.blkA0[i];
                 I.blkB0 = g.blkB0[i];
-                if (g.tyF) g.step_grid(i, I);
+                if (g.form.height) set_step_grid(I, g.form, {d->p.nx, d->p.ny}, g.blkF0[i]);
                 hinst[((size_t)b * K + k) * nm + i] = I;
             }
         AdjInst A{};
@@ -2138,7 +2174,7 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
         }
     }
     // the last state is slot N - tL, the second state of the step before it
-    launch_flush(st, g.tyF ? inst_seg + (size_t)(N - tL - 1) * nm : g.fwd_insts, nm, g.tyF > 0,
+    launch_flush(st, g.form.height ? inst_seg + (size_t)(N - tL - 1) * nm : g.fwd_insts, nm, g.form.height > 0,
                  sizeof(S) == 8 ? LBB_FP64 : LBB_FP32, 1, 1);
     LBB_HIP(hipStreamSynchronize(st));
     std::vector<Scalars> s1(nm);
@@ -2284,10 +2320,10 @@ extern "C" int lbb_adjoint(lbb_domain *d, int64_t N, int64_t K, const int32_t *h
     g.shA = d->shA;
     g.shB = d->shB;
     if (one_launch(d)) {
-        g.tyF = d->tyF;
-        g.totF = d->nbxF * d->nbyF + 1;
+        g.form = d->form;
+        g.totF = (int)step_blocks({d->p.nx, d->p.ny}, d->form) + 1;
         g.blkF = d->d_blkF;
-        g.step_grid = [](int, lbb::Inst &) {};  // as make_inst sets it
+        g.blkF0 = {0};
     }
     const size_t before = d->adj_bytes;
     g.mem = &d->adj_mem;
@@ -2333,12 +2369,14 @@ extern "C" int lbb_batch_adjoint(lbb_batch *b, int64_t N, int64_t K, double *J, 
     g.shA = b->shA;
     g.shB = b->shB;
     if (one_launch(b)) {
-        g.tyF = b->tyF;
+        g.form = b->form;
         g.totF = b->totF;
         g.blkF = b->d_blkF;
-        std::vector<int> f0(1, 0);
-        for (lbb_domain *d : b->doms) f0.push_back(f0.back() + (int)step_tiles({d->p.nx, d->p.ny}, b->tyF) + 1);
-        g.step_grid = [b, f0](int i, lbb::Inst &I) { batch_step_grid(b, b->doms[i], f0[i], I); };
+        int f0 = 0;
+        for (lbb_domain *d : b->doms) {
+            g.blkF0.push_back(f0);
+            f0 += (int)step_blocks({d->p.nx, d->p.ny}, b->form) + 1;
+        }
     }
     g.mem = &b->adj_mem;
     g.bytes = &b->adj_bytes;
@@ -2416,7 +2454,8 @@ int noalloc_scratch(int dev, unsigned char **out)
 struct NoallocLayout {
     size_t inst, sc, blkA, blkB, mass, hf, rel, mpart, blkF, total;
     int nbxA, nbyA, nbxB, nbyB;
-    int tyF, nbxF, nbyF;  // one-launch step (tyF = 0: two launches)
+    StepForm form;  // tiles or two launches
+    int npF;
 };
 
 NoallocLayout noalloc_layout(int nx, int ny, int precision, int mode, int ncu)
@@ -2444,18 +2483,18 @@ NoallocLayout noalloc_layout(int nx, int ny, int precision, int mode, int ncu)
     o += up((size_t)L.nbxB * sizeof(double));
     L.total = o;
     // the one-launch step adds its partials only where they fit as well
-    const int ty = step_height({{nx, ny}}, precision, mode, ncu);
-    const size_t np = ty ? (size_t)step_tiles({nx, ny}, ty) : 0;
+    StepForm f = step_form({{nx, ny}}, precision, mode, ncu);
+    if (f.march) f = StepForm{};  // strips do not hand out rho and v
+    const size_t np = (size_t)step_blocks({nx, ny}, f);
     L.rel = o;
     o += up(2 * sizeof(long long));
     L.mpart = o;
     o += up(2 * np * sizeof(lbb::MassSum));
     L.blkF = o;
     o += up((np + 1) * sizeof(int));
-    if (ty && o <= LBB_NOALLOC_SCRATCH_BYTES) {
-        L.tyF = ty;
-        L.nbxF = (nx + lbb::TXF - 1) / lbb::TXF;
-        L.nbyF = (ny + ty - 1) / ty;
+    if (f.height && o <= LBB_NOALLOC_SCRATCH_BYTES) {
+        L.form = f;
+        L.npF = (int)np;
         L.total = o;
     }
     return L;
@@ -2528,10 +2567,10 @@ void noalloc_enqueue(const lbb::Inst &I, unsigned char *base, const NoallocLayou
     hipLaunchKernelGGL(k_noalloc_begin<S>, dim3(nm), dim3(NT), 0, st, I, f, inst, blkA, nA, blkB, nB, blkF,
                        sc, part);
     hipLaunchKernelGGL(k_reduce_mass, dim3(1), dim3(NT), 0, st, I.P, part, nm, sc);
-    if (L.tyF && n > 0) {
+    if (L.form.height && n > 0) {
         // the first launch samples the heat flux of the given state itself
         for (int64_t k = 0; k < n; ++k) {
-            launch_step<S>(st, inst, blkF, L.nbxF * L.nbyF + 1, cf, cT, (int)(k & 1), k == n - 1, L.tyF);
+            launch_step<S>(st, inst, blkF, L.npF + 1, cf, cT, (int)(k & 1), k == n - 1, L.form);
             cf ^= 1;
             cT ^= 1;
         }
@@ -2599,10 +2638,7 @@ extern "C" int lbb_step_noalloc(const lbb_params *pin, void *const f[2], void *c
     I.nbyB = L.nbyB;
     I.rel = reinterpret_cast<long long *>(base + L.rel);
     I.mpart = reinterpret_cast<lbb::MassSum *>(base + L.mpart);
-    I.tyF = L.tyF;
-    I.nbxF = L.nbxF;
-    I.nbyF = L.nbyF;
-    I.npF = L.nbxF * L.nbyF;
+    set_step_grid(I, L.form, {p.nx, p.ny}, 0);
     int cf = phase[0], cT = phase[1];
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (p.precision == LBB_FP64) noalloc_enqueue<double>(I, base, L, cf, cT, n, result, st);

@@ -237,6 +237,251 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
     }
 }
 
+// Density and moments of a wall node, its populations completed on a copy.
+__device__ __forceinline__ double wall_density(const double f[9], int bottom)
+{
+    double g[9];
+#pragma unroll
+    for (int a = 0; a < 9; ++a) g[a] = f[a];
+    zou_he(g, bottom);
+    return node_density(g);
+}
+
+__device__ __forceinline__ Moments wall_moments(const double f[9], int bottom)
+{
+    double g[9];
+#pragma unroll
+    for (int a = 0; a < 9; ++a) g[a] = f[a];
+    zou_he(g, bottom);
+    return node_moments(g);
+}
+
+// The marching form, for lattices that fill the chip many times over.  A wave
+// owns a strip of TXF columns (with its halo one wave wide, lane = column) and
+// marches up I.tyF rows; everything a row needs from the rows around it stays
+// in the wave's registers and everything from the columns around it comes by
+// lane shifts, so there is no LDS traffic and no barrier: the loads of row
+// j + 1, the density and psi of row j, force, velocity, collision and streaming
+// of row j - 1, the coefficients and the first RK4 stage of row j - 2 and the
+// stages 2 to 4 of rows j - 3 to j - 5 run side by side in one iteration.  Five
+// rows below and above the wave's own are formed again (their collision not).
+// Blocks are WB waves on neighbouring strips; they only meet at the end, to
+// add up their mass.
+template <typename S, int WB>
+__global__ __launch_bounds__(64 * WB, sizeof(S) == 4 ? 3 : 2) void k_march(const Inst *__restrict__ insts,
+                                                                           const int *__restrict__ blk2inst, int cf,
+                                                                           int cT, int par)
+{
+    using C = typename ThermalCfg<S>::C;
+    __shared__ MassSum red[WB];
+    const Inst &I = insts[blk2inst[blockIdx.x]];
+    const DevParams &P = I.P;
+    Scalars *__restrict__ sc = I.sc;
+    const S *__restrict__ fin = static_cast<const S *>(I.f[cf]);
+    const S *__restrict__ Tin = static_cast<const S *>(I.T[cT]);
+    const int blk = (int)blockIdx.x - I.blkF0;
+    // (global loads: a flat one still pending would turn waits in the loop into
+    // waits for everything)
+    const gmem<Scalars> *scg = (const gmem<Scalars> *)sc;
+    const long long since = ((const gmem<long long> *)I.rel)[par], t = scg->tA + since;
+    if (blk == 0) {
+        sample_heat_flux<S, WB>(I, fin, Tin, t);
+        if (threadIdx.x == 0) I.rel[par ^ 1] = since + 1;
+        return;
+    }
+    S *__restrict__ fout = static_cast<S *>(I.f[cf ^ 1]);
+    S *__restrict__ Tout = static_cast<S *>(I.T[cT ^ 1]);
+    const int nx = P.nx, ny = P.ny;
+    const size_t N = (size_t)nx * ny;
+    const int tile = xcd_tile(blk - 1, I.npF);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int id = tile * WB + wv;  // strips row by row; the last block may have waves to spare
+    const int by = id / I.nbxF, strip = id - by * I.nbxF;
+    const int x0 = strip * TXF;
+    const int gx = wrapi(x0 + lane - HF, nx);
+    const int y0 = by * I.tyF, y1 = by < I.nbyF ? min(y0 + I.tyF, ny) : y0;
+    const bool walls = !P.periodic_y;
+    const bool mine = lane >= HF && lane < HF + TXF && x0 + lane - HF < nx;
+    double rho_ave = scg->rho_ave;
+    if (since) rho_ave = wave_rho_ave(I, I.mpart + (size_t)par * I.npF);
+    asm volatile("" : "+v"(rho_ave));  // here, before the loop
+
+    // lattice row of row r (at most ny beyond the lattice when periodic), and
+    // whether there is one
+    auto inside = [&](int r) { return !walls || (r >= 0 && r < ny); };
+    auto row = [&](int r) { return walls ? r : (r < 0 ? r + ny : (r >= ny ? r - ny : r)); };
+    // A row's place in a plane is uniform over the wave and goes into the
+    // scalar base; a lane adds its column and the columns its populations
+    // stream to.
+    constexpr unsigned sz = (unsigned)sizeof(S);
+    const unsigned og = (unsigned)gx * sz;
+    const unsigned oe = (unsigned)(gx + 1 == nx ? 0 : gx + 1) * sz, ow = (unsigned)(gx == 0 ? nx - 1 : gx - 1) * sz;
+
+    // rows by their number mod 3: populations and T as loaded, psi, rho, vx,
+    // vy, inputs of the stages 2 to 4
+    S fr[3][9], Tr[3];
+    Moments mp = {};  // of row j - 1
+    double ps[3] = {};
+    C xr[3] = {}, xu[3] = {}, xv[3] = {}, T1[3] = {}, T2[3] = {}, T3[3] = {};
+    // T of rows j - 5 .. j; coefficients and slope sums of rows j - 5 .. j - 2
+    C t0[6] = {}, acc[4] = {};
+    SlopeCoef<C> kf[4] = {};
+    double rc = 1.0;  // density of row j - 1
+    long long units = 0;
+    const C Tref = (C)P.T_ref;
+    const C chi6 = (C)(P.chi * (1.0 / 6.0));
+
+    auto load = [&](int r, S f[9], S &T) {
+        // always ten loads, of the nearest row where there is none, so that the
+        // wait for the row before needs not wait for these
+        const size_t o = (size_t)(walls ? min(max(r, 0), ny - 1) : row(r)) * nx;
+        // opaque copies: scalar plane bases formed on the way, one 32-bit lane
+        // offset, instead of a 64-bit address per plane and lane
+        size_t n = N;
+        unsigned v = og;
+        asm volatile("" : "+s"(n), "+v"(v));
+        T = ld_at(Tin + o, v);
+        const S *p = fin + o;
+#pragma unroll
+        for (int a = 0; a < 9; ++a, p += n) f[a] = ld_at(p, v);
+    };
+
+    // Iteration j; K = j - (y0 - HF) mod 3.  The rows of the first iterations
+    // that lie below the wave's halo are computed like any other, from whatever
+    // the registers hold, and never used.
+    auto body = [&](auto Kc, int j) {
+        constexpr int K = decltype(Kc)::value, K1 = (K + 1) % 3, K2 = (K + 2) % 3;  // rows j, j - 2 (and j + 1), j - 1
+        load(j + 1, fr[K1], Tr[K1]);
+        // row j: density and psi
+        double rj = 1.0;
+        Moments mj = mp;
+#pragma unroll
+        for (int q = 0; q < 5; ++q) t0[q] = t0[q + 1];
+        if (inside(j)) {
+            double fl[9];
+#pragma unroll
+            for (int a = 0; a < 9; ++a) fl[a] = (double)fr[K][a];
+            rj = node_density(fl);
+            mj = node_moments(fl);
+            if (walls && (j == 0 || j == ny - 1)) {
+                rj = j == 0 ? wall_density(fl, 1) : wall_density(fl, 0);
+                mj = j == 0 ? wall_moments(fl, 1) : wall_moments(fl, 0);
+            }
+            ps[K] = checked_psi(P, rj, P.T_ref + (double)Tr[K], sc, t);
+            t0[5] = (C)Tr[K];
+        }
+        // row c = j - 1: force, velocity; collision and streaming
+        {
+            const int c = j - 1, gy = row(c);
+            const bool bot = walls && gy == 0, top = walls && gy == ny - 1;
+            double pN = ps[K], pS = ps[K1];
+            if (bot) pS = pN;  // a ghost layer mirrors the first fluid row
+            if (top) pN = pS;
+            const double u = 4.0 * ps[K2] + (pN + pS), d = pN - pS;
+            double Fx, Fy, Q;
+            force_of(P, ps[K2], lane_from_right(u) - lane_from_left(u),
+                     4.0 * d + (lane_from_right(d) + lane_from_left(d)), bot || top, gy, rc, rho_ave, Fx, Fy, Q);
+            if ((bot || top) && !P.ghost) Fx = Fy = Q = 0.0;
+            double f[9];
+            const Moments mo = mp;
+            const double tau = P.tau_0 + rc * P.tau_slope, i2 = rcp_nr(rc * tau);
+            const double inv_rho = tau * i2, s_nu = rc * i2;
+            const double hx = mo.jx + 0.5 * Fx, hy = mo.jy + 0.5 * Fy;
+            const double vx = hx * inv_rho, vy = hy * inv_rho;
+            xr[K2] = (C)(S)rc;
+            xu[K2] = (C)(S)vx;
+            xv[K2] = (C)(S)vy;
+            if (bot || top) xu[K2] = xv[K2] = C(0);
+            if (c >= y0 && c < y1) {
+                collide(P, mo, rc, hx, hy, vx, vy, Fx, Fy, Q, s_nu, f);
+                const long long m = pushed_mass(P, gy, f);
+                if (mine) {
+                    // push streaming as push_node
+                    units += m;
+                    size_t n = N;
+                    unsigned vg = og, ve = oe, vw = ow;
+                    asm volatile("" : "+s"(n), "+v"(vg), "+v"(ve), "+v"(vw));
+                    S *p = fout + (size_t)gy * nx;
+                    st_at(p, vg, S(f[0]));
+                    st_at(p + n, ve, S(f[1]));
+                    st_at(p + 3 * n, vw, S(f[3]));
+                    if (!walls || gy + 1 < ny) {
+                        S *q = fout + 2 * n + (size_t)(gy + 1 == ny ? 0 : gy + 1) * nx;
+                        st_at(q, vg, S(f[2]));
+                        st_at(q + 3 * n, ve, S(f[5]));
+                        st_at(q + 4 * n, vw, S(f[6]));
+                    }
+                    if (!walls || gy > 0) {
+                        S *q = fout + 4 * n + (size_t)(gy == 0 ? ny - 1 : gy - 1) * nx;
+                        st_at(q, vg, S(f[4]));
+                        st_at(q + 3 * n, vw, S(f[7]));
+                        st_at(q + 4 * n, ve, S(f[8]));
+                    }
+                }
+            }
+        }
+        rc = rj;
+        mp = mj;
+        // rows j - 2 .. j - 5: coefficients and the four stages (no slope on
+        // the wall rows)
+        auto at_wall = [&](int r) { return walls && (r <= 0 || r >= ny - 1); };
+#pragma unroll
+        for (int q = 3; q > 0; --q) {
+            kf[q] = kf[q - 1];
+            acc[q] = acc[q - 1];
+        }
+        kf[0] = slope_coef<C>(P, chi6, xr[K1], xr[K2], xr[K], xu[K1], xu[K2], xu[K], xv[K1], xv[K2], xv[K]);
+        C h = stage_slope<C>(t0[3], t0[4], t0[2], kf[0], Tref, chi6);
+        if (at_wall(j - 2)) h = C(0);
+        acc[0] = h;
+        T1[K1] = fma(C(0.5), h, t0[3]);
+        h = stage_slope<C>(T1[K], T1[K1], T1[K2], kf[1], Tref, chi6);
+        if (at_wall(j - 3)) h = C(0);
+        acc[1] = fma(C(2), h, acc[1]);
+        T2[K] = fma(C(0.5), h, t0[2]);
+        h = stage_slope<C>(T2[K2], T2[K], T2[K1], kf[2], Tref, chi6);
+        if (at_wall(j - 4)) h = C(0);
+        acc[2] = fma(C(2), h, acc[2]);
+        T3[K2] = fma(C(1), h, t0[1]);
+        h = stage_slope<C>(T3[K1], T3[K2], T3[K], kf[3], Tref, chi6);
+        const int r = j - 5;
+        if (r >= y0 && r < y1 && !at_wall(r)) {
+            const C a = fma(C(1), h, acc[3]);
+            const S Tn = (S)(t0[0] + a * C(1.0 / 6.0));
+            if (mine) {
+                const double Tabs = P.T_ref + (double)Tn;
+                if (!(Tabs > 0.0) || !(Tabs < 1e300)) flag_error(sc, t, ERR_T);
+                unsigned v = og;
+                asm volatile("" : "+v"(v));
+                st_at(Tout + (size_t)row(r) * nx, v, Tn);
+            }
+        }
+    };
+
+    if (y0 < y1) {
+        load(y0 - HF, fr[0], Tr[0]);
+        // whole turns of the three register names; rows past y1 + HF - 1 do no
+        // harm (the host takes heights for which there are none)
+        for (int j = y0 - HF; j < y1 + HF; j += 3) {
+            body(std::integral_constant<int, 0>{}, j);
+            body(std::integral_constant<int, 1>{}, j + 1);
+            body(std::integral_constant<int, 2>{}, j + 2);
+        }
+    }
+    MassSum m{0, 0};
+    m.add(units);
+    m.hi = wave_sum_to_last(m.hi);
+    m.lo = wave_sum_to_last(m.lo);
+    if (lane == 63) red[wv] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        MassSum u{0, 0};
+#pragma unroll
+        for (int k = 0; k < WB; ++k) u.add(red[k]);
+        I.mpart[(size_t)(par ^ 1) * I.npF + tile] = u;
+    }
+}
+
 // End of a sequence of one-launch steps: rho_ave, the heat-flux sample and
 // the state index of the last state, whose buffers are cf, cT; without a
 // launch since the last flush, the sample of the current state.  One block of

@@ -1,10 +1,12 @@
-"""The one-launch step (k_step) against the two launches per step it stands
-for: the same expressions on the same operands and exact mass sums, so the
+"""The one-launch step (tiles, k_step, and marching strips, k_march) against
+the two launches per step it stands for: the same expressions on the same operands and exact mass sums, so the
 state, the heat-flux history and the checkpoint blob must agree bit for bit,
 whatever mix of graph replays and single launches made the steps.  The sizes
 reach every block shape (16, 32, 48 and 64 region rows) with ragged last tile
 columns and rows, one tile, lattices smaller than the halo, and the largest
-lattice whose tiles fit one round; walls, periodic y and the ghost layer."""
+lattice whose tiles fit one round; strips from the smallest lattice that takes
+them on, with ragged last strips, rows and blocks; walls, periodic y and the
+ghost layer."""
 import numpy as np
 import pytest
 
@@ -56,6 +58,40 @@ def test_one_launch_equals_two_launches_bitwise(nx, ny, kw, precision):
         one.step(n)
         two.step(n)
     _same_state(one, two)
+
+
+@pytest.mark.parametrize("precision,nx,ny,kw", [
+    (L.FP64, 1250, 1000, {}), (L.FP64, 1733, 767, dict(periodic_y=1)), (L.FP64, 8192, 150, dict(ghost_layer=1)),
+    (L.FP32, 2050, 1500, {}), (L.FP32, 3001, 1103, dict(periodic_y=1)), (L.FP32, 1201, 2600, dict(ghost_layer=1)),
+    (L.FP32, 4096, 2048, {}), (L.FP32, 8193, 400, {}), (L.FP64, 9000, 31, {}),
+])
+def test_marching_strips_equal_two_launches_bitwise(precision, nx, ny, kw):
+    _say("marching strips vs two launches", precision, nx, ny, kw)
+    args = _domain(nx, ny, precision, **kw)
+    one, two = L.Domain(*args), L.Domain(*args)
+    two.set_tiles(0, 0)
+    for n in (33, 2, 0, 1):
+        one.step(n)
+        two.step(n)
+    _same_state(one, two)
+
+
+@pytest.mark.parametrize("precision,sizes", [
+    (L.FP32, [(512, 256), (384, 192), (256, 128), (100, 61), (1024, 33)] * 9),
+    (L.FP64, [(512, 256), (384, 193), (256, 128)] * 6),
+    (L.FP32, [(512, 256), (384, 192), (256, 31)] * 12),
+])
+def test_marching_batch_equals_members_alone(precision, sizes):
+    """Batches large enough for marching strips (the last has a lattice of too
+    few rows for them): each member as alone, where it takes tiles."""
+    _say("marching batch", precision, len(sizes))
+    args = [_domain(nx, ny, precision) for nx, ny in dict.fromkeys(sizes)]
+    mem = [args[list(dict.fromkeys(sizes)).index(x)] for x in sizes]
+    b = L.Batch([m[0] for m in mem], [m[1] for m in mem], [m[2] for m in mem]).step(37)
+    for i, m in enumerate(args):
+        d = L.Domain(*m).step(37)
+        for k in (i, len(mem) - len(args) + i):
+            _same_state(b.domain(k), d)
 
 
 @pytest.mark.parametrize("precision", [L.FP64, L.FP32])
