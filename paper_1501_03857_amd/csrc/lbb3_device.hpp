@@ -411,7 +411,8 @@ __device__ __forceinline__ void strided_sum2(const double *__restrict__ a_, cons
 }
 
 __global__ __launch_bounds__(NR3) void k3_reduce(Geom3 g, const double *__restrict__ mpart,
-                                                 const double *__restrict__ hpart, int nb, Scalars3 *sc, int advance)
+                                                 const double *__restrict__ hpart, int nb, Scalars3 *sc, int advance,
+                                                 Scalars3 *host)
 {
     __shared__ double red[NR3 / 64];
     double m, h;
@@ -429,6 +430,7 @@ __global__ __launch_bounds__(NR3) void k3_reduce(Geom3 g, const double *__restri
             sc->last_counted = sc->t;
         }
         if (advance) sc->t += 1;
+        if (host) *host = *sc;  // host memory: the end of a sequence of steps
     }
 }
 
@@ -789,8 +791,7 @@ template <typename S>
 __global__ __launch_bounds__(NT3) void k3_read(DevParams P, Geom3 g, const S *__restrict__ fin,
                                               const S *__restrict__ Tin, const double *__restrict__ psi,
                                               const Scalars3 *sc, double *__restrict__ rho_o, double *__restrict__ u_o,
-                                              double *__restrict__ T_o, double *__restrict__ f_o,
-                                              double *__restrict__ qloc)
+                                              double *__restrict__ T_o, double *__restrict__ f_o)
 {
     const unsigned c = node_of_thread();
     if (c >= g.n) return;
@@ -816,10 +817,24 @@ __global__ __launch_bounds__(NT3) void k3_read(DevParams P, Geom3 g, const S *__
     if (T_o) T_o[c] = P.T_ref + (double)Tin[c];
     if (f_o)
         for (int a = 0; a < Q19; ++a) f_o[(size_t)a * g.n + c] = f[a];
-    if (qloc && !P.periodic_y && y == 0) {
-        const double t0 = (double)Tin[c], t1 = (double)Tin[c + (unsigned)g.nx], t2 = (double)Tin[c + 2u * (unsigned)g.nx];
-        qloc[(size_t)z * g.nx + x] = -P.cv_chi * r * (-3.0 * t0 + 4.0 * t1 - t2) / 2.0;
-    }
+}
+
+// Local heat flux of the current state, one thread a bottom node.
+template <typename S>
+__global__ __launch_bounds__(NT3) void k3_wall_flux(DevParams P, Geom3 g, const S *__restrict__ fin,
+                                                    const S *__restrict__ Tin, double *__restrict__ qloc)
+{
+    const unsigned k = blockIdx.x * NT3 + threadIdx.x;
+    if (k >= (unsigned)g.nx * (unsigned)g.nz) return;
+    const unsigned z = k / (unsigned)g.nx, x = k - z * (unsigned)g.nx;
+    const unsigned c = node(g, (int)x, 0, (int)z);
+    double f[Q19];
+    load_f(P, g, fin, c, 0, f);
+    double r = f[0];
+#pragma unroll
+    for (int a = 1; a < Q19; ++a) r += f[a];
+    const double t0 = (double)Tin[c], t1 = (double)Tin[c + (unsigned)g.nx], t2 = (double)Tin[c + 2u * (unsigned)g.nx];
+    qloc[k] = -P.cv_chi * r * (-3.0 * t0 + 4.0 * t1 - t2) / 2.0;
 }
 
 template <typename S>

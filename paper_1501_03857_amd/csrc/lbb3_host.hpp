@@ -17,6 +17,11 @@ struct lbb3_domain {
     void *rho = nullptr, *v = nullptr, *coef = nullptr, *Ts = nullptr, *acc = nullptr;
     double *psi = nullptr, *mpart = nullptr, *hpart = nullptr, *Tb_dev = nullptr;
     lbb3::Scalars3 *sc = nullptr;
+    // pinned host memory the kernels write to: the scalars as the last sequence
+    // of steps left them (`fresh`: nothing changed them since), the local flux
+    lbb3::Scalars3 *host = nullptr;
+    double *host_q = nullptr;
+    bool fresh = false;
     int nb = 0;   // blocks of the per-node launches
     int ncu = 0;  // compute units of the device
     int cf = 0, cT = 0;
@@ -34,6 +39,7 @@ void release3(lbb3_domain *d)
         for (auto &g : row)
             if (g) (void)hipGraphExecDestroy(g);
     for (void *p : d->allocs) (void)hipFree(p);
+    if (d->host) (void)hipHostFree(d->host);
     if (d->stream) (void)hipStreamDestroy(d->stream);
     release_bytes(d->held);
     delete d;
@@ -42,7 +48,7 @@ void release3(lbb3_domain *d)
 // The state reductions of the current state (rho_ave, heat-flux sample):
 // psi and rho of the current state, then one reduction block.
 template <typename S>
-void enqueue_reductions3(lbb3_domain *d, int advance)
+void enqueue_reductions3(lbb3_domain *d, int advance, bool last = false)
 {
     using namespace lbb3;
     S *v = static_cast<S *>(d->v);
@@ -50,7 +56,8 @@ void enqueue_reductions3(lbb3_domain *d, int advance)
                        static_cast<const S *>(d->f[d->cf]), static_cast<const S *>(d->T[d->cT]),
                        static_cast<S *>(d->rho), d->psi, v, v + d->g.n, v + 2 * (size_t)d->g.n, d->mpart, d->hpart,
                        d->sc);
-    hipLaunchKernelGGL(k3_reduce, dim3(1), dim3(NR3), 0, d->stream, d->g, d->mpart, d->hpart, d->nb, d->sc, advance);
+    hipLaunchKernelGGL(k3_reduce, dim3(1), dim3(NR3), 0, d->stream, d->g, d->mpart, d->hpart, d->nb, d->sc, advance,
+                       last ? d->host : nullptr);
 }
 
 // Column tiles and plane runs of the first RK4 stage.  The runs are sized
@@ -108,10 +115,10 @@ void enqueue_step3_any(lbb3_domain *d)
     else enqueue_step3<float>(d);
 }
 
-void enqueue_reductions3_any(lbb3_domain *d, int advance)
+void enqueue_reductions3_any(lbb3_domain *d, int advance, bool last)
 {
-    if (d->p.precision == LBB_FP64) enqueue_reductions3<double>(d, advance);
-    else enqueue_reductions3<float>(d, advance);
+    if (d->p.precision == LBB_FP64) enqueue_reductions3<double>(d, advance, last);
+    else enqueue_reductions3<float>(d, advance, last);
 }
 
 int build_graph3(lbb3_domain *d, hipGraphExec_t *out)
@@ -131,6 +138,7 @@ int build_graph3(lbb3_domain *d, hipGraphExec_t *out)
 
 int enqueue_steps3(lbb3_domain *d, int64_t n)
 {
+    d->fresh = false;
     while (n >= kGraphSteps) {
         hipGraphExec_t &g = d->graph[d->cf][d->cT];
         if (!g) {
@@ -141,16 +149,26 @@ int enqueue_steps3(lbb3_domain *d, int64_t n)
         n -= kGraphSteps;  // an even count: the buffers return to their parity
     }
     for (int64_t k = 0; k < n; ++k) enqueue_step3_any(d);
-    enqueue_reductions3_any(d, 0);  // rho_ave and the heat-flux sample of the final state
+    enqueue_reductions3_any(d, 0, true);  // rho_ave and the heat-flux sample of the final state
     LBB_HIP(hipGetLastError());
+    d->fresh = true;
+    return LBB_OK;
+}
+
+// The device's scalars, from their host copy where that is up to date.
+int read_scalars3(lbb3_domain *d, lbb3::Scalars3 *s)
+{
+    if (!d->fresh) LBB_HIP(hipMemcpyAsync(s, d->sc, sizeof *s, hipMemcpyDeviceToHost, d->stream));
+    LBB_HIP(hipStreamSynchronize(d->stream));
+    if (d->fresh) *s = *d->host;
     return LBB_OK;
 }
 
 int check_errors3(lbb3_domain *d)
 {
     lbb3::Scalars3 s;
-    LBB_HIP(hipMemcpyAsync(&s, d->sc, sizeof s, hipMemcpyDeviceToHost, d->stream));
-    LBB_HIP(hipStreamSynchronize(d->stream));
+    const int rc = read_scalars3(d, &s);
+    if (rc) return rc;
     if (s.err_step != ~0ULL) {
         d->poisoned = true;
         std::string what;
@@ -167,6 +185,7 @@ template <typename S>
 int set_state3(lbb3_domain *d, const double *rho, const double *u, const double *T)
 {
     const size_t n = d->g.n;
+    d->fresh = false;
     double *buf = nullptr;
     LBB_HIP(hipMalloc(&buf, 5 * n * sizeof(double)));
     int rc = LBB_OK;
@@ -270,6 +289,9 @@ int lbb3_init_domain(const lbb_params *pin, int32_t nz, const double *T_bottom, 
     d->nb = nb;
     d->ncu = std::max(1, prop.multiProcessorCount);
     bool ok = hipStreamCreateWithFlags(&d->stream, hipStreamNonBlocking) == hipSuccess;
+    ok = ok && hipHostMalloc((void **)&d->host, sizeof(lbb3::Scalars3) + Tb.size() * sizeof(double),
+                             hipHostMallocMapped | hipHostMallocPortable) == hipSuccess;
+    if (ok) d->host_q = reinterpret_cast<double *>(d->host + 1);
     auto alloc = [&](void **ptr, size_t bytes) -> bool {
         if (!ok || hipMalloc(ptr, bytes) != hipSuccess) return false;
         d->allocs.push_back(*ptr);
@@ -343,18 +365,27 @@ void *lbb3_stream(lbb3_domain *d) { return d ? (void *)d->stream : nullptr; }
 int lbb3_read_fields(lbb3_domain *d, double *rho, double *u, double *T, double *f)
 {
     if (!d) return fail(LBB_EINVAL, "domain is NULL");
+    // staging for the fields asked for only
     const size_t n = d->g.n;
+    const size_t need = n * ((rho ? 1 : 0) + (u ? 3 : 0) + (T ? 1 : 0) + (f ? 19 : 0));
+    if (!need) return LBB_OK;
     double *buf = nullptr;
-    LBB_HIP(hipMalloc(&buf, 24 * n * sizeof(double)));
-    double *drho = buf, *du = buf + n, *dT = buf + 4 * n, *df = buf + 5 * n;
+    LBB_HIP(hipMalloc(&buf, need * sizeof(double)));
+    double *at = buf;
+    auto take = [&](const double *dst, size_t k) {
+        double *p = dst ? at : nullptr;
+        at += dst ? k * n : 0;
+        return p;
+    };
+    double *drho = take(rho, 1), *du = take(u, 3), *dT = take(T, 1), *df = take(f, 19);
     if (d->p.precision == LBB_FP64)
         hipLaunchKernelGGL(lbb3::k3_read<double>, dim3(d->nb), dim3(lbb3::NT3), 0, d->stream, d->dp, d->g,
                            static_cast<const double *>(d->f[d->cf]), static_cast<const double *>(d->T[d->cT]),
-                           d->psi, d->sc, drho, du, dT, df, (double *)nullptr);
+                           d->psi, d->sc, drho, du, dT, df);
     else
         hipLaunchKernelGGL(lbb3::k3_read<float>, dim3(d->nb), dim3(lbb3::NT3), 0, d->stream, d->dp, d->g,
                            static_cast<const float *>(d->f[d->cf]), static_cast<const float *>(d->T[d->cT]),
-                           d->psi, d->sc, drho, du, dT, df, (double *)nullptr);
+                           d->psi, d->sc, drho, du, dT, df);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && rho) e = hipMemcpyAsync(rho, drho, n * sizeof(double), hipMemcpyDeviceToHost, d->stream);
     if (e == hipSuccess && u) e = hipMemcpyAsync(u, du, 3 * n * sizeof(double), hipMemcpyDeviceToHost, d->stream);
@@ -369,30 +400,25 @@ int lbb3_read_fields(lbb3_domain *d, double *rho, double *u, double *T, double *
 int lbb3_wall_heat_flux(lbb3_domain *d, double *q_now, double *q_mean, double *q_local, int64_t *n_samples)
 {
     if (!d) return fail(LBB_EINVAL, "domain is NULL");
-    lbb3::Scalars3 s;
-    LBB_HIP(hipMemcpyAsync(&s, d->sc, sizeof s, hipMemcpyDeviceToHost, d->stream));
-    if (q_local) {
-        const size_t m = (size_t)d->g.nx * d->g.nz;
-        double *buf = nullptr;
-        LBB_HIP(hipMalloc(&buf, m * sizeof(double)));
-        hipError_t e = hipMemsetAsync(buf, 0, m * sizeof(double), d->stream);
-        if (e == hipSuccess) {
-            if (d->p.precision == LBB_FP64)
-                hipLaunchKernelGGL(lbb3::k3_read<double>, dim3(d->nb), dim3(lbb3::NT3), 0, d->stream, d->dp, d->g,
-                                   static_cast<const double *>(d->f[d->cf]), static_cast<const double *>(d->T[d->cT]),
-                                   d->psi, d->sc, nullptr, nullptr, nullptr, nullptr, buf);
-            else
-                hipLaunchKernelGGL(lbb3::k3_read<float>, dim3(d->nb), dim3(lbb3::NT3), 0, d->stream, d->dp, d->g,
-                                   static_cast<const float *>(d->f[d->cf]), static_cast<const float *>(d->T[d->cT]),
-                                   d->psi, d->sc, nullptr, nullptr, nullptr, nullptr, buf);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess) e = hipMemcpyAsync(q_local, buf, m * sizeof(double), hipMemcpyDeviceToHost, d->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(d->stream);
-        (void)hipFree(buf);
-        if (e != hipSuccess) return fail(LBB_EDEVICE, std::string("heat flux read-back: ") + hipGetErrorString(e));
+    const size_t m = (size_t)d->g.nx * d->g.nz;
+    const bool local = q_local && !d->p.periodic_y;
+    if (local) {  // written to host memory by the kernel
+        const dim3 nbk((unsigned)((m + lbb3::NT3 - 1) / lbb3::NT3));
+        if (d->p.precision == LBB_FP64)
+            hipLaunchKernelGGL(lbb3::k3_wall_flux<double>, nbk, dim3(lbb3::NT3), 0, d->stream, d->dp, d->g,
+                               static_cast<const double *>(d->f[d->cf]), static_cast<const double *>(d->T[d->cT]),
+                               d->host_q);
+        else
+            hipLaunchKernelGGL(lbb3::k3_wall_flux<float>, nbk, dim3(lbb3::NT3), 0, d->stream, d->dp, d->g,
+                               static_cast<const float *>(d->f[d->cf]), static_cast<const float *>(d->T[d->cT]),
+                               d->host_q);
+        LBB_HIP(hipGetLastError());
     }
-    LBB_HIP(hipStreamSynchronize(d->stream));
+    lbb3::Scalars3 s;
+    const int rc = read_scalars3(d, &s);
+    if (rc) return rc;
+    if (local) std::memcpy(q_local, d->host_q, m * sizeof(double));
+    else if (q_local) std::memset(q_local, 0, m * sizeof(double));  // no walls
     if (q_now) *q_now = s.q_now;
     if (q_mean) *q_mean = s.n_samples > 0 ? s.q_sum / (double)s.n_samples : std::nan("");
     if (n_samples) *n_samples = s.n_samples;
@@ -405,6 +431,7 @@ int lbb3_reset_average(lbb3_domain *d)
     lbb3::Scalars3 s;
     LBB_HIP(hipMemcpyAsync(&s, d->sc, sizeof s, hipMemcpyDeviceToHost, d->stream));
     LBB_HIP(hipStreamSynchronize(d->stream));
+    d->fresh = false;
     s.q_sum = 0.0;
     s.n_samples = 0;
     LBB_HIP(hipMemcpyAsync(d->sc, &s, sizeof s, hipMemcpyHostToDevice, d->stream));
@@ -428,7 +455,8 @@ int lbb3_set_heater(lbb3_domain *d, const double *T_bottom)
                            d->Tb_dev, static_cast<float *>(d->T[0]), static_cast<float *>(d->T[1]));
     LBB_HIP(hipGetLastError());
     // the heat flux of the current state changes with T_b
-    enqueue_reductions3_any(d, 0);
+    d->fresh = false;
+    enqueue_reductions3_any(d, 0, false);
     LBB_HIP(hipStreamSynchronize(d->stream));
     return LBB_OK;
 }
@@ -437,8 +465,8 @@ int lbb3_info(lbb3_domain *d, int64_t *t, int64_t *device_bytes)
 {
     if (!d) return fail(LBB_EINVAL, "domain is NULL");
     lbb3::Scalars3 s;
-    LBB_HIP(hipMemcpyAsync(&s, d->sc, sizeof s, hipMemcpyDeviceToHost, d->stream));
-    LBB_HIP(hipStreamSynchronize(d->stream));
+    const int rc = read_scalars3(d, &s);
+    if (rc) return rc;
     if (t) *t = s.t;
     if (device_bytes) *device_bytes = d->held;
     return LBB_OK;

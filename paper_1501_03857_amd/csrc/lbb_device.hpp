@@ -265,6 +265,7 @@ struct Inst {
     long long *rel;
     MassSum *mpart;
     int nbxF, nbyF, tyF, npF, blkF0;
+    Scalars *host;  // copy of *sc in host memory, written as a sequence ends (or null)
 };
 
 // Tile of a lattice's q-th block (0 <= q < nb).  Workgroups are dispatched
@@ -1286,6 +1287,7 @@ __global__ void k_flush_heat_flux(const Inst *__restrict__ insts)
 {
     const Inst &I = insts[blockIdx.x];
     reduce_heat_flux(I.hf_part, I.nbxB, I.P.nx, I.sc, I.sc->tA);
+    if (threadIdx.x == 0 && I.host) *I.host = *I.sc;
 }
 
 // Read-back: rho, v of Eq. (6) with the force of the current state, T, and

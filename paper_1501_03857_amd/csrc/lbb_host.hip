@@ -246,9 +246,17 @@ struct lbb_domain {
     hipGraphExec_t graph[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
     std::vector<double> Tb;
     int64_t dev_bytes = 0;
+    void *small = nullptr;               // holds the launch tables, partials and scalars above
     void *adj_mem = nullptr;             // adjoint workspace, kept between calls
     size_t adj_bytes = 0;
     int64_t held = 0;                    // device bytes held against the budget
+    // Pinned host memory the kernels write results to: the scalars as of the
+    // last flush and the local heat flux.  `fresh`: nothing has changed the
+    // device's scalars since the flush that was enqueued last.
+    lbb::Scalars *host = nullptr;
+    double *host_q = nullptr;
+    bool fresh = false;
+    hipEvent_t order = nullptr;          // orders read-backs with a caller's stream
 };
 
 struct lbb_param_dims {
@@ -487,6 +495,7 @@ lbb::Inst make_inst(const lbb_domain *d)
     I.rel = d->rel;
     I.mpart = d->mpart;
     set_step_grid(I, d->form, {d->p.nx, d->p.ny}, 0);
+    I.host = d->host;
     return I;
 }
 
@@ -685,6 +694,7 @@ int build_graph(lbb_domain *d, hipGraphExec_t *out)
 
 int enqueue_steps(lbb_domain *d, int64_t n)
 {
+    d->fresh = false;
     while (n >= kGraphSteps) {
         hipGraphExec_t &g = d->graph[d->cf][d->cT];
         if (!g) {
@@ -698,14 +708,13 @@ int enqueue_steps(lbb_domain *d, int64_t n)
     for (int64_t k = 0; k < n; ++k) enqueue_step_any(d, k);
     launch_flush(d->stream, d->d_inst, 1, one_launch(d), d->p.precision, d->cf, d->cT);
     LBB_HIP(hipGetLastError());
+    d->fresh = true;
     return LBB_OK;
 }
 
-int check_errors(lbb_domain *d)
+// The error state in the scalars *s of a domain: poisons it and says where.
+int report_errors(lbb_domain *d, const lbb::Scalars &s)
 {
-    lbb::Scalars s;
-    LBB_HIP(hipMemcpyAsync(&s, d->sc, sizeof s, hipMemcpyDeviceToHost, d->stream));
-    LBB_HIP(hipStreamSynchronize(d->stream));
     if (s.err_step != ~0ULL) {
         d->poisoned = true;
         std::string what;
@@ -716,6 +725,25 @@ int check_errors(lbb_domain *d)
     }
     return LBB_OK;
 }
+
+// The device's scalars, from their host copy when the last flush left it up to
+// date (the stream `st` that flush ran on is waited for), else copied.
+int read_scalars(lbb_domain *d, hipStream_t st, lbb::Scalars *s)
+{
+    if (!d->fresh) LBB_HIP(hipMemcpyAsync(s, d->sc, sizeof *s, hipMemcpyDeviceToHost, st));
+    LBB_HIP(hipStreamSynchronize(st));
+    if (d->fresh) *s = *d->host;
+    return LBB_OK;
+}
+
+int check_errors(lbb_domain *d, hipStream_t st)
+{
+    lbb::Scalars s;
+    const int rc = read_scalars(d, st, &s);
+    return rc ? rc : report_errors(d, s);
+}
+
+int check_errors(lbb_domain *d) { return check_errors(d, d->stream); }
 
 // Recompute rho_ave and the heat-flux partials from the current state.
 template <typename S>
@@ -754,6 +782,7 @@ int set_state(lbb_domain *d, const double *rho, const double *ux, const double *
         }
         lbb::Scalars s{};
         s.err_step = ~0ULL;
+        d->fresh = false;
         if (hipMemcpyAsync(d->sc, &s, sizeof s, hipMemcpyHostToDevice, d->stream) != hipSuccess) {
             rc = fail(LBB_EDEVICE, "scalar reset failed");
             break;
@@ -784,10 +813,10 @@ void release(lbb_domain *d)
     drop_graphs(d);
     for (void *q : {d->f[0], d->f[1], d->T[0], d->T[1], d->rho, d->vx, d->vy})
         if (q) (void)hipFree(q);
-    for (void *q : {(void *)d->mass_part, (void *)d->hf_part, (void *)d->Tb_dev, (void *)d->sc,
-                    (void *)d->d_inst, (void *)d->d_blkA, (void *)d->d_blkB, (void *)d->d_blkF, (void *)d->rel,
-                    (void *)d->mpart, d->adj_mem})
+    for (void *q : {d->small, d->adj_mem})
         if (q) (void)hipFree(q);
+    if (d->host) (void)hipHostFree(d->host);
+    if (d->order) (void)hipEventDestroy(d->order);
     if (d->stream) (void)hipStreamDestroy(d->stream);
     delete d;
 }
@@ -795,17 +824,26 @@ void release(lbb_domain *d)
 template <typename S>
 int read_impl(lbb_domain *d, double *rho, double *ux, double *uy, double *T, double *f)
 {
-    const size_t N = d->N, nb = N * sizeof(double);
+    // staging for the fields asked for only
+    const size_t N = d->N;
+    struct { double *dst, *src; size_t n; } cp[] = {{rho, nullptr, N}, {ux, nullptr, N}, {uy, nullptr, N}, {T, nullptr, N}, {f, nullptr, 9 * N}};
+    size_t need = 0;
+    for (auto &c : cp) need += c.dst ? c.n : 0;
+    if (!need) return LBB_OK;
     double *buf = nullptr;
-    LBB_HIP(hipMalloc(&buf, 13 * nb));
-    double *r = buf, *u = buf + N, *v = buf + 2 * N, *t = buf + 3 * N, *ff = buf + 4 * N;
+    LBB_HIP(hipMalloc(&buf, need * sizeof(double)));
+    double *at = buf;
+    for (auto &c : cp)
+        if (c.dst) {
+            c.src = at;
+            at += c.n;
+        }
     const int nbxR = (d->p.nx + lbb::TXR - 1) / lbb::TXR, nbyR = (d->p.ny + lbb::TYR - 1) / lbb::TYR;
     hipLaunchKernelGGL(lbb::k_read<S>, dim3(nbxR * nbyR), dim3(lbb::NT), 0, d->stream, d->dp,
-                       static_cast<const S *>(d->f[d->cf]), static_cast<const S *>(d->T[d->cT]), r, u, v, t, ff,
-                       d->sc, nbxR);
+                       static_cast<const S *>(d->f[d->cf]), static_cast<const S *>(d->T[d->cT]), cp[0].src, cp[1].src,
+                       cp[2].src, cp[3].src, cp[4].src, d->sc, nbxR);
     int rc = LBB_OK;
     if (hipGetLastError() != hipSuccess) rc = fail(LBB_EDEVICE, "read-back kernel failed");
-    const struct { double *dst, *src; size_t n; } cp[] = {{rho, r, N}, {ux, u, N}, {uy, v, N}, {T, t, N}, {f, ff, 9 * N}};
     for (auto &c : cp)
         if (!rc && c.dst && hipMemcpyAsync(c.dst, c.src, c.n * sizeof(double), hipMemcpyDeviceToHost, d->stream) != hipSuccess)
             rc = fail(LBB_EDEVICE, "read-back copy failed");
@@ -962,26 +1000,42 @@ int lbb_init_domain(const lbb_params *pin, const double *T_bottom, const double 
     };
     const size_t es = d->esz;
     bool ok = hipStreamCreateWithFlags(&d->stream, hipStreamNonBlocking) == hipSuccess;
+    ok = ok && hipHostMalloc((void **)&d->host, sizeof(lbb::Scalars) + p.nx * sizeof(double),
+                             hipHostMallocMapped | hipHostMallocPortable) == hipSuccess;
+    if (ok) d->host_q = reinterpret_cast<double *>(d->host + 1);
     ok = ok && alloc(&d->f[0], 9 * N * es) && alloc(&d->f[1], 9 * N * es);
     ok = ok && alloc(&d->T[0], N * es) && alloc(&d->T[1], N * es);
     ok = ok && alloc(&d->rho, N * es) && alloc(&d->vx, N * es) && alloc(&d->vy, N * es);
-    // mass partials: one per lattice row and LB tile column (also holds the
-    // per-block partials of the set-up mass kernel, fewer)
-    ok = ok && alloc((void **)&d->mass_part,
-                     (size_t)std::max(mbA, (isothermal_one(p) ? 2 : 1) * d->nbxA * p.ny) * sizeof(double));
-    ok = ok && alloc((void **)&d->hf_part, (size_t)d->nbxB * sizeof(double));
-    ok = ok && alloc((void **)&d->Tb_dev, (size_t)p.nx * sizeof(double));
-    ok = ok && alloc((void **)&d->sc, sizeof(lbb::Scalars));
-    ok = ok && alloc((void **)&d->d_inst, sizeof(lbb::Inst));
-    ok = ok && alloc((void **)&d->d_blkA, (size_t)(mbA + 1) * sizeof(int));
-    ok = ok && alloc((void **)&d->d_blkB, (size_t)(mbB + 1) * sizeof(int));
-    ok = ok && alloc((void **)&d->rel, 2 * sizeof(long long));
-    if (p.thermal_mode == LBB_COUPLED) {
-        // a batch may step a lattice in one launch that alone takes two
-        const StepDims l{p.nx, p.ny};
-        const size_t np = (size_t)step_max_blocks(l, p.precision, p.thermal_mode, prop.multiProcessorCount);
-        ok = ok && alloc((void **)&d->mpart, 2 * np * sizeof(lbb::MassSum));
-        ok = ok && alloc((void **)&d->d_blkF, (size_t)(step_blocks(l, d->form) + 1) * sizeof(int));
+    // The small buffers share one allocation: a call to allocate and clear
+    // costs more than their contents, and a set of lattices makes many.
+    // A batch may step a lattice in one launch that alone takes two.
+    const StepDims lat{p.nx, p.ny};
+    const bool coupled = p.thermal_mode == LBB_COUPLED;
+    const size_t np = coupled ? (size_t)step_max_blocks(lat, p.precision, p.thermal_mode, prop.multiProcessorCount) : 0;
+    struct { void **ptr; size_t bytes; } const small[] = {
+        // mass partials: one per lattice row and LB tile column (also holds the
+        // per-block partials of the set-up mass kernel, fewer)
+        {(void **)&d->mass_part,
+         (size_t)std::max(mbA, (isothermal_one(p) ? 2 : 1) * d->nbxA * p.ny) * sizeof(double)},
+        {(void **)&d->hf_part, (size_t)d->nbxB * sizeof(double)},
+        {(void **)&d->Tb_dev, (size_t)p.nx * sizeof(double)},
+        {(void **)&d->sc, sizeof(lbb::Scalars)},
+        {(void **)&d->d_inst, sizeof(lbb::Inst)},
+        {(void **)&d->d_blkA, (size_t)(mbA + 1) * sizeof(int)},
+        {(void **)&d->d_blkB, (size_t)(mbB + 1) * sizeof(int)},
+        {(void **)&d->rel, 2 * sizeof(long long)},
+        {(void **)&d->mpart, 2 * np * sizeof(lbb::MassSum)},
+        {(void **)&d->d_blkF, coupled ? (size_t)(step_blocks(lat, d->form) + 1) * sizeof(int) : 0}};
+    const auto rounded = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    size_t total = 0;
+    for (const auto &q : small) total += rounded(q.bytes);
+    ok = ok && alloc(&d->small, total);
+    if (ok) {
+        char *at = static_cast<char *>(d->small);
+        for (const auto &q : small) {
+            if (q.bytes) *q.ptr = at;
+            at += rounded(q.bytes);
+        }
     }
     if (!ok) {
         (void)hipGetLastError();
@@ -1046,6 +1100,7 @@ int lbb_time_kernels(lbb_domain *d, int64_t n, double *ms_lb, double *ms_thermal
     if (!d) return fail(LBB_EINVAL, "domain is NULL");
     if (n < 1) return fail(LBB_EINVAL, "n must be >= 1");
     if (d->poisoned) return fail(LBB_ESTATE, "domain poisoned by an earlier invalid state; load a state first");
+    d->fresh = false;
     // per step: kernel start/end events of both launches, plus the ends of the run
     std::vector<hipEvent_t> ev(4 * (size_t)n + 2, nullptr);
     for (auto &e : ev) LBB_HIP(hipEventCreate(&e));
@@ -1085,16 +1140,14 @@ int lbb_read_fields_dev(lbb_domain *d, double *rho, double *ux, double *uy, doub
     // the library stream does not synchronize with the null stream by
     // itself, so the ordering is made explicit for any stream, NULL included
     hipStream_t cs = static_cast<hipStream_t>(stream);
-    hipEvent_t ev = nullptr;
-    LBB_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    if (!d->order) LBB_HIP(hipEventCreateWithFlags(&d->order, hipEventDisableTiming));
+    const hipEvent_t ev = d->order;
     {
         // the caller's earlier work on these buffers comes first
         hipError_t e0 = hipEventRecord(ev, cs);
         if (e0 == hipSuccess) e0 = hipStreamWaitEvent(d->stream, ev, 0);
-        if (e0 != hipSuccess) {
-            (void)hipEventDestroy(ev);
+        if (e0 != hipSuccess)
             return fail(LBB_EDEVICE, std::string("read-back to device buffers: ") + hipGetErrorString(e0));
-        }
     }
     const int nbxR = (d->p.nx + lbb::TXR - 1) / lbb::TXR, nbyR = (d->p.ny + lbb::TYR - 1) / lbb::TYR;
     if (d->p.precision == LBB_FP64)
@@ -1111,7 +1164,6 @@ int lbb_read_fields_dev(lbb_domain *d, double *rho, double *ux, double *uy, doub
         e = hipEventRecord(ev, d->stream);
         if (e == hipSuccess) e = hipStreamWaitEvent(cs, ev, 0);
     }
-    (void)hipEventDestroy(ev);
     if (e != hipSuccess) return fail(LBB_EDEVICE, std::string("read-back to device buffers: ") + hipGetErrorString(e));
     return LBB_OK;
 }
@@ -1134,25 +1186,22 @@ int lbb_wall_heat_flux(const lbb_domain *dc, double *q_now, double *q_mean, doub
     if (!dc) return fail(LBB_EINVAL, "domain is NULL");
     // the read-back uses the domain's stream but leaves its state alone
     lbb_domain *d = const_cast<lbb_domain *>(dc);
-    lbb::Scalars s;
-    LBB_HIP(hipMemcpyAsync(&s, d->sc, sizeof s, hipMemcpyDeviceToHost, d->stream));
-    if (q_local) {
-        double *ql = nullptr;
-        LBB_HIP(hipMalloc(&ql, d->p.nx * sizeof(double)));
+    if (q_local) {  // written to host memory by the kernel
         if (d->p.precision == LBB_FP64)
             hipLaunchKernelGGL(lbb::k_heat_flux_state<double>, dim3(d->nbxB), dim3(64), 0, d->stream, d->dp,
                                static_cast<const double *>(d->f[d->cf]), static_cast<const double *>(d->T[d->cT]),
-                               (double *)nullptr, ql);
+                               (double *)nullptr, d->host_q);
         else
             hipLaunchKernelGGL(lbb::k_heat_flux_state<float>, dim3(d->nbxB), dim3(64), 0, d->stream, d->dp,
                                static_cast<const float *>(d->f[d->cf]), static_cast<const float *>(d->T[d->cT]),
-                               (double *)nullptr, ql);
-        hipError_t e = hipMemcpyAsync(q_local, ql, d->p.nx * sizeof(double), hipMemcpyDeviceToHost, d->stream);
-        hipError_t e2 = hipStreamSynchronize(d->stream);
-        (void)hipFree(ql);
-        if (e != hipSuccess || e2 != hipSuccess) return fail(LBB_EDEVICE, "heat-flux read-back failed");
+                               (double *)nullptr, d->host_q);
+        if (hipGetLastError() != hipSuccess) return fail(LBB_EDEVICE, "heat-flux read-back failed");
     }
-    LBB_HIP(hipStreamSynchronize(d->stream));
+    lbb::Scalars s;
+    const int rc = read_scalars(d, d->stream, &s);
+    if (rc) return rc;
+    if (q_local && d->p.periodic_y) std::memset(q_local, 0, d->p.nx * sizeof(double));  // no walls
+    else if (q_local) std::memcpy(q_local, d->host_q, d->p.nx * sizeof(double));
     if (q_now) *q_now = s.q_now;
     if (q_mean) *q_mean = s.n_samples ? s.q_sum / (double)s.n_samples : NAN;
     if (n_samples) *n_samples = s.n_samples;
@@ -1165,6 +1214,7 @@ int lbb_reset_average(lbb_domain *d)
     lbb::Scalars s;
     LBB_HIP(hipMemcpyAsync(&s, d->sc, sizeof s, hipMemcpyDeviceToHost, d->stream));
     LBB_HIP(hipStreamSynchronize(d->stream));
+    d->fresh = false;
     s.q_sum = 0.0;
     s.n_samples = 0;
     LBB_HIP(hipMemcpyAsync(d->sc, &s, sizeof s, hipMemcpyHostToDevice, d->stream));
@@ -1285,6 +1335,7 @@ int lbb_load_state(lbb_domain *d, const void *buf, size_t len)
     p += sizeof s;
     s.err_step = ~0ULL;
     s.err_code = 0;
+    d->fresh = false;
     LBB_HIP(hipMemcpyAsync(d->sc, &s, sizeof s, hipMemcpyHostToDevice, d->stream));
     LBB_HIP(hipMemcpyAsync(d->hf_part, p, d->nbxB * sizeof(double), hipMemcpyHostToDevice, d->stream));
     LBB_HIP(hipStreamSynchronize(d->stream));
@@ -1305,8 +1356,8 @@ int lbb_info(lbb_domain *d, int64_t *t, int32_t *nx, int32_t *ny, int64_t *devic
     if (!d) return fail(LBB_EINVAL, "domain is NULL");
     if (t) {
         lbb::Scalars s;
-        LBB_HIP(hipMemcpyAsync(&s, d->sc, sizeof s, hipMemcpyDeviceToHost, d->stream));
-        LBB_HIP(hipStreamSynchronize(d->stream));
+        const int rc = read_scalars(d, d->stream, &s);
+        if (rc) return rc;
         *t = s.tA;
     }
     if (nx) *nx = d->p.nx;
@@ -1331,6 +1382,7 @@ struct lbb_batch {
     int totF = 0;                        // blocks of the one-launch step
     int *d_blkF = nullptr;
     hipGraphExec_t graph[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
+    std::vector<lbb::Inst> pushed;       // the launch table as last uploaded
     void *adj_mem = nullptr;             // adjoint workspace, kept between calls
     size_t adj_bytes = 0;
     int64_t held = 0;                    // device bytes held against the budget
@@ -1421,9 +1473,16 @@ static int batch_push(lbb_batch *b)
         f0 += I.npF + 1;
         insts.push_back(I);
     }
+    // upload only what differs from the device's table (padding never does:
+    // make_inst clears it)
+    if (b->pushed.size() == insts.size() &&
+        std::memcmp(b->pushed.data(), insts.data(), insts.size() * sizeof(lbb::Inst)) == 0)
+        return LBB_OK;
+    b->pushed.clear();
     LBB_HIP(hipMemcpyAsync(b->d_insts, insts.data(), insts.size() * sizeof(lbb::Inst), hipMemcpyHostToDevice,
                            b->stream));
     LBB_HIP(hipStreamSynchronize(b->stream));
+    b->pushed = insts;
     return LBB_OK;
 }
 
@@ -1522,6 +1581,7 @@ extern "C" int lbb_batch_step_async(lbb_batch *b, int64_t n)
     if (rc) return rc;
     rc = batch_push(b);  // members' parameters may have changed through their handles
     if (rc) return rc;
+    for (lbb_domain *d : b->doms) d->fresh = false;
     while (n >= kGraphSteps) {
         hipGraphExec_t &g = b->graph[b->cf][b->cT];
         if (!g) {
@@ -1545,6 +1605,7 @@ extern "C" int lbb_batch_step_async(lbb_batch *b, int64_t n)
     for (lbb_domain *d : b->doms) {
         d->cf = b->cf;
         d->cT = b->cT;
+        d->fresh = true;
     }
     return LBB_OK;
 }
@@ -1554,7 +1615,8 @@ extern "C" int lbb_batch_sync(lbb_batch *b)
     if (!b) return fail(LBB_EINVAL, "batch is NULL");
     LBB_HIP(hipStreamSynchronize(b->stream));
     for (size_t i = 0; i < b->doms.size(); ++i) {
-        int rc = check_errors(b->doms[i]);
+        lbb_domain *d = b->doms[i];
+        int rc = d->fresh ? report_errors(d, *d->host) : check_errors(d);
         if (rc) return fail(rc, "batch member " + std::to_string(i) + ": " + g_err);
     }
     return LBB_OK;
@@ -1572,14 +1634,16 @@ extern "C" void *lbb_batch_stream(lbb_batch *b) { return b ? (void *)b->stream :
 extern "C" int lbb_batch_heat_flux(lbb_batch *b, double *q_now, double *q_mean, int64_t *n_samples)
 {
     if (!b) return fail(LBB_EINVAL, "batch is NULL");
+    LBB_HIP(hipStreamSynchronize(b->stream));
     for (size_t i = 0; i < b->doms.size(); ++i) {
-        double qn = 0, qm = 0;
-        int64_t ns = 0;
-        int rc = lbb_wall_heat_flux(b->doms[i], &qn, &qm, nullptr, &ns);
+        lbb_domain *d = b->doms[i];
+        lbb::Scalars s;
+        // a member may have been stepped on its own stream since
+        const int rc = read_scalars(d, d->stream, &s);
         if (rc) return rc;
-        if (q_now) q_now[i] = qn;
-        if (q_mean) q_mean[i] = qm;
-        if (n_samples) n_samples[i] = ns;
+        if (q_now) q_now[i] = s.q_now;
+        if (q_mean) q_mean[i] = s.n_samples ? s.q_sum / (double)s.n_samples : NAN;
+        if (n_samples) n_samples[i] = s.n_samples;
     }
     return LBB_OK;
 }
@@ -1640,6 +1704,7 @@ int restore_state_dev(lbb_domain *d, const SavedState &s, hipStream_t st)
     LBB_HIP(hipMemcpyAsync(d->T[1], s.T, n * es, hipMemcpyDeviceToDevice, st));
     LBB_HIP(hipMemcpyAsync(d->sc, s.sc, sizeof(lbb::Scalars), hipMemcpyDeviceToDevice, st));
     LBB_HIP(hipMemcpyAsync(d->hf_part, s.hf, d->nbxB * sizeof(double), hipMemcpyDeviceToDevice, st));
+    d->fresh = false;
     d->cf = d->cT = 0;
     d->poisoned = false;
     return LBB_OK;
@@ -1661,6 +1726,7 @@ bool valid_shapes(int a, int b) { return a >= 0 && a < lbb::NSHAPE_A && b >= 0 &
 template <typename S>
 int batch_time_kernels(lbb_batch *b, int64_t n, double *ms_lb, double *ms_thermal)
 {
+    for (lbb_domain *d : b->doms) d->fresh = false;
     std::vector<hipEvent_t> ev(4 * (size_t)n, nullptr);
     for (auto &e : ev) LBB_HIP(hipEventCreate(&e));
     for (int64_t k = 0; k < n; ++k) {
@@ -2088,6 +2154,7 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
     // keep each lattice's state, counters and heat-flux partials
     for (int i = 0; i < nm; ++i) {
         lbb_domain *d = g.doms[i];
+        d->fresh = false;
         LBB_HIP(copy_state_out(i, m[i].backup));
         LBB_HIP(hipMemcpyAsync(&m[i].ck_sc[nck], d->sc, sizeof(Scalars), hipMemcpyDeviceToDevice, st));
         LBB_HIP(hipMemcpyAsync(m[i].hf_backup, d->hf_part, d->nbxB * sizeof(double), hipMemcpyDeviceToDevice, st));
@@ -2177,14 +2244,12 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
     launch_flush(st, g.form.height ? inst_seg + (size_t)(N - tL - 1) * nm : g.fwd_insts, nm, g.form.height > 0,
                  sizeof(S) == 8 ? LBB_FP64 : LBB_FP32, 1, 1);
     LBB_HIP(hipStreamSynchronize(st));
-    std::vector<Scalars> s1(nm);
-    for (int i = 0; i < nm; ++i) {
-        int rc = check_errors(g.doms[i]);
+    for (int i = 0; i < nm; ++i) {  // the flush has left the scalars in host memory
+        const int rc = report_errors(g.doms[i], *g.doms[i]->host);
         if (rc) return nm > 1 ? fail(rc, "batch member " + std::to_string(i) + ": " + g_err) : rc;
-        LBB_HIP(hipMemcpyAsync(&s1[i], g.doms[i]->sc, sizeof(Scalars), hipMemcpyDeviceToHost, st));
+        J[i] = g.doms[i]->host->q_sum / (double)N;
+        g.doms[i]->fresh = false;  // what follows steps and restores the device's scalars
     }
-    LBB_HIP(hipStreamSynchronize(st));
-    for (int i = 0; i < nm; ++i) J[i] = s1[i].q_sum / (double)N;
 
     // reverse sweep: the adjoint of the final state starts from its heat-flux sample
     const double wq = 1.0 / (double)N;

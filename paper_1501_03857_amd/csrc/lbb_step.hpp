@@ -527,7 +527,9 @@ __device__ __forceinline__ void flush_step(const Inst &I, int cf, int cT)
 template <typename S>
 __global__ __launch_bounds__(NT) void k_flush_step(const Inst *__restrict__ insts, int cf, int cT)
 {
-    flush_step<S>(insts[blockIdx.x], cf, cT);
+    const Inst &I = insts[blockIdx.x];
+    flush_step<S>(I, cf, cT);
+    if (threadIdx.x == 0 && I.host) *I.host = *I.sc;  // the thread that wrote the scalars
 }
 
 }  // namespace lbb
