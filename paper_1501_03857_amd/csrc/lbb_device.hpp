@@ -70,16 +70,14 @@ __device__ __forceinline__ double rcp_nr(double x)
     return fma(r, fma(e, e, e), r);
 }
 
-// 1/sqrt(x) from the hardware estimate refined by two Newton-Raphson steps,
-// y <- y + y (1/2 - x y^2 / 2): within a few ulp for normal x > 0.
+// 1/sqrt(x) from the hardware estimate refined by one third-order step,
+// y <- y + y (e/2 + 3 e^2/8) with e = 1 - x y^2: within a few ulp for normal
+// x > 0.
 __device__ __forceinline__ double rsq_nr(double x)
 {
-    double y = __builtin_amdgcn_rsq(x);
-    const double h = 0.5 * x;
-    double e = fma(-h * y, y, 0.5);
-    y = fma(y, e, y);
-    e = fma(-h * y, y, 0.5);
-    return fma(y, e, y);
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
 // sqrt(x) for normal x > 0 (no zero or negative handling), for arguments that

@@ -2012,6 +2012,41 @@ struct RecomputeStream {
     }
 };
 
+// Shape of the temperature adjoint's tiles.  A block fills a compute unit and
+// its time goes with its region rows, at any shape near 0.37 us a row, so the
+// least rounds x region rows wins (us per gradient step, the taken shape
+// first: 256x128 FP64 4-row tiles 30.9, 10-row 32.3, 18-row 34.4; 600x151
+// 10-row 40.1, 18-row 42.4, 4-row 45.5; 1024x512 22-row 123, 18-row 131,
+// 34-row 135; sixteen 384x192 FP32 34-row 205, 22-row 215, 18-row 218).
+template <typename S>
+struct TherShape {
+    void (*kernel)(const lbb::AdjInst *, const int *, int, int);
+    int threads, rows;
+};
+template <typename S>
+TherShape<S> ther_shape(const std::vector<lbb_domain *> &doms, int cus)
+{
+    using lbb::a_theradj;
+    const TherShape<S> shapes[] = {{a_theradj<S, 3, 16>, 16 * 64, 34},
+                                   {a_theradj<S, 3, 12>, 12 * 64, 22},
+                                   {a_theradj<S, 2, 16>, 16 * 64, 18},
+                                   {a_theradj<S, 2, 12>, 12 * 64, 10},
+                                   {a_theradj<S, 2, 9>, 9 * 64, 4}};
+    TherShape<S> best = shapes[0];
+    int64_t least = INT64_MAX;
+    for (const TherShape<S> &s : shapes) {
+        int64_t tiles = 0;
+        for (const lbb_domain *d : doms)
+            tiles += (int64_t)((d->p.nx + lbb::TAX - 1) / lbb::TAX) * ((d->p.ny + s.rows - 1) / s.rows);
+        const int64_t cost = (tiles + cus - 1) / cus * (s.rows + 2 * lbb::TAH);
+        if (cost < least) {
+            least = cost;
+            best = s;
+        }
+    }
+    return best;
+}
+
 // Reverse sweep with checkpoints every K steps.  With more than one segment
 // the segment storage is doubled: while the reverse steps of segment s run on
 // the group's stream from one buffer, a second stream recomputes segment
@@ -2031,39 +2066,30 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
     AdjInst *d_ai = nullptr;
     int *d_amap = nullptr, *d_tmap = nullptr;
     int tot = 0, ttot = 0;
+    // The LB adjoint takes one launch where its tiles fit one round of the
+    // compute units (two blocks each): the second launch then costs more than
+    // the halo (us per gradient step, one launch / two: 256x128 FP64 30.9 /
+    // 32.5, 600x151 FP64 40.1 / 41.0; past a round 1024x512 FP32 91.0 / 89.1,
+    // sixteen 384x192 FP32 209 / 205).
+    const int cus = compute_units();
+    const auto lb_tiles = [&](bool one) {
+        int64_t n = 0;
+        for (const lbb_domain *d : g.doms)
+            n += (int64_t)((d->p.nx + LBX - 1) / LBX) * ((d->p.ny + lb_rows(one) - 1) / lb_rows(one));
+        return n;
+    };
+    const bool lb_one = lb_tiles(true) <= 2 * cus;
+    const int lby = lb_rows(lb_one);
     for (int i = 0; i < nm; ++i) {
         const lbb_domain *d = g.doms[i];
         m[i].n = d->N;
         m[i].state_bytes = 10 * d->N * es;
-        m[i].gx = (d->p.nx + AXB - 1) / AXB;
-        m[i].nb = m[i].gx * ((d->p.ny + AYB - 1) / AYB);
+        m[i].gx = (d->p.nx + LBX - 1) / LBX;
+        m[i].nb = m[i].gx * ((d->p.ny + lby - 1) / lby);
         tot += m[i].nb;
     }
-    // temperature-adjoint tiles: 16 rows high unless that gives fewer than
-    // two tiles per compute unit, then 4 (16 waves either way; a 4-row tile
-    // and its halo are 18 region rows, so most waves own one row and the
-    // seven stencil phases are short)
-    int tay = 16;
-    {
-        int t16 = 0;
-        for (int i = 0; i < nm; ++i)
-            t16 += ((g.doms[i]->p.nx + TAX - 1) / TAX) * ((g.doms[i]->p.ny + 15) / 16);
-        if (t16 < 2 * 256) tay = 4;
-        // 24-row tiles (LDS for one block per CU) cut the halo share where
-        // there are at least four tiles per CU
-        int t24 = 0;
-        for (int i = 0; i < nm; ++i)
-            t24 += ((g.doms[i]->p.nx + TAX - 1) / TAX) * ((g.doms[i]->p.ny + 23) / 24);
-        if (t24 >= 4 * 256) tay = 24;
-        // FP32 planes take half the LDS: 32-row tiles where there are at
-        // least three per CU
-        if (sizeof(S) == 4) {
-            int t32 = 0;
-            for (int i = 0; i < nm; ++i)
-                t32 += ((g.doms[i]->p.nx + TAX - 1) / TAX) * ((g.doms[i]->p.ny + 31) / 32);
-            if (t32 >= 3 * 256) tay = 32;
-        }
-    }
+    const TherShape<S> ther = ther_shape<S>(g.doms, cus);
+    const int tay = ther.rows;
     for (int i = 0; i < nm; ++i) {
         const lbb_domain *d = g.doms[i];
         m[i].tgx = (d->p.nx + TAX - 1) / TAX;
@@ -2087,11 +2113,12 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
                 a.gr[k] = cv.take<double>(n);
             }
             AdjW &w = a.w;
-            void **arr[] = {&w.rho, &w.jx, &w.jy, &w.psi, &w.T1, &w.sx, &w.sy, &w.Fx, &w.Fy, &w.vx,
-                            &w.vy, &w.gDrx, &w.gDry, &w.gdiv, &w.grho, &w.gvx, &w.gvy, &w.gpsi, &w.gsx, &w.gsy};
+            void **arr[] = {&w.rho[0], &w.rho[1], &w.psi[0], &w.psi[1], &w.jx, &w.jy, &w.gdiv, &w.grho, &w.gvx, &w.gvy};
             for (void **p : arr) *p = cv.take<S>(n);
-            w.mpart = cv.take<double>(a.nb);
-            w.fpart = cv.take<double>(2 * (size_t)a.nb);
+            for (void **p : {&w.gpsi, &w.gsx, &w.gsy}) *p = lb_one ? nullptr : cv.take<S>(n);
+            w.mpart = cv.take<MassSum>(a.nb);
+            w.fpart = cv.take<double>((size_t)a.gx * g.doms[i]->p.ny);
+            w.gpart = cv.take<double>(a.gx);
             w.scal = cv.take<double>(4);
         }
         inst_seg = cv.take<Inst>((size_t)nbuf * K * nm);
@@ -2197,15 +2224,15 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
         A.tblk0 = (int)htmap.size();
         for (int b = 0; b < nbuf; ++b) {
             A.seg = m[i].seg[b];
+            A.T0 = own_T(i);
             hai[(size_t)b * nm + i] = A;
-            hipLaunchKernelGGL(a_bcast_T<S>, dim3(256), dim3(256), 0, st, static_cast<const S *>(own_T(i)),
-                               reinterpret_cast<S *>(m[i].seg[b]), n, (int)(K + 1));
         }
         hamap.insert(hamap.end(), m[i].nb, i);
         htmap.insert(htmap.end(), m[i].tnb, i);
     }
     LBB_HIP(hipMemcpyAsync(inst_seg, hinst.data(), hinst.size() * sizeof(Inst), hipMemcpyHostToDevice, st));
     LBB_HIP(hipMemcpyAsync(d_ai, hai.data(), hai.size() * sizeof(AdjInst), hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(a_walls_T<S>, dim3((unsigned)(nbuf * nm * (K + 1))), dim3(256), 0, st, d_ai, (int)(K + 1));
     LBB_HIP(hipMemcpyAsync(d_amap, hamap.data(), tot * sizeof(int), hipMemcpyHostToDevice, st));
     LBB_HIP(hipMemcpyAsync(d_tmap, htmap.data(), ttot * sizeof(int), hipMemcpyHostToDevice, st));
 
@@ -2257,11 +2284,15 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
         LBB_HIP(hipMemsetAsync(m[i].lf[0], 0, 9 * m[i].n * es, st));
         LBB_HIP(hipMemsetAsync(m[i].lT[0], 0, m[i].n * sizeof(double), st));
         LBB_HIP(hipMemsetAsync(m[i].gr[0], 0, m[i].n * sizeof(double), st));
-        LBB_HIP(hipMemsetAsync(m[i].w.scal, 0, 4 * sizeof(double), st));
+        LBB_HIP(hipMemsetAsync(m[i].w.fpart, 0, (size_t)m[i].gx * g.doms[i]->p.ny * sizeof(double), st));
+        LBB_HIP(hipMemsetAsync(m[i].w.gpart, 0, (size_t)m[i].gx * sizeof(double), st));
     }
-    const dim3 grid(tot), blk(NTA);
+    const dim3 grid(tot), blk(64 * lb_waves(lb_one));
+    const auto lbk_hf = lb_one ? a_hf<S, true> : a_hf<S, false>;
+    const auto lbk_macro = lb_one ? a_macro<S, true> : a_macro<S, false>;
+    const auto lbk_lb = lb_one ? a_lb<S, true> : a_lb<S, false>;
     int cur = 0;
-    hipLaunchKernelGGL(a_hf<S>, grid, blk, 0, st, d_ai, d_amap, (int)(N - tL), wq, cur);
+    hipLaunchKernelGGL(lbk_hf, grid, blk, 0, st, d_ai, d_amap, (int)(N - tL), wq, cur);
     // recompute of segment sg from its checkpoint into its buffer, on the
     // second stream once the reverse steps that last read that buffer are done
     auto recompute = [&](int64_t sg) -> hipError_t {
@@ -2287,23 +2318,19 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
         const AdjInst *ai = d_ai + (size_t)buf_of(sg) * nm;
         if (sg < nck - 1) LBB_HIP(hipStreamWaitEvent(st, rs.done, 0));  // segment sg recomputed
         if (sg > 0) LBB_HIP(recompute(sg - 1));
-        hipLaunchKernelGGL(a_macro<S>, grid, blk, 0, st, ai, d_amap, (int)(t1 - 1 - t0));
+        hipLaunchKernelGGL(lbk_macro, grid, blk, 0, st, ai, d_amap, (int)(t1 - 1 - t0), cur);
         for (int64_t t = t1 - 1; t >= t0; --t) {
             const int k = (int)(t - t0);
-            if (tay == 32) {
-                if constexpr (sizeof(S) == 4)
-                    hipLaunchKernelGGL((a_theradj<S, 32, 16>), dim3(ttot), dim3(64 * 16), 0, st, ai, d_tmap, cur);
-            } else if (tay == 24) hipLaunchKernelGGL((a_theradj<S, 24, 16>), dim3(ttot), dim3(64 * 16), 0, st, ai, d_tmap, cur);
-            else if (tay == 16) hipLaunchKernelGGL((a_theradj<S, 16, 16>), dim3(ttot), dim3(64 * 16), 0, st, ai, d_tmap, cur);
-            else hipLaunchKernelGGL((a_theradj<S, 4, 16>), dim3(ttot), dim3(64 * 16), 0, st, ai, d_tmap, cur);
-            hipLaunchKernelGGL(a_lb<S>, grid, blk, 0, st, ai, d_amap, k, cur);
-            hipLaunchKernelGGL(a_final<S>, grid, blk, 0, st, ai, d_amap, k, cur, t >= 1 ? wq : 0.0,
-                               t > t0 ? 1 : 0);
+            hipLaunchKernelGGL(ther.kernel, dim3(ttot), dim3(ther.threads), 0, st, ai, d_tmap, k, cur);
+            hipLaunchKernelGGL(lbk_lb, grid, blk, 0, st, ai, d_amap, k, cur, t >= 1 ? wq : 0.0, t > t0 ? 1 : 0);
+            if (!lb_one)
+                hipLaunchKernelGGL(a_final<S>, grid, blk, 0, st, ai, d_amap, k, cur, t >= 1 ? wq : 0.0, t > t0 ? 1 : 0);
             cur ^= 1;
         }
         LBB_HIP(hipGetLastError());
     }
     // gradients: row 0 of the adjoint of T^0, and the accumulated G_w part
+    hipLaunchKernelGGL(a_wall, dim3(nm), dim3(64), 0, st, d_ai);
     std::vector<std::vector<double>> gT(nm);
     std::vector<double> gGw(nm, 0.0);
     for (int i = 0; i < nm; ++i) {
