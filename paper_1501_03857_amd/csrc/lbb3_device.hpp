@@ -15,8 +15,8 @@
 //   Ts[2], acc            RK4 stage values and slope sum
 // Walls at y = 0 and y = ny-1 (gravity along -y), periodic x and z.
 //
-// One step t -> t+1 is seven launches, one node per thread except the first
-// RK4 stage:
+// One step t -> t+1 is five launches, or seven where pairs of RK4 stages do not
+// pay; one node per thread except where noted:
 //   k3_psi      rho (Eq. (6)) and psi (FP64 Peng-Robinson EOS, Eq. (21)) of
 //               state t; per-block FP64 partials of the mass and, on the
 //               bottom wall, of the heat flux of state t (Sec. 3.2)
@@ -24,12 +24,16 @@
 //   k3_lb       forces (Eqs. (7), (9), (22)), velocity, MRT collision with
 //               the improved forcing (Eqs. (2), (4), (5), (8)) and push
 //               streaming (Eq. (3))
-//   k3_stage0   the first RK4 stage (Eqs. (19)-(20)) of Eq. (18), one
-//               thread a column of nodes marching along z with a ring of
-//               planes in LDS; it also forms the per-node coefficients
+//   k3_pair x2  two RK4 stages each (Eqs. (19)-(20)) of Eq. (18), rows of
+//               columns marching along z; the first also forms the per-node
+//               coefficients.  Or, on small and narrow lattices:
+//   k3_stage0   the first RK4 stage and the coefficients, one thread a column
+//               of nodes marching along z with a ring of planes in LDS
 //   k3_stage x3 the other three stages; the last writes T
 // All reductions run in a fixed order, so results are reproducible bitwise.
 #pragma once
+
+#include <type_traits>
 
 #include "lbb_device.hpp"
 
@@ -752,6 +756,197 @@ __global__ __launch_bounds__(NSZ) void k3_stage0(DevParams P, Geom3 g, Tiles3 tl
         __syncthreads();
         sm = sc;
     }
+}
+
+// ---------------------------------------------------------------------------
+// Two RK4 stages in one launch, marching along z (stages 0 and 1, then 2 and
+// 3).  A wave is a row of 64 columns, a block NW rows; two columns and a row
+// either side are halo (60 x NW - 2 columns of nodes), and a block marches over
+// a run of planes.  A stencil is made of column sums: a row's value c, its
+// neighbours' sum s = N + S and difference d = N - S, kept for two planes in
+// registers, combined over x by lane shifts (the D3Q19 weights are 2 on the
+// axes and 1 on the edges).  The first stage runs one plane ahead of the
+// second; only its result passes through LDS, to the rows either side, with
+// one barrier a plane.
+// Bound by vector issue, 317 instructions a plane of the first launch (it also
+// forms the coefficients) and 193 of the second, at 157 and 114 registers:
+// hence 12 and 16 rows a block, 73.6 and 37.0 us on 150 x 151 x 150 in FP32,
+// where a launch a stage takes 66 + 27 + 27 + 26.  16 rows spill the first
+// launch (135 us), 8 rows cost more halo (91 and 40-53).
+constexpr int TXP = 60;             // columns of nodes of a tile
+constexpr int NWP[2] = {12, 16};    // rows of a block of either launch
+
+struct Col3 {
+    double c, s, d;
+};
+struct Grad3 {
+    double x, y, z, lap;  // 12 d_x, 12 d_y, 12 d_z, 6 lap
+};
+// planes z - 1, z, z + 1 of a column
+__device__ __forceinline__ Grad3 grad3(const Col3 &o, const Col3 &m, const Col3 &n)
+{
+    using lbb::lane_from_left;
+    using lbb::lane_from_right;
+    const double v = n.c + o.c, A = (2.0 * m.c + m.s) + v, Z = n.c - o.c;
+    const double aE = lane_from_right(A), aW = lane_from_left(A);
+    return {aE - aW, ((lane_from_left(m.d) + lane_from_right(m.d)) + 2.0 * m.d) + (n.d + o.d),
+            ((lane_from_left(Z) + lane_from_right(Z)) + 2.0 * Z) + (n.s - o.s),
+            ((aE + aW) + 2.0 * (m.s + v)) + ((n.s + o.s) - 24.0 * m.c)};
+}
+
+template <typename S, int NW, bool FIRST>
+__global__ __launch_bounds__(64 * NW) void k3_pair(DevParams P, Geom3 g, Tiles3 tl, const S *__restrict__ T0,
+                                                   S *__restrict__ Tmid, S *__restrict__ acc, S *__restrict__ coef,
+                                                   const S *__restrict__ rho, const S *__restrict__ vel,
+                                                   S *__restrict__ Tout, Scalars3 *sc)
+{
+    __shared__ S sh[2][NW][64];
+    constexpr unsigned B = sizeof(S);
+    const int tile = lbb::xcd_tile((int)blockIdx.x, tl.ntx * tl.nty * tl.ntz);
+    const int bx = tile % tl.ntx, by = (tile / tl.ntx) % tl.nty, bz = tile / (tl.ntx * tl.nty);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int z0 = bz * tl.zc, z1 = min(z0 + tl.zc, g.nz);
+    const int xi = bx * TXP + lane - 2, yi = by * (NW - 2) + wv - 1;
+    const bool walls = !P.periodic_y;
+    const int x = lbb::wrapi(xi, g.nx);
+    auto row = [&](int y) -> unsigned {  // row y wrapped, or clamped to the walls
+        const int r = walls ? min(max(y, 0), g.ny - 1) : lbb::wrapi(y, g.ny);
+        return ((unsigned)r * (unsigned)g.nx + (unsigned)x) * B;
+    };
+    const unsigned oc = row(yi), oN = row(yi + 1), oS = row(yi - 1);
+    const bool live = !walls || (yi > 0 && yi < g.ny - 1);  // a node the equation acts on
+    const bool mine = wv >= 1 && wv < NW - 1 && lane >= 2 && lane < 62 && xi < g.nx && yi < g.ny;
+    const size_t pl = (size_t)g.nx * g.ny, n = g.n;
+    const int wN = wv + 1 < NW ? wv + 1 : wv, wS = wv > 0 ? wv - 1 : 0;
+    const double c12 = 1.0 / 12.0, chi6 = P.chi * (1.0 / 6.0);
+    auto slope = [&](const Grad3 &G, const S a[5], double t) {
+        const double Tabs = P.T_ref + t;
+        return (chi6 * G.lap - c12 * ((double)a[0] * G.x + (double)a[1] * G.y + (double)a[2] * G.z)) +
+               ((double)a[3] * Tabs + (double)a[4] * sqrt_pos(Tabs));
+    };
+    auto widen = [](const S v[3]) { return Col3{(double)v[0], (double)v[1] + (double)v[2], (double)v[1] - (double)v[2]}; };
+
+    // the input of the first stage, and what forms or holds its coefficients
+    const S *Tin = FIRST ? T0 : Tmid;
+    struct Plane {
+        S T[3], r[FIRST ? 3 : 1], u[FIRST ? 3 : 1], v[FIRST ? 3 : 1], w[FIRST ? 3 : 1];
+    };
+    auto three = [&](const S *p, size_t z, S out[3]) {
+        out[0] = lbb::ld_at(p + z * pl, oc);
+        out[1] = lbb::ld_at(p + z * pl, oN);
+        out[2] = lbb::ld_at(p + z * pl, oS);
+    };
+    auto load = [&](int z_, Plane &q) {
+        const size_t z = (size_t)wrap3(z_, g.nz);
+        three(Tin, z, q.T);
+        if constexpr (FIRST) {
+            three(rho, z, q.r);
+            three(vel, z, q.u);
+            three(vel + n, z, q.v);
+            three(vel + 2 * n, z, q.w);
+        }
+    };
+    Col3 T[2], M[2], R[2], U[2], V[2], W[2];  // planes by parity
+    auto put = [&](int b, const Plane &q) {
+        T[b] = widen(q.T);
+        if constexpr (FIRST) {
+            R[b] = widen(q.r);
+            U[b] = widen(q.u);
+            V[b] = widen(q.v);
+            W[b] = widen(q.w);
+        }
+    };
+    Plane q;
+    load(z0 - 2, q);
+    put(0, q);
+    load(z0 - 1, q);
+    put(1, q);
+    M[0] = M[1] = Col3{0.0, 0.0, 0.0};
+    load(z0, q);
+    // of the plane the first stage left last: coefficients, T^t, slope sum
+    S a1[5] = {}, t01 = S(0);
+    double sum1 = 0.0;
+
+    // one plane: p is the newest, b its parity within the run
+    auto step = [&](int p, auto bc) {
+        constexpr int b = decltype(bc)::value;
+        Col3 nT = widen(q.T), nR{}, nU{}, nV{}, nW{};
+        if constexpr (FIRST) {
+            nR = widen(q.r);
+            nU = widen(q.u);
+            nV = widen(q.v);
+            nW = widen(q.w);
+        }
+        // first stage, plane p - 1
+        const size_t zm = (size_t)wrap3(p - 1, g.nz);
+        S a[5], t0;
+        double sum;
+        if constexpr (!FIRST) {
+            t0 = lbb::ld_at(T0 + zm * pl, oc);
+            sum = (double)lbb::ld_at(acc + zm * pl, oc);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) a[k] = lbb::ld_at(coef + k * n + zm * pl, oc);
+        }
+        if (p <= z1) load(p + 1, q);
+        if constexpr (FIRST) {
+            const double r = R[b ^ 1].c;
+            const Grad3 gr = grad3(R[b], R[b ^ 1], nR);
+            const double div = (grad3(U[b], U[b ^ 1], nU).x + grad3(V[b], V[b ^ 1], nV).y +
+                                grad3(W[b], W[b ^ 1], nW).z) * c12;
+            const double D1 = 1.0 - P.b * r, D2 = 1.0 + 2.0 * P.b * r - P.b * P.b * r * r;
+            const double inv = rcp_nr(r * D1 * D2);
+            const double kr = P.chi * c12 * (D1 * D2 * inv);
+            const double Aw = P.R_cv * div * (r * D2 * inv), Bw = P.a_cv * r * div * (r * D1 * inv);
+            a[0] = S(U[b ^ 1].c - kr * gr.x);
+            a[1] = S(V[b ^ 1].c - kr * gr.y);
+            a[2] = S(W[b ^ 1].c - kr * gr.z);
+            a[3] = S(Bw * P.k2_Tc - Aw);
+            a[4] = S(-Bw * P.k1k_rsTc);
+            t0 = S(T[b ^ 1].c);
+            sum = 0.0;
+        }
+        const double tc = T[b ^ 1].c;
+        const double h = slope(grad3(T[b], T[b ^ 1], nT), a, tc);
+        const S mid = live ? S((double)t0 + (FIRST ? 0.5 : 1.0) * h) : t0;
+        sh[b][wv][lane] = mid;
+        __syncthreads();
+        const double N = (double)sh[b][wN][lane], So = (double)sh[b][wS][lane];
+        const Col3 nM{(double)mid, N + So, N - So};
+        // second stage, plane p - 2
+        const double h2 = slope(grad3(M[b], M[b ^ 1], nM), a1, M[b ^ 1].c);
+        if (mine && p - 2 >= z0) {
+            const unsigned o = oc;
+            const size_t z = (size_t)(p - 2) * pl;
+            if constexpr (FIRST) {
+                lbb::st_at(Tmid + z, o, live ? S((double)t01 + 0.5 * h2) : t01);
+                lbb::st_at(acc + z, o, S(sum1 + 2.0 * h2));
+#pragma unroll
+                for (int k = 0; k < 5; ++k) lbb::st_at(coef + k * n + z, o, a1[k]);
+            } else {
+                const S Tn = live ? S((double)t01 + (sum1 + h2) * (1.0 / 6.0)) : t01;
+                if (live && !(P.T_ref + (double)Tn > 0.0)) flag3(sc, sc->t, lbb::ERR_T);
+                lbb::st_at(Tout + z, o, Tn);
+            }
+        }
+        M[b] = nM;
+        T[b] = nT;
+        if constexpr (FIRST) {
+            R[b] = nR;
+            U[b] = nU;
+            V[b] = nV;
+            W[b] = nW;
+        }
+#pragma unroll
+        for (int k = 0; k < 5; ++k) a1[k] = a[k];
+        t01 = t0;
+        sum1 = sum + (FIRST ? 1.0 : 2.0) * h;
+    };
+    int p = z0;
+    for (; p + 1 <= z1 + 1; p += 2) {
+        step(p, std::integral_constant<int, 0>{});
+        step(p + 1, std::integral_constant<int, 1>{});
+    }
+    if (p <= z1 + 1) step(p, std::integral_constant<int, 0>{});
 }
 
 // ---------------------------------------------------------------------------

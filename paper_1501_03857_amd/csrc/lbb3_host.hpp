@@ -77,6 +77,28 @@ lbb3::Tiles3 stage0_tiles(const lbb3::Geom3 &g, int target)
     return t;
 }
 
+// Tiles and plane runs of the two launches of two RK4 stages, one round of
+// blocks, and whether they beat a launch a stage: where at least 0.42 of the
+// lanes' plane visits of the first launch are nodes of its own, the rest being
+// halo, ragged tiles and the two planes before a run.  Timed both ways (us per
+// step, launch a stage / pairs): 0.58 150x151x150 FP32 337 / 313, FP64 617 /
+// 590; 0.47 100x100x60 73 / 65, 107 / 96; 0.46 150x151x30 76 / 69, 122 / 109;
+// 0.39 120x40x40 37 / 35, 45 / 46; 0.31 64x64x128 67 / 66, 93 / 94; 0.25
+// 64x64x64 43 / 45, 57 / 61; 0.24 24x151x120 61 / 69, 81 / 88.
+bool pair_tiles(const lbb3::Geom3 &g, int ncu, lbb3::Tiles3 t[2])
+{
+    using namespace lbb3;
+    for (int k = 0; k < 2; ++k) {
+        const int rows = NWP[k] - 2;
+        t[k] = Tiles3{(g.nx + TXP - 1) / TXP, (g.ny + rows - 1) / rows, 1, g.nz};
+        const int runs = std::max(1, std::min(g.nz, ncu / (t[k].ntx * t[k].nty)));
+        t[k].zc = (g.nz + runs - 1) / runs;
+        t[k].ntz = (g.nz + t[k].zc - 1) / t[k].zc;
+    }
+    const double visits = (double)t[0].ntx * 64 * t[0].nty * NWP[0] * t[0].ntz * (t[0].zc + 2);
+    return (double)g.n >= 0.42 * visits;
+}
+
 // One time step: reductions of state t, LB update, RK4 temperature step.
 template <typename S>
 void enqueue_step3(lbb3_domain *d)
@@ -95,6 +117,13 @@ void enqueue_step3(lbb3_domain *d)
         S *Ts0 = static_cast<S *>(d->Ts), *Ts1 = Ts0 + n;
         S *acc = static_cast<S *>(d->acc), *coef = static_cast<S *>(d->coef);
         const S *rho = static_cast<const S *>(d->rho);
+        Tiles3 tp[2];
+        if (pair_tiles(d->g, d->ncu, tp)) {
+            hipLaunchKernelGGL((k3_pair<S, NWP[0], true>), dim3(tp[0].ntx * tp[0].nty * tp[0].ntz), dim3(64 * NWP[0]), 0,
+                               d->stream, d->dp, d->g, tp[0], T0, Ts0, acc, coef, rho, v, T1, d->sc);
+            hipLaunchKernelGGL((k3_pair<S, NWP[1], false>), dim3(tp[1].ntx * tp[1].nty * tp[1].ntz), dim3(64 * NWP[1]), 0,
+                               d->stream, d->dp, d->g, tp[1], T0, Ts0, acc, coef, rho, v, T1, d->sc);
+        } else {
         const Tiles3 tl = stage0_tiles(d->g, (sizeof(S) == 4 ? 16 : 2) * d->ncu);
         hipLaunchKernelGGL(k3_stage0<S>, dim3(tl.ntx * tl.nty * tl.ntz), dim3(NSZ), 0, d->stream, d->dp, d->g, tl, T0,
                            Ts0, acc, coef, rho, v, v + n, v + 2 * n);
@@ -104,6 +133,7 @@ void enqueue_step3(lbb3_domain *d)
                            coef, d->sc);
         hipLaunchKernelGGL((k3_stage<S, 3>), dim3(d->nb), dim3(NT3), 0, d->stream, d->dp, d->g, T0, Ts0, T1, acc,
                            coef, d->sc);
+        }
     }
     if (d->dp.mode != lbb::MODE_THERMAL_ONLY) d->cf ^= 1;
     if (d->dp.mode != lbb::MODE_ISOTHERMAL) d->cT ^= 1;
