@@ -15,12 +15,13 @@
 //   Ts[2], acc            RK4 stage values and slope sum
 // Walls at y = 0 and y = ny-1 (gravity along -y), periodic x and z.
 //
-// One step t -> t+1 is five launches, or seven where pairs of RK4 stages do not
+// One step t -> t+1 is five launches, or six where pairs of RK4 stages do not
 // pay; one node per thread except where noted:
 //   k3_psi      rho (Eq. (6)) and psi (FP64 Peng-Robinson EOS, Eq. (21)) of
 //               state t; per-block FP64 partials of the mass and, on the
 //               bottom wall, of the heat flux of state t (Sec. 3.2)
-//   k3_reduce   one block: rho_ave (Eq. (9)) and the heat-flux sample
+//   k3_reduce   one block: rho_ave (Eq. (9)) and the heat-flux sample (part of
+//               k3_lb on small lattices)
 //   k3_lb       forces (Eqs. (7), (9), (22)), velocity, MRT collision with
 //               the improved forcing (Eqs. (2), (4), (5), (8)) and push
 //               streaming (Eq. (3))
@@ -414,6 +415,20 @@ __device__ __forceinline__ void strided_sum2(const double *__restrict__ a_, cons
     }
 }
 
+// rho_ave of state t from its mass and its heat-flux sample, by one thread
+__device__ __forceinline__ void count_sample(const Geom3 &g, Scalars3 *sc, double mass, double flux, int advance)
+{
+    sc->rho_ave = mass / (double)g.n;
+    const double q = flux / ((double)g.nx * (double)g.nz);
+    sc->q_now = q;
+    if (sc->t > sc->last_counted) {
+        sc->q_sum += q;
+        sc->n_samples += 1;
+        sc->last_counted = sc->t;
+    }
+    if (advance) sc->t += 1;
+}
+
 __global__ __launch_bounds__(NR3) void k3_reduce(Geom3 g, const double *__restrict__ mpart,
                                                  const double *__restrict__ hpart, int nb, Scalars3 *sc, int advance,
                                                  Scalars3 *host)
@@ -425,24 +440,42 @@ __global__ __launch_bounds__(NR3) void k3_reduce(Geom3 g, const double *__restri
     __syncthreads();
     const double hs = block_sum_r(h, red);
     if (threadIdx.x == 0) {
-        sc->rho_ave = ms / (double)g.n;
-        const double q = hs / ((double)g.nx * (double)g.nz);
-        sc->q_now = q;
-        if (sc->t > sc->last_counted) {
-            sc->q_sum += q;
-            sc->n_samples += 1;
-            sc->last_counted = sc->t;
-        }
-        if (advance) sc->t += 1;
+        count_sample(g, sc, ms, hs, advance);
         if (host) *host = *sc;  // host memory: the end of a sequence of steps
     }
 }
 
-// total force on a node of state t (Eq. (7) + Eq. (22) + Eq. (9)) and
+// Sums of up to NR3 partials in the order of k3_reduce, by a block of NT3
+// threads that all need the mass: the partials of 64 consecutive blocks by a
+// wave, then those sums in order.
+constexpr int NG3 = NR3 / 64;
+__device__ __forceinline__ double group_sums3(const double *__restrict__ part, int nb, double *red /* [NG3] */)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double v[NG3 / (NT3 / 64)];
+#pragma unroll
+    for (int j = 0; j < NG3 / (NT3 / 64); ++j) {
+        const int k = 64 * (w + j * (NT3 / 64)) + lane;
+        v[j] = k < nb ? 0.0 + ((const gmem<double> *)part)[k] : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < NG3 / (NT3 / 64); ++j) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[j] += __shfl_xor(v[j], off, 64);
+        if (lane == 0) red[w + j * (NT3 / 64)] = v[j];
+    }
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < NG3; ++k) s += red[k];
+    return s;
+}
+
+// force on a node of state t but for gravity (Eq. (7) + Eq. (22)) and
 // Q = |F_m|^2/psi^2 (Eq. (8)): none on the wall rows; the fluid-solid force
 // on the rows next to them, the wall rows being the solid
 __device__ __forceinline__ void force3(const DevParams &P, const Geom3 &g, const Nb3 &nb, const double *__restrict__ psi,
-                                       int y, unsigned c, double rho, double rho_ave, double F[3], double &Q)
+                                       int y, unsigned c, double F[3], double &Q)
 {
     F[0] = F[1] = F[2] = 0.0;
     Q = 0.0;
@@ -464,7 +497,6 @@ __device__ __forceinline__ void force3(const DevParams &P, const Geom3 &g, const
         if (y == 1) F[1] += P.Gw_bottom * pc * pc * (1.0 / 6.0);
         if (y == g.ny - 2) F[1] -= P.Gw_top * pc * pc * (1.0 / 6.0);
     }
-    F[1] -= (rho - rho_ave) * P.g;
 }
 
 // MRT collision of one node in the D3Q19 basis with the improved forcing,
@@ -501,26 +533,44 @@ __device__ __forceinline__ void collide3(const DevParams &P, const double m[Q19]
     from_moments(mh, f);
 }
 
-// forces, velocity, collision and push streaming of state t
-template <typename S>
+// Forces, velocity, collision and push streaming of state t.  With SUM every
+// block sums the mass partials itself (there are at most NR3) and one more
+// block counts the heat-flux sample: the reduction is no launch of its own.
+template <typename S, bool SUM>
 __global__ __launch_bounds__(NT3) void k3_lb(DevParams P, Geom3 g, const S *__restrict__ fin, S *__restrict__ fout,
                                             const double *__restrict__ psi, S *__restrict__ vx_o,
-                                            S *__restrict__ vy_o, S *__restrict__ vz_o, const Scalars3 *sc)
+                                            S *__restrict__ vy_o, S *__restrict__ vz_o, Scalars3 *sc,
+                                            const double *__restrict__ mpart, const double *__restrict__ hpart)
 {
-    const unsigned c = node_of_thread();
+    __shared__ double red[SUM ? 2 : 1][NG3];
+    const int nblk = (int)gridDim.x - (SUM ? 1 : 0);
+    if constexpr (SUM)
+        if ((int)blockIdx.x == nblk) {
+            const double mass = group_sums3(mpart, nblk, red[0]);
+            const double flux = group_sums3(hpart, nblk, red[1]);
+            if (threadIdx.x == 0) count_sample(g, sc, mass, flux, 1);
+            return;
+        }
+    const unsigned c = (unsigned)lbb::xcd_tile((int)blockIdx.x, nblk) * 256u + threadIdx.x;
+    int x = 0, y = 0, z = 0;
+    double f[Q19], m[Q19], F[3], Q;
+    Nb3 nb{};
+    if (c < g.n) {
+        coords(g, c, x, y, z);
+        load_f(P, g, fin, c, y, f);
+        moments(f, m);  // m_0 = rho, (m_3, m_5, m_7) = sum e f
+        nb = neighbours(P, g, x, y, z);
+        force3(P, g, nb, psi, y, c, F, Q);
+    }
+    double rho_ave;
+    if constexpr (SUM) rho_ave = group_sums3(mpart, nblk, red[0]) / (double)g.n;  // the loads above are on their way
+    else rho_ave = sc->rho_ave;
     if (c >= g.n) return;
-    int x, y, z;
-    coords(g, c, x, y, z);
-    double f[Q19], m[Q19];
-    load_f(P, g, fin, c, y, f);
-    moments(f, m);  // m_0 = rho, (m_3, m_5, m_7) = sum e f
+    const bool wall = !P.periodic_y && (y == 0 || y == g.ny - 1);
     const double rho = m[0];
-    const Nb3 nb = neighbours(P, g, x, y, z);
-    double F[3], Q;
-    force3(P, g, nb, psi, y, c, rho, sc->rho_ave, F, Q);
+    if (!wall) F[1] -= (rho - rho_ave) * P.g;
     const double inv = rcp_nr(rho);
     const double v[3] = {(m[3] + 0.5 * F[0]) * inv, (m[5] + 0.5 * F[1]) * inv, (m[7] + 0.5 * F[2]) * inv};
-    const bool wall = !P.periodic_y && (y == 0 || y == g.ny - 1);
     ((gmem<S> *)vx_o)[c] = wall ? S(0) : S(v[0]);
     ((gmem<S> *)vy_o)[c] = wall ? S(0) : S(v[1]);
     ((gmem<S> *)vz_o)[c] = wall ? S(0) : S(v[2]);
@@ -998,7 +1048,10 @@ __global__ __launch_bounds__(NT3) void k3_read(DevParams P, Geom3 g, const S *__
 #pragma unroll
     for (int a = 1; a < Q19; ++a) r += f[a];
     double F[3] = {0.0, 0.0, 0.0}, Q;
-    if (P.mode != lbb::MODE_THERMAL_ONLY) force3(P, g, neighbours(P, g, x, y, z), psi, y, c, r, sc->rho_ave, F, Q);
+    if (P.mode != lbb::MODE_THERMAL_ONLY) {
+        force3(P, g, neighbours(P, g, x, y, z), psi, y, c, F, Q);
+        if (P.periodic_y || (y > 0 && y < g.ny - 1)) F[1] -= (r - sc->rho_ave) * P.g;  // Eq. (9)
+    }
     double j[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int a = 1; a < Q19; ++a) {

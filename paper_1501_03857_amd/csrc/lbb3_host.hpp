@@ -48,7 +48,7 @@ void release3(lbb3_domain *d)
 // The state reductions of the current state (rho_ave, heat-flux sample):
 // psi and rho of the current state, then one reduction block.
 template <typename S>
-void enqueue_reductions3(lbb3_domain *d, int advance, bool last = false)
+void enqueue_reductions3(lbb3_domain *d, int advance, bool last = false, bool reduce = true)
 {
     using namespace lbb3;
     S *v = static_cast<S *>(d->v);
@@ -56,8 +56,9 @@ void enqueue_reductions3(lbb3_domain *d, int advance, bool last = false)
                        static_cast<const S *>(d->f[d->cf]), static_cast<const S *>(d->T[d->cT]),
                        static_cast<S *>(d->rho), d->psi, v, v + d->g.n, v + 2 * (size_t)d->g.n, d->mpart, d->hpart,
                        d->sc);
-    hipLaunchKernelGGL(k3_reduce, dim3(1), dim3(NR3), 0, d->stream, d->g, d->mpart, d->hpart, d->nb, d->sc, advance,
-                       last ? d->host : nullptr);
+    if (reduce)
+        hipLaunchKernelGGL(k3_reduce, dim3(1), dim3(NR3), 0, d->stream, d->g, d->mpart, d->hpart, d->nb, d->sc, advance,
+                           last ? d->host : nullptr);
 }
 
 // Column tiles and plane runs of the first RK4 stage.  The runs are sized
@@ -104,13 +105,19 @@ template <typename S>
 void enqueue_step3(lbb3_domain *d)
 {
     using namespace lbb3;
-    enqueue_reductions3<S>(d, 1);
+    const bool flow = d->dp.mode != lbb::MODE_THERMAL_ONLY;
+    // up to NR3 partials the blocks of k3_lb sum themselves, four loads a
+    // thread beside its own: us per step with a reduction launch / without,
+    // 40x51x20 FP64 26.1 / 24.3, 64x64x60 55.2 / 53.0, FP32 43.2 / 41.6 (940
+    // partials); every block would read more than its own nodes beyond
+    const bool sum = flow && d->nb <= NR3;
+    enqueue_reductions3<S>(d, 1, false, !sum);
     const size_t n = d->g.n;
     S *v = static_cast<S *>(d->v);
-    if (d->dp.mode != lbb::MODE_THERMAL_ONLY)
-        hipLaunchKernelGGL(k3_lb<S>, dim3(d->nb), dim3(NT3), 0, d->stream, d->dp, d->g,
+    if (flow)
+        hipLaunchKernelGGL((sum ? k3_lb<S, true> : k3_lb<S, false>), dim3(d->nb + (sum ? 1 : 0)), dim3(NT3), 0, d->stream, d->dp, d->g,
                            static_cast<const S *>(d->f[d->cf]), static_cast<S *>(d->f[d->cf ^ 1]), d->psi, v,
-                           v + n, v + 2 * n, d->sc);
+                           v + n, v + 2 * n, d->sc, d->mpart, d->hpart);
     if (d->dp.mode != lbb::MODE_ISOTHERMAL) {
         const S *T0 = static_cast<const S *>(d->T[d->cT]);
         S *T1 = static_cast<S *>(d->T[d->cT ^ 1]);

@@ -45,3 +45,29 @@ def test_stage_pairs_repeat_a_small_lattice(nx, ny, nz, rx, rz, kw, precision, b
     if not kw.get("periodic_y"):
         ha, hb = small.heat_flux(), big.heat_flux()
         assert abs(ha["q_mean"] - hb["q_mean"]) <= 100 * bound * np.abs(ha["q_local"]).max()
+
+
+@pytest.mark.parametrize("nx,ny,nz,kw", [
+    (5, 4, 3, {}), (19, 14, 11, dict(periodic_y=1)), (64, 64, 64, {}), (64, 64, 65, {}),
+    (19, 14, 11, dict(thermal_mode=L.ISOTHERMAL)),
+])
+def test_reductions_do_not_depend_on_how_steps_are_split(nx, ny, nz, kw):
+    """rho_ave and the heat-flux samples come from the LB launch's own blocks up
+    to 1024 partials (64^3 has 1024, 64 x 64 x 65 more) and from a reduction
+    launch at the end of a sequence: the same sums in the same order."""
+    print("[gpu-case] 3-D split steps", nx, ny, nz, kw, flush=True)
+    p, Tb, rho = _domain(nx, ny, L.FP64, **kw)
+    rho = np.broadcast_to(np.asarray(rho).reshape(1, ny, nx), (nz, ny, nx)).copy()
+    Tb = np.broadcast_to(np.asarray(Tb).reshape(1, nx), (nz, nx)).copy()
+    a, b = L.Domain3(p, nz, Tb, rho), L.Domain3(p, nz, Tb, rho)
+    a.step(37)
+    q = []
+    for n in (1, 1, 32, 0, 3):
+        b.step(n)
+        q.append(b.heat_flux()["q_now"])
+    fa, fb = a.fields(), b.fields()
+    for k in ("f", "T", "rho", "ux", "uy", "uz"):
+        assert np.array_equal(fa[k], fb[k]), k
+    ha, hb = a.heat_flux(), b.heat_flux()
+    assert ha["n_samples"] == hb["n_samples"] == 37 and a.t == b.t == 37
+    assert ha["q_now"] == hb["q_now"] and ha["q_mean"] == hb["q_mean"]
