@@ -257,12 +257,19 @@ __device__ __forceinline__ unsigned nb_at(const Nb3 &b, unsigned c, int a)
     return (unsigned)((int)c + b.dx[EX3[a] + 1] + b.dy[EY3[a] + 1] + b.dz[EZ3[a] + 1]);
 }
 
-template <typename S>
+// Populations of a node, completed on the wall rows.  STREAM: lattices whose
+// two buffers of them do not stay in the 256 MB last-level cache between
+// launches load them past it, which leaves it to the fields that the next
+// launches read again.
+template <bool STREAM = false, typename S>
 __device__ __forceinline__ void load_f(const DevParams &P, const Geom3 &g, const S *__restrict__ f, unsigned c, int y,
                                        double fl[Q19])
 {
 #pragma unroll
-    for (int a = 0; a < Q19; ++a) fl[a] = (double)lbb::ld_at(f + (size_t)a * g.n, c * (unsigned)sizeof(S));
+    for (int a = 0; a < Q19; ++a) {
+        const S *p = f + (size_t)a * g.n;
+        fl[a] = (double)(STREAM ? lbb::ld_stream(p, c * (unsigned)sizeof(S)) : lbb::ld_at(p, c * (unsigned)sizeof(S)));
+    }
     if (!P.periodic_y && P.mode != lbb::MODE_THERMAL_ONLY) {
         if (y == 0) zou_he3(fl, true);
         else if (y == g.ny - 1) zou_he3(fl, false);
@@ -312,7 +319,7 @@ __device__ __forceinline__ double psi_of(const DevParams &P, double rho, double 
 // ---------------------------------------------------------------------------
 // rho and psi of state t; mass and bottom-wall heat-flux partials per block.
 // In THERMAL_ONLY mode (f frozen) it also writes v = sum e f / rho.
-template <typename S>
+template <typename S, bool STREAM>
 __global__ __launch_bounds__(NT3) void k3_psi(DevParams P, Geom3 g, const S *__restrict__ f, const S *__restrict__ T,
                                              S *__restrict__ rho_o, double *__restrict__ psi_o, S *__restrict__ vx_o,
                                              S *__restrict__ vy_o, S *__restrict__ vz_o, double *__restrict__ mpart,
@@ -326,7 +333,7 @@ __global__ __launch_bounds__(NT3) void k3_psi(DevParams P, Geom3 g, const S *__r
         int x, y, z;
         coords(g, c, x, y, z);
         double fl[Q19];
-        load_f(P, g, f, c, y, fl);
+        load_f<STREAM>(P, g, f, c, y, fl);
         double r = fl[0];
 #pragma unroll
         for (int a = 1; a < Q19; ++a) r += fl[a];
@@ -536,7 +543,7 @@ __device__ __forceinline__ void collide3(const DevParams &P, const double m[Q19]
 // Forces, velocity, collision and push streaming of state t.  With SUM every
 // block sums the mass partials itself (there are at most NR3) and one more
 // block counts the heat-flux sample: the reduction is no launch of its own.
-template <typename S, bool SUM>
+template <typename S, bool SUM, bool STREAM>
 __global__ __launch_bounds__(NT3) void k3_lb(DevParams P, Geom3 g, const S *__restrict__ fin, S *__restrict__ fout,
                                             const double *__restrict__ psi, S *__restrict__ vx_o,
                                             S *__restrict__ vy_o, S *__restrict__ vz_o, Scalars3 *sc,
@@ -557,7 +564,7 @@ __global__ __launch_bounds__(NT3) void k3_lb(DevParams P, Geom3 g, const S *__re
     Nb3 nb{};
     if (c < g.n) {
         coords(g, c, x, y, z);
-        load_f(P, g, fin, c, y, f);
+        load_f<STREAM>(P, g, fin, c, y, f);
         moments(f, m);  // m_0 = rho, (m_3, m_5, m_7) = sum e f
         nb = neighbours(P, g, x, y, z);
         force3(P, g, nb, psi, y, c, F, Q);

@@ -22,6 +22,7 @@ struct lbb3_domain {
     lbb3::Scalars3 *host = nullptr;
     double *host_q = nullptr;
     bool fresh = false;
+    bool stream_f = false;  // f is loaded past the caches
     int nb = 0;   // blocks of the per-node launches
     int ncu = 0;  // compute units of the device
     int cf = 0, cT = 0;
@@ -52,7 +53,7 @@ void enqueue_reductions3(lbb3_domain *d, int advance, bool last = false, bool re
 {
     using namespace lbb3;
     S *v = static_cast<S *>(d->v);
-    hipLaunchKernelGGL(k3_psi<S>, dim3(d->nb), dim3(NT3), 0, d->stream, d->dp, d->g,
+    hipLaunchKernelGGL((d->stream_f ? k3_psi<S, true> : k3_psi<S, false>), dim3(d->nb), dim3(NT3), 0, d->stream, d->dp, d->g,
                        static_cast<const S *>(d->f[d->cf]), static_cast<const S *>(d->T[d->cT]),
                        static_cast<S *>(d->rho), d->psi, v, v + d->g.n, v + 2 * (size_t)d->g.n, d->mpart, d->hpart,
                        d->sc);
@@ -115,7 +116,7 @@ void enqueue_step3(lbb3_domain *d)
     const size_t n = d->g.n;
     S *v = static_cast<S *>(d->v);
     if (flow)
-        hipLaunchKernelGGL((sum ? k3_lb<S, true> : k3_lb<S, false>), dim3(d->nb + (sum ? 1 : 0)), dim3(NT3), 0, d->stream, d->dp, d->g,
+        hipLaunchKernelGGL((sum ? k3_lb<S, true, false> : d->stream_f ? k3_lb<S, false, true> : k3_lb<S, false, false>), dim3(d->nb + (sum ? 1 : 0)), dim3(NT3), 0, d->stream, d->dp, d->g,
                            static_cast<const S *>(d->f[d->cf]), static_cast<S *>(d->f[d->cf ^ 1]), d->psi, v,
                            v + n, v + 2 * n, d->sc, d->mpart, d->hpart);
     if (d->dp.mode != lbb::MODE_ISOTHERMAL) {
@@ -322,6 +323,12 @@ int lbb3_init_domain(const lbb_params *pin, int32_t nz, const double *T_bottom, 
     d->p = p;
     d->esz = esz;
     make_dev_params(p, Tc, kap, d->dp);
+    // Non-temporal loads of f from 210 MB of it on (us per step, plain / non-
+    // temporal): 640 MB 200x200x200 FP32 715 / 691; 513 MB 150x151x150 FP32 315
+    // / 302; 368 MB 110x100x110 FP64 215 / 184; 311 MB 128x100x80 FP64 175 / 151;
+    // 233 MB 96x80x100 FP64 126 / 118; 184 MB 110x100x110 FP32 98 / 110; 156 MB
+    // 128x100x80 FP32 91 / 97.
+    d->stream_f = 2.0 * 19.0 * (double)n * (double)esz > 210e6;
     d->g = lbb3::Geom3{p.nx, p.ny, nz, (unsigned)n};
     d->nb = nb;
     d->ncu = std::max(1, prop.multiProcessorCount);

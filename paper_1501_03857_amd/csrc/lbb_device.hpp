@@ -299,6 +299,13 @@ __device__ __forceinline__ T ld_at(const T *plane, unsigned byte_off)
     return *(const gmem<T> *)((const gmem<char> *)plane + byte_off);
 }
 
+// the same without a claim on the caches (data larger than they hold)
+template <typename T>
+__device__ __forceinline__ T ld_stream(const T *plane, unsigned byte_off)
+{
+    return __builtin_nontemporal_load((const gmem<T> *)((const gmem<char> *)plane + byte_off));
+}
+
 template <typename T>
 __device__ __forceinline__ void st_at(T *plane, unsigned byte_off, T v)
 {
