@@ -4,8 +4,8 @@
 Workload: the 1024x512 boiling lattice (a = 2/49, T_s = 0.86 T_c,
 full-width heater at 0.10 T_c, G_w = 0.107 for a 60 deg contact angle), FP32 storage, inputs
 resident in HBM before the timed region.  A "step" is one time step of the
-whole hot path (LB launch + thermal launch, with the mass and heat-flux
-reductions) over the lattice.  --steps K steps are timed with HIP events on
+whole hot path (one launch on this lattice: LB, temperature, the mass and
+heat-flux reductions) over the lattice.  --steps K steps are timed with HIP events on
 the library's stream around graph replays; value = nx*ny*K / time in MLUPS.
 
 Prints ONE JSON line.  --gpus N > 1 exits: the benchmark runs on one GPU.
@@ -41,47 +41,51 @@ def _kernel_roofline(alg_bytes, ms, traffic, per_update):
             "traffic_unit": "bytes per launch"}
 
 # HBM traffic of each launch from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE
-# (KiB per dispatch, mean over the dispatches of a --profile run with the
-# given tiles), each scaled by what the same counter reads for an
-# elementwise kernel that reads 1 GiB and writes 1 GiB (FETCH_SIZE 524297.8
-# KiB -> factor 2.00, WRITE_SIZE 1048576 KiB -> factor 1.0).  The factor is
-# the one under which the 3-D kernels whose reads are fixed by their design
-# fetch exactly those bytes; a copy whose input sits partly in the
-# last-level cache reads less (one session read 436918.5 KiB), since
-# FETCH_SIZE does not count those hits.  Valid for the kernel source whose
-# hash is recorded and the same tile shape; null otherwise.
+# (KiB per dispatch, mean over the dispatches of a --profile run), each scaled
+# by what the same counter reads for an elementwise kernel that reads 1 GiB and
+# writes 1 GiB (FETCH_SIZE 524296.2 KiB -> factor 2.00, WRITE_SIZE 1048576 KiB
+# -> factor 1.0).  The factor is the one under which the 3-D kernels whose
+# reads are fixed by their design fetch exactly those bytes; a copy whose input
+# sits partly in the last-level cache reads less (one session read 436918.5
+# KiB), since FETCH_SIZE does not count those hits.  Valid for the kernel
+# sources whose hash is recorded and, for the launches of a two-launch step,
+# the same tile shape; null otherwise.
 MEASURED_TRAFFIC = {
-    "source_hash": "7f926bdeb6b7b8bd",
-    "fetch_factor": 1048576.0 / 524297.8,
+    "source_hash": "48009d3487f51a00",
+    "fetch_factor": 1048576.0 / 524296.2,
     "write_factor": 1048576.0 / 1048576.0,
+    # the one-launch step: k_step at 1024x512, k_march at 4096x2048
+    "step": {
+        "large_1024x512_fp32": [{"tiles": [], "fetch_kib": 12512.5, "write_kib": 20582.4}],
+        "large_4096x2048_fp32": [{"tiles": [], "fetch_kib": 207708.5, "write_kib": 353921.3}],
+    },
     "k_lb": {
         "large_1024x512_fp32": [
-            {"tiles": [62, 4, 4], "fetch_kib": 10725.0, "write_kib": 24620.1},
-            {"tiles": [62, 8, 8], "fetch_kib": 10719.3, "write_kib": 24640.2},
+            {"tiles": [62, 4, 4], "fetch_kib": 10763.8, "write_kib": 24620.8},
+            {"tiles": [62, 8, 8], "fetch_kib": 10782.8, "write_kib": 24637.0},
         ],
         "large_4096x2048_fp32": [
-            {"tiles": [62, 4, 4], "fetch_kib": 166708.7, "write_kib": 395598.9},
+            {"tiles": [62, 4, 4], "fetch_kib": 166362.9, "write_kib": 394872.4},
         ],
     },
     "k_thermal": {
         "large_1024x512_fp32": [
-            {"tiles": [56, 24, 16], "fetch_kib": 4838.3, "write_kib": 2040.2},
+            {"tiles": [56, 24, 16], "fetch_kib": 4839.6, "write_kib": 2040.2},
         ],
         "large_4096x2048_fp32": [
-            {"tiles": [56, 40, 16], "fetch_kib": 68760.1, "write_kib": 32749.2},
+            {"tiles": [56, 40, 16], "fetch_kib": 68742.9, "write_kib": 32753.5},
         ],
     },
 }
 
-# The same counters for the seven launches of one 3-D step (150x151x150 pool,
+# The same counters for the five launches of one 3-D step (150x151x150 pool,
 # FP32 storage; KiB per dispatch), valid for the 3-D kernel and host sources
-# whose hash is recorded (the host source sets the first stage's plane runs).
+# whose hash is recorded (the host source sets the runs of planes).
 MEASURED_TRAFFIC_3D = {
-    "source_hash": "c97ad07e51234cee",
+    "source_hash": "ba499d55ee9db650",
     "pool3d_150x151x150_fp32": {
-        "k3_psi": (132765.1, 40023.5), "k3_reduce": (108.5, 0.1), "k3_lb": (146640.1, 294904.3),
-        "k3_stage0": (37460.4, 93766.5), "k3_stage1": (53429.2, 26544.7), "k3_stage2": (53429.4, 26543.0),
-        "k3_stage3": (53351.1, 13271.5),
+        "k3_psi": (141346.0, 40022.3), "k3_reduce": (108.6, 0.1), "k3_lb": (151109.2, 293363.3),
+        "k3_pair_0_1": (39365.0, 92992.5), "k3_pair_2_3": (62158.6, 13344.4),
     },
 }
 
@@ -120,7 +124,7 @@ def source_hash(*names: str) -> str:
     in 2-D, on the tile shape; the 3-D launch shapes are set in the 3-D host
     source, which is hashed with its kernels)."""
     h = hashlib.sha256()
-    for name in names or ("lbb_device.hpp",):
+    for name in names or ("lbb_device.hpp", "lbb_step.hpp"):
         with open(os.path.join(ROOT, "paper_1501_03857_amd", "csrc", name), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -362,7 +366,7 @@ def three_d_bench(steps=300, warmup=64, nx=150, ny=151, nz=150):
                          "frac": round(gbs / HBM_PEAK_GBS, 4), "alg_bytes_per_update": 160,
                          "traffic": traffic, "traffic_unit": "bytes per step",
                          "traffic_gbs": None if traffic is None else round(traffic / (ms * 1e-3) / 1e9, 1)},
-            "launches_per_step": 7, "q_mean": q["q_mean"]}
+            "launches_per_step": 5, "q_mean": q["q_mean"]}
 
 
 def main():
@@ -463,7 +467,11 @@ def main():
     achieved = step_bytes / (ms_step * 1e-3) / 1e9
     tr_lb = measured_traffic("k_lb", w.name, tiles["lb"])
     tr_th = measured_traffic("k_thermal", w.name, tiles["thermal"])
-    traffic = None if tr_lb is None or tr_th is None else tr_lb + tr_th
+    # the timed step is one launch unless tile shapes were given
+    if args.tiles:
+        traffic = None if tr_lb is None or tr_th is None else tr_lb + tr_th
+    else:
+        traffic = measured_traffic("step", w.name, [])
     sweep = sweep_bench(args.sweep_steps) if args.sweep_steps > 0 else None
     if sweep:
         print(f"[bench] sweep: batched {sweep['batched_mlups']} MLUPS vs sequential {sweep['plain_sequential_mlups']} "
@@ -494,12 +502,12 @@ def main():
         "dtype": arithmetic(store),
         "data": "synthetic",
         "config": {"workload": w.name, "nx": w.nx, "ny": w.ny, "storage": store, "global_batch": 1,
-                   "parallelism": "none", "launches_per_step": 2, "graph_steps": 32, "tiles": tiles},
+                   "parallelism": "none", "launches_per_step": 2 if args.tiles else 1, "graph_steps": 32, "tiles": tiles},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_unit": "bytes per step",
                      "traffic_gbs": None if traffic is None else round(traffic / (ms_step * 1e-3) / 1e9, 1),
-                     "kernel": "step (k_lb + k_thermal)", "step_ms": round(ms_step, 6),
+                     "kernel": "step (k_lb + k_thermal)" if args.tiles else "step (one launch)", "step_ms": round(ms_step, 6),
                      "alg_bytes_per_update": ALG_BYTES_STEP[store],
                      "copy_gbs": round(copy_gbs, 1), "frac_of_copy": round(achieved / copy_gbs, 4)},
         "kernel_rooflines": {

@@ -205,8 +205,8 @@ int lbb_load_state(lbb_domain *d, const void *buf, size_t len);
 
 /* ---- Batched lattices (boiling-curve sweeps) ---------------------------
  * n independent lattices of any sizes and parameters (superheat, wettability,
- * seed) advanced together: each step is one LB launch and one thermal launch
- * covering every lattice, replayed from captured HIP graphs.  Each lattice
+ * seed) advanced together: the one or two launches of a step cover every
+ * lattice, replayed from captured HIP graphs.  Each lattice
  * evolves bitwise as it would alone.  All members share precision and
  * thermal_mode.
  *   ps [n]        : parameters of each lattice (validated as lbb_init_domain).
@@ -275,8 +275,10 @@ int lbb_batch_info(lbb_batch *b, int64_t *device_bytes);
  * block come from small tables of shapes.  lbb_tile_shapes reports them:
  * n_lb and n_thermal entries of (width, height, waves) in lb[3 n_lb] and
  * thermal[3 n_thermal] (any pointer may be NULL).  Shape 0 of each is the
- * default of a new domain or batch.  Results do not depend on the shapes
- * beyond the summation order of the domain-mean density (ulp level). */
+ * default of a new domain or batch.  A step takes these two launches where
+ * one launch is not faster, and wherever shapes were selected by
+ * lbb_set_tiles or lbb_batch_set_tiles.  Results depend neither on the shapes
+ * nor on the form of the step. */
 int lbb_tile_shapes(int32_t *n_lb, int32_t *n_thermal, int32_t *lb, int32_t *thermal);
 int lbb_get_tiles(lbb_domain *d, int32_t *shape_lb, int32_t *shape_thermal);
 /* Select the shapes (indices into the tables); EINVAL for an unknown index.
@@ -284,8 +286,8 @@ int lbb_get_tiles(lbb_domain *d, int32_t *shape_lb, int32_t *shape_thermal);
 int lbb_set_tiles(lbb_domain *d, int32_t shape_lb, int32_t shape_thermal);
 /* Time every LB shape, then every thermal shape with the best LB shape, for
  * `steps` steps each on the domain's own state (per-kernel durations from
- * events recorded by the dispatches), keep the fastest of each, and restore
- * the state, step count and heat-flux average.  Outputs (may be NULL): the
+ * events recorded by the dispatches), keep the fastest of each for steps of
+ * two launches, and restore the state, step count and heat-flux average.  Outputs (may be NULL): the
  * chosen shapes and the mean durations in ms per shape (ms_lb[n_lb],
  * ms_thermal[n_thermal]).  EINVAL for steps < 1; ESTATE on a poisoned
  * domain; ENONFINITE if a trial step produces an invalid state (the state is

@@ -1,6 +1,8 @@
-// Device code of the lbboil library: the two kernels of one time step of the
-// hybrid thermal pseudopotential LB boiling model (arXiv:1501.03857, Sec. 2)
-// plus the small kernels used at set-up and read-back.  gfx950, wave64.
+// Device code of the lbboil library: the LB and thermal kernels of one time
+// step of the hybrid thermal pseudopotential LB boiling model
+// (arXiv:1501.03857, Sec. 2), the per-node expressions that every form of the
+// step shares, and the small kernels used at set-up and read-back.  gfx950,
+// wave64.
 //
 // Data layout in HBM (structure of arrays, x fastest, row pitch nx):
 //   f[2][9][ny][nx]  post-streaming distributions, double-buffered.  Wall-row
@@ -12,15 +14,17 @@
 //                    rows hold the Dirichlet values in both buffers.
 //   rho, vx, vy      density and the velocity the temperature equation sees,
 //                    written by the LB kernel for the thermal kernel.
-//   partials         per-block FP64 partial sums of mass and heat flux.
+//   partials         partial sums of mass (whole numbers) and heat flux (FP64).
 //
-// One step t -> t+1 is two launches:
-//   k_lb      : per tile (62 x 12 by default, halo 1): rho and psi (FP64 EOS, Eq. (21)) of
+// One step t -> t+1 is one launch where that is faster (lbb_step.hpp: tiles on
+// small lattices, marching strips on large ones; k_lb with ONE on isothermal
+// lattices), else two:
+//   k_lb      : per tile (62 x 4 by default, halo 1): rho and psi (FP64 EOS, Eq. (21)) of
 //               the tile and its halo into LDS; per interior node the forces
 //               (Eqs. (7), (9), (22)), velocity (Eq. (6)), MRT collision with
 //               the improved forcing (Eqs. (2), (4), (5), (8)) and push
-//               streaming (Eq. (3)) into the other buffer; FP64 mass partials
-//               of the streamed state (exact identity, so the next step's
+//               streaming (Eq. (3)) into the other buffer; mass partials of
+//               the streamed state (exact identity, so the next step's
 //               rho_ave needs no extra pass).  One extra block, first in the
 //               grid, reduces the heat-flux partials of the previous thermal launch.
 //   k_thermal: per tile (56 x 24 by default, halo 4): RK4 (Eqs. (19)-(20)) of Eq. (18) in
@@ -48,9 +52,10 @@ constexpr int TXB = 64 - 2 * HB;  // thermal tile width: tile + halo is one wave
 // Tile shapes the launches can take (height, waves per block); the host picks
 // one of each per lattice or batch, by default or by timing them on the
 // lattice (autotune).  Index 0 is the default.  With one lattice row per
-// wave the LB kernel needs 72 VGPRs (7 waves per SIMD), against 118 with
+// wave the LB kernel needs 76 VGPRs (6 waves per SIMD), against 124 with
 // three rows per wave, and the extra waves in flight hide the load latency
-// of phase 1 behind the arithmetic of other waves.
+// of phase 1 behind the arithmetic of other waves (held to 72 VGPRs for a
+// seventh wave it spills: 209 against 172 us at 4096x2048 FP32).
 struct TileShape {
     int ty, nw;
 };

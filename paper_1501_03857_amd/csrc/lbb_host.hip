@@ -1476,8 +1476,12 @@ static int batch_push(lbb_batch *b)
     // upload only what differs from the device's table (padding never does:
     // make_inst clears it)
     if (b->pushed.size() == insts.size() &&
-        std::memcmp(b->pushed.data(), insts.data(), insts.size() * sizeof(lbb::Inst)) == 0)
-        return LBB_OK;
+        std::memcmp(b->pushed.data(), insts.data(), insts.size() * sizeof(lbb::Inst)) == 0) {
+        // a batch does not step under a caller's capture, table changed or not
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        LBB_HIP(hipStreamIsCapturing(b->stream, &cap));
+        return cap == hipStreamCaptureStatusNone ? LBB_OK : fail(LBB_EDEVICE, "the batch's stream is being captured");
+    }
     b->pushed.clear();
     LBB_HIP(hipMemcpyAsync(b->d_insts, insts.data(), insts.size() * sizeof(lbb::Inst), hipMemcpyHostToDevice,
                            b->stream));
