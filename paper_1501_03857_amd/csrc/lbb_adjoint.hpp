@@ -111,7 +111,7 @@ struct AdjInst {
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); \
     const int x = (q % I.gx) * LBX + lane - HC;                                             \
     const int gj = (q / I.gx) * LBY + wv - (ONE ? 1 : 0);                                   \
-    const int gx = wrapi(x, P.nx);                                                          \
+    const int gx = wrap_col(x, P.nx);                                                       \
     const size_t N = (size_t)P.nx * P.ny;                                                   \
     const bool inside = gj >= 0 && gj < P.ny;                                               \
     const bool own_row = inside && (!ONE || (wv >= 1 && wv < LBW - 1));                     \
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(64 * TAW) void a_theradj(const AdjInst *__restrict_
     const int x0 = (q % I.tgx) * TAX, y0 = (q / I.tgx) * TAY;
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wN = wv + 1 < TAW ? wv + 1 : wv, wS = wv > 0 ? wv - 1 : 0;  // waves of the rows beyond this wave's
-    const int gx = wrapi(x0 + lane - TAH, P.nx);
+    const int gx = wrap_col(x0 + lane - TAH, P.nx);
     const gmem<double> *__restrict__ lT1 = gp(I.lT[cur]);
     gmem<double> *__restrict__ lT0 = gp(I.lT[cur ^ 1]);
     const S *__restrict__ T = a_slot<S>(I, k0) + 9 * (size_t)P.nx * P.ny;

@@ -268,6 +268,7 @@ struct Inst {
     long long *rel;
     MassSum *mpart;
     int nbxF, nbyF, tyF, npF, blkF0;
+    unsigned divF;  // tile / nbxF = (tile divF) >> 32, or tile itself if 0
     Scalars *host;  // copy of *sc in host memory, written as a sequence ends (or null)
 };
 
@@ -287,6 +288,14 @@ __device__ __forceinline__ int wrapi(int i, int n)
 {
     int r = i % n;
     return r < 0 ? r + n : r;
+}
+
+// The same for a tile's column i in (-64, n + 64): a division stands between a
+// block and its first loads only on lattices narrower than a wave.
+__device__ __forceinline__ int wrap_col(int i, int n)
+{
+    if (n < 64) return wrapi(i, n);
+    return i < 0 ? i + n : (i >= n ? i - n : i);
 }
 
 // Plane-wise global memory access.  A field plane's base address is uniform
@@ -394,7 +403,8 @@ __device__ __forceinline__ void flag_error(Scalars *sc_, long long t, unsigned c
 // psi of a node at step t, with the validity of its density and psi checked.
 // Positive normal numbers pass two class tests; only what fails them (a zero
 // psi among it, which is valid) is looked at closely.
-__device__ __forceinline__ double checked_psi(const DevParams &P, double rho, double T, Scalars *sc, long long t)
+template <typename Step>
+__device__ __forceinline__ double checked_psi(const DevParams &P, double rho, double T, Scalars *sc, Step t)
 {
     constexpr int kPosNormal = 1 << 8;
     const double r = psi_squared(P, rho, T);
@@ -808,7 +818,7 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 6 : 1) void k_lb(const Inst 
     const bool walls = !P.periodic_y;
     // the wave index is uniform over the wave: keep row logic on the scalar unit
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int gx = wrapi(x0 + lane - 1, P.nx);
+    const int gx = wrap_col(x0 + lane - 1, P.nx);
     const unsigned gxu = (unsigned)gx;
 
     // lattice row of region row r (wrapped when periodic); false beyond a wall
@@ -1083,7 +1093,7 @@ __global__ __launch_bounds__(64 * NWB) void k_thermal(const Inst *__restrict__ i
     const bool walls = !P.periodic_y;
     const bool run = P.mode != MODE_ISOTHERMAL;
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int gx = wrapi(x0 + lane - HB, P.nx);
+    const int gx = wrap_col(x0 + lane - HB, P.nx);
     const unsigned gxu = (unsigned)gx;
 
     // lattice row of region row r; false beyond a wall

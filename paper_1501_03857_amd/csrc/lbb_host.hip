@@ -461,6 +461,8 @@ void set_step_grid(lbb::Inst &I, const StepForm &f, const StepDims &l, int blk0)
     I.nbyF = f.height ? (l.ny + f.height - 1) / f.height : 0;
     I.npF = (int)step_blocks(l, f);
     I.blkF0 = blk0;
+    // exact below 2^32 / nbxF tiles, far above what fits one round
+    I.divF = I.nbxF > 1 ? (unsigned)((((uint64_t)1 << 32) + I.nbxF - 1) / I.nbxF) : 0;
 }
 
 // Compute units of the current device (0 if it cannot be asked).

@@ -28,15 +28,15 @@ constexpr int TXF = 64 - 2 * HF;  // its tile width: tile + halo is one wave wid
 
 // Sum of this launch's input mass partials by one wave (all lanes take part),
 // valid in every lane.
-__device__ __forceinline__ double wave_rho_ave(const Inst &I, const MassSum *__restrict__ part_)
+__device__ __forceinline__ double wave_rho_ave(const Inst &I, const MassSum *__restrict__ part_, int npF)
 {
     const gmem<MassSum> *__restrict__ part = (const gmem<MassSum> *)part_;
     MassSum s{0, 0};
-    for (int k = threadIdx.x & 63; k < I.npF; k += 4 * 64) {
+    for (int k = threadIdx.x & 63; k < npF; k += 4 * 64) {
         long long hi[4], lo[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const bool in = k + 64 * j < I.npF;
+            const bool in = k + 64 * j < npF;
             hi[j] = in ? part[k + 64 * j].hi : 0;
             lo[j] = in ? part[k + 64 * j].lo : 0;
         }
@@ -60,6 +60,13 @@ __device__ __forceinline__ double wave_rho_ave(const Inst &I, const MassSum *__r
 // belongs to wave r mod NW (RPW rows a wave), lane = column.  psi, rho, v and
 // the stage inputs pass between rows through LDS, between columns by lane
 // shifts.
+// Index of the state a launch starts from, read where it is used.
+struct StepIndex {
+    const gmem<long long> *rel;
+    const gmem<Scalars> *sc;
+    __device__ __forceinline__ operator long long() const { return sc->tA + *rel; }
+};
+
 template <typename S, int NW, int RPW>
 __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ insts, const int *__restrict__ blk2inst,
                                                      int cf, int cT, int par, int aux)
@@ -73,11 +80,23 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
     __shared__ double s_rho_ave;
     const Inst &I = insts[blk2inst[blockIdx.x]];
     const DevParams &P = I.P;
+    // All that the first loads of populations need is read from the table
+    // together, and the step index not waited for before they are issued: as
+    // the uses came, four scalar loads and that one followed each other (128x64
+    // FP64 6.83 us per step, 7.03 before; 600x151 FP32 8.12, 8.49 before).
     Scalars *__restrict__ sc = I.sc;
     const S *__restrict__ fin = static_cast<const S *>(I.f[cf]);
     const S *__restrict__ Tin = static_cast<const S *>(I.T[cT]);
-    const int blk = (int)blockIdx.x - I.blkF0;
-    const long long since = I.rel[par], t = sc->tA + since;
+    const gmem<long long> *rel = (const gmem<long long> *)I.rel;
+    const int blkF0 = I.blkF0, nbx = I.nbxF, nby = I.nbyF, TY = I.tyF, nx_ = P.nx, ny_ = P.ny, per = P.periodic_y;
+    const unsigned divF = I.divF;
+    const int npF = I.npF;
+    MassSum *mpart = I.mpart;
+    asm volatile("" : : "s"(divF), "s"(npF), "s"(mpart), "s"(sc), "s"(fin), "s"(Tin), "s"(rel), "s"(blkF0), "s"(nbx), "s"(nby), "s"(TY), "s"(nx_),
+                 "s"(ny_), "s"(per));
+    const int blk = (int)blockIdx.x - blkF0;
+    const StepIndex t{rel + par, (const gmem<Scalars> *)sc};
+    const long long since = *t.rel;
     if (blk == 0) {
         sample_heat_flux<S, NW>(I, fin, Tin, t);
         if (threadIdx.x == 0) I.rel[par ^ 1] = since + 1;
@@ -85,14 +104,14 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
     }
     S *__restrict__ fout = static_cast<S *>(I.f[cf ^ 1]);
     S *__restrict__ Tout = static_cast<S *>(I.T[cT ^ 1]);
-    const int tile = xcd_tile(blk - 1, I.nbxF * I.nbyF);
-    const int bx = tile % I.nbxF, by = tile / I.nbxF;
-    const int TY = I.tyF, H = TY + 2 * HF;
+    const int tile = xcd_tile(blk - 1, nbx * nby);
+    const int by = divF ? (int)__umulhi((unsigned)tile, divF) : tile, bx = tile - by * nbx;
+    const int H = TY + 2 * HF;
     const int x0 = bx * TXF, y0 = by * TY;
     const size_t N = (size_t)P.nx * P.ny;
     const bool walls = !P.periodic_y;
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int gx = wrapi(x0 + lane - HF, P.nx);
+    const int gx = wrap_col(x0 + lane - HF, nx_);
     const unsigned gxu = (unsigned)gx;
 
     // lattice row of region row r (wrapped when periodic); false beyond a wall
@@ -120,7 +139,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
         Tv[m] = ld_at(Tin, o);
     }
     if (wv == 0) {  // wave 0 owns a halo row: it has the least to do
-        const double ra = since ? wave_rho_ave(I, I.mpart + (size_t)par * I.npF) : sc->rho_ave;
+        const double ra = since ? wave_rho_ave(I, mpart + (size_t)par * npF, npF) : ((const gmem<Scalars> *)sc)->rho_ave;
         if (lane == 0) s_rho_ave = ra;
     }
 #pragma unroll
@@ -180,7 +199,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
     if (threadIdx.x == 0) {
         MassSum s{0, 0};
         for (int k = 0; k < NW; ++k) s.add(red[k]);
-        I.mpart[(size_t)(par ^ 1) * I.npF + tile] = s;
+        mpart[(size_t)(par ^ 1) * npF + tile] = s;
     }
 
     // phase 3: coefficients of the temperature equation
@@ -298,12 +317,12 @@ __global__ __launch_bounds__(64 * WB, sizeof(S) == 4 ? 3 : 2) void k_march(const
     const int id = tile * WB + wv;  // strips row by row; the last block may have waves to spare
     const int by = id / I.nbxF, strip = id - by * I.nbxF;
     const int x0 = strip * TXF;
-    const int gx = wrapi(x0 + lane - HF, nx);
+    const int gx = wrap_col(x0 + lane - HF, nx);
     const int y0 = by * I.tyF, y1 = by < I.nbyF ? min(y0 + I.tyF, ny) : y0;
     const bool walls = !P.periodic_y;
     const bool mine = lane >= HF && lane < HF + TXF && x0 + lane - HF < nx;
     double rho_ave = scg->rho_ave;
-    if (since) rho_ave = wave_rho_ave(I, I.mpart + (size_t)par * I.npF);
+    if (since) rho_ave = wave_rho_ave(I, I.mpart + (size_t)par * I.npF, I.npF);
     asm volatile("" : "+v"(rho_ave));  // here, before the loop
 
     // lattice row of row r (at most ny beyond the lattice when periodic), and
