@@ -255,6 +255,7 @@ struct lbb_domain {
     // device's scalars since the flush that was enqueued last.
     lbb::Scalars *host = nullptr;
     double *host_q = nullptr;
+    bool own_host = false;               // else a slice of its batch's
     bool fresh = false;
     hipEvent_t order = nullptr;          // orders read-backs with a caller's stream
 };
@@ -817,7 +818,7 @@ void release(lbb_domain *d)
         if (q) (void)hipFree(q);
     for (void *q : {d->small, d->adj_mem})
         if (q) (void)hipFree(q);
-    if (d->host) (void)hipHostFree(d->host);
+    if (d->host && d->own_host) (void)hipHostFree(d->host);
     if (d->order) (void)hipEventDestroy(d->order);
     if (d->stream) (void)hipStreamDestroy(d->stream);
     delete d;
@@ -855,6 +856,10 @@ int read_impl(lbb_domain *d, double *rho, double *ux, double *uy, double *T, dou
 }
 
 }  // namespace
+
+// bytes of a domain's pinned memory: scalars, local heat flux
+static size_t host_bytes(int nx) { return (sizeof(lbb::Scalars) + (size_t)nx * sizeof(double) + 255) & ~(size_t)255; }
+static int init_domain(const lbb_params *pin, const double *T_bottom, const double *rho0, void *host, lbb_domain **out);
 
 extern "C" {
 
@@ -932,134 +937,7 @@ int lbb_eos_pressure(double a, double b, double R, double omega, double rho, dou
 
 int lbb_init_domain(const lbb_params *pin, const double *T_bottom, const double *rho0, lbb_domain **out)
 {
-    if (!out) return fail(LBB_EINVAL, "out is NULL");
-    *out = nullptr;
-    int rc = validate(pin);
-    if (rc) return rc;
-    lbb_params p = *pin;
-    double Tc = 0, kap = 0;
-    lbb_eos_constants(p.a, p.b, p.R, p.omega, &Tc, &kap);
-    const double Ts = p.Ts_over_Tc * Tc;
-    if (p.rho_L == 0.0 && p.rho_V == 0.0) {
-        rc = lbb_coexistence(p.a, p.b, p.R, p.omega, Ts, &p.rho_V, &p.rho_L);
-        if (rc) return fail(LBB_EINVAL, "rho_L = rho_V = 0 needs T_s < T_c for the Maxwell densities");
-    }
-    if (p.rho_L == p.rho_V) return fail(LBB_EINVAL, "rho_L must differ from rho_V");
-    const size_t N = (size_t)p.nx * p.ny;
-    std::vector<double> rho_host;
-    if (!rho0) {
-        rho_host.resize(N);
-        for (int j = 0; j < p.ny; ++j)
-            for (int i = 0; i < p.nx; ++i) {
-                const size_t c = (size_t)j * p.nx + i;
-                const double u = (double)(splitmix64_at(p.seed, c) >> 11) * (1.0 / 9007199254740992.0);
-                rho_host[c] = (j < p.liquid_rows ? p.rho_L : p.rho_V) + p.noise_amp * (2.0 * u - 1.0);
-            }
-        rho0 = rho_host.data();
-    }
-    for (size_t c = 0; c < N; ++c)
-        if (!finite_pos(rho0[c]) || p.b * rho0[c] >= 1.0) return fail(LBB_EINVAL, "initial density must satisfy 0 < rho < 1/b");
-    std::vector<double> Tb(p.nx, Ts);
-    if (T_bottom)
-        for (int i = 0; i < p.nx; ++i) {
-            if (!finite_pos(T_bottom[i])) return fail(LBB_EINVAL, "T_bottom must be finite and > 0");
-            Tb[i] = T_bottom[i];
-        }
-
-    // the device bytes this domain will hold, reserved under the budget first
-    const size_t esz = p.precision == LBB_FP64 ? 8 : 4;
-    const int64_t planned = (int64_t)(N * esz * (2 * 9 + 2 + 3)) + (int64_t)N * 8 + ((int64_t)1 << 20);
-    rc = reserve_bytes(planned, "domain");
-    if (rc) return rc;
-    struct Unreserve {
-        int64_t n;
-        ~Unreserve() { release_bytes(n); }
-    } unreserve{planned};
-
-    int dev = 0;
-    LBB_HIP(hipGetDevice(&dev));
-    hipDeviceProp_t prop;
-    LBB_HIP(hipGetDeviceProperties(&prop, dev));
-    if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0)
-        return fail(LBB_EDEVICE, std::string("this library is built for gfx950, device is ") + prop.gcnArchName);
-
-    lbb_domain *d = new (std::nothrow) lbb_domain();
-    if (!d) return fail(LBB_ENOMEM, "host allocation failed");
-    d->p = p;
-    d->N = N;
-    d->esz = p.precision == LBB_FP64 ? 8 : 4;
-    d->Tb = Tb;
-    make_dev_params(p, Tc, kap, d->dp);
-    set_grid(d);
-    d->form = step_form({{p.nx, p.ny}}, p.precision, p.thermal_mode, prop.multiProcessorCount);
-    const lbb_param_dims dims{p.nx, p.ny};
-    const int mbA = max_blocks_A(dims), mbB = max_blocks_B(dims);
-
-    auto alloc = [&](void **ptr, size_t bytes) -> bool {
-        if (hipMalloc(ptr, bytes) != hipSuccess) return false;
-        d->dev_bytes += (int64_t)bytes;
-        return hipMemset(*ptr, 0, bytes) == hipSuccess;
-    };
-    const size_t es = d->esz;
-    bool ok = hipStreamCreateWithFlags(&d->stream, hipStreamNonBlocking) == hipSuccess;
-    ok = ok && hipHostMalloc((void **)&d->host, sizeof(lbb::Scalars) + p.nx * sizeof(double),
-                             hipHostMallocMapped | hipHostMallocPortable) == hipSuccess;
-    if (ok) d->host_q = reinterpret_cast<double *>(d->host + 1);
-    ok = ok && alloc(&d->f[0], 9 * N * es) && alloc(&d->f[1], 9 * N * es);
-    ok = ok && alloc(&d->T[0], N * es) && alloc(&d->T[1], N * es);
-    ok = ok && alloc(&d->rho, N * es) && alloc(&d->vx, N * es) && alloc(&d->vy, N * es);
-    // The small buffers share one allocation: a call to allocate and clear
-    // costs more than their contents, and a set of lattices makes many.
-    // A batch may step a lattice in one launch that alone takes two.
-    const StepDims lat{p.nx, p.ny};
-    const bool coupled = p.thermal_mode == LBB_COUPLED;
-    const size_t np = coupled ? (size_t)step_max_blocks(lat, p.precision, p.thermal_mode, prop.multiProcessorCount) : 0;
-    struct { void **ptr; size_t bytes; } const small[] = {
-        // mass partials: one per lattice row and LB tile column (also holds the
-        // per-block partials of the set-up mass kernel, fewer)
-        {(void **)&d->mass_part,
-         (size_t)std::max(mbA, (isothermal_one(p) ? 2 : 1) * d->nbxA * p.ny) * sizeof(double)},
-        {(void **)&d->hf_part, (size_t)d->nbxB * sizeof(double)},
-        {(void **)&d->Tb_dev, (size_t)p.nx * sizeof(double)},
-        {(void **)&d->sc, sizeof(lbb::Scalars)},
-        {(void **)&d->d_inst, sizeof(lbb::Inst)},
-        {(void **)&d->d_blkA, (size_t)(mbA + 1) * sizeof(int)},
-        {(void **)&d->d_blkB, (size_t)(mbB + 1) * sizeof(int)},
-        {(void **)&d->rel, 2 * sizeof(long long)},
-        {(void **)&d->mpart, 2 * np * sizeof(lbb::MassSum)},
-        {(void **)&d->d_blkF, coupled ? (size_t)(step_blocks(lat, d->form) + 1) * sizeof(int) : 0}};
-    const auto rounded = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    size_t total = 0;
-    for (const auto &q : small) total += rounded(q.bytes);
-    ok = ok && alloc(&d->small, total);
-    if (ok) {
-        char *at = static_cast<char *>(d->small);
-        for (const auto &q : small) {
-            if (q.bytes) *q.ptr = at;
-            at += rounded(q.bytes);
-        }
-    }
-    if (!ok) {
-        (void)hipGetLastError();
-        release(d);
-        return fail(LBB_ENOMEM, "device allocation failed");
-    }
-    if (hipMemcpy(d->Tb_dev, Tb.data(), p.nx * sizeof(double), hipMemcpyHostToDevice) != hipSuccess ||
-        push_inst(d) != LBB_OK) {
-        release(d);
-        return fail(LBB_EDEVICE, "upload of T_bottom or the launch table failed");
-    }
-    rc = p.precision == LBB_FP64 ? set_state<double>(d, rho0, nullptr, nullptr, nullptr)
-                                 : set_state<float>(d, rho0, nullptr, nullptr, nullptr);
-    if (rc) {
-        std::string m = g_err;
-        release(d);
-        return fail(rc, m);
-    }
-    g_held.fetch_add(d->dev_bytes);
-    d->held = d->dev_bytes;
-    *out = d;
-    return LBB_OK;
+    return init_domain(pin, T_bottom, rho0, nullptr, out);
 }
 
 int lbb_set_fields(lbb_domain *d, const double *rho, const double *ux, const double *uy, const double *T)
@@ -1370,6 +1248,142 @@ int lbb_info(lbb_domain *d, int64_t *t, int32_t *nx, int32_t *ny, int64_t *devic
 
 // ---- batched lattices --------------------------------------------------
 
+// lbb_init_domain; `host`: pinned memory of host_bytes(nx) that outlives the domain, or null (its own).
+static int init_domain(const lbb_params *pin, const double *T_bottom, const double *rho0, void *host, lbb_domain **out)
+{
+    if (!out) return fail(LBB_EINVAL, "out is NULL");
+    *out = nullptr;
+    int rc = validate(pin);
+    if (rc) return rc;
+    lbb_params p = *pin;
+    double Tc = 0, kap = 0;
+    lbb_eos_constants(p.a, p.b, p.R, p.omega, &Tc, &kap);
+    const double Ts = p.Ts_over_Tc * Tc;
+    if (p.rho_L == 0.0 && p.rho_V == 0.0) {
+        rc = lbb_coexistence(p.a, p.b, p.R, p.omega, Ts, &p.rho_V, &p.rho_L);
+        if (rc) return fail(LBB_EINVAL, "rho_L = rho_V = 0 needs T_s < T_c for the Maxwell densities");
+    }
+    if (p.rho_L == p.rho_V) return fail(LBB_EINVAL, "rho_L must differ from rho_V");
+    const size_t N = (size_t)p.nx * p.ny;
+    std::vector<double> rho_host;
+    if (!rho0) {
+        rho_host.resize(N);
+        for (int j = 0; j < p.ny; ++j)
+            for (int i = 0; i < p.nx; ++i) {
+                const size_t c = (size_t)j * p.nx + i;
+                const double u = (double)(splitmix64_at(p.seed, c) >> 11) * (1.0 / 9007199254740992.0);
+                rho_host[c] = (j < p.liquid_rows ? p.rho_L : p.rho_V) + p.noise_amp * (2.0 * u - 1.0);
+            }
+        rho0 = rho_host.data();
+    }
+    for (size_t c = 0; c < N; ++c)
+        if (!finite_pos(rho0[c]) || p.b * rho0[c] >= 1.0) return fail(LBB_EINVAL, "initial density must satisfy 0 < rho < 1/b");
+    std::vector<double> Tb(p.nx, Ts);
+    if (T_bottom)
+        for (int i = 0; i < p.nx; ++i) {
+            if (!finite_pos(T_bottom[i])) return fail(LBB_EINVAL, "T_bottom must be finite and > 0");
+            Tb[i] = T_bottom[i];
+        }
+
+    // the device bytes this domain will hold, reserved under the budget first
+    const size_t esz = p.precision == LBB_FP64 ? 8 : 4;
+    const int64_t planned = (int64_t)(N * esz * (2 * 9 + 2 + 3)) + (int64_t)N * 8 + ((int64_t)1 << 20);
+    rc = reserve_bytes(planned, "domain");
+    if (rc) return rc;
+    struct Unreserve {
+        int64_t n;
+        ~Unreserve() { release_bytes(n); }
+    } unreserve{planned};
+
+    int dev = 0;
+    LBB_HIP(hipGetDevice(&dev));
+    hipDeviceProp_t prop;
+    LBB_HIP(hipGetDeviceProperties(&prop, dev));
+    if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0)
+        return fail(LBB_EDEVICE, std::string("this library is built for gfx950, device is ") + prop.gcnArchName);
+
+    lbb_domain *d = new (std::nothrow) lbb_domain();
+    if (!d) return fail(LBB_ENOMEM, "host allocation failed");
+    d->p = p;
+    d->N = N;
+    d->esz = p.precision == LBB_FP64 ? 8 : 4;
+    d->Tb = Tb;
+    make_dev_params(p, Tc, kap, d->dp);
+    set_grid(d);
+    d->form = step_form({{p.nx, p.ny}}, p.precision, p.thermal_mode, prop.multiProcessorCount);
+    const lbb_param_dims dims{p.nx, p.ny};
+    const int mbA = max_blocks_A(dims), mbB = max_blocks_B(dims);
+
+    auto alloc = [&](void **ptr, size_t bytes) -> bool {
+        if (hipMalloc(ptr, bytes) != hipSuccess) return false;
+        d->dev_bytes += (int64_t)bytes;
+        return hipMemset(*ptr, 0, bytes) == hipSuccess;
+    };
+    const size_t es = d->esz;
+    bool ok = hipStreamCreateWithFlags(&d->stream, hipStreamNonBlocking) == hipSuccess;
+    d->own_host = !host;
+    d->host = static_cast<lbb::Scalars *>(host);
+    if (!host)
+        ok = ok && hipHostMalloc((void **)&d->host, host_bytes(p.nx), hipHostMallocMapped | hipHostMallocPortable) ==
+                       hipSuccess;
+    if (ok) d->host_q = reinterpret_cast<double *>(d->host + 1);
+    ok = ok && alloc(&d->f[0], 9 * N * es) && alloc(&d->f[1], 9 * N * es);
+    ok = ok && alloc(&d->T[0], N * es) && alloc(&d->T[1], N * es);
+    ok = ok && alloc(&d->rho, N * es) && alloc(&d->vx, N * es) && alloc(&d->vy, N * es);
+    // The small buffers share one allocation: a call to allocate and clear
+    // costs more than their contents, and a set of lattices makes many.
+    // A batch may step a lattice in one launch that alone takes two.
+    const StepDims lat{p.nx, p.ny};
+    const bool coupled = p.thermal_mode == LBB_COUPLED;
+    const size_t np = coupled ? (size_t)step_max_blocks(lat, p.precision, p.thermal_mode, prop.multiProcessorCount) : 0;
+    struct { void **ptr; size_t bytes; } const small[] = {
+        // mass partials: one per lattice row and LB tile column (also holds the
+        // per-block partials of the set-up mass kernel, fewer)
+        {(void **)&d->mass_part,
+         (size_t)std::max(mbA, (isothermal_one(p) ? 2 : 1) * d->nbxA * p.ny) * sizeof(double)},
+        {(void **)&d->hf_part, (size_t)d->nbxB * sizeof(double)},
+        {(void **)&d->Tb_dev, (size_t)p.nx * sizeof(double)},
+        {(void **)&d->sc, sizeof(lbb::Scalars)},
+        {(void **)&d->d_inst, sizeof(lbb::Inst)},
+        {(void **)&d->d_blkA, (size_t)(mbA + 1) * sizeof(int)},
+        {(void **)&d->d_blkB, (size_t)(mbB + 1) * sizeof(int)},
+        {(void **)&d->rel, 2 * sizeof(long long)},
+        {(void **)&d->mpart, 2 * np * sizeof(lbb::MassSum)},
+        {(void **)&d->d_blkF, coupled ? (size_t)(step_blocks(lat, d->form) + 1) * sizeof(int) : 0}};
+    const auto rounded = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    size_t total = 0;
+    for (const auto &q : small) total += rounded(q.bytes);
+    ok = ok && alloc(&d->small, total);
+    if (ok) {
+        char *at = static_cast<char *>(d->small);
+        for (const auto &q : small) {
+            if (q.bytes) *q.ptr = at;
+            at += rounded(q.bytes);
+        }
+    }
+    if (!ok) {
+        (void)hipGetLastError();
+        release(d);
+        return fail(LBB_ENOMEM, "device allocation failed");
+    }
+    if (hipMemcpy(d->Tb_dev, Tb.data(), p.nx * sizeof(double), hipMemcpyHostToDevice) != hipSuccess ||
+        push_inst(d) != LBB_OK) {
+        release(d);
+        return fail(LBB_EDEVICE, "upload of T_bottom or the launch table failed");
+    }
+    rc = p.precision == LBB_FP64 ? set_state<double>(d, rho0, nullptr, nullptr, nullptr)
+                                 : set_state<float>(d, rho0, nullptr, nullptr, nullptr);
+    if (rc) {
+        std::string m = g_err;
+        release(d);
+        return fail(rc, m);
+    }
+    g_held.fetch_add(d->dev_bytes);
+    d->held = d->dev_bytes;
+    *out = d;
+    return LBB_OK;
+}
+
 struct lbb_batch {
     std::vector<lbb_domain *> doms;
     hipStream_t stream = nullptr;
@@ -1388,6 +1402,7 @@ struct lbb_batch {
     void *adj_mem = nullptr;             // adjoint workspace, kept between calls
     size_t adj_bytes = 0;
     int64_t held = 0;                    // device bytes held against the budget
+    char *host = nullptr;                // the members' pinned memory, one allocation
 };
 
 static void batch_release(lbb_batch *b)
@@ -1401,6 +1416,7 @@ static void batch_release(lbb_batch *b)
         if (q) (void)hipFree(q);
     if (b->stream) (void)hipStreamDestroy(b->stream);
     for (lbb_domain *d : b->doms) release(d);
+    if (b->host) (void)hipHostFree(b->host);  // after the members that write to it
     delete b;
 }
 
@@ -1529,9 +1545,17 @@ extern "C" int lbb_batch_init(const lbb_params *ps, int n, const double *const *
     if (!b) return fail(LBB_ENOMEM, "host allocation failed");
     b->precision = ps[0].precision;
     b->mode = ps[0].thermal_mode;
+    size_t pinned = 0, at = 0;
+    for (int i = 0; i < n; ++i) pinned += host_bytes(std::max(ps[i].nx, 0));
+    if (hipHostMalloc((void **)&b->host, pinned, hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        batch_release(b);
+        return fail(LBB_ENOMEM, "host allocation failed");
+    }
     for (int i = 0; i < n; ++i) {
         lbb_domain *d = nullptr;
-        int rc = lbb_init_domain(&ps[i], T_bottoms ? T_bottoms[i] : nullptr, rho0s ? rho0s[i] : nullptr, &d);
+        int rc = init_domain(&ps[i], T_bottoms ? T_bottoms[i] : nullptr, rho0s ? rho0s[i] : nullptr, b->host + at, &d);
+        at += host_bytes(std::max(ps[i].nx, 0));
         if (rc) {
             std::string m = "batch member " + std::to_string(i) + ": " + g_err;
             batch_release(b);
