@@ -51,29 +51,29 @@ def _kernel_roofline(alg_bytes, ms, traffic, per_update):
 # sources whose hash is recorded and, for the launches of a two-launch step,
 # the same tile shape; null otherwise.
 MEASURED_TRAFFIC = {
-    "source_hash": "48009d3487f51a00",
+    "source_hash": "6d79e6c04dda8898",
     "fetch_factor": 1048576.0 / 524296.2,
     "write_factor": 1048576.0 / 1048576.0,
     # the one-launch step: k_step at 1024x512, k_march at 4096x2048
     "step": {
-        "large_1024x512_fp32": [{"tiles": [], "fetch_kib": 12512.5, "write_kib": 20582.4}],
-        "large_4096x2048_fp32": [{"tiles": [], "fetch_kib": 207708.5, "write_kib": 353921.3}],
+        "large_1024x512_fp32": [{"tiles": [], "fetch_kib": 12509.4, "write_kib": 20582.3}],
+        "large_4096x2048_fp32": [{"tiles": [], "fetch_kib": 208427.1, "write_kib": 354576.0}],
     },
     "k_lb": {
         "large_1024x512_fp32": [
-            {"tiles": [62, 4, 4], "fetch_kib": 10763.8, "write_kib": 24620.8},
-            {"tiles": [62, 8, 8], "fetch_kib": 10782.8, "write_kib": 24637.0},
+            {"tiles": [62, 4, 4], "fetch_kib": 10762.8, "write_kib": 24620.5},
+            {"tiles": [62, 8, 8], "fetch_kib": 10744.8, "write_kib": 24638.1},
         ],
         "large_4096x2048_fp32": [
-            {"tiles": [62, 4, 4], "fetch_kib": 166362.9, "write_kib": 394872.4},
+            {"tiles": [62, 4, 4], "fetch_kib": 166343.4, "write_kib": 394905.1},
         ],
     },
     "k_thermal": {
         "large_1024x512_fp32": [
-            {"tiles": [56, 24, 16], "fetch_kib": 4839.6, "write_kib": 2040.2},
+            {"tiles": [56, 24, 16], "fetch_kib": 4836.1, "write_kib": 2040.2},
         ],
         "large_4096x2048_fp32": [
-            {"tiles": [56, 40, 16], "fetch_kib": 68742.9, "write_kib": 32753.5},
+            {"tiles": [56, 40, 16], "fetch_kib": 68761.4, "write_kib": 32753.8},
         ],
     },
 }
