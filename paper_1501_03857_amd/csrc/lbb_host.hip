@@ -252,11 +252,13 @@ struct lbb_domain {
     int64_t held = 0;                    // device bytes held against the budget
     // Pinned host memory the kernels write results to: the scalars as of the
     // last flush and the local heat flux.  `fresh`: nothing has changed the
-    // device's scalars since the flush that was enqueued last.
+    // device's scalars since the flush that was enqueued last, on `flushed`
+    // (the domain's stream or its batch's).
     lbb::Scalars *host = nullptr;
     double *host_q = nullptr;
     bool own_host = false;               // else a slice of its batch's
     bool fresh = false;
+    hipStream_t flushed = nullptr;
     hipEvent_t order = nullptr;          // orders read-backs with a caller's stream
 };
 
@@ -712,6 +714,7 @@ int enqueue_steps(lbb_domain *d, int64_t n)
     launch_flush(d->stream, d->d_inst, 1, one_launch(d), d->p.precision, d->cf, d->cT);
     LBB_HIP(hipGetLastError());
     d->fresh = true;
+    d->flushed = d->stream;
     return LBB_OK;
 }
 
@@ -730,23 +733,25 @@ int report_errors(lbb_domain *d, const lbb::Scalars &s)
 }
 
 // The device's scalars, from their host copy when the last flush left it up to
-// date (the stream `st` that flush ran on is waited for), else copied.
-int read_scalars(lbb_domain *d, hipStream_t st, lbb::Scalars *s)
+// date, else copied.  Waits for the domain's stream and, for the host copy, for
+// the one that flush ran on.
+int read_scalars(lbb_domain *d, lbb::Scalars *s)
 {
-    if (!d->fresh) LBB_HIP(hipMemcpyAsync(s, d->sc, sizeof *s, hipMemcpyDeviceToHost, st));
-    LBB_HIP(hipStreamSynchronize(st));
-    if (d->fresh) *s = *d->host;
+    if (!d->fresh) LBB_HIP(hipMemcpyAsync(s, d->sc, sizeof *s, hipMemcpyDeviceToHost, d->stream));
+    LBB_HIP(hipStreamSynchronize(d->stream));
+    if (d->fresh) {
+        if (d->flushed != d->stream) LBB_HIP(hipStreamSynchronize(d->flushed));
+        *s = *d->host;
+    }
     return LBB_OK;
 }
 
-int check_errors(lbb_domain *d, hipStream_t st)
+int check_errors(lbb_domain *d)
 {
     lbb::Scalars s;
-    const int rc = read_scalars(d, st, &s);
+    const int rc = read_scalars(d, &s);
     return rc ? rc : report_errors(d, s);
 }
-
-int check_errors(lbb_domain *d) { return check_errors(d, d->stream); }
 
 // Recompute rho_ave and the heat-flux partials from the current state.
 template <typename S>
@@ -1078,7 +1083,7 @@ int lbb_wall_heat_flux(const lbb_domain *dc, double *q_now, double *q_mean, doub
         if (hipGetLastError() != hipSuccess) return fail(LBB_EDEVICE, "heat-flux read-back failed");
     }
     lbb::Scalars s;
-    const int rc = read_scalars(d, d->stream, &s);
+    const int rc = read_scalars(d, &s);
     if (rc) return rc;
     if (q_local && d->p.periodic_y) std::memset(q_local, 0, d->p.nx * sizeof(double));  // no walls
     else if (q_local) std::memcpy(q_local, d->host_q, d->p.nx * sizeof(double));
@@ -1236,7 +1241,7 @@ int lbb_info(lbb_domain *d, int64_t *t, int32_t *nx, int32_t *ny, int64_t *devic
     if (!d) return fail(LBB_EINVAL, "domain is NULL");
     if (t) {
         lbb::Scalars s;
-        const int rc = read_scalars(d, d->stream, &s);
+        const int rc = read_scalars(d, &s);
         if (rc) return rc;
         *t = s.tA;
     }
@@ -1636,6 +1641,7 @@ extern "C" int lbb_batch_step_async(lbb_batch *b, int64_t n)
         d->cf = b->cf;
         d->cT = b->cT;
         d->fresh = true;
+        d->flushed = b->stream;
     }
     return LBB_OK;
 }
@@ -1645,8 +1651,8 @@ extern "C" int lbb_batch_sync(lbb_batch *b)
     if (!b) return fail(LBB_EINVAL, "batch is NULL");
     LBB_HIP(hipStreamSynchronize(b->stream));
     for (size_t i = 0; i < b->doms.size(); ++i) {
-        lbb_domain *d = b->doms[i];
-        int rc = d->fresh ? report_errors(d, *d->host) : check_errors(d);
+        // a member may have work of its own pending on its own stream
+        int rc = check_errors(b->doms[i]);
         if (rc) return fail(rc, "batch member " + std::to_string(i) + ": " + g_err);
     }
     return LBB_OK;
@@ -1668,8 +1674,7 @@ extern "C" int lbb_batch_heat_flux(lbb_batch *b, double *q_now, double *q_mean, 
     for (size_t i = 0; i < b->doms.size(); ++i) {
         lbb_domain *d = b->doms[i];
         lbb::Scalars s;
-        // a member may have been stepped on its own stream since
-        const int rc = read_scalars(d, d->stream, &s);
+        const int rc = read_scalars(d, &s);
         if (rc) return rc;
         if (q_now) q_now[i] = s.q_now;
         if (q_mean) q_mean[i] = s.n_samples ? s.q_sum / (double)s.n_samples : NAN;
