@@ -259,6 +259,9 @@ struct lbb_domain {
     bool own_host = false;               // else a slice of its batch's
     bool fresh = false;
     hipStream_t flushed = nullptr;
+    // A read-back since that flush may have flagged the state in the device's
+    // scalars only; `read_dev`: one that may not have run yet.
+    bool read = false, read_dev = false;
     hipEvent_t order = nullptr;          // orders read-backs with a caller's stream
 };
 
@@ -715,6 +718,7 @@ int enqueue_steps(lbb_domain *d, int64_t n)
     LBB_HIP(hipGetLastError());
     d->fresh = true;
     d->flushed = d->stream;
+    d->read = d->read_dev = false;  // earlier read-backs ran on this stream
     return LBB_OK;
 }
 
@@ -748,9 +752,13 @@ int read_scalars(lbb_domain *d, lbb::Scalars *s)
 
 int check_errors(lbb_domain *d)
 {
+    if (d->read || d->read_dev) d->fresh = false;
     lbb::Scalars s;
-    const int rc = read_scalars(d, &s);
-    return rc ? rc : report_errors(d, s);
+    int rc = read_scalars(d, &s);
+    if (rc) return rc;
+    rc = report_errors(d, s);
+    if (!rc) d->read = d->read_dev = false;  // over, and nothing flagged
+    return rc;
 }
 
 // Recompute rho_ave and the heat-flux partials from the current state.
@@ -847,6 +855,7 @@ int read_impl(lbb_domain *d, double *rho, double *ux, double *uy, double *T, dou
             at += c.n;
         }
     const int nbxR = (d->p.nx + lbb::TXR - 1) / lbb::TXR, nbyR = (d->p.ny + lbb::TYR - 1) / lbb::TYR;
+    d->read = true;
     hipLaunchKernelGGL(lbb::k_read<S>, dim3(nbxR * nbyR), dim3(lbb::NT), 0, d->stream, d->dp,
                        static_cast<const S *>(d->f[d->cf]), static_cast<const S *>(d->T[d->cT]), cp[0].src, cp[1].src,
                        cp[2].src, cp[3].src, cp[4].src, d->sc, nbxR);
@@ -1035,6 +1044,7 @@ int lbb_read_fields_dev(lbb_domain *d, double *rho, double *ux, double *uy, doub
             return fail(LBB_EDEVICE, std::string("read-back to device buffers: ") + hipGetErrorString(e0));
     }
     const int nbxR = (d->p.nx + lbb::TXR - 1) / lbb::TXR, nbyR = (d->p.ny + lbb::TYR - 1) / lbb::TYR;
+    d->read_dev = true;
     if (d->p.precision == LBB_FP64)
         hipLaunchKernelGGL(lbb::k_read<double>, dim3(nbxR * nbyR), dim3(lbb::NT), 0, d->stream, d->dp,
                            static_cast<const double *>(d->f[d->cf]), static_cast<const double *>(d->T[d->cT]), rho,
@@ -1642,6 +1652,7 @@ extern "C" int lbb_batch_step_async(lbb_batch *b, int64_t n)
         d->cT = b->cT;
         d->fresh = true;
         d->flushed = b->stream;
+        d->read = false;  // read-backs to host memory were over before
     }
     return LBB_OK;
 }

@@ -74,3 +74,38 @@ def test_batch_sync_reports_a_member_that_fails_alone():
     with pytest.raises(L.LbbError) as e:
         b.sync()
     assert e.value.code == L.LBB_ENONFINITE and "member 1" in str(e.value)
+
+
+@pytest.mark.parametrize("read", ["host", "device", "one field"])
+def test_a_read_that_finds_an_invalid_state_is_reported_by_sync(read):
+    """The state after the last step is checked by whatever reads it next: a
+    read-back flags it, and the next synchronising call reports it."""
+    import torch
+
+    _say("invalid state found by a read", read)
+    d = L.Domain(_hot(), rho0=np.full((8, 16), 6.0))
+    _invalid(d)
+    d.step(0)  # ends a sequence of steps; steps nothing, so nothing is checked
+    if read == "host":
+        d.fields()
+    elif read == "one field":
+        d.bottom_temperature()
+    else:
+        rho = torch.empty((8, 16), dtype=torch.float64, device="cuda")
+        d.read_into(rho=rho.data_ptr(), stream=torch.cuda.current_stream().cuda_stream)
+    with pytest.raises(L.LbbError) as e:
+        d.sync()
+    assert e.value.code == L.LBB_ENONFINITE
+
+
+def test_a_member_read_that_finds_an_invalid_state_is_reported_by_its_batch():
+    _say("invalid state found by a member's read")
+    b = L.Batch([_hot(), _hot()], None, [np.full((8, 16), 6.0)] * 2)
+    _invalid(b.domain(1))
+    b.step(0)
+    for i in (0, 1):
+        b.domain(i).fields()
+    for _ in range(2):
+        with pytest.raises(L.LbbError) as e:
+            b.sync()
+        assert e.value.code == L.LBB_ENONFINITE and "member 1" in str(e.value)
