@@ -18,10 +18,12 @@ struct lbb3_domain {
     double *psi = nullptr, *mpart = nullptr, *hpart = nullptr, *Tb_dev = nullptr;
     lbb3::Scalars3 *sc = nullptr;
     // pinned host memory the kernels write to: the scalars as the last sequence
-    // of steps left them (`fresh`: nothing changed them since), the local flux
+    // of steps left them (`fresh`: nothing changed them since; never once steps
+    // were `recorded` into a caller's graph, which may run at any time), the
+    // local flux
     lbb3::Scalars3 *host = nullptr;
     double *host_q = nullptr;
-    bool fresh = false;
+    bool fresh = false, recorded = false;
     bool stream_f = false;  // f is loaded past the caches
     int nb = 0;   // blocks of the per-node launches
     int ncu = 0;  // compute units of the device
@@ -177,6 +179,7 @@ int build_graph3(lbb3_domain *d, hipGraphExec_t *out)
 int enqueue_steps3(lbb3_domain *d, int64_t n)
 {
     d->fresh = false;
+    d->recorded = d->recorded || capturing(d->stream);
     while (n >= kGraphSteps) {
         hipGraphExec_t &g = d->graph[d->cf][d->cT];
         if (!g) {
@@ -189,7 +192,7 @@ int enqueue_steps3(lbb3_domain *d, int64_t n)
     for (int64_t k = 0; k < n; ++k) enqueue_step3_any(d);
     enqueue_reductions3_any(d, 0, true);  // rho_ave and the heat-flux sample of the final state
     LBB_HIP(hipGetLastError());
-    d->fresh = true;
+    d->fresh = !d->recorded;
     return LBB_OK;
 }
 

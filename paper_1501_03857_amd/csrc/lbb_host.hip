@@ -262,6 +262,9 @@ struct lbb_domain {
     // A read-back since that flush may have flagged the state in the device's
     // scalars only; `read_dev`: one that may not have run yet.
     bool read = false, read_dev = false;
+    // Work of the domain is part of a caller's graph, which may run at any
+    // time from then on: the host copy is no longer used.
+    bool recorded = false;
     hipEvent_t order = nullptr;          // orders read-backs with a caller's stream
 };
 
@@ -675,6 +678,13 @@ void launch_flush(hipStream_t st, const lbb::Inst *insts, int n, bool one, int p
     else hipLaunchKernelGGL(lbb::k_flush_step<float>, dim3(n), dim3(lbb::NT), 0, st, insts, cf, cT);
 }
 
+// Whether a stream is being captured into a caller's graph.
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &c) == hipSuccess && c != hipStreamCaptureStatusNone;
+}
+
 void drop_graphs(lbb_domain *d)
 {
     for (auto &row : d->graph)
@@ -703,6 +713,7 @@ int build_graph(lbb_domain *d, hipGraphExec_t *out)
 int enqueue_steps(lbb_domain *d, int64_t n)
 {
     d->fresh = false;
+    d->recorded = d->recorded || capturing(d->stream);
     while (n >= kGraphSteps) {
         hipGraphExec_t &g = d->graph[d->cf][d->cT];
         if (!g) {
@@ -716,7 +727,7 @@ int enqueue_steps(lbb_domain *d, int64_t n)
     for (int64_t k = 0; k < n; ++k) enqueue_step_any(d, k);
     launch_flush(d->stream, d->d_inst, 1, one_launch(d), d->p.precision, d->cf, d->cT);
     LBB_HIP(hipGetLastError());
-    d->fresh = true;
+    d->fresh = !d->recorded;
     d->flushed = d->stream;
     d->read = d->read_dev = false;  // earlier read-backs ran on this stream
     return LBB_OK;
@@ -1045,6 +1056,8 @@ int lbb_read_fields_dev(lbb_domain *d, double *rho, double *ux, double *uy, doub
     }
     const int nbxR = (d->p.nx + lbb::TXR - 1) / lbb::TXR, nbyR = (d->p.ny + lbb::TYR - 1) / lbb::TYR;
     d->read_dev = true;
+    d->recorded = d->recorded || capturing(d->stream);
+    if (d->recorded) d->fresh = false;
     if (d->p.precision == LBB_FP64)
         hipLaunchKernelGGL(lbb::k_read<double>, dim3(nbxR * nbyR), dim3(lbb::NT), 0, d->stream, d->dp,
                            static_cast<const double *>(d->f[d->cf]), static_cast<const double *>(d->T[d->cT]), rho,
@@ -1511,9 +1524,7 @@ static int batch_push(lbb_batch *b)
     if (b->pushed.size() == insts.size() &&
         std::memcmp(b->pushed.data(), insts.data(), insts.size() * sizeof(lbb::Inst)) == 0) {
         // a batch does not step under a caller's capture, table changed or not
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        LBB_HIP(hipStreamIsCapturing(b->stream, &cap));
-        return cap == hipStreamCaptureStatusNone ? LBB_OK : fail(LBB_EDEVICE, "the batch's stream is being captured");
+        return capturing(b->stream) ? fail(LBB_EDEVICE, "the batch's stream is being captured") : LBB_OK;
     }
     b->pushed.clear();
     LBB_HIP(hipMemcpyAsync(b->d_insts, insts.data(), insts.size() * sizeof(lbb::Inst), hipMemcpyHostToDevice,
@@ -1650,7 +1661,7 @@ extern "C" int lbb_batch_step_async(lbb_batch *b, int64_t n)
     for (lbb_domain *d : b->doms) {
         d->cf = b->cf;
         d->cT = b->cT;
-        d->fresh = true;
+        d->fresh = !d->recorded;
         d->flushed = b->stream;
         d->read = false;  // read-backs to host memory were over before
     }
