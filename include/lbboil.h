@@ -151,8 +151,8 @@ int lbb_sync(lbb_domain *d);
  * record events around lbb_step_async. */
 void *lbb_stream(lbb_domain *d);
 
-/* Advance n >= 1 steps with single launches (no graph), each launch
- * carrying HIP events that its dispatch records at kernel start and end;
+/* Advance n >= 1 steps of two launches each (also where lbb_step takes one),
+ * launched one by one (no graph), each launch carrying HIP events that its dispatch records at kernel start and end;
  * returns the mean kernel duration in milliseconds of the LB launch
  * (collision, forces, streaming) and of the thermal launch (RK4 temperature
  * step), and the mean wall time per step of the whole sequence.  For
@@ -287,7 +287,7 @@ int lbb_set_tiles(lbb_domain *d, int32_t shape_lb, int32_t shape_thermal);
 /* Time every LB shape, then every thermal shape with the best LB shape, for
  * `steps` steps each on the domain's own state (per-kernel durations from
  * events recorded by the dispatches), keep the fastest of each for steps of
- * two launches, and restore the state, step count and heat-flux average.  Outputs (may be NULL): the
+ * two launches (the form of the step does not change), and restore the state, step count and heat-flux average.  Outputs (may be NULL): the
  * chosen shapes and the mean durations in ms per shape (ms_lb[n_lb],
  * ms_thermal[n_thermal]).  EINVAL for steps < 1; ESTATE on a poisoned
  * domain; ENONFINITE if a trial step produces an invalid state (the state is

@@ -790,8 +790,8 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 6 : 1) void k_lb(const Inst 
     S *__restrict__ vx_o = static_cast<S *>(I.vx);
     S *__restrict__ vy_o = static_cast<S *>(I.vy);
     Scalars *__restrict__ sc = I.sc;
-    const int nbx = I.nbxA, nby = I.nbyA;
-    const int blk = (int)blockIdx.x - I.blkA0;
+    const int nbx = I.nbxA, nby = ONE ? I.nbyF : I.nbyA;
+    const int blk = (int)blockIdx.x - (ONE ? I.blkF0 : I.blkA0);
     static_assert(TYA % NWA == 0, "LB rows must split evenly over the waves");
     constexpr int IPW_A = TYA / NWA;             // interior rows per wave
     constexpr int H = TYA + 2;                   // region rows (halo rows 0 and H-1)

@@ -212,10 +212,11 @@ struct BlobHeader {
 constexpr uint64_t kMagic = 0x6c62626f696c3031ULL;  // "lbboil01"
 
 // How lattices step: two launches (height 0), or one in tiles or marching
-// strips of `height` rows.
+// strips of `height` rows, or one in the LB tiles of isothermal lattices.
 struct StepForm {
     int height = 0;
     bool march = false;
+    bool lb = false;
 };
 
 }  // namespace
@@ -429,14 +430,30 @@ constexpr int step_max_rows(int precision) { return precision == LBB_FP64 ? 48 :
 int64_t step_blocks(const StepDims &l, const StepForm &f)
 {
     if (!f.height) return 0;
-    const int64_t tiles = (int64_t)((l.nx + lbb::TXF - 1) / lbb::TXF) * ((l.ny + f.height - 1) / f.height);
+    const int width = f.lb ? lbb::TXA : lbb::TXF;
+    const int64_t tiles = (int64_t)((l.nx + width - 1) / width) * ((l.ny + f.height - 1) / f.height);
     return f.march ? (tiles + kMarchWaves - 1) / kMarchWaves : tiles;
 }
+
+// Isothermal lattices step in one launch of k_lb (ONE, default tiles) where
+// every block can add up the mass partials (one per lattice row and LB tile
+// column) with at most eight loads a thread.  Eleven 160x60 FP64 lattices:
+// 7.5 us per step against 12.0 with the temperature launch, which reduces in
+// 4.4 us.  Tuned shapes do not matter to it: 248x512 FP64 8.5 us, against 9.8
+// in two launches of the fastest shapes.
+constexpr int kOneMaxPartials = 2048;
 
 // Form of the step of lattices that step together.
 StepForm step_form(const std::vector<StepDims> &ls, int precision, int mode, int ncu)
 {
     StepForm f;
+    if (mode == LBB_ISOTHERMAL) {
+        for (const StepDims &l : ls)
+            if ((int64_t)((l.nx + lbb::TXA - 1) / lbb::TXA) * l.ny > kOneMaxPartials) return f;
+        f.height = lbb::kShapeA[0].ty;
+        f.lb = true;
+        return f;
+    }
     if (mode != LBB_COUPLED) return f;
     auto blocks = [&](const StepForm &g) {
         int64_t n = 0;
@@ -466,7 +483,7 @@ int64_t step_max_blocks(const StepDims &l, int precision, int mode, int ncu)
 void set_step_grid(lbb::Inst &I, const StepForm &f, const StepDims &l, int blk0)
 {
     I.tyF = f.height;
-    I.nbxF = f.height ? (l.nx + lbb::TXF - 1) / lbb::TXF : 0;
+    I.nbxF = f.height ? (l.nx + (f.lb ? lbb::TXA : lbb::TXF) - 1) / (f.lb ? lbb::TXA : lbb::TXF) : 0;
     I.nbyF = f.height ? (l.ny + f.height - 1) / f.height : 0;
     I.npF = (int)step_blocks(l, f);
     I.blkF0 = blk0;
@@ -566,6 +583,11 @@ void launch_step(hipStream_t st, const lbb::Inst *insts, const int *blk, int nbl
                  const StepForm &f)
 {
     using namespace lbb;
+    if (f.lb) {
+        hipLaunchKernelGGL((k_lb<S, kShapeA[0].ty, kShapeA[0].nw, true>), dim3(nblocks), dim3(64 * kShapeA[0].nw), 0, st,
+                           insts, blk, cf, cT, par);
+        return;
+    }
     if (f.march) {
         hipLaunchKernelGGL((k_march<S, kMarchWaves>), dim3(nblocks), dim3(64 * kMarchWaves), 0, st, insts, blk, cf, cT, par);
         return;
@@ -577,25 +599,6 @@ void launch_step(hipStream_t st, const lbb::Inst *insts, const int *blk, int nbl
     else if (rows <= 48) hipLaunchKernelGGL((k_step<S, 16, 3>), g, b, 0, st, insts, blk, cf, cT, par, aux);
     else if constexpr (sizeof(S) == 4)
         hipLaunchKernelGGL((k_step<S, 16, 4>), g, b, 0, st, insts, blk, cf, cT, par, aux);
-}
-
-// Whole step of isothermal lattices (k_lb, ONE) in the default tiles.
-template <typename S>
-void launch_lb_one(hipStream_t st, const lbb::Inst *insts, const int *blk, int nblocks, int cf, int cT, int par)
-{
-    using namespace lbb;
-    hipLaunchKernelGGL((k_lb<S, kShapeA[0].ty, kShapeA[0].nw, true>), dim3(nblocks), dim3(64 * kShapeA[0].nw), 0, st,
-                       insts, blk, cf, cT, par);
-}
-
-// Isothermal lattices that step in one launch: every block adds up the mass
-// partials (one per lattice row and LB tile column) with at most eight loads a
-// thread.  Eleven 160x60 FP64 lattices: 7.5 us per step against 12.0 with the
-// temperature launch, which reduces in 4.4 us.
-constexpr int kOneMaxPartials = 2048;
-bool isothermal_one(const lbb_params &p)
-{
-    return p.thermal_mode == LBB_ISOTHERMAL && (int64_t)((p.nx + lbb::TXA - 1) / lbb::TXA) * p.ny <= kOneMaxPartials;
 }
 
 template <typename S>
@@ -640,11 +643,7 @@ void advance_buffers(lbb_domain *d)
     if (d->dp.mode != lbb::MODE_ISOTHERMAL) d->cT ^= 1;
 }
 
-// Whether the domain steps in one launch: by k_step, or isothermal by k_lb.
-bool one_launch(const lbb_domain *d)
-{
-    return !d->fixed_tiles && (d->form.height > 0 || (isothermal_one(d->p) && d->shA == 0));
-}
+bool one_launch(const lbb_domain *d) { return !d->fixed_tiles && d->form.height > 0; }
 
 // Step number k of a sequence that ends in enqueue_flush.
 template <typename S>
@@ -652,11 +651,8 @@ void enqueue_step(lbb_domain *d, int64_t k)
 {
     const int par = (int)(k & 1);
     if (one_launch(d)) {
-        if (d->form.height)
-            launch_step<S>(d->stream, d->d_inst, d->d_blkF, (int)step_blocks({d->p.nx, d->p.ny}, d->form) + 1, d->cf,
-                           d->cT, par, 0, d->form);
-        else
-            launch_lb_one<S>(d->stream, d->d_inst, d->d_blkA, d->nbxA * d->nbyA + 1, d->cf, d->cT, par);
+        launch_step<S>(d->stream, d->d_inst, d->d_blkF, (int)step_blocks({d->p.nx, d->p.ny}, d->form) + 1, d->cf, d->cT,
+                       par, 0, d->form);
     } else {
         launch_lb<S>(d);
         launch_thermal<S>(d);
@@ -1368,7 +1364,7 @@ static int init_domain(const lbb_params *pin, const double *T_bottom, const doub
         // mass partials: one per lattice row and LB tile column (also holds the
         // per-block partials of the set-up mass kernel, fewer)
         {(void **)&d->mass_part,
-         (size_t)std::max(mbA, (isothermal_one(p) ? 2 : 1) * d->nbxA * p.ny) * sizeof(double)},
+         (size_t)std::max(mbA, (d->form.lb ? 2 : 1) * d->nbxA * p.ny) * sizeof(double)},
         {(void **)&d->hf_part, (size_t)d->nbxB * sizeof(double)},
         {(void **)&d->Tb_dev, (size_t)p.nx * sizeof(double)},
         {(void **)&d->sc, sizeof(lbb::Scalars)},
@@ -1377,7 +1373,7 @@ static int init_domain(const lbb_params *pin, const double *T_bottom, const doub
         {(void **)&d->d_blkB, (size_t)(mbB + 1) * sizeof(int)},
         {(void **)&d->rel, 2 * sizeof(long long)},
         {(void **)&d->mpart, 2 * np * sizeof(lbb::MassSum)},
-        {(void **)&d->d_blkF, coupled ? (size_t)(step_blocks(lat, d->form) + 1) * sizeof(int) : 0}};
+        {(void **)&d->d_blkF, d->form.height ? (size_t)(step_blocks(lat, d->form) + 1) * sizeof(int) : 0}};
     const auto rounded = [](size_t b) { return (b + 255) & ~(size_t)255; };
     size_t total = 0;
     for (const auto &q : small) total += rounded(q.bytes);
@@ -1476,16 +1472,7 @@ static int batch_tables(lbb_batch *b)
     return LBB_OK;
 }
 
-// Whether the batch steps in one launch: by k_step, or isothermal by k_lb.
-static bool one_launch(const lbb_batch *b)
-{
-    if (b->fixed_tiles) return false;
-    if (b->form.height > 0) return true;
-    if (b->shA != 0) return false;
-    for (const lbb_domain *d : b->doms)
-        if (!isothermal_one(d->p)) return false;
-    return true;
-}
+static bool one_launch(const lbb_batch *b) { return !b->fixed_tiles && b->form.height > 0; }
 
 // Upload the launch table (all members, with their block offsets); members
 // take the batch's tile shapes.
@@ -1539,11 +1526,7 @@ static void batch_enqueue_step(lbb_batch *b, int64_t k)
 {
     const int par = (int)(k & 1);
     if (one_launch(b)) {
-        if (!b->form.height && b->precision == LBB_FP64)
-            launch_lb_one<double>(b->stream, b->d_insts, b->d_blkA, b->totA, b->cf, b->cT, par);
-        else if (!b->form.height)
-            launch_lb_one<float>(b->stream, b->d_insts, b->d_blkA, b->totA, b->cf, b->cT, par);
-        else if (b->precision == LBB_FP64)
+        if (b->precision == LBB_FP64)
             launch_step<double>(b->stream, b->d_insts, b->d_blkF, b->totF, b->cf, b->cT, par, 0, b->form);
         else
             launch_step<float>(b->stream, b->d_insts, b->d_blkF, b->totF, b->cf, b->cT, par, 0, b->form);
@@ -2633,7 +2616,7 @@ NoallocLayout noalloc_layout(int nx, int ny, int precision, int mode, int ncu)
     L.total = o;
     // the one-launch step adds its partials only where they fit as well
     StepForm f = step_form({{nx, ny}}, precision, mode, ncu);
-    if (f.march) f = StepForm{};  // strips do not hand out rho and v
+    if (f.march || f.lb) f = StepForm{};  // these forms do not hand out rho and v
     const size_t np = (size_t)step_blocks({nx, ny}, f);
     L.rel = o;
     o += up(2 * sizeof(long long));

@@ -279,7 +279,9 @@ class Domain:
 
     def time_kernels(self, n: int):
         """Mean (LB launch, thermal launch, whole step) durations in ms over n
-        single-launch steps, from HIP events on the library stream."""
+        steps of two launches, enqueued one by one, from HIP events on the
+        library stream; a lattice that otherwise steps in one launch takes
+        another time per step."""
         a, b, c = _d(), _d(), _d()
         _check(lib().lbb_time_kernels(self._h, int(n), C.byref(a), C.byref(b), C.byref(c)))
         return a.value, b.value, c.value
@@ -300,8 +302,10 @@ class Domain:
         return self
 
     def autotune(self, steps: int = 20):
-        """Time every tile shape on this lattice, keep the fastest; the state
-        is left unchanged.  Returns the choice and the per-shape times (ms)."""
+        """Time every tile shape on this lattice and keep the fastest for steps
+        of two launches (steps of one launch have no such shapes and stay as
+        they are); the state is left unchanged.  Returns the choice and the
+        per-shape times (ms)."""
         return _autotune(lib().lbb_autotune, self._h, steps)
 
     def adjoint(self, n_steps: int, K: int = 0, heater_idx=None):
