@@ -483,21 +483,23 @@ __device__ __forceinline__ MassSum mass_sum(const long long *__restrict__ a_, si
     return t;
 }
 
-// Heat-flux bookkeeping: q of state t from the partial sums over x; counted
-// once per state index (t > last_counted), never for the initial state.
+// Heat-flux bookkeeping: q of state t from the sum of the partial sums over x;
+// counted once per state index (t > last_counted), never for the initial state.
+__device__ __forceinline__ void count_heat_flux(double sum, int nx, Scalars *sc, long long t)
+{
+    const double q = sum / (double)nx;
+    sc->q_now = q;
+    if (t > sc->last_counted) {
+        sc->q_sum += q;
+        sc->n_samples += 1;
+        sc->last_counted = t;
+    }
+}
+
 __device__ __forceinline__ void reduce_heat_flux(const double *__restrict__ hf_part, int n_hf, int nx,
                                                  Scalars *sc, long long t)
 {
-    if (threadIdx.x == 0) {
-        const double s = ordered_sum(hf_part, 0, n_hf, 1, 0.0);
-        const double q = s / (double)nx;
-        sc->q_now = q;
-        if (t > sc->last_counted) {
-            sc->q_sum += q;
-            sc->n_samples += 1;
-            sc->last_counted = t;
-        }
-    }
+    if (threadIdx.x == 0) count_heat_flux(ordered_sum(hf_part, 0, n_hf, 1, 0.0), nx, sc, t);
 }
 
 // ---------------------------------------------------------------------------
@@ -729,34 +731,86 @@ __device__ __forceinline__ void tile_psi(const DevParams &P, const S *__restrict
     }
 }
 
+// Heat-flux partial of chunk b of the state (f, T) by one wave, in every lane.
+template <typename S>
+__device__ __forceinline__ double chunk_flux(const DevParams &P, const S *__restrict__ f, const S *__restrict__ T, int b,
+                                             double *__restrict__ q_local = nullptr)
+{
+    const int lane = threadIdx.x & 63, gx = b * TXB + lane - HB;
+    double qw = 0.0;
+    if (!P.periodic_y && lane >= HB && lane < HB + TXB && gx < P.nx) {
+        double fl[9];
+        load_node(P, f, (size_t)P.nx * P.ny, (size_t)gx, 0, fl);
+        double r0 = fl[0];
+#pragma unroll
+        for (int a = 1; a < 9; ++a) r0 += fl[a];
+        const double t0 = (double)T[gx], t1 = (double)T[P.nx + gx], t2 = (double)T[2 * P.nx + gx];
+        qw = -P.cv_chi * r0 * (-3.0 * t0 + 4.0 * t1 - t2) / 2.0;
+        if (q_local) q_local[gx] = qw;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) qw += __shfl_xor(qw, off, 64);
+    return qw;
+}
+
 // Heat flux of the state (f, T) from its bottom rows by one block of NW
-// waves: the per-tile partials of k_thermal (same chunks, same order) and the
-// sample of state index t.
-template <typename S, int NW>
-__device__ __forceinline__ void sample_heat_flux(const Inst &I, const S *__restrict__ f_, const S *__restrict__ T_,
-                                                 long long t)
+// waves (a coupled or isothermal lattice): the per-tile partials of k_thermal
+// (same chunks, same order) and the sample of state index t.  A wave takes U
+// chunks at a time, whose loads are issued together; the three populations
+// that the completion of a bottom node replaces are not read, and the partials
+// reach the thread that adds them through LDS.
+constexpr int NSAMPLE = 256;  // partials that fit there
+template <typename S, int NW, int U>
+__device__ __forceinline__ void sample_heat_flux(const Inst &I, const S *__restrict__ f, const S *__restrict__ T,
+                                                 long long t, double *part /* LDS [NSAMPLE] */)
 {
     const DevParams &P = I.P;
-    const gmem<S> *f = (const gmem<S> *)f_, *T = (const gmem<S> *)T_;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int b = wv; b < I.nbxB; b += NW) {
-        const int gx = b * TXB + lane - HB;
-        double qw = 0.0;
-        if (!P.periodic_y && lane >= HB && lane < HB + TXB && gx < P.nx) {
-            double fl[9];
-            load_node(P, f, (size_t)P.nx * P.ny, (size_t)gx, 0, fl);
-            double r0 = fl[0];
+    const unsigned nx = (unsigned)P.nx;
+    const size_t N = (size_t)nx * P.ny;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int b0 = wv; b0 < I.nbxB; b0 += NW * U) {
+        S fs[U][9], ts[U][3];
+        bool on[U];
 #pragma unroll
-            for (int a = 1; a < 9; ++a) r0 += fl[a];
-            const double t0 = (double)T[gx], t1 = (double)T[P.nx + gx], t2 = (double)T[2 * P.nx + gx];
-            qw = -P.cv_chi * r0 * (-3.0 * t0 + 4.0 * t1 - t2) / 2.0;
+        for (int u = 0; u < U; ++u) {
+            const int gx = (b0 + u * NW) * TXB + lane - HB;
+            on[u] = !P.periodic_y && lane >= HB && lane < HB + TXB && gx < P.nx;
+            if (!on[u]) continue;
+            const unsigned c = (unsigned)gx * (unsigned)sizeof(S);
+#pragma unroll
+            for (int a = 0; a < 9; ++a) fs[u][a] = a == 2 || a == 5 || a == 6 ? S(0) : ld_at(f + (size_t)a * N, c);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) ts[u][k] = ld_at(T + (size_t)k * nx, c);
         }
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) qw += __shfl_xor(qw, off, 64);
-        if (lane == 0) I.hf_part[b] = qw;
+        for (int u = 0; u < U; ++u) {
+            const int b = b0 + u * NW;
+            if (b >= I.nbxB) break;
+            double qw = 0.0;
+            if (on[u]) {
+                double fl[9];
+                complete_node(P, fs[u], 0, fl);
+                double r0 = fl[0];
+#pragma unroll
+                for (int a = 1; a < 9; ++a) r0 += fl[a];
+                const double t0 = (double)ts[u][0], t1 = (double)ts[u][1], t2 = (double)ts[u][2];
+                qw = -P.cv_chi * r0 * (-3.0 * t0 + 4.0 * t1 - t2) / 2.0;
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) qw += __shfl_xor(qw, off, 64);
+            if (lane == 0) {
+                I.hf_part[b] = qw;
+                if (b < NSAMPLE) part[b] = qw;
+            }
+        }
     }
     __syncthreads();
-    reduce_heat_flux(I.hf_part, I.nbxB, P.nx, I.sc, t);
+    if (threadIdx.x != 0) return;
+    double s = 0.0;
+    const int n = min(I.nbxB, NSAMPLE);
+#pragma unroll 8
+    for (int k = 0; k < n; ++k) s += part[k];
+    count_heat_flux(ordered_sum(I.hf_part, n, I.nbxB, 1, s), P.nx, I.sc, t);
 }
 
 // ---------------------------------------------------------------------------
@@ -800,7 +854,8 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 6 : 1) void k_lb(const Inst 
     const long long t = sc->tA + since;
     if constexpr (ONE)
         if (blk == 0) {
-            sample_heat_flux<S, NWA>(I, fin, Tin, t);
+            sample_heat_flux<S, NWA, 2>(I, fin, Tin, t, psi_s);
+            static_assert(H * 64 >= NSAMPLE, "");
             if (threadIdx.x == 0) I.rel[par ^ 1] = since + 1;
             return;
         }
@@ -1283,23 +1338,8 @@ template <typename S>
 __global__ void k_heat_flux_state(DevParams P, const S *__restrict__ f, const S *__restrict__ T,
                                   double *__restrict__ hf_part, double *__restrict__ q_local)
 {
-    const int lane = threadIdx.x;
-    const int gx = blockIdx.x * TXB + lane - HB;
-    double qw = 0.0;
-    if (!P.periodic_y && lane >= HB && lane < HB + TXB && gx < P.nx) {
-        const size_t N = (size_t)P.nx * P.ny;
-        double fl[9];
-        load_node(P, f, N, (size_t)gx, 0, fl);
-        double r0 = fl[0];
-#pragma unroll
-        for (int a = 1; a < 9; ++a) r0 += fl[a];
-        const double t0 = (double)T[gx], t1 = (double)T[P.nx + gx], t2 = (double)T[2 * P.nx + gx];
-        qw = -P.cv_chi * r0 * (-3.0 * t0 + 4.0 * t1 - t2) / 2.0;
-        if (q_local) q_local[gx] = qw;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) qw += __shfl_xor(qw, off, 64);
-    if (lane == 0 && hf_part) hf_part[blockIdx.x] = qw;
+    const double qw = chunk_flux<S>(P, f, T, (int)blockIdx.x, q_local);
+    if (threadIdx.x == 0 && hf_part) hf_part[blockIdx.x] = qw;
 }
 
 // Heat-flux bookkeeping of the state after the last step, one block per lattice.

@@ -443,13 +443,26 @@ int64_t step_blocks(const StepDims &l, const StepForm &f)
 // in two launches of the fastest shapes.
 constexpr int kOneMaxPartials = 2048;
 
+// One block of a lattice samples the heat flux of its bottom row in every
+// step, a chunk of TXB columns a wave; on wide lattices of few rows it is the
+// last to end.  Isothermal (four waves; us per step, one launch / two): 1000x120
+// FP64 8.6 / 10.7, 1500x80 9.3 / 10.8 (a step with its flush 14.7 / 14.2),
+// 2000x60 11.4 / 11.1, 8000x15 34 / 12.  Tiles (16 waves): 3400x16 FP32
+// 7.7 / 11.9, 5000x100 21.1 / 23.3, 6800x8 FP64 14.3 / 12.0, 13700x4 24.4 / 13.4,
+// but 13700x38 29.5 / 37.4: tall tiles take longer than the sample.
+constexpr int kOneMaxChunks = 28;
+constexpr int kTileMaxChunks = 96, kTileLongRows = 32;
+constexpr int heat_flux_chunks(int nx) { return (nx + lbb::TXB - 1) / lbb::TXB; }
+
 // Form of the step of lattices that step together.
 StepForm step_form(const std::vector<StepDims> &ls, int precision, int mode, int ncu)
 {
     StepForm f;
     if (mode == LBB_ISOTHERMAL) {
         for (const StepDims &l : ls)
-            if ((int64_t)((l.nx + lbb::TXA - 1) / lbb::TXA) * l.ny > kOneMaxPartials) return f;
+            if ((int64_t)((l.nx + lbb::TXA - 1) / lbb::TXA) * l.ny > kOneMaxPartials ||
+                heat_flux_chunks(l.nx) > kOneMaxChunks)
+                return f;
         f.height = lbb::kShapeA[0].ty;
         f.lb = true;
         return f;
@@ -460,8 +473,10 @@ StepForm step_form(const std::vector<StepDims> &ls, int precision, int mode, int
         for (const StepDims &l : ls) n += step_blocks(l, g) + 1;
         return n;
     };
+    bool wide = false;
+    for (const StepDims &l : ls) wide = wide || (heat_flux_chunks(l.nx) > kTileMaxChunks && l.ny < kTileLongRows);
     for (f.height = kStepMinHeight; f.height + 2 * lbb::HF <= step_max_rows(precision); ++f.height)
-        if (blocks(f) <= ncu) return f;
+        if (blocks(f) <= ncu) return wide ? StepForm{} : f;
     f = StepForm{march_min(precision), true};
     const int64_t slots = (int64_t)ncu * (precision == LBB_FP64 ? 2 : 3);  // blocks resident at once
     for (const StepDims &l : ls)
@@ -666,13 +681,51 @@ void enqueue_step_any(lbb_domain *d, int64_t k)
     else enqueue_step<float>(d, k);
 }
 
+// Largest numbers of heat-flux chunks and of mass partials of lattices that
+// step together.
+struct FlushSize {
+    int chunks = 0;
+    int64_t partials = 0;
+};
+FlushSize flush_size(const std::vector<lbb_domain *> &doms, const StepForm &f)
+{
+    FlushSize m;
+    for (const lbb_domain *d : doms) {
+        m.chunks = std::max(m.chunks, d->nbxB);
+        m.partials = std::max(m.partials, f.lb ? (int64_t)d->nbxA * d->p.ny : step_blocks({d->p.nx, d->p.ny}, f));
+    }
+    return m;
+}
+
 // Heat-flux bookkeeping of the last state of `n` lattices' sequences.
-void launch_flush(hipStream_t st, const lbb::Inst *insts, int n, bool one, int precision, int cf, int cT)
+//
+// A sequence of one step waits for it, so its block has 16 waves where four
+// would take many chunks or partials one after another, and a long bottom row
+// has a launch of its own: a compute unit by itself reads some 50 GB/s.  us of
+// one step and its flush, with four waves that take a chunk at a time / now:
+// 1024x512 FP32 27.8 / 27.1, 4096x2048 FP32 224 / 210, 8192x400 FP32 116 / 86,
+// 13700x54 FP32 72 / 33.5.
+constexpr int kFlushChunks = 16, kFlushPartials = 1024, kFlushRow = 48;
+
+template <typename S>
+void launch_flush_step(hipStream_t st, const lbb::Inst *insts, int n, const FlushSize &m, int cf, int cT)
+{
+    using namespace lbb;
+    const int ready = m.chunks > kFlushRow;
+    if (ready) hipLaunchKernelGGL(k_flush_chunks<S>, dim3(m.chunks, n), dim3(64), 0, st, insts, cf, cT);
+    if (m.chunks > kFlushChunks || m.partials > kFlushPartials)
+        hipLaunchKernelGGL((k_flush_step<S, 1024>), dim3(n), dim3(1024), 0, st, insts, cf, cT, ready);
+    else
+        hipLaunchKernelGGL((k_flush_step<S, NT>), dim3(n), dim3(NT), 0, st, insts, cf, cT, ready);
+}
+
+void launch_flush(hipStream_t st, const lbb::Inst *insts, int n, bool one, const FlushSize &m, int precision, int cf, int cT)
 {
     if (!one) hipLaunchKernelGGL(lbb::k_flush_heat_flux, dim3(n), dim3(lbb::NT), 0, st, insts);
-    else if (precision == LBB_FP64) hipLaunchKernelGGL(lbb::k_flush_step<double>, dim3(n), dim3(lbb::NT), 0, st, insts, cf, cT);
-    else hipLaunchKernelGGL(lbb::k_flush_step<float>, dim3(n), dim3(lbb::NT), 0, st, insts, cf, cT);
+    else if (precision == LBB_FP64) launch_flush_step<double>(st, insts, n, m, cf, cT);
+    else launch_flush_step<float>(st, insts, n, m, cf, cT);
 }
+
 
 // Whether a stream is being captured into a caller's graph.
 bool capturing(hipStream_t st)
@@ -721,7 +774,7 @@ int enqueue_steps(lbb_domain *d, int64_t n)
         n -= kGraphSteps;
     }
     for (int64_t k = 0; k < n; ++k) enqueue_step_any(d, k);
-    launch_flush(d->stream, d->d_inst, 1, one_launch(d), d->p.precision, d->cf, d->cT);
+    launch_flush(d->stream, d->d_inst, 1, one_launch(d), flush_size({d}, d->form), d->p.precision, d->cf, d->cT);
     LBB_HIP(hipGetLastError());
     d->fresh = !d->recorded;
     d->flushed = d->stream;
@@ -745,23 +798,23 @@ int report_errors(lbb_domain *d, const lbb::Scalars &s)
 
 // The device's scalars, from their host copy when the last flush left it up to
 // date, else copied.  Waits for the domain's stream and, for the host copy, for
-// the one that flush ran on.
-int read_scalars(lbb_domain *d, lbb::Scalars *s)
+// the one that flush ran on (unless the caller has: `waited`).
+int read_scalars(lbb_domain *d, lbb::Scalars *s, hipStream_t waited = nullptr)
 {
     if (!d->fresh) LBB_HIP(hipMemcpyAsync(s, d->sc, sizeof *s, hipMemcpyDeviceToHost, d->stream));
     LBB_HIP(hipStreamSynchronize(d->stream));
     if (d->fresh) {
-        if (d->flushed != d->stream) LBB_HIP(hipStreamSynchronize(d->flushed));
+        if (d->flushed != d->stream && d->flushed != waited) LBB_HIP(hipStreamSynchronize(d->flushed));
         *s = *d->host;
     }
     return LBB_OK;
 }
 
-int check_errors(lbb_domain *d)
+int check_errors(lbb_domain *d, hipStream_t waited = nullptr)
 {
     if (d->read || d->read_dev) d->fresh = false;
     lbb::Scalars s;
-    int rc = read_scalars(d, &s);
+    int rc = read_scalars(d, &s, waited);
     if (rc) return rc;
     rc = report_errors(d, s);
     if (!rc) d->read = d->read_dev = false;  // over, and nothing flagged
@@ -1639,7 +1692,8 @@ extern "C" int lbb_batch_step_async(lbb_batch *b, int64_t n)
         n -= kGraphSteps;
     }
     for (int64_t k = 0; k < n; ++k) batch_enqueue_step(b, k);
-    launch_flush(b->stream, b->d_insts, (int)b->doms.size(), one_launch(b), b->precision, b->cf, b->cT);
+    launch_flush(b->stream, b->d_insts, (int)b->doms.size(), one_launch(b), flush_size(b->doms, b->form), b->precision, b->cf,
+                 b->cT);
     LBB_HIP(hipGetLastError());
     for (lbb_domain *d : b->doms) {
         d->cf = b->cf;
@@ -1657,7 +1711,7 @@ extern "C" int lbb_batch_sync(lbb_batch *b)
     LBB_HIP(hipStreamSynchronize(b->stream));
     for (size_t i = 0; i < b->doms.size(); ++i) {
         // a member may have work of its own pending on its own stream
-        int rc = check_errors(b->doms[i]);
+        int rc = check_errors(b->doms[i], b->stream);
         if (rc) return fail(rc, "batch member " + std::to_string(i) + ": " + g_err);
     }
     return LBB_OK;
@@ -1679,7 +1733,7 @@ extern "C" int lbb_batch_heat_flux(lbb_batch *b, double *q_now, double *q_mean, 
     for (size_t i = 0; i < b->doms.size(); ++i) {
         lbb_domain *d = b->doms[i];
         lbb::Scalars s;
-        const int rc = read_scalars(d, &s);
+        const int rc = read_scalars(d, &s, b->stream);
         if (rc) return rc;
         if (q_now) q_now[i] = s.q_now;
         if (q_mean) q_mean[i] = s.n_samples ? s.q_sum / (double)s.n_samples : NAN;
@@ -2309,7 +2363,7 @@ int adjoint_run(AdjGroup &g, int64_t N, int64_t K, double *J, double *dJ_dTb, do
     }
     // the last state is slot N - tL, the second state of the step before it
     launch_flush(st, g.form.height ? inst_seg + (size_t)(N - tL - 1) * nm : g.fwd_insts, nm, g.form.height > 0,
-                 sizeof(S) == 8 ? LBB_FP64 : LBB_FP32, 1, 1);
+                 flush_size(g.doms, g.form), sizeof(S) == 8 ? LBB_FP64 : LBB_FP32, 1, 1);
     LBB_HIP(hipStreamSynchronize(st));
     for (int i = 0; i < nm; ++i) {  // the flush has left the scalars in host memory
         const int rc = report_errors(g.doms[i], *g.doms[i]->host);
@@ -2674,9 +2728,10 @@ __global__ void k_noalloc_result(const lbb::Scalars *sc, lbb_noalloc_result *out
 // End of a sequence of one-launch steps and the result (thread 0 writes the
 // scalars it then reads).
 template <typename S>
-__global__ __launch_bounds__(lbb::NT) void k_noalloc_end(const lbb::Inst *inst, int cf, int cT, lbb_noalloc_result *out)
+__global__ __launch_bounds__(lbb::NT) void k_noalloc_end(const lbb::Inst *inst, int cf, int cT, int ready,
+                                                         lbb_noalloc_result *out)
 {
-    lbb::flush_step<S>(*inst, cf, cT);
+    lbb::flush_step<S, lbb::NT>(*inst, cf, cT, ready != 0);
     if (threadIdx.x == 0) noalloc_result(inst->sc, out);
 }
 
@@ -2706,7 +2761,9 @@ void noalloc_enqueue(const lbb::Inst &I, unsigned char *base, const NoallocLayou
             cf ^= 1;
             cT ^= 1;
         }
-        hipLaunchKernelGGL(k_noalloc_end<S>, dim3(1), dim3(NT), 0, st, inst, cf, cT, result);
+        const int ready = L.nbxB > kFlushChunks;
+        if (ready) hipLaunchKernelGGL(k_flush_chunks<S>, dim3(L.nbxB), dim3(64), 0, st, inst, cf, cT);
+        hipLaunchKernelGGL(k_noalloc_end<S>, dim3(1), dim3(NT), 0, st, inst, cf, cT, ready, result);
         return;
     }
     hipLaunchKernelGGL(k_heat_flux_state<S>, dim3(L.nbxB), dim3(64), 0, st, I.P, f,

@@ -98,7 +98,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
     const StepIndex t{rel + par, (const gmem<Scalars> *)sc};
     const long long since = *t.rel;
     if (blk == 0) {
-        sample_heat_flux<S, NW>(I, fin, Tin, t);
+        sample_heat_flux<S, NW, 2>(I, fin, Tin, t, &buf[0][0]);
         if (threadIdx.x == 0) I.rel[par ^ 1] = since + 1;
         return;
     }
@@ -293,6 +293,7 @@ __global__ __launch_bounds__(64 * WB, sizeof(S) == 4 ? 3 : 2) void k_march(const
 {
     using C = typename ThermalCfg<S>::C;
     __shared__ MassSum red[WB];
+    __shared__ double part[NSAMPLE];
     const Inst &I = insts[blk2inst[blockIdx.x]];
     const DevParams &P = I.P;
     Scalars *__restrict__ sc = I.sc;
@@ -304,7 +305,7 @@ __global__ __launch_bounds__(64 * WB, sizeof(S) == 4 ? 3 : 2) void k_march(const
     const gmem<Scalars> *scg = (const gmem<Scalars> *)sc;
     const long long since = ((const gmem<long long> *)I.rel)[par], t = scg->tA + since;
     if (blk == 0) {
-        sample_heat_flux<S, WB>(I, fin, Tin, t);
+        sample_heat_flux<S, WB, 4>(I, fin, Tin, t, part);
         if (threadIdx.x == 0) I.rel[par ^ 1] = since + 1;
         return;
     }
@@ -501,17 +502,37 @@ __global__ __launch_bounds__(64 * WB, sizeof(S) == 4 ? 3 : 2) void k_march(const
     }
 }
 
-// End of a sequence of one-launch steps: rho_ave, the heat-flux sample and
-// the state index of the last state, whose buffers are cf, cT; without a
-// launch since the last flush, the sample of the current state.  One block of
-// NT threads.
-template <typename S>
-__device__ __forceinline__ void flush_step(const Inst &I, int cf, int cT)
+// Launches since the last flush: the larger of the two counts.
+__device__ __forceinline__ long long steps_since(const Inst &I, int &par)
 {
-    __shared__ MassSum red[NT / 64];
-    const long long r0 = I.rel[0], r1 = I.rel[1], t0 = I.sc->tA;
-    const int par = r1 > r0;
-    const long long since = par ? r1 : r0;
+    const long long r0 = I.rel[0], r1 = I.rel[1];
+    par = r1 > r0;
+    return par ? r1 : r0;
+}
+
+// The heat-flux partials of the last state of a sequence of one-launch steps,
+// a wave a chunk: before the flush of wide lattices (block y: the lattice).
+template <typename S>
+__global__ __launch_bounds__(64) void k_flush_chunks(const Inst *__restrict__ insts, int cf, int cT)
+{
+    const Inst &I = insts[blockIdx.y];
+    int par;
+    if ((int)blockIdx.x >= I.nbxB || steps_since(I, par) == 0) return;
+    const double q = chunk_flux<S>(I.P, static_cast<const S *>(I.f[cf]), static_cast<const S *>(I.T[cT]), (int)blockIdx.x);
+    if (threadIdx.x == 0) I.hf_part[blockIdx.x] = q;
+}
+
+// End of a sequence of one-launch steps: rho_ave, the heat-flux sample and
+// the state index of the last state, whose buffers are cf, cT (its partials
+// there already if `ready`); without a launch since the last flush, the sample
+// of the current state.  One block of NTH threads.
+template <typename S, int NTH>
+__device__ __forceinline__ void flush_step(const Inst &I, int cf, int cT, bool ready)
+{
+    __shared__ MassSum red[NTH / 64];
+    __shared__ double part[NSAMPLE];
+    int par;
+    const long long t0 = I.sc->tA, since = steps_since(I, par);
     if (since == 0) {
         reduce_heat_flux(I.hf_part, I.nbxB, I.P.nx, I.sc, t0);
         return;
@@ -520,10 +541,10 @@ __device__ __forceinline__ void flush_step(const Inst &I, int cf, int cT)
     if (I.P.mode == MODE_ISOTHERMAL) {  // the partials of k_lb
         const size_t np = (size_t)I.nbxA * I.P.ny;
         const gmem<long long> *part = (const gmem<long long> *)I.mass_part + par * np;
-        for (size_t k = threadIdx.x; k < np; k += NT) s.add(part[k]);
+        for (size_t k = threadIdx.x; k < np; k += NTH) s.add(part[k]);
     } else {
         const gmem<MassSum> *part = (const gmem<MassSum> *)I.mpart + (size_t)par * I.npF;
-        for (int k = threadIdx.x; k < I.npF; k += NT) {
+        for (int k = threadIdx.x; k < I.npF; k += NTH) {
             s.hi += part[k].hi;
             s.lo += part[k].lo;
         }
@@ -531,11 +552,17 @@ __device__ __forceinline__ void flush_step(const Inst &I, int cf, int cT)
     s.hi = wave_sum_to_last(s.hi);
     s.lo = wave_sum_to_last(s.lo);
     if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = s;
-    // the barrier inside also covers red and the reads of rel and tA above
-    sample_heat_flux<S, NT / 64>(I, static_cast<const S *>(I.f[cf]), static_cast<const S *>(I.T[cT]), t0 + since);
+    // the barrier of either branch also covers red and the reads of rel and tA above
+    if (ready) {
+        __syncthreads();
+        reduce_heat_flux(I.hf_part, I.nbxB, I.P.nx, I.sc, t0 + since);
+    } else {
+        sample_heat_flux<S, NTH / 64, 4>(I, static_cast<const S *>(I.f[cf]), static_cast<const S *>(I.T[cT]), t0 + since,
+                                         part);
+    }
     if (threadIdx.x == 0) {
         MassSum u{0, 0};
-        for (int k = 0; k < NT / 64; ++k) u.add(red[k]);
+        for (int k = 0; k < NTH / 64; ++k) u.add(red[k]);
         I.sc->rho_ave = u.value(I.P.mass_q) / ((double)I.P.nx * (double)I.P.ny);
         I.sc->tA = t0 + since;
         I.sc->tB = t0 + since - 1;  // as the two-launch step leaves it
@@ -543,11 +570,11 @@ __device__ __forceinline__ void flush_step(const Inst &I, int cf, int cT)
     }
 }
 
-template <typename S>
-__global__ __launch_bounds__(NT) void k_flush_step(const Inst *__restrict__ insts, int cf, int cT)
+template <typename S, int NTH>
+__global__ __launch_bounds__(NTH) void k_flush_step(const Inst *__restrict__ insts, int cf, int cT, int ready)
 {
     const Inst &I = insts[blockIdx.x];
-    flush_step<S>(I, cf, cT);
+    flush_step<S, NTH>(I, cf, cT, ready != 0);
     if (threadIdx.x == 0 && I.host) *I.host = *I.sc;  // the thread that wrote the scalars
 }
 
