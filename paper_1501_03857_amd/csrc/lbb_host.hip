@@ -420,6 +420,12 @@ constexpr int kStepMinHeight = 4;
 constexpr int kMarchWaves = 4;  // waves of a block
 constexpr int kMarchMax = 53;
 constexpr int march_min(int precision) { return precision == LBB_FP64 ? 11 : 17; }
+// Every wave adds up the mass partials of its lattice's blocks before its first
+// row, so that work would grow with the square of the lattice: higher strips
+// keep the partials of a lattice below this (ms per step FP32, two launches /
+// strips of 53 rows / higher ones: 8192x24576, 17632 partials, 6.58 / 4.96 /
+// 4.98; 8192x65536, 17.3 / 16.3 / 14.2; 8192x131000, 34.0 / 41.6 / 29.5).
+constexpr int kMarchMaxPartials = 8192;
 constexpr int kMarchMinNy = 32;     // rows a strip's halo may wrap around once
 constexpr int kMarchMaxNx = 8192;   // its one block for the heat flux walks the bottom rows
 // region rows a block of 16 waves has room for: four rows a wave in FP32,
@@ -483,6 +489,8 @@ StepForm step_form(const std::vector<StepDims> &ls, int precision, int mode, int
         if (l.ny < kMarchMinNy || l.nx > kMarchMaxNx) return StepForm{};
     if (blocks(f) <= slots) return StepForm{};
     while (f.height < kMarchMax && blocks(f) > slots) f.height += 3;
+    for (const StepDims &l : ls)
+        while (step_blocks(l, f) > kMarchMaxPartials) f.height += 3;
     return f;
 }
 
