@@ -214,7 +214,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
         cfr[m] = SlopeCoef<C>{};
         act[m] = inl[m] && !(walls && (gys[m] == 0 || gys[m] == P.ny - 1));
         if (!act[m] || r < 2 || r >= H - 2) continue;
-        cfr[m] = slope_coef<C>(P, chi6, X[0][r][lane], X[0][r + 1][lane], X[0][r - 1][lane], X[1][r][lane], X[1][r + 1][lane],
+        cfr[m] = slope_coef<C>(P, X[0][r][lane], X[0][r + 1][lane], X[0][r - 1][lane], X[1][r][lane], X[1][r + 1][lane],
                                X[1][r - 1][lane], X[2][r][lane], X[2][r + 1][lane], X[2][r - 1][lane]);
     }
 
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(64 * WB, sizeof(S) == 4 ? 3 : 2) void k_march(const
             kf[q] = kf[q - 1];
             acc[q] = acc[q - 1];
         }
-        kf[0] = slope_coef<C>(P, chi6, xr[K1], xr[K2], xr[K], xu[K1], xu[K2], xu[K], xv[K1], xv[K2], xv[K]);
+        kf[0] = slope_coef<C>(P, xr[K1], xr[K2], xr[K], xu[K1], xu[K2], xu[K], xv[K1], xv[K2], xv[K]);
         C h = stage_slope<C>(t0[3], t0[4], t0[2], kf[0], Tref, chi6);
         if (at_wall(j - 2)) h = C(0);
         acc[0] = h;
