@@ -142,8 +142,7 @@ __device__ __forceinline__ bool a_int(const DevParams &P, int j) { return j > 0 
 template <int LBW>
 __device__ __forceinline__ MassSum a_block_mass(const DevParams &P, double rho, MassSum *red /* [LBW] */)
 {
-    MassSum s{0, 0};
-    s.add(wave_sum_to_last(mass_units(P.mass_c, rho)));
+    MassSum s = wave_mass(mass_units(P.mass_c, P.mass_r, rho));
     if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = s;
     __syncthreads();
     s = {0, 0};

@@ -115,17 +115,25 @@ template <typename S> struct ThermalCfg;
 // the hardware instruction (1 ulp) in FP32
 __device__ __forceinline__ double stage_sqrt(double x) { return sqrt_nr(x); }
 __device__ __forceinline__ float stage_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
-// Mass sums are exact: a node's mass is rounded once to a whole number of
-// units of P.mass_q and the whole numbers are added in 64 bits, so the domain
-// mean density of Eq. (9) does not depend on the tiles, the launches or the
-// order that formed the sum.  mass_c = 1.5 2^e, so m + mass_c lies in
-// [2^e, 2^(e+1)) for |m| < 2^(e-1), where doubles are 2^(e-52) = mass_q apart;
-// the host takes 2^(e-1) >= 4/b, four times the largest density the equation
-// of state admits (b = 2/21: units of 2.8e-14, below the rounding of a
-// 64-term sum of node masses in FP64).
-__device__ __forceinline__ long long mass_units(const double mass_c, double m)
+// Mass sums are exact: a node's mass is rounded once to whole numbers and the
+// whole numbers are added, so the domain mean density of Eq. (9) does not
+// depend on the tiles, the launches or the order that formed the sum.  hi
+// counts units of 2^(e-52) and lo what hi leaves, in 2^-16 of them: mass_c =
+// 1.5 2^e, so m + mass_c lies in [2^e, 2^(e+1)) for |m| < 2^(e-1), where doubles
+// are 2^(e-52) apart, the remainder is exact, and mass_r = mass_c 2^-16 rounds
+// it the same way.  The host takes 2^(e-1) >= 4/b, four times the largest
+// density the equation of state admits (b = 2/21: 4.3e-19, below half the last
+// place of a double from densities of 4e-3 on; hi alone would round a node to
+// 2.8e-14 and the mass of a 30x20 vapour lattice by a relative 3e-15).
+struct NodeMass {
+    long long hi;
+    int lo;
+};
+__device__ __forceinline__ NodeMass mass_units(const double mass_c, const double mass_r, double m)
 {
-    return __double_as_longlong(m + mass_c) - __double_as_longlong(mass_c);
+    const double t = m + mass_c;
+    const double r = m - (t - mass_c);
+    return {__double_as_longlong(t) - __double_as_longlong(mass_c), __double2loint(r + mass_r)};
 }
 
 // DPP move of a 64-bit value (two 32-bit moves) with control CTL; lanes the
@@ -153,22 +161,47 @@ __device__ __forceinline__ long long wave_sum_to_last(long long v)
     return v;
 }
 
-// Two-part sums of whole numbers below 2^62: low 24 bits and the rest apart,
-// so that 2^30 terms cannot overflow.
+__device__ __forceinline__ int wave_sum_to_last(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+}
+
+// Sums of node masses: hi counts 2^36 of the smallest units and lo the units,
+// so that neither overflows over 2^30 nodes.  The value is a function of the
+// whole sum alone (how it is split depends on the order that formed it),
+// rounded once up to 2^53 of hi.
 struct MassSum {
     long long hi, lo;
-    __device__ __forceinline__ void add(long long v)
+    __device__ __forceinline__ void add(long long h, long long l)
     {
-        hi += v >> 24;
-        lo += v & 0xffffff;
+        hi += h >> 20;
+        lo += ((h & 0xfffff) << 16) + l;
     }
     __device__ __forceinline__ void add(const MassSum &o)
     {
         hi += o.hi;
         lo += o.lo;
     }
-    __device__ __forceinline__ double value(double q) const { return ((double)hi * 16777216.0 + (double)lo) * q; }
+    __device__ __forceinline__ double value(double q) const
+    {
+        const long long h = hi + (lo >> 36), l = lo & 0xfffffffffLL;
+        return ((double)h * 68719476736.0 + (double)l) * q;
+    }
 };
+
+// Mass of a wave's nodes, one a lane, valid in lane 63.
+__device__ __forceinline__ MassSum wave_mass(const NodeMass &m)
+{
+    MassSum s{0, 0};
+    s.add(wave_sum_to_last(m.hi), wave_sum_to_last(m.lo));
+    return s;
+}
 
 // The value a lane's left (lane - 1) or right (lane + 1) neighbour holds,
 // through the wave-wide row shift of DPP (0 in the first and last lane).
@@ -224,7 +257,7 @@ struct DevParams {
     double k1k, k2_Tc;            // kappa (1 + kappa), kappa^2 / T_c
     double k1k_rsTc;              // kappa (1 + kappa) / sqrt(T_c)
     double R_cv12, a_cv12;        // R / (12 c_v), a / (12 c_v)
-    double mass_c, mass_q;        // mass sums: rounding constant and unit (mass_units)
+    double mass_c, mass_r, mass_q;  // mass sums: rounding constants and smallest unit (mass_units)
     // collision: (1 - s_e)/36, s_e/36, 6 (1 - s_e/2)/36, (1 - s_e/2) sig_e/36,
     // the same of s_zeta, (1 - s_q)/12, s_q/12, (1 - s_q/2)/12
     double ce_m, ce_r, ce_F, ce_Q, cz_m, cz_r, cz_F, cz_Q, cq_m, cq_r, cq_F;
@@ -258,7 +291,7 @@ struct Inst {
     DevParams P;
     void *f[2], *T[2];
     void *rho, *vx, *vy;
-    long long *mass_part;
+    MassSum *mass_part;
     double *hf_part;
     Scalars *sc;
     int nbxA, nbyA, nbxB, nbyB;
@@ -459,19 +492,26 @@ __device__ __forceinline__ double ordered_sum(const double *__restrict__ a_, int
     return s;
 }
 
-// Sum of n whole numbers by one block of NTH threads, valid in thread 0; the
-// loads are issued 8 at a time.  All threads of the block must call it.
+// Sum of n mass partials by one block of NTH threads, valid in thread 0; the
+// loads are issued 4 at a time.  All threads of the block must call it.
 template <int NTH>
-__device__ __forceinline__ MassSum mass_sum(const long long *__restrict__ a_, size_t n, MassSum *red /* [NTH / 64] */)
+__device__ __forceinline__ MassSum mass_sum(const MassSum *__restrict__ a_, size_t n, MassSum *red /* [NTH / 64] */)
 {
-    const gmem<long long> *__restrict__ a = (const gmem<long long> *)a_;
+    const gmem<MassSum> *__restrict__ a = (const gmem<MassSum> *)a_;
     MassSum s{0, 0};
-    for (size_t k = threadIdx.x; k < n; k += 8 * NTH) {
-        long long v[8];
+    for (size_t k = threadIdx.x; k < n; k += 4 * NTH) {
+        long long hi[4], lo[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = k + j * NTH < n ? a[k + j * NTH] : 0;
+        for (int j = 0; j < 4; ++j) {
+            const bool in = k + j * NTH < n;
+            hi[j] = in ? a[k + j * NTH].hi : 0;
+            lo[j] = in ? a[k + j * NTH].lo : 0;
+        }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) s.add(v[j]);
+        for (int j = 0; j < 4; ++j) {
+            s.hi += hi[j];
+            s.lo += lo[j];
+        }
     }
     s.hi = wave_sum_to_last(s.hi);
     s.lo = wave_sum_to_last(s.lo);
@@ -637,14 +677,14 @@ __device__ __forceinline__ void collide(const DevParams &P, const Moments &m, do
     f[8] = dm + cm;
 }
 
-// Mass that node row gy hands to the streamed state, in units of P.mass_q:
+// Mass that a node of row gy hands to the streamed state (mass_units):
 // each population counts once, except those that leave through a wall (0) and
 // those that arrive on a wall row, whose Zou-He partners are reconstructed
 // with the same sum (2).  The mass sums the populations before they are
 // rounded to the storage precision: in FP32 storage it then differs from the
 // stored mass by the rounding of the populations (relative ~1e-7 per node,
 // ~1e-10 over a lattice), far below what rho_ave moves the buoyancy by.
-__device__ __forceinline__ long long pushed_mass(const DevParams &P, int gy, const double f[9])
+__device__ __forceinline__ NodeMass pushed_mass(const DevParams &P, int gy, const double f[9])
 {
     const double up = f[2] + f[5] + f[6];
     const double dn = f[4] + f[7] + f[8];
@@ -655,14 +695,14 @@ __device__ __forceinline__ long long pushed_mass(const DevParams &P, int gy, con
         const double wd = gy == 0 ? 0.0 : (gy == 1 ? 2.0 : 1.0);
         mm = mid + (wu * up + wd * dn);
     }
-    return mass_units(P.mass_c, mm);
+    return mass_units(P.mass_c, P.mass_r, mm);
 }
 
 // Push streaming (Eq. (3)) of the post-collision populations of node
 // (gx, gy) into fout; populations leaving through a wall are dropped.  Returns
 // the mass handed on.
 template <typename S>
-__device__ __forceinline__ long long push_node(const DevParams &P, S *__restrict__ fout, size_t N, int gx, int gy,
+__device__ __forceinline__ NodeMass push_node(const DevParams &P, S *__restrict__ fout, size_t N, int gx, int gy,
                                                const double f[9])
 {
     constexpr unsigned sz = (unsigned)sizeof(S);
@@ -826,8 +866,8 @@ __device__ __forceinline__ void sample_heat_flux(const Inst &I, const S *__restr
 // ONE: the whole step of an isothermal lattice, whose temperature launch would
 // only reduce.  Nothing in a launch may then wait for another block of it, so
 // the bookkeeping runs one launch behind: every block adds up the mass
-// partials of the launch before (integers, I.rel launches since state sc->tA,
-// two halves of I.mass_part used in turn), block 0 samples the heat flux of
+// partials of the launch before (I.rel launches since state sc->tA, two halves
+// of I.mpart used in turn), block 0 samples the heat flux of
 // the launch's own input state, and flush_step ends the sequence.  rho and v
 // are not written.
 template <typename S, int TYA, int NWA, bool ONE = false>
@@ -928,12 +968,15 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 6 : 1) void k_lb(const Inst 
         Th = frozen ? S(0) : ld_at(Tin, o);
     }
     __shared__ MassSum red[ONE ? NWA : 1];
-    const size_t np = (size_t)nbx * P.ny;
+    const int np = nbx * nby;
     if constexpr (ONE) {
-        const gmem<long long> *part = (const gmem<long long> *)I.mass_part + par * np;
+        const gmem<MassSum> *part = (const gmem<MassSum> *)I.mpart + par * np;
         MassSum ms{0, 0};
         if (since)
-            for (size_t k = threadIdx.x; k < np; k += 64 * NWA) ms.add(part[k]);
+            for (int k = threadIdx.x; k < np; k += 64 * NWA) {
+                ms.hi += part[k].hi;
+                ms.lo += part[k].lo;
+            }
         ms.hi = wave_sum_to_last(ms.hi);
         ms.lo = wave_sum_to_last(ms.lo);
         if (lane == 63) red[wv] = ms;
@@ -954,12 +997,12 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 6 : 1) void k_lb(const Inst 
             rho_ave = ms.value(P.mass_q) / ((double)P.nx * (double)P.ny);
         }
 
-    long long mrow[IPW_A];
+    NodeMass mrow[IPW_A];
 #pragma unroll
     for (int m = 0; m < IPW_A; ++m) {
         const int r = 1 + wv + NWA * m;
         const int gy = gys[m];
-        mrow[m] = 0;
+        mrow[m] = {0, 0};
         if (!live[m] || lane < 1 || lane > TXA || x0 + lane - 1 >= P.nx) continue;
         constexpr unsigned sz = (unsigned)sizeof(S);
         const unsigned rowc = (unsigned)gy * (unsigned)P.nx, oc = (rowc + gxu) * sz;
@@ -976,7 +1019,7 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 6 : 1) void k_lb(const Inst 
             double mm = 0.0;
 #pragma unroll
             for (int a = 0; a < 9; ++a) mm += f[a];
-            mrow[m] = mass_units(P.mass_c, mm);
+            mrow[m] = mass_units(P.mass_c, P.mass_r, mm);
             continue;
         }
         double Fx, Fy, Q;
@@ -994,11 +1037,20 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 6 : 1) void k_lb(const Inst 
         collide(P, mo, rh, hx, hy, vx, vy, Fx, Fy, Q, s_nu, f);
         mrow[m] = push_node<S>(P, fout, N, gx, gy, f);
     }
-    // mass partials per lattice row and 62-column chunk
+    // mass partial of the tile
+    __shared__ MassSum tile_mass[NWA];
+    MassSum ms{0, 0};
 #pragma unroll
-    for (int m = 0; m < IPW_A; ++m) {
-        const long long v = wave_sum_to_last(mrow[m]);
-        if (live[m] && lane == 63) I.mass_part[(ONE ? (par ^ 1) * np : 0) + (size_t)gys[m] * nbx + bx] = v;
+    for (int m = 0; m < IPW_A; ++m)
+        if (live[m]) ms.add(wave_mass(mrow[m]));
+    if (lane == 63) tile_mass[wv] = ms;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        MassSum u{0, 0};
+#pragma unroll
+        for (int k = 0; k < NWA; ++k) u.add(tile_mass[k]);
+        if constexpr (ONE) I.mpart[(size_t)((par ^ 1) * np + tile)] = u;
+        else I.mass_part[tile] = u;
     }
 }
 
@@ -1113,7 +1165,7 @@ __global__ __launch_bounds__(64 * NWB) void k_thermal(const Inst *__restrict__ i
     __shared__ MassSum red[NWB];
     const long long t = sc->tB;
     if (blk == 0) {  // reduction of the LB launch's mass partials, first in the grid
-        const MassSum m = mass_sum<64 * NWB>(I.mass_part, (size_t)I.nbxA * P.ny, red);
+        const MassSum m = mass_sum<64 * NWB>(I.mass_part, (size_t)I.nbxA * I.nbyA, red);
         if (threadIdx.x == 0) {
             sc->rho_ave = m.value(P.mass_q) / ((double)P.nx * (double)P.ny);
             sc->tA = t + 1;

@@ -230,7 +230,7 @@ struct lbb_domain {
     void *f[2] = {nullptr, nullptr};
     void *T[2] = {nullptr, nullptr};
     void *rho = nullptr, *vx = nullptr, *vy = nullptr;
-    long long *mass_part = nullptr;
+    lbb::MassSum *mass_part = nullptr;
     double *hf_part = nullptr, *Tb_dev = nullptr;
     lbb::Scalars *sc = nullptr;
     int nbxA = 0, nbyA = 0, nbxB = 0, nbyB = 0;
@@ -374,7 +374,8 @@ void make_dev_params(const lbb_params &p, double Tc, double kap, lbb::DevParams 
     int e = 0;
     (void)std::frexp(8.0 / p.b, &e);  // 2^(e-1) <= 8/b < 2^e
     q.mass_c = std::ldexp(1.5, e);
-    q.mass_q = std::ldexp(1.0, e - 52);
+    q.mass_r = std::ldexp(1.5, e - 16);
+    q.mass_q = std::ldexp(1.0, e - 52 - 16);
 }
 
 uint64_t param_hash(const lbb_params &p)
@@ -442,12 +443,12 @@ int64_t step_blocks(const StepDims &l, const StepForm &f)
 }
 
 // Isothermal lattices step in one launch of k_lb (ONE, default tiles) where
-// every block can add up the mass partials (one per lattice row and LB tile
-// column) with at most eight loads a thread.  Eleven 160x60 FP64 lattices:
+// every block can add up the mass partials of the tiles with few loads a
+// thread: up to 2048 rows of tile columns, four of which make a tile.  Eleven 160x60 FP64 lattices:
 // 7.5 us per step against 12.0 with the temperature launch, which reduces in
 // 4.4 us.  Tuned shapes do not matter to it: 248x512 FP64 8.5 us, against 9.8
 // in two launches of the fastest shapes.
-constexpr int kOneMaxPartials = 2048;
+constexpr int kOneMaxRows = 2048;
 
 // One block of a lattice samples the heat flux of its bottom row in every
 // step, a chunk of TXB columns a wave; on wide lattices of few rows it is the
@@ -466,7 +467,7 @@ StepForm step_form(const std::vector<StepDims> &ls, int precision, int mode, int
     StepForm f;
     if (mode == LBB_ISOTHERMAL) {
         for (const StepDims &l : ls)
-            if ((int64_t)((l.nx + lbb::TXA - 1) / lbb::TXA) * l.ny > kOneMaxPartials ||
+            if ((int64_t)((l.nx + lbb::TXA - 1) / lbb::TXA) * l.ny > kOneMaxRows ||
                 heat_flux_chunks(l.nx) > kOneMaxChunks)
                 return f;
         f.height = lbb::kShapeA[0].ty;
@@ -700,7 +701,7 @@ FlushSize flush_size(const std::vector<lbb_domain *> &doms, const StepForm &f)
     FlushSize m;
     for (const lbb_domain *d : doms) {
         m.chunks = std::max(m.chunks, d->nbxB);
-        m.partials = std::max(m.partials, f.lb ? (int64_t)d->nbxA * d->p.ny : step_blocks({d->p.nx, d->p.ny}, f));
+        m.partials = std::max(m.partials, step_blocks({d->p.nx, d->p.ny}, f));
     }
     return m;
 }
@@ -1420,12 +1421,12 @@ static int init_domain(const lbb_params *pin, const double *T_bottom, const doub
     // A batch may step a lattice in one launch that alone takes two.
     const StepDims lat{p.nx, p.ny};
     const bool coupled = p.thermal_mode == LBB_COUPLED;
-    const size_t np = coupled ? (size_t)step_max_blocks(lat, p.precision, p.thermal_mode, prop.multiProcessorCount) : 0;
+    const size_t np = coupled ? (size_t)step_max_blocks(lat, p.precision, p.thermal_mode, prop.multiProcessorCount)
+                              : (size_t)step_blocks(lat, d->form);
     struct { void **ptr; size_t bytes; } const small[] = {
-        // mass partials: one per lattice row and LB tile column (also holds the
-        // per-block partials of the set-up mass kernel, fewer)
-        {(void **)&d->mass_part,
-         (size_t)std::max(mbA, (d->form.lb ? 2 : 1) * d->nbxA * p.ny) * sizeof(double)},
+        // mass partials: one per LB tile (also holds the partials of the set-up
+        // mass kernel, a double a tile)
+        {(void **)&d->mass_part, (size_t)mbA * sizeof(lbb::MassSum)},
         {(void **)&d->hf_part, (size_t)d->nbxB * sizeof(double)},
         {(void **)&d->Tb_dev, (size_t)p.nx * sizeof(double)},
         {(void **)&d->sc, sizeof(lbb::Scalars)},
@@ -2661,7 +2662,10 @@ NoallocLayout noalloc_layout(int nx, int ny, int precision, int mode, int ncu)
     L.nbxB = (nx + lbb::TXB - 1) / lbb::TXB;
     L.nbyB = (ny + lbb::kShapeB[0].ty - 1) / lbb::kShapeB[0].ty;
     const size_t nA = (size_t)L.nbxA * L.nbyA + 1, nB = (size_t)L.nbxB * L.nbyB + 1;
-    const size_t nmass = std::max((size_t)L.nbxA * ny, (size_t)L.nbxA * L.nbyA);
+    // room for the mass partials: one per LB tile takes no more (ny >= 3), but
+    // the need that a caller may reckon with stays
+    const size_t nmass = (size_t)L.nbxA * ny;
+    static_assert(sizeof(lbb::MassSum) <= 2 * sizeof(double) && lbb::kShapeA[0].ty == 4, "");
     size_t o = 0;
     L.inst = o;
     o += up(sizeof(lbb::Inst));
@@ -2826,7 +2830,7 @@ extern "C" int lbb_step_noalloc(const lbb_params *pin, void *const f[2], void *c
     I.rho = rho;
     I.vx = vx;
     I.vy = vy;
-    I.mass_part = reinterpret_cast<long long *>(base + L.mass);
+    I.mass_part = reinterpret_cast<lbb::MassSum *>(base + L.mass);
     I.hf_part = reinterpret_cast<double *>(base + L.hf);
     I.sc = reinterpret_cast<lbb::Scalars *>(base + L.sc);
     I.nbxA = L.nbxA;

@@ -166,7 +166,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
         if (!inl[m] || r < 1 || r >= H - 1) continue;
         const bool wall_row = walls && (gy == 0 || gy == P.ny - 1);
         const bool live = r >= HF && r < HF + TY && y0 + r - HF < P.ny;
-        long long units = 0;
+        NodeMass units{0, 0};
         if (lane >= 1 && lane < 63) {
             double f[9];
             const double rh = rho[m];
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
                 units = push_node<S>(P, fout, N, gx, gy, f);
             }
         }
-        if (live) mass.add(wave_sum_to_last(units));
+        if (live) mass.add(wave_mass(units));
     }
     if (lane == 63) red[wv] = mass;
     __syncthreads();
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(64 * WB, sizeof(S) == 4 ? 3 : 2) void k_march(const
     C t0[6] = {}, acc[4] = {};
     SlopeCoef<C> kf[4] = {};
     double rc = 1.0;  // density of row j - 1
-    long long units = 0;
+    NodeMass units{0, 0};
     const C Tref = (C)P.T_ref;
     const C chi6 = (C)(P.chi * (1.0 / 6.0));
 
@@ -414,10 +414,11 @@ __global__ __launch_bounds__(64 * WB, sizeof(S) == 4 ? 3 : 2) void k_march(const
             if (bot || top) xu[K2] = xv[K2] = C(0);
             if (c >= y0 && c < y1) {
                 collide(P, mo, rc, hx, hy, vx, vy, Fx, Fy, Q, s_nu, f);
-                const long long m = pushed_mass(P, gy, f);
+                const NodeMass m = pushed_mass(P, gy, f);
                 if (mine) {
                     // push streaming as push_node
-                    units += m;
+                    units.hi += m.hi;
+                    units.lo += m.lo;
                     size_t n = N;
                     unsigned vg = og, ve = oe, vw = ow;
                     asm volatile("" : "+s"(n), "+v"(vg), "+v"(ve), "+v"(vw));
@@ -489,7 +490,7 @@ __global__ __launch_bounds__(64 * WB, sizeof(S) == 4 ? 3 : 2) void k_march(const
         }
     }
     MassSum m{0, 0};
-    m.add(units);
+    m.add(units.hi, units.lo);
     m.hi = wave_sum_to_last(m.hi);
     m.lo = wave_sum_to_last(m.lo);
     if (lane == 63) red[wv] = m;
@@ -538,16 +539,10 @@ __device__ __forceinline__ void flush_step(const Inst &I, int cf, int cT, bool r
         return;
     }
     MassSum s{0, 0};
-    if (I.P.mode == MODE_ISOTHERMAL) {  // the partials of k_lb
-        const size_t np = (size_t)I.nbxA * I.P.ny;
-        const gmem<long long> *part = (const gmem<long long> *)I.mass_part + par * np;
-        for (size_t k = threadIdx.x; k < np; k += NTH) s.add(part[k]);
-    } else {
-        const gmem<MassSum> *part = (const gmem<MassSum> *)I.mpart + (size_t)par * I.npF;
-        for (int k = threadIdx.x; k < I.npF; k += NTH) {
-            s.hi += part[k].hi;
-            s.lo += part[k].lo;
-        }
+    const gmem<MassSum> *mp = (const gmem<MassSum> *)I.mpart + (size_t)par * I.npF;
+    for (int k = threadIdx.x; k < I.npF; k += NTH) {
+        s.hi += mp[k].hi;
+        s.lo += mp[k].lo;
     }
     s.hi = wave_sum_to_last(s.hi);
     s.lo = wave_sum_to_last(s.lo);
