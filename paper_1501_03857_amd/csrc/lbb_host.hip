@@ -942,7 +942,12 @@ int read_impl(lbb_domain *d, double *rho, double *ux, double *uy, double *T, dou
 
 // bytes of a domain's pinned memory: scalars, local heat flux
 static size_t host_bytes(int nx) { return (sizeof(lbb::Scalars) + (size_t)nx * sizeof(double) + 255) & ~(size_t)255; }
-static int init_domain(const lbb_params *pin, const double *T_bottom, const double *rho0, void *host, lbb_domain **out);
+// Pinned memory that domains share, allocated when the first of them needs it.
+struct PinnedPool {
+    char *base = nullptr;
+    size_t bytes = 0, used = 0;
+};
+static int init_domain(const lbb_params *pin, const double *T_bottom, const double *rho0, PinnedPool *pool, lbb_domain **out);
 
 extern "C" {
 
@@ -1334,8 +1339,8 @@ int lbb_info(lbb_domain *d, int64_t *t, int32_t *nx, int32_t *ny, int64_t *devic
 
 // ---- batched lattices --------------------------------------------------
 
-// lbb_init_domain; `host`: pinned memory of host_bytes(nx) that outlives the domain, or null (its own).
-static int init_domain(const lbb_params *pin, const double *T_bottom, const double *rho0, void *host, lbb_domain **out)
+// lbb_init_domain; `pool`: pinned memory with host_bytes(nx) left that outlives the domain, or null (its own).
+static int init_domain(const lbb_params *pin, const double *T_bottom, const double *rho0, PinnedPool *pool, lbb_domain **out)
 {
     if (!out) return fail(LBB_EINVAL, "out is NULL");
     *out = nullptr;
@@ -1407,11 +1412,17 @@ static int init_domain(const lbb_params *pin, const double *T_bottom, const doub
     };
     const size_t es = d->esz;
     bool ok = hipStreamCreateWithFlags(&d->stream, hipStreamNonBlocking) == hipSuccess;
-    d->own_host = !host;
-    d->host = static_cast<lbb::Scalars *>(host);
-    if (!host)
-        ok = ok && hipHostMalloc((void **)&d->host, host_bytes(p.nx), hipHostMallocMapped | hipHostMallocPortable) ==
-                       hipSuccess;
+    d->own_host = !pool;
+    const auto pinned = [](void **ptr, size_t bytes) {
+        return hipHostMalloc(ptr, bytes, hipHostMallocMapped | hipHostMallocPortable) == hipSuccess;
+    };
+    if (!pool) {
+        ok = ok && pinned((void **)&d->host, host_bytes(p.nx));
+    } else {
+        ok = ok && (pool->base || pinned((void **)&pool->base, pool->bytes));
+        if (ok) d->host = reinterpret_cast<lbb::Scalars *>(pool->base + pool->used);
+        pool->used += host_bytes(p.nx);
+    }
     if (ok) d->host_q = reinterpret_cast<double *>(d->host + 1);
     ok = ok && alloc(&d->f[0], 9 * N * es) && alloc(&d->f[1], 9 * N * es);
     ok = ok && alloc(&d->T[0], N * es) && alloc(&d->T[1], N * es);
@@ -1488,7 +1499,7 @@ struct lbb_batch {
     void *adj_mem = nullptr;             // adjoint workspace, kept between calls
     size_t adj_bytes = 0;
     int64_t held = 0;                    // device bytes held against the budget
-    char *host = nullptr;                // the members' pinned memory, one allocation
+    PinnedPool pinned;                   // the members' pinned memory
 };
 
 static void batch_release(lbb_batch *b)
@@ -1502,7 +1513,7 @@ static void batch_release(lbb_batch *b)
         if (q) (void)hipFree(q);
     if (b->stream) (void)hipStreamDestroy(b->stream);
     for (lbb_domain *d : b->doms) release(d);
-    if (b->host) (void)hipHostFree(b->host);  // after the members that write to it
+    if (b->pinned.base) (void)hipHostFree(b->pinned.base);  // after the members that write to it
     delete b;
 }
 
@@ -1616,17 +1627,11 @@ extern "C" int lbb_batch_init(const lbb_params *ps, int n, const double *const *
     if (!b) return fail(LBB_ENOMEM, "host allocation failed");
     b->precision = ps[0].precision;
     b->mode = ps[0].thermal_mode;
-    size_t pinned = 0, at = 0;
-    for (int i = 0; i < n; ++i) pinned += host_bytes(std::max(ps[i].nx, 0));
-    if (hipHostMalloc((void **)&b->host, pinned, hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) {
-        (void)hipGetLastError();
-        batch_release(b);
-        return fail(LBB_ENOMEM, "host allocation failed");
-    }
+    for (int i = 0; i < n; ++i)  // a member that is not valid ends the batch below, at its turn
+        if (validate(&ps[i]) == LBB_OK) b->pinned.bytes += host_bytes(ps[i].nx);
     for (int i = 0; i < n; ++i) {
         lbb_domain *d = nullptr;
-        int rc = init_domain(&ps[i], T_bottoms ? T_bottoms[i] : nullptr, rho0s ? rho0s[i] : nullptr, b->host + at, &d);
-        at += host_bytes(std::max(ps[i].nx, 0));
+        int rc = init_domain(&ps[i], T_bottoms ? T_bottoms[i] : nullptr, rho0s ? rho0s[i] : nullptr, &b->pinned, &d);
         if (rc) {
             std::string m = "batch member " + std::to_string(i) + ": " + g_err;
             batch_release(b);
