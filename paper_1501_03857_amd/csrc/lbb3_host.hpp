@@ -415,7 +415,10 @@ int lbb3_read_fields(lbb3_domain *d, double *rho, double *u, double *T, double *
     // staging for the fields asked for only
     const size_t n = d->g.n;
     const size_t need = n * ((rho ? 1 : 0) + (u ? 3 : 0) + (T ? 1 : 0) + (f ? 19 : 0));
-    if (!need) return LBB_OK;
+    if (!need) {  // waits all the same
+        LBB_HIP(hipStreamSynchronize(d->stream));
+        return LBB_OK;
+    }
     double *buf = nullptr;
     LBB_HIP(hipMalloc(&buf, need * sizeof(double)));
     double *at = buf;

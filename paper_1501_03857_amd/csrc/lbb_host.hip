@@ -914,9 +914,8 @@ int read_impl(lbb_domain *d, double *rho, double *ux, double *uy, double *T, dou
     struct { double *dst, *src; size_t n; } cp[] = {{rho, nullptr, N}, {ux, nullptr, N}, {uy, nullptr, N}, {T, nullptr, N}, {f, nullptr, 9 * N}};
     size_t need = 0;
     for (auto &c : cp) need += c.dst ? c.n : 0;
-    if (!need) return LBB_OK;
     double *buf = nullptr;
-    LBB_HIP(hipMalloc(&buf, need * sizeof(double)));
+    if (need) LBB_HIP(hipMalloc(&buf, need * sizeof(double)));  // a read of nothing still waits and checks the state
     double *at = buf;
     for (auto &c : cp)
         if (c.dst) {
