@@ -134,15 +134,15 @@ void enqueue_step3(lbb3_domain *d)
             hipLaunchKernelGGL((k3_pair<S, NWP[1], false>), dim3(tp[1].ntx * tp[1].nty * tp[1].ntz), dim3(64 * NWP[1]), 0,
                                d->stream, d->dp, d->g, tp[1], T0, Ts0, acc, coef, rho, v, T1, d->sc);
         } else {
-        const Tiles3 tl = stage0_tiles(d->g, (sizeof(S) == 4 ? 16 : 2) * d->ncu);
-        hipLaunchKernelGGL(k3_stage0<S>, dim3(tl.ntx * tl.nty * tl.ntz), dim3(NSZ), 0, d->stream, d->dp, d->g, tl, T0,
-                           Ts0, acc, coef, rho, v, v + n, v + 2 * n);
-        hipLaunchKernelGGL((k3_stage<S, 1>), dim3(d->nb), dim3(NT3), 0, d->stream, d->dp, d->g, T0, Ts0, Ts1, acc,
-                           coef, d->sc);
-        hipLaunchKernelGGL((k3_stage<S, 2>), dim3(d->nb), dim3(NT3), 0, d->stream, d->dp, d->g, T0, Ts1, Ts0, acc,
-                           coef, d->sc);
-        hipLaunchKernelGGL((k3_stage<S, 3>), dim3(d->nb), dim3(NT3), 0, d->stream, d->dp, d->g, T0, Ts0, T1, acc,
-                           coef, d->sc);
+            const Tiles3 tl = stage0_tiles(d->g, (sizeof(S) == 4 ? 16 : 2) * d->ncu);
+            hipLaunchKernelGGL(k3_stage0<S>, dim3(tl.ntx * tl.nty * tl.ntz), dim3(NSZ), 0, d->stream, d->dp, d->g, tl, T0,
+                               Ts0, acc, coef, rho, v, v + n, v + 2 * n);
+            hipLaunchKernelGGL((k3_stage<S, 1>), dim3(d->nb), dim3(NT3), 0, d->stream, d->dp, d->g, T0, Ts0, Ts1, acc,
+                               coef, d->sc);
+            hipLaunchKernelGGL((k3_stage<S, 2>), dim3(d->nb), dim3(NT3), 0, d->stream, d->dp, d->g, T0, Ts1, Ts0, acc,
+                               coef, d->sc);
+            hipLaunchKernelGGL((k3_stage<S, 3>), dim3(d->nb), dim3(NT3), 0, d->stream, d->dp, d->g, T0, Ts0, T1, acc,
+                               coef, d->sc);
         }
     }
     if (d->dp.mode != lbb::MODE_THERMAL_ONLY) d->cf ^= 1;

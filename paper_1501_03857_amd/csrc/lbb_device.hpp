@@ -253,8 +253,8 @@ struct DevParams {
     double inv_Tc, two_over_G;
     // uniform factors of the thermal step, formed on the host (the GPU has no
     // scalar FP64 unit, so each wave would otherwise divide in its vector ALU)
-    double R_cv, a_cv, inv_cv;    // R / c_v, a / c_v, 1 / c_v
-    double k1k, k2_Tc;            // kappa (1 + kappa), kappa^2 / T_c
+    double R_cv, a_cv;            // R / c_v, a / c_v
+    double k2_Tc;                 // kappa^2 / T_c
     double k1k_rsTc;              // kappa (1 + kappa) / sqrt(T_c)
     double R_cv12, a_cv12;        // R / (12 c_v), a / (12 c_v)
     double mass_c, mass_r, mass_q;  // mass sums: rounding constants and smallest unit (mass_units)

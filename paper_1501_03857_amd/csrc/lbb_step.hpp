@@ -481,8 +481,10 @@ __global__ __launch_bounds__(64 * WB, sizeof(S) == 4 ? 3 : 2) void k_march(const
 
     if (y0 < y1) {
         load(y0 - HF, fr[0], Tr[0]);
-        // whole turns of the three register names; rows past y1 + HF - 1 do no
-        // harm (the host takes heights for which there are none)
+        // whole turns of the three register names.  Heights are 2 modulo 3, so
+        // full strips end with row y1 + HF - 1; a ragged last strip may run two
+        // rows past it and load one more, which are never used, and wrap once
+        // into a periodic lattice of at least 8 rows (the host asks for 32).
         for (int j = y0 - HF; j < y1 + HF; j += 3) {
             body(std::integral_constant<int, 0>{}, j);
             body(std::integral_constant<int, 1>{}, j + 1);
