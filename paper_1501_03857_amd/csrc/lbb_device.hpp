@@ -284,6 +284,15 @@ struct Scalars {
     unsigned int pad;
 };
 
+// What a read-back of state `step` found wrong, in host memory: the host's copy
+// of the scalars may be of an earlier time than the read-back.  Plain stores
+// (host memory need not take atomics); every thread that finds something stores
+// the same.
+struct ReadFlags {
+    unsigned long long step;
+    unsigned int rho, psi;
+};
+
 // One lattice of a launch: its parameters, buffers and place in the grid.
 // The LB and thermal launches cover any number of lattices of any sizes; a
 // block finds its lattice through a block -> lattice table.
@@ -736,11 +745,11 @@ __device__ __forceinline__ NodeMass push_node(const DevParams &P, S *__restrict_
 __constant__ const int kEX[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
 __constant__ const int kEY[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
 
-// Phase 1 shared by the LB step and the read-back: rho and psi of the tile
-// and a halo of one into LDS.  Nodes beyond a wall get psi = 0 (never read).
+// Phase 1 of the read-back: rho and psi of the tile and a halo of one into
+// LDS, checked.  Nodes beyond a wall get psi = 0 (never read).
 template <typename S, int TX, int TY>
 __device__ __forceinline__ void tile_psi(const DevParams &P, const S *__restrict__ fin, const S *__restrict__ Tin,
-                                         int x0, int y0, double *psi_s, Scalars *sc, long long t)
+                                         int x0, int y0, double *psi_s, Scalars *sc, long long t, ReadFlags *flags)
 {
     constexpr int W = TX + 2, H = TY + 2;
     const size_t N = (size_t)P.nx * P.ny;
@@ -765,8 +774,13 @@ __device__ __forceinline__ void tile_psi(const DevParams &P, const S *__restrict
         }
         const double T = P.T_ref + (double)Tin[c];
         const double psi = pseudopotential(P, rho, T);
-        if (!(rho > 0.0) || !(rho < 1e300)) flag_error(sc, t, ERR_RHO);
-        if (!(psi >= 0.0) || !(psi < 1e300)) flag_error(sc, t, ERR_PSI);
+        const bool bad_rho = !(rho > 0.0) || !(rho < 1e300), bad_psi = !(psi >= 0.0) || !(psi < 1e300);
+        if (bad_rho || bad_psi) {
+            flag_error(sc, t, (bad_rho ? ERR_RHO : 0) | (bad_psi ? ERR_PSI : 0));
+            flags->step = (unsigned long long)t;
+            if (bad_rho) flags->rho = 1;
+            if (bad_psi) flags->psi = 1;
+        }
         psi_s[k] = psi;
     }
 }
@@ -1386,14 +1400,14 @@ template <typename S>
 __global__ __launch_bounds__(NT) void k_read(DevParams P, const S *__restrict__ fin, const S *__restrict__ Tin,
                                              double *__restrict__ rho_o, double *__restrict__ ux_o,
                                              double *__restrict__ uy_o, double *__restrict__ T_o,
-                                             double *__restrict__ f_o, Scalars *sc, int nbx)
+                                             double *__restrict__ f_o, Scalars *sc, ReadFlags *flags, int nbx)
 {
     __shared__ double psi_s[(TXR + 2) * (TYR + 2)];
     const int bx = blockIdx.x % nbx, by = blockIdx.x / nbx;
     const int x0 = bx * TXR, y0 = by * TYR;
     const size_t N = (size_t)P.nx * P.ny;
     const bool frozen = P.mode == MODE_THERMAL_ONLY;
-    if (!frozen) tile_psi<S, TXR, TYR>(P, fin, Tin, x0, y0, psi_s, sc, sc->tA);
+    if (!frozen) tile_psi<S, TXR, TYR>(P, fin, Tin, x0, y0, psi_s, sc, sc->tA, flags);
     __syncthreads();
     const double rho_ave = sc->rho_ave;
     const int tx = threadIdx.x % TXR;

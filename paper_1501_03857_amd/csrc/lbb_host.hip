@@ -253,9 +253,7 @@ struct lbb_domain {
     bool own_host = false;               // else a slice of its batch's
     bool fresh = false;
     hipStream_t flushed = nullptr;
-    // A read-back since that flush may have flagged the state in the device's
-    // scalars only; `read_dev`: one that may not have run yet.
-    bool read = false, read_dev = false;
+    lbb::ReadFlags *host_read = nullptr;  // what read-backs found, pinned too
     // Work of the domain is part of a caller's graph, which may run at any
     // time from then on: the host copy is no longer used.
     bool recorded = false;
@@ -663,7 +661,6 @@ int enqueue_steps(lbb_domain *d, int64_t n)
     LBB_HIP(hipGetLastError());
     d->fresh = !d->recorded;
     d->flushed = d->stream;
-    d->read = d->read_dev = false;  // earlier read-backs ran on this stream
     return LBB_OK;
 }
 
@@ -697,13 +694,15 @@ int read_scalars(lbb_domain *d, lbb::Scalars *s, hipStream_t waited = nullptr)
 
 int check_errors(lbb_domain *d, hipStream_t waited = nullptr)
 {
-    if (d->read || d->read_dev) d->fresh = false;
     lbb::Scalars s;
-    int rc = read_scalars(d, &s, waited);
+    const int rc = read_scalars(d, &s, waited);
     if (rc) return rc;
-    rc = report_errors(d, s);
-    if (!rc) d->read = d->read_dev = false;  // over, and nothing flagged
-    return rc;
+    const lbb::ReadFlags r = *d->host_read;  // read-backs ran on the domain's stream, waited for above
+    if (r.rho || r.psi) {
+        s.err_step = std::min(s.err_step, r.step);
+        s.err_code |= (r.rho ? lbb::ERR_RHO : 0) | (r.psi ? lbb::ERR_PSI : 0);
+    }
+    return report_errors(d, s);
 }
 
 // Recompute rho_ave and the heat-flux partials from the current state.
@@ -758,6 +757,7 @@ int set_state(lbb_domain *d, const double *rho, const double *ux, const double *
             rc = fail(LBB_EDEVICE, "set-up kernels failed");
             break;
         }
+        *d->host_read = lbb::ReadFlags{};  // of the state before
     } while (0);
     (void)hipFree(buf);
     if (rc) return rc;
@@ -799,10 +799,9 @@ int read_impl(lbb_domain *d, double *rho, double *ux, double *uy, double *T, dou
             at += c.n;
         }
     const int nbxR = (d->p.nx + lbb::TXR - 1) / lbb::TXR, nbyR = (d->p.ny + lbb::TYR - 1) / lbb::TYR;
-    d->read = true;
     hipLaunchKernelGGL(lbb::k_read<S>, dim3(nbxR * nbyR), dim3(lbb::NT), 0, d->stream, d->dp,
                        static_cast<const S *>(d->f[d->cf]), static_cast<const S *>(d->T[d->cT]), cp[0].src, cp[1].src,
-                       cp[2].src, cp[3].src, cp[4].src, d->sc, nbxR);
+                       cp[2].src, cp[3].src, cp[4].src, d->sc, d->host_read, nbxR);
     int rc = LBB_OK;
     if (hipGetLastError() != hipSuccess) rc = fail(LBB_EDEVICE, "read-back kernel failed");
     for (auto &c : cp)
@@ -815,8 +814,11 @@ int read_impl(lbb_domain *d, double *rho, double *ux, double *uy, double *T, dou
 
 }  // namespace
 
-// bytes of a domain's pinned memory: scalars, local heat flux
-static size_t host_bytes(int nx) { return (sizeof(lbb::Scalars) + (size_t)nx * sizeof(double) + 255) & ~(size_t)255; }
+// bytes of a domain's pinned memory: scalars, read-back flags, local heat flux
+static size_t host_bytes(int nx)
+{
+    return (sizeof(lbb::Scalars) + sizeof(lbb::ReadFlags) + (size_t)nx * sizeof(double) + 255) & ~(size_t)255;
+}
 // Pinned memory that domains share, allocated when the first of them needs it.
 struct PinnedPool {
     char *base = nullptr;
@@ -993,17 +995,16 @@ int lbb_read_fields_dev(lbb_domain *d, double *rho, double *ux, double *uy, doub
             return fail(LBB_EDEVICE, std::string("read-back to device buffers: ") + hipGetErrorString(e0));
     }
     const int nbxR = (d->p.nx + lbb::TXR - 1) / lbb::TXR, nbyR = (d->p.ny + lbb::TYR - 1) / lbb::TYR;
-    d->read_dev = true;
     d->recorded = d->recorded || capturing(d->stream);
     if (d->recorded) d->fresh = false;
     if (d->p.precision == LBB_FP64)
         hipLaunchKernelGGL(lbb::k_read<double>, dim3(nbxR * nbyR), dim3(lbb::NT), 0, d->stream, d->dp,
                            static_cast<const double *>(d->f[d->cf]), static_cast<const double *>(d->T[d->cT]), rho,
-                           ux, uy, T, f, d->sc, nbxR);
+                           ux, uy, T, f, d->sc, d->host_read, nbxR);
     else
         hipLaunchKernelGGL(lbb::k_read<float>, dim3(nbxR * nbyR), dim3(lbb::NT), 0, d->stream, d->dp,
                            static_cast<const float *>(d->f[d->cf]), static_cast<const float *>(d->T[d->cT]), rho,
-                           ux, uy, T, f, d->sc, nbxR);
+                           ux, uy, T, f, d->sc, d->host_read, nbxR);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
         // and the caller's later work on its stream waits for the read
@@ -1185,6 +1186,7 @@ int lbb_load_state(lbb_domain *d, const void *buf, size_t len)
     LBB_HIP(hipMemcpyAsync(d->sc, &s, sizeof s, hipMemcpyHostToDevice, d->stream));
     LBB_HIP(hipMemcpyAsync(d->hf_part, p, d->nbxB * sizeof(double), hipMemcpyHostToDevice, d->stream));
     LBB_HIP(hipStreamSynchronize(d->stream));
+    *d->host_read = lbb::ReadFlags{};  // of the state before
     d->Tb = Tb;
     LBB_HIP(hipMemcpy(d->Tb_dev, Tb.data(), d->p.nx * sizeof(double), hipMemcpyHostToDevice));
     d->cf = d->cT = 0;
@@ -1298,7 +1300,11 @@ static int init_domain(const lbb_params *pin, const double *T_bottom, const doub
         if (ok) d->host = reinterpret_cast<lbb::Scalars *>(pool->base + pool->used);
         pool->used += host_bytes(p.nx);
     }
-    if (ok) d->host_q = reinterpret_cast<double *>(d->host + 1);
+    if (ok) {
+        d->host_read = reinterpret_cast<lbb::ReadFlags *>(d->host + 1);
+        *d->host_read = lbb::ReadFlags{};
+        d->host_q = reinterpret_cast<double *>(d->host_read + 1);
+    }
     ok = ok && alloc(&d->f[0], 9 * N * es) && alloc(&d->f[1], 9 * N * es);
     ok = ok && alloc(&d->T[0], N * es) && alloc(&d->T[1], N * es);
     ok = ok && alloc(&d->rho, N * es) && alloc(&d->vx, N * es) && alloc(&d->vy, N * es);
@@ -1589,7 +1595,6 @@ extern "C" int lbb_batch_step_async(lbb_batch *b, int64_t n)
         d->cT = b->cT;
         d->fresh = !d->recorded;
         d->flushed = b->stream;
-        d->read = false;  // read-backs to host memory were over before
     }
     return LBB_OK;
 }

@@ -109,3 +109,35 @@ def test_a_member_read_that_finds_an_invalid_state_is_reported_by_its_batch():
         with pytest.raises(L.LbbError) as e:
             b.sync()
         assert e.value.code == L.LBB_ENONFINITE and "member 1" in str(e.value)
+
+
+@pytest.mark.parametrize("recover", ["set_fields", "load"])
+def test_a_new_state_clears_what_a_read_found(recover):
+    _say("recovery after a read that found an invalid state", recover)
+    d = L.Domain(_hot(), rho0=np.full((8, 16), 6.0))
+    blob = d.save()
+    _invalid(d)
+    d.step(0)
+    d.fields()
+    if recover == "load":
+        d.load(blob)
+    else:
+        d.set_fields(np.full((8, 16), 6.0))
+    d.step(3)
+    d.fields()
+    d.sync()
+
+
+def test_batch_reports_a_member_read_into_device_memory():
+    import torch
+
+    _say("batch sync after a member's device read")
+    b = L.Batch([_hot(), _hot()], None, [np.full((8, 16), 6.0)] * 2)
+    _invalid(b.domain(1))
+    b.step(0)
+    out = torch.empty((2, 8, 16), dtype=torch.float64, device="cuda")
+    for i in (0, 1):
+        b.domain(i).read_into(rho=out[i].data_ptr(), stream=torch.cuda.current_stream().cuda_stream)
+    with pytest.raises(L.LbbError) as e:
+        b.sync()
+    assert e.value.code == L.LBB_ENONFINITE and "member 1" in str(e.value)
