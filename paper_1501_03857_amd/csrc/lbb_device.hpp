@@ -128,6 +128,11 @@ __device__ __forceinline__ float stage_sqrt(float x) { return __builtin_amdgcn_s
 struct NodeMass {
     long long hi;
     int lo;
+    __device__ __forceinline__ void add(const NodeMass &o)  // of some hundred nodes at most
+    {
+        hi += o.hi;
+        lo += o.lo;
+    }
 };
 __device__ __forceinline__ NodeMass mass_units(const double mass_c, const double mass_r, double m)
 {
@@ -195,7 +200,7 @@ struct MassSum {
     }
 };
 
-// Mass of a wave's nodes, one a lane, valid in lane 63.
+// Mass that the lanes of a wave hold, valid in lane 63.
 __device__ __forceinline__ MassSum wave_mass(const NodeMass &m)
 {
     MassSum s{0, 0};
@@ -1011,12 +1016,11 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 6 : 1) void k_lb(const Inst 
             rho_ave = ms.value(P.mass_q) / ((double)P.nx * (double)P.ny);
         }
 
-    NodeMass mrow[IPW_A];
+    NodeMass units{0, 0};  // of the wave's rows
 #pragma unroll
     for (int m = 0; m < IPW_A; ++m) {
         const int r = 1 + wv + NWA * m;
         const int gy = gys[m];
-        mrow[m] = {0, 0};
         if (!live[m] || lane < 1 || lane > TXA || x0 + lane - 1 >= P.nx) continue;
         constexpr unsigned sz = (unsigned)sizeof(S);
         const unsigned rowc = (unsigned)gy * (unsigned)P.nx, oc = (rowc + gxu) * sz;
@@ -1033,7 +1037,7 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 6 : 1) void k_lb(const Inst 
             double mm = 0.0;
 #pragma unroll
             for (int a = 0; a < 9; ++a) mm += f[a];
-            mrow[m] = mass_units(P.mass_c, P.mass_r, mm);
+            units.add(mass_units(P.mass_c, P.mass_r, mm));
             continue;
         }
         double Fx, Fy, Q;
@@ -1049,14 +1053,11 @@ __global__ __launch_bounds__(64 * NWA, TYA == NWA ? 6 : 1) void k_lb(const Inst 
             st_at(vy_o, oc, wall_row ? S(0) : S(vy));
         }
         collide(P, mo, rh, hx, hy, vx, vy, Fx, Fy, Q, s_nu, f);
-        mrow[m] = push_node<S>(P, fout, N, gx, gy, f);
+        units.add(push_node<S>(P, fout, N, gx, gy, f));
     }
     // mass partial of the tile
     __shared__ MassSum tile_mass[NWA];
-    MassSum ms{0, 0};
-#pragma unroll
-    for (int m = 0; m < IPW_A; ++m)
-        if (live[m]) ms.add(wave_mass(mrow[m]));
+    const MassSum ms = wave_mass(units);
     if (lane == 63) tile_mass[wv] = ms;
     __syncthreads();
     if (threadIdx.x == 0) {

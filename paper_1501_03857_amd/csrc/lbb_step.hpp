@@ -159,14 +159,13 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
 
     // phase 2: force and velocity on the region shrunk by one node; collision
     // and streaming of the interior nodes
-    MassSum mass{0, 0};
+    NodeMass units{0, 0};  // of the wave's rows
 #pragma unroll
     for (int m = 0; m < RPW; ++m) {
         const int r = wv + NW * m, gy = gys[m];
         if (!inl[m] || r < 1 || r >= H - 1) continue;
         const bool wall_row = walls && (gy == 0 || gy == P.ny - 1);
         const bool live = r >= HF && r < HF + TY && y0 + r - HF < P.ny;
-        NodeMass units{0, 0};
         if (lane >= 1 && lane < 63) {
             double f[9];
             const double rh = rho[m];
@@ -189,11 +188,11 @@ __global__ __launch_bounds__(64 * NW, 4) void k_step(const Inst *__restrict__ in
                     st_at(static_cast<S *>(I.vy), oc, vys);
                 }
                 collide(P, mo, rh, hx, hy, vx, vy, Fx, Fy, Q, s_nu, f);
-                units = push_node<S>(P, fout, N, gx, gy, f);
+                units.add(push_node<S>(P, fout, N, gx, gy, f));
             }
         }
-        if (live) mass.add(wave_mass(units));
     }
+    const MassSum mass = wave_mass(units);
     if (lane == 63) red[wv] = mass;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -417,8 +416,7 @@ __global__ __launch_bounds__(64 * WB, sizeof(S) == 4 ? 3 : 2) void k_march(const
                 const NodeMass m = pushed_mass(P, gy, f);
                 if (mine) {
                     // push streaming as push_node
-                    units.hi += m.hi;
-                    units.lo += m.lo;
+                    units.add(m);
                     size_t n = N;
                     unsigned vg = og, ve = oe, vw = ow;
                     asm volatile("" : "+s"(n), "+v"(vg), "+v"(ve), "+v"(vw));
