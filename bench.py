@@ -11,6 +11,7 @@ the library's stream around graph replays; value = nx*ny*K / time in MLUPS.
 Prints ONE JSON line.  --gpus N > 1 exits: the benchmark runs on one GPU.
 """
 import argparse
+import ctypes as C
 import hashlib
 import json
 import os
@@ -47,33 +48,35 @@ def _kernel_roofline(alg_bytes, ms, traffic, per_update):
 # -> factor 1.0).  The factor is the one under which the 3-D kernels whose
 # reads are fixed by their design fetch exactly those bytes; a copy whose input
 # sits partly in the last-level cache reads less (one session read 436918.5
-# KiB), since FETCH_SIZE does not count those hits.  Valid for the kernel
-# sources whose hash is recorded and, for the launches of a two-launch step,
-# the same tile shape; null otherwise.
+# KiB), since FETCH_SIZE does not count those hits.  Valid for the sources of
+# the kernels and of the rule that picks the form of the step (with the compute
+# units it was picked for), whose hash is recorded, and, for the launches of a
+# two-launch step, the same tile shape; null otherwise.
 MEASURED_TRAFFIC = {
-    "source_hash": "6d79e6c04dda8898",
+    "source_hash": "2864bc53537049dc",
+    "compute_units": 256,
     "fetch_factor": 1048576.0 / 524296.2,
     "write_factor": 1048576.0 / 1048576.0,
     # the one-launch step: k_step at 1024x512, k_march at 4096x2048
     "step": {
-        "large_1024x512_fp32": [{"tiles": [], "fetch_kib": 12509.4, "write_kib": 20582.3}],
-        "large_4096x2048_fp32": [{"tiles": [], "fetch_kib": 208427.1, "write_kib": 354576.0}],
+        "large_1024x512_fp32": [{"tiles": [], "fetch_kib": 12501.0, "write_kib": 20582.3}],
+        "large_4096x2048_fp32": [{"tiles": [], "fetch_kib": 207654.1, "write_kib": 352816.6}],
     },
     "k_lb": {
         "large_1024x512_fp32": [
-            {"tiles": [62, 4, 4], "fetch_kib": 10762.8, "write_kib": 24620.5},
-            {"tiles": [62, 8, 8], "fetch_kib": 10744.8, "write_kib": 24638.1},
+            {"tiles": [62, 4, 4], "fetch_kib": 10661.9, "write_kib": 24587.6},
+            {"tiles": [62, 8, 8], "fetch_kib": 10627.7, "write_kib": 24599.8},
         ],
         "large_4096x2048_fp32": [
-            {"tiles": [62, 4, 4], "fetch_kib": 166343.4, "write_kib": 394905.1},
+            {"tiles": [62, 4, 4], "fetch_kib": 166199.3, "write_kib": 394065.9},
         ],
     },
     "k_thermal": {
         "large_1024x512_fp32": [
-            {"tiles": [56, 24, 16], "fetch_kib": 4836.1, "write_kib": 2040.2},
+            {"tiles": [56, 24, 16], "fetch_kib": 4826.3, "write_kib": 2040.2},
         ],
         "large_4096x2048_fp32": [
-            {"tiles": [56, 40, 16], "fetch_kib": 68761.4, "write_kib": 32753.8},
+            {"tiles": [56, 40, 16], "fetch_kib": 68589.0, "write_kib": 32757.6},
         ],
     },
 }
@@ -82,10 +85,10 @@ MEASURED_TRAFFIC = {
 # FP32 storage; KiB per dispatch), valid for the 3-D kernel and host sources
 # whose hash is recorded (the host source sets the runs of planes).
 MEASURED_TRAFFIC_3D = {
-    "source_hash": "ba499d55ee9db650",
+    "source_hash": "b023ab08cbeca33b",
     "pool3d_150x151x150_fp32": {
-        "k3_psi": (141346.0, 40022.3), "k3_reduce": (108.6, 0.1), "k3_lb": (151109.2, 293363.3),
-        "k3_pair_0_1": (39365.0, 92992.5), "k3_pair_2_3": (62158.6, 13344.4),
+        "k3_psi": (141259.3, 40022.3), "k3_reduce": (108.6, 0.1), "k3_lb": (151042.8, 293525.1),
+        "k3_pair_0_1": (39378.1, 92992.1), "k3_pair_2_3": (62157.2, 13344.8),
     },
 }
 
@@ -104,12 +107,33 @@ def measured_traffic(kernel: str, workload: str, tiles):
     """HBM bytes per launch of `kernel` from the recorded counters, or None
     when the kernel source, the workload or the tile shape differ."""
     m = MEASURED_TRAFFIC
-    if not m or m.get("source_hash") != source_hash():
+    if not m or m.get("source_hash") != source_hash() or m["compute_units"] != compute_units():
         return None
     for c in m.get(kernel, {}).get(workload, []):
         if list(c["tiles"]) == list(tiles):
             return int(round((c["fetch_kib"] * m["fetch_factor"] + c["write_kib"] * m["write_factor"]) * 1024))
     return None
+
+
+def compute_units() -> int:
+    """Compute units of the GPU (the form of the step depends on them)."""
+    import torch
+
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def launches_per_step(d) -> int:
+    """Launches of one step of a 2-D domain, counted: four steps, which end in
+    one or two launches more, are recorded into a graph that never runs."""
+    from paper_1501_03857_amd import lbboil as L
+
+    hip, stream = L.lib(), C.c_void_p(d.stream)
+    graph, nodes = C.c_void_p(), C.c_size_t(0)
+    assert hip.hipStreamBeginCapture(stream, 1) == 0  # thread-local capture
+    d.step_async(4)
+    assert hip.hipStreamEndCapture(stream, C.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, C.byref(nodes)) == 0 and hip.hipGraphDestroy(graph) == 0
+    return nodes.value // 4
 
 
 def arithmetic(store: str) -> str:
@@ -120,11 +144,11 @@ def arithmetic(store: str) -> str:
 
 
 def source_hash(*names: str) -> str:
-    """Hash of kernel source files (the recorded counters depend on them and,
-    in 2-D, on the tile shape; the 3-D launch shapes are set in the 3-D host
-    source, which is hashed with its kernels)."""
+    """Hash of source files that the recorded counters depend on: the kernels
+    and what sets their launch shapes, in 2-D the rule for the form of the step,
+    in 3-D the host source."""
     h = hashlib.sha256()
-    for name in names or ("lbb_device.hpp", "lbb_step.hpp"):
+    for name in names or ("lbb_device.hpp", "lbb_step.hpp", "lbb_form.hpp"):
         with open(os.path.join(ROOT, "paper_1501_03857_amd", "csrc", name), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -435,11 +459,14 @@ def main():
         d.set_tiles(*(int(x) for x in args.tiles.split(",")))
     elif args.tune_steps > 0:
         tune = d.autotune(args.tune_steps)
+    # the shapes of the two-launch step: those of the timed step only if that is its form
     shapes_lb, shapes_th = L.tile_shapes()
     tiles = {"lb": list(shapes_lb[d.tiles[0]]), "thermal": list(shapes_th[d.tiles[1]]),
              "autotuned": tune is not None}
-    print(f"[bench] {w.name}: {w.nx}x{w.ny} {store} storage, tiles {tiles}, warmup {args.warmup}, "
-          f"timed {args.steps}", file=sys.stderr, flush=True)
+    launches = 2 if args.tiles else launches_per_step(d)
+    print(f"[bench] {w.name}: {w.nx}x{w.ny} {store} storage, {launches} launch(es) a step"
+          f"{f', tiles {tiles}' if launches == 2 else ''}, warmup {args.warmup}, timed {args.steps}", file=sys.stderr,
+          flush=True)
 
     d.step(args.warmup)
     stream = torch.cuda.ExternalStream(d.stream)
@@ -467,8 +494,7 @@ def main():
     achieved = step_bytes / (ms_step * 1e-3) / 1e9
     tr_lb = measured_traffic("k_lb", w.name, tiles["lb"])
     tr_th = measured_traffic("k_thermal", w.name, tiles["thermal"])
-    # the timed step is one launch unless tile shapes were given
-    if args.tiles:
+    if launches == 2:
         traffic = None if tr_lb is None or tr_th is None else tr_lb + tr_th
     else:
         traffic = measured_traffic("step", w.name, [])
@@ -502,18 +528,20 @@ def main():
         "dtype": arithmetic(store),
         "data": "synthetic",
         "config": {"workload": w.name, "nx": w.nx, "ny": w.ny, "storage": store, "global_batch": 1,
-                   "parallelism": "none", "launches_per_step": 2 if args.tiles else 1, "graph_steps": 32, "tiles": tiles},
+                   "parallelism": "none", "launches_per_step": launches, "graph_steps": 32,
+                   "tiles": tiles if launches == 2 else None},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_unit": "bytes per step",
                      "traffic_gbs": None if traffic is None else round(traffic / (ms_step * 1e-3) / 1e9, 1),
-                     "kernel": "step (k_lb + k_thermal)" if args.tiles else "step (one launch)", "step_ms": round(ms_step, 6),
+                     "kernel": "step (k_lb + k_thermal)" if launches == 2 else "step (one launch)", "step_ms": round(ms_step, 6),
                      "alg_bytes_per_update": ALG_BYTES_STEP[store],
                      "copy_gbs": round(copy_gbs, 1), "frac_of_copy": round(achieved / copy_gbs, 4)},
         "kernel_rooflines": {
             "k_lb": _kernel_roofline(ALG_BYTES_LB[store] * cells, ms_lb, tr_lb, ALG_BYTES_LB[store]),
             "k_thermal": _kernel_roofline(ALG_BYTES_TH[store] * cells, ms_th, tr_th, ALG_BYTES_TH[store]),
         },
+        "two_launch_tiles": tiles,
         "kernels_ms": {"k_lb": round(ms_lb, 6), "k_thermal": round(ms_th, 6), "step_single_launch": round(ms_seq, 6)},
         "heat_flux_mean": hf["q_mean"],
         "batched_sweep": sweep,

@@ -128,7 +128,7 @@ __device__ __forceinline__ float stage_sqrt(float x) { return __builtin_amdgcn_s
 struct NodeMass {
     long long hi;
     int lo;
-    __device__ __forceinline__ void add(const NodeMass &o)  // of some hundred nodes at most
+    __device__ __forceinline__ void add(const NodeMass &o)  // of fewer than 2^15 nodes
     {
         hi += o.hi;
         lo += o.lo;
