@@ -152,7 +152,8 @@ int lbb_sync(lbb_domain *d);
 void *lbb_stream(lbb_domain *d);
 
 /* Advance n >= 1 steps of two launches each (also where lbb_step takes one),
- * launched one by one (no graph), each launch carrying HIP events that its dispatch records at kernel start and end;
+ * launched one by one (no graph), each launch carrying HIP events that its
+ * dispatch records at kernel start and end;
  * returns the mean kernel duration in milliseconds of the LB launch
  * (collision, forces, streaming) and of the thermal launch (RK4 temperature
  * step), and the mean wall time per step of the whole sequence.  For
@@ -227,8 +228,10 @@ void *lbb_batch_stream(lbb_batch *b);
 int lbb_batch_heat_flux(lbb_batch *b, double *q_now, double *q_mean, int64_t *n_samples);
 /* Borrowed handle of member i for the single-lattice calls (read_fields,
  * heat flux, save/load, set_heater ...); owned by the batch, NULL if out of
- * range.  Stepping a member alone puts it out of phase with the batch, which
- * then refuses to step (EINVAL). */
+ * range.  Stepping a member alone by an odd number of steps puts it out of
+ * phase with the batch, which then refuses to step (EINVAL); after an even
+ * number, wait for the member (any waiting call of it or of the batch) before
+ * the batch steps on. */
 lbb_domain *lbb_batch_domain(lbb_batch *b, int i);
 int lbb_batch_size(lbb_batch *b);
 int lbb_batch_destroy(lbb_batch *b);
@@ -241,7 +244,7 @@ int lbb_batch_destroy(lbb_batch *b);
  * nx nodes in order, n_heater must be nx), and the bottom wall strength G_w
  * (Eq. (22)), by a hand-written discrete adjoint of the whole coupled step
  * (FP64 arithmetic; the population adjoints, the per-node work arrays and
- * the temperature adjoint's LDS planes are stored in the domain's precision,
+ * what the temperature adjoint holds between stages are in the domain's precision,
  * the adjoint of T and the sums in FP64).  J is required; dJ_dTb and dJ_dGw
  * may be NULL.  EINVAL for a heater index outside [0, nx).  States are checkpointed
  * every K steps and each segment but the last is recomputed before its
@@ -250,7 +253,7 @@ int lbb_batch_destroy(lbb_batch *b);
  * memory, else K = ceil(sqrt(N)).  The domain's state, step count and
  * heat-flux average are restored afterwards.  Device memory, allocated on
  * the first call and kept by the domain (reported by lbb_info): about
- * (N/K + K + 2) * 10 * nx*ny * sizeof(real) + 38 * nx*ny * sizeof(real) +
+ * (N/K + K + 2) * 10 * nx*ny * sizeof(real) + 31 * nx*ny * sizeof(real) +
  * 4 * nx*ny * 8 bytes.
  * EUNSUPPORTED for periodic_y or a test mode; EINVAL for N < 1; ENOMEM when
  * the workspace cannot be allocated. */

@@ -52,7 +52,7 @@ constexpr int TXB = 64 - 2 * HB;  // thermal tile width: tile + halo is one wave
 // Tile shapes the launches can take (height, waves per block); the host picks
 // one of each per lattice or batch, by default or by timing them on the
 // lattice (autotune).  Index 0 is the default.  With one lattice row per
-// wave the LB kernel needs 76 VGPRs (6 waves per SIMD), against 124 with
+// wave the LB kernel needs 78 VGPRs (6 waves per SIMD), against 122 with
 // three rows per wave, and the extra waves in flight hide the load latency
 // of phase 1 behind the arithmetic of other waves (held to 72 VGPRs for a
 // seventh wave it spills: 209 against 172 us at 4096x2048 FP32).

@@ -31,9 +31,9 @@ struct StepForm {
 // columns, so they pay while a step is bound by launch and phase latencies,
 // not by the work itself: when tiles of some height fit the compute units in
 // one round.  Timed on graph replays, one launch against two (us per step):
-// 128x64 FP64 7.1 against 13.6, 301x77 FP32 6.9 against 12.4, 600x151 FP32 9.2
-// against 13.1, 511x257 FP64 12.1 against 15.8, 512x256 FP32 10.2 against 13.2,
-// 1024x512 FP32 21.6 against 23.0.  One block more than compute units costs a
+// 128x64 FP64 7.1 against 13.1, 301x77 FP32 6.6 against 12.1, 600x151 FP32 8.5
+// against 12.6, 511x257 FP64 10.9 against 15.4, 512x256 FP32 8.9 against 12.7,
+// 1024x512 FP32 20.2 against 22.7.  One block more than compute units costs a
 // second round (600x151: 18.3 with 912 blocks, 14.6 with 612, 9.2 with 228),
 // and a block alone on a compute unit cannot hide its loads under another's
 // arithmetic (2048x1024: 77 against 64).
@@ -43,9 +43,9 @@ struct StepForm {
 // with 3 and 7.9 with 4; 600x151 9.2 with 8, 10.1 with 13, 12.6 with 22).
 //
 // Where marching strips (k_march) are taken: from the size on at which strips
-// of kMarchMin rows fill every wave slot.  The height is then the smallest
+// of march_min rows fill every wave slot.  The height is then the smallest
 // that still fits one round, up to kMarchMax, where more rows no longer pay
-// (4096x2048 FP32: 205, 202, 202 us with 26, 32, 53 rows; two launches 265).
+// (4096x2048 FP32: 205, 202, 202 us with 26, 32, 53 rows; two launches 275).
 // Below, too few rows a wave leave too much halo: 2048x1024 FP32 61 us either
 // way with 14 rows, 1024x512 36 against 22 with 8; FP64 gains earlier, since its
 // two launches are slower: 1500x700 51 against 59 with 11 rows.  Heights are 2
@@ -77,19 +77,19 @@ int64_t step_blocks(const StepDims &l, const StepForm &f)
 
 // Isothermal lattices step in one launch of k_lb (ONE, default tiles) where
 // every block can add up the mass partials of the tiles with few loads a
-// thread: up to 2048 rows of tile columns, four of which make a tile.  Eleven 160x60 FP64 lattices:
-// 7.5 us per step against 12.0 with the temperature launch, which reduces in
-// 4.4 us.  Tuned shapes do not matter to it: 248x512 FP64 8.5 us, against 9.8
-// in two launches of the fastest shapes.
+// thread: up to 2048 rows of tile columns, four of which make a tile.  Eleven
+// 160x60 FP64 lattices: 7.3 us per step against 11.1 with the temperature
+// launch, which only reduces.  Tuned shapes do not matter to it: 248x512 FP64
+// 7.2 us, against 9.8 in two launches of the fastest shapes.
 constexpr int kOneMaxRows = 2048;
 
 // One block of a lattice samples the heat flux of its bottom row in every
 // step, a chunk of TXB columns a wave; on wide lattices of few rows it is the
 // last to end.  Isothermal (four waves; us per step, one launch / two): 1000x120
-// FP64 8.6 / 10.7, 1500x80 9.3 / 10.8 (a step with its flush 14.7 / 14.2),
+// FP64 7.5 / 10.4, 1500x80 9.4 / 10.5 (a step with its flush 14.4 / 13.6),
 // 2000x60 11.4 / 11.1, 8000x15 34 / 12.  Tiles (16 waves): 3400x16 FP32
-// 7.7 / 11.9, 5000x100 21.1 / 23.3, 6800x8 FP64 14.3 / 12.0, 13700x4 24.4 / 13.4,
-// but 13700x38 29.5 / 37.4: tall tiles take longer than the sample.
+// 7.7 / 11.3, 5000x100 21.0 / 22.6, 6800x8 FP64 14.3 / 12.0, 13700x4 24.4 / 13.4,
+// but 13700x38 29.3 / 37.1: tall tiles take longer than the sample.
 constexpr int kOneMaxChunks = 28;
 constexpr int kTileMaxChunks = 96, kTileLongRows = 32;
 constexpr int heat_flux_chunks(int nx) { return (nx + lbb::TXB - 1) / lbb::TXB; }

@@ -586,8 +586,8 @@ FlushSize flush_size(const std::vector<lbb_domain *> &doms, const StepForm &f)
 // would take many chunks or partials one after another, and a long bottom row
 // has a launch of its own: a compute unit by itself reads some 50 GB/s.  us of
 // one step and its flush, with four waves that take a chunk at a time / now:
-// 1024x512 FP32 27.8 / 27.1, 4096x2048 FP32 224 / 210, 8192x400 FP32 116 / 86,
-// 13700x54 FP32 72 / 33.5.
+// 1024x512 FP32 27.8 / 25.3, 4096x2048 FP32 224 / 210, 8192x400 FP32 116 / 87,
+// 13700x54 FP32 72 / 33.
 constexpr int kFlushChunks = 16, kFlushPartials = 1024, kFlushRow = 48;
 
 template <typename S>
